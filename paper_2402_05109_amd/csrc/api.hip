@@ -392,7 +392,7 @@ int hydra_draft_tree(hydra_ctx *c, void *stream, int B, void *ws, const float *h
             // the wide first layer of the later heads has few output bands and a long K
             auto mlp_layer = [&](const void *xin, size_t w_off, size_t b_off, int K, bool residual, void *xout) -> int {
                 const GemmPlan fused = plan_gemm(c, Mi, d, K, GEMM_KIND_FUSED), split = plan_gemm(c, Mi, d, K, GEMM_KIND_PLAIN);
-                if (split.splits > 1 && split.cost_us + 5.f < fused.cost_us) {
+                if ((split.splits > 1 || split.tile) && split.cost_us + 5.f < fused.cost_us) {
                     int r2 = launch_gemm(c, s, xin, A + w_off, part, Mi, d, K, &p);
                     if (r2) return r2;
                     return launch_bias_silu(c, s, part, p.splits, gemm_npad(c, d), (size_t)align_up(Mi, 32) * gemm_npad(c, d),

@@ -38,6 +38,7 @@ GemmPlan plan_gemm(const hydra_ctx *c, int M, int N, int K, int kind) {
     GemmPlan p;
     p.splits = 1;
     p.shared_x = 0;
+    p.tile = 0;
     p.cost_us = 0.f;
     if (!c->bf16) { p.mb = 1; p.nt = 1; p.nw = 1; p.kw = 1; p.kpw = K; return p; }
     const int mblocks = ceil_div(M, 32);
@@ -126,10 +127,24 @@ GemmPlan plan_gemm(const hydra_ctx *c, int M, int N, int K, int kind) {
             p.splits = ceil_div(KT, p.kpw);
         }
     }
+    // Beyond 64 rows: both operands through LDS (bf16_gemm_tile.hip).  For plain outputs always: it was the faster one in 143
+    // of 147 timed shapes, up to 1.8 times, and the others lose 2 us at most.  For fused epilogues (no K split, so small
+    // matrices leave it too few workgroups) where it is estimated cheaper; the estimate above leaves out the ramp and is
+    // 13 to 25 % short of what is measured at 96 and more rows.  Not for KIND_FUSED and KIND_PAIRS, whose epilogues it is not
+    // built for (q|k|v: launch_gemm_qkv_rope).
+    // HYDRA_PLAN_TILE: 0 never, 1 wherever a tile exists.
+    const int tile_mode = (int)env_or("HYDRA_PLAN_TILE", -1.0);
+    if (kind != GEMM_KIND_FUSED && kind != GEMM_KIND_PAIRS && tile_mode != 0 && !getenv("HYDRA_PLAN_SHARED_X_MIN_WGS")) {
+        GemmPlan t = p;
+        if (plan_tile(c, M, N, K, kind, &t)) {
+            p.cost_us = 1.15f * p.cost_us + 1.0f;
+            if (tile_mode == 1 || kind == GEMM_KIND_PLAIN || t.cost_us < p.cost_us) p = t;
+        }
+    }
     static const bool debug = getenv("HYDRA_PLAN_DEBUG") != nullptr;       // tuning aid: every plan to stderr
     if (debug)
-        fprintf(stderr, "plan M=%d N=%d K=%d kind=%d -> mb=%d nt=%d nw=%d kw=%d splits=%d shared_x=%d cost=%.1f\n", M, N, K, kind, p.mb, p.nt, p.nw,
-                p.kw, p.splits, p.shared_x, p.cost_us);
+        fprintf(stderr, "plan M=%d N=%d K=%d kind=%d -> mb=%d nt=%d nw=%d kw=%d splits=%d shared_x=%d tile=%d cost=%.1f\n", M, N, K, kind, p.mb, p.nt, p.nw,
+                p.kw, p.splits, p.shared_x, p.tile, p.cost_us);
     return p;
 }
 
@@ -149,6 +164,10 @@ static void launch_one(dim3 grid, dim3 block, size_t lds, hipStream_t s, const G
     if (e0) hipExtLaunchKernelGGL((gemm_bf16_kernel<MB, NT, MAXT, Epi>), grid, block, lds, s, e0, e1, 0, g, epi);
     else    hipLaunchKernelGGL((gemm_bf16_kernel<MB, NT, MAXT, Epi>), grid, block, lds, s, g, epi);
 }
+
+template <class Epi>
+int launch_tile(hydra_ctx *c, hipStream_t s, const void *X, const void *W, int M, int N, int K, const GemmPlan &p, const Epi &epi, hipEvent_t e0,
+                hipEvent_t e1);                                    // bf16_gemm_tile.hip
 
 enum { NT_ANY = 0, NT_TWO = 2 };
 template <class Epi, int NT_SET>
@@ -175,7 +194,14 @@ static int launch_bf16(hydra_ctx *c, hipStream_t s, const void *X, const void *W
         e0 = c->ev[c->ev_used++]; e1 = c->ev[c->ev_used++];
     }
     const int key = p.mb * 10 + p.nt;
-    if (p.shared_x) {
+    if (p.tile) {
+        if constexpr (!std::is_same<Epi, EpiPlain>::value && !std::is_same<Epi, EpiResid>::value && !std::is_same<Epi, EpiSilu>::value) {      // never planned for these
+            return fail(HYDRA_E_UNSUPPORTED, "gemm: no tile kernel for this epilogue");
+        } else {
+            const int rc = launch_tile<Epi>(c, s, X, W, M, N, K, p, epi, e0, e1);
+            if (rc) return rc;
+        }
+    } else if (p.shared_x) {
         if constexpr (std::is_same<Epi, EpiTop2>::value) {           // never planned for this epilogue (launch_gemm_top2): no such kernel is built
             return fail(HYDRA_E_UNSUPPORTED, "gemm: the band-wise top-2 epilogue has no shared-X kernel");
         } else if (p.shared_x == 8) {
@@ -270,10 +296,15 @@ __global__ __launch_bounds__(256) void resid_norm_kernel(float *__restrict__ x, 
     if (threadIdx.x == 0) ss[(size_t)blockIdx.x * Mpad + m] = red[0] + red[1] + red[2] + red[3];
 }
 
+// What a kernel behind a plain GEMM of M x N outputs costs: its launch, the partial sums read and `bytes` more per output moved
+static float second_kernel_us(int splits, int M, int N, int bytes) { return 4.0f + (float)((double)M * N * (4 * splits + bytes) / 4.5e6); }
+
 int launch_gemm_resid(hydra_ctx *c, hipStream_t s, const void *X, const void *W, int M, int N, int K, float *x,
                       const float *gain, void *xg, float *ss, int Mpad, float *part, int *ss_bands) {
     GemmPlan p = plan_gemm(c, M, N, K, GEMM_KIND_PLAIN);
-    if (p.splits > 1) {
+    const GemmPlan fused = plan_gemm(c, M, N, K, GEMM_KIND_RESID);
+    const bool second = p.tile ? p.cost_us + second_kernel_us(p.splits, M, N, 10) < fused.cost_us : p.splits > 1;
+    if (second) {
         const int npad = gemm_npad(c, N);
         const size_t stride = (size_t)ceil_div(M, 32) * 32 * npad;
         EpiPlain epi{part, npad, stride};
@@ -286,19 +317,20 @@ int launch_gemm_resid(hydra_ctx *c, hipStream_t s, const void *X, const void *W,
         return HYDRA_OK;
     }
     *ss_bands = N / 32;                      // the fused epilogue leaves one partial sum per 32-column band
-    p = plan_gemm(c, M, N, K, GEMM_KIND_FUSED);
+    p = fused;
     EpiResid epi{x, N, gain, (a16_t *)xg, ss, Mpad, flags_dev(c)};
     return launch_bf16<EpiResid, NT_ANY>(c, s, X, W, M, N, K, p, epi);
 }
 
 // LM head straight to per-band top-2 candidates (no logits): *fused = 0 and nothing launched where the plan that splits K
-// over workgroups is estimated clearly faster than one workgroup per band group (the candidates need complete sums).
+// over workgroups is estimated clearly faster than one workgroup per band group (the candidates need complete sums), and
+// beyond 64 rows, where the logits come from the tile kernel.
 // Opt-in (HYDRA_LM_HEAD_TOP2=1): measured at the 7B shape it is a wash, 50.3 + 5.8 us against 47.0 + 11.6 us at 64 rows and
 // 52.1 + 5.7 against 41.8 + ~8 us for the one-node tree, so by default the logits go through memory.
 int launch_gemm_top2(hydra_ctx *c, hipStream_t s, const void *X, const void *W, int M, int N, int K, float *cand, int Mpad, int *fused) {
     const GemmPlan ps = plan_gemm(c, M, N, K, GEMM_KIND_PLAIN);
     const GemmPlan p = plan_gemm(c, M, N, K, GEMM_KIND_FUSED);
-    *fused = (p.shared_x == 0 && p.cost_us <= ps.cost_us + 4.0f && env_or("HYDRA_LM_HEAD_TOP2", 0.0) != 0.0) ? 1 : 0;
+    *fused = (p.shared_x == 0 && ps.tile == 0 && p.cost_us <= ps.cost_us + 4.0f && env_or("HYDRA_LM_HEAD_TOP2", 0.0) != 0.0) ? 1 : 0;
     if (!*fused) return HYDRA_OK;
     EpiTop2 epi{cand, Mpad, N};
     return launch_bf16<EpiTop2, NT_ANY>(c, s, X, W, M, N, K, p, epi);
@@ -322,16 +354,15 @@ int launch_gemm_bias_silu(hydra_ctx *c, hipStream_t s, const void *X, const void
 int launch_gemm_qkv_rope(hydra_ctx *c, hipStream_t s, const void *X, const void *W, int M, RowScale rs, int layer,
                          const int32_t *seq_len, const hydra_kv *kv, void *qbuf, float *part, int32_t *flags) {
     {
-        // Beyond 128 rows a plan that splits K over workgroups (plain partial sums, then rotary embedding and cache append
-        // as a kernel of their own) can beat the fused one: each workgroup pulls a shorter slice of X (measured: steps at
-        // 192 rows 7.7 -> 7.3 ms, the 33B shape at 256 rows 30.8 -> 29.5 ms; at 96 and 128 rows it lost 1.5 %).  It is taken where
-        // the planner's estimate plus the cost of the second kernel is lower (HYDRA_PLAN_QKV_UNFUSED: 0 never, 1 always).
+        // Beyond 64 rows: plain sums from the tile kernel, then rotary embedding and cache append as a kernel of their own,
+        // where the estimates say so (HYDRA_PLAN_QKV_UNFUSED: 0 never, 1 always).  7B shape: 96 rows 39.8 us for the fused
+        // kernel against 25 + 8, 128 rows 40.2 against 27 + 7, 1024 rows 144 against 105 + 26 (140 with the epilogue fused into
+        // the tile kernel: its stores are two bytes each); 33B shape at 256 rows 102 + 26 before, 96 + 12 now.
         const int dd = c->m.d;
         const GemmPlan pf = plan_gemm(c, M, 3 * dd, dd, GEMM_KIND_PAIRS), pu = plan_gemm(c, M, 3 * dd, dd, GEMM_KIND_PLAIN);
         const int mode = (int)env_or("HYDRA_PLAN_QKV_UNFUSED", -1.0);
-        // the second kernel: its launch, and S partial outputs of M x 3d floats read back at about 4 TB/s
-        const float second = 5.0f + (float)((double)pu.splits * M * 3 * dd * 4 / 4e6);
-        const bool unfused = mode == 1 || (mode != 0 && M > 128 && pu.splits > 1 && pu.cost_us + second < pf.cost_us);
+        const float second = second_kernel_us(pu.splits, M, 3 * dd, 2);
+        const bool unfused = mode == 1 || (mode != 0 && pu.tile && pu.cost_us + second < 1.15f * pf.cost_us + 1.0f);
         if (unfused) {
             const int npad = gemm_npad(c, 3 * dd);
             const size_t stride = (size_t)ceil_div(M, 32) * 32 * npad;
@@ -390,7 +421,7 @@ int gemm_max_dynamic_lds(hydra_ctx *c) {
     if (e == hipSuccess) e = set_attr<1, 4, EpiQkvRope>();
     if (e == hipSuccess) e = set_attr<2, 4, EpiQkvRope>();
     if (e != hipSuccess) return hip_fail(e, "hipFuncSetAttribute(gemm_bf16_kernel)");
-    return HYDRA_OK;
+    return gemm_tile_max_dynamic_lds();
 }
 
 // ---------------------------------------------------------------------------

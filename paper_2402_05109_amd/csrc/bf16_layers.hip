@@ -243,7 +243,7 @@ __device__ __forceinline__ void gemm_stage(const GemmGeom &g, const Epilogue &ep
     }
     const int lane = opaque_tid() & 63, kw = wk.kw;
     GemmTile<MB, NT> t;
-    t.tile0 = wk.bx * NT; t.mb0 = 0; t.lane = lane; t.wave = kw; t.split = wk.by; t.lds = lds;
+    t.tile0 = wk.bx * NT; t.mb0 = t.wg_mb0 = 0; t.row_off = 0; t.lane = lane; t.wave = kw; t.split = wk.by; t.lds = lds; t.stage = lds + GEMM_LDS_STAGE;
     float *redbuf = lds + GEMM_LDS_SCRATCH;
     f32x16_t acc[MB][NT];
 #pragma unroll

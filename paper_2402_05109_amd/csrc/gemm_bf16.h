@@ -76,8 +76,7 @@ __device__ __forceinline__ bool gemm_block(const GemmGeom &g, int &bx, int &by, 
 // floats reserved in front of the reduction buffer: per-wave partial row sums [8 waves][128 rows], then per
 // wave a 1 KiB staging block (epilogues that assemble whole operand tiles) and a 128-row table of row scales
 // and three 128-row tables of per-row integers shared by the workgroup
-enum { GEMM_LDS_ROWSUM = 0, GEMM_LDS_ROWINFO = 8 * 128, GEMM_LDS_STAGE = 8 * 128 + 3 * 128, GEMM_LDS_STAGE_WAVE = 256 + 128,
-       GEMM_LDS_SCRATCH = 8 * 128 + 3 * 128 + 8 * (256 + 128) };
+enum { GEMM_LDS_STAGE = 8 * 128 + 3 * 128, GEMM_LDS_STAGE_WAVE = 256 + 128, GEMM_LDS_SCRATCH = 8 * 128 + 3 * 128 + 8 * (256 + 128) };
 
 // prefetch distance in k-steps: two register sets of U*(NT+MB) KiB per wave
 template <int MB, int NT> struct GemmU {
@@ -91,13 +90,19 @@ __device__ __forceinline__ void static_for_impl(F &&f, std::integer_sequence<int
 template <int N, class F>
 __device__ __forceinline__ void static_for(F &&f) { static_for_impl(f, std::make_integer_sequence<int, N>{}); }
 
-template <int MB, int NT>
+// MB row blocks x NT bands of one wave; XB: row blocks of its workgroup (more than MB where waves take different rows)
+template <int MB, int NT, int XB = MB>
 struct GemmTile {
+    // rows that the scratch tables hold per wave (partial row sums) or per workgroup (row information)
+    static constexpr int ROWS = XB <= 4 ? 128 : 256, ROWSUM = 0, ROWINFO = 8 * ROWS;
     int tile0;      // first band of this wave
-    int mb0;        // first 32-row block
+    int mb0;        // first 32-row block of this wave
+    int wg_mb0;     // first 32-row block of its workgroup
+    int row_off;    // 32 * (mb0 - wg_mb0): the wave's first row in the workgroup's tables
     int lane, wave;
     int split;      // blockIdx.y
-    float *lds;     // GEMM_LDS_SCRATCH floats of per-workgroup scratch
+    float *lds;     // per-workgroup tables: ROWSUM [8 waves][ROWS], ROWINFO [3][ROWS]
+    float *stage;   // per-wave blocks of GEMM_LDS_STAGE_WAVE floats, for the epilogue only
 };
 
 // One workgroup of the GEMM: (bx, by, bz) are its band-group, K-split and row-group indices (the plain kernel passes
@@ -110,11 +115,13 @@ __device__ __forceinline__ void gemm_bf16_body(const GemmGeom &g, const Epilogue
     const int group = bx * g.NW + nw;               // band group of this wave
     GemmTile<MB, NT> t;
     t.tile0 = group * NT;
-    t.mb0 = bz * MB;
+    t.mb0 = t.wg_mb0 = bz * MB;
+    t.row_off = 0;
     t.lane = lane;
     t.wave = wave;
     t.split = by;
     t.lds = red;
+    t.stage = red + GEMM_LDS_STAGE;
     float *redbuf = red + GEMM_LDS_SCRATCH;
     // the KW waves of a workgroup share the k-range of their split block by block (wave kw takes the blocks
     // kw, kw + KW, ... of GEMM_U steps), so that together they sweep each band as one contiguous front
@@ -309,11 +316,13 @@ __global__ __launch_bounds__(NWT * 64) void gemm_bf16_sharedx_kernel(GemmGeom g,
     if (!gemm_block(g, bx, by, bz)) return;
     GemmTile<MB, NT> t;
     t.tile0 = (bx * NWT + wave) * NT;
-    t.mb0 = bz * MB;
+    t.mb0 = t.wg_mb0 = bz * MB;
+    t.row_off = 0;
     t.lane = lane;
     t.wave = wave;
     t.split = by;
     t.lds = red;
+    t.stage = red + GEMM_LDS_STAGE;
     constexpr int XT = GEMM_U * MB;                 // X tiles per block
     constexpr int XS = (XT + NWT - 1) / NWT;        // of which this wave fetches up to XS
     u32x4_t *xbuf = reinterpret_cast<u32x4_t *>(red + GEMM_LDS_SCRATCH);

@@ -24,10 +24,10 @@ __device__ __forceinline__ int acc_row(int mb, int v, int lane) { return mb * 32
 struct RowSumRegs { f32x4_t v[8]; };
 struct NoPre {};
 
-template <int MB>
+template <int XB>
 __device__ __forceinline__ RowSumRegs rowsum_issue(const float *__restrict__ ss, int nb, int Mpad, int row0, int lane,
                                                    int wave, int base) {
-    constexpr int LPR = 8 * MB, G = 64 / LPR;
+    constexpr int LPR = 8 * XB, G = 64 / LPR;
     const int nwaves = blockDim.x >> 6;
     const int grp = lane / LPR, r4 = (lane % LPR) * 4;
     RowSumRegs r;
@@ -40,10 +40,10 @@ __device__ __forceinline__ RowSumRegs rowsum_issue(const float *__restrict__ ss,
     return r;
 }
 
-template <int MB>
+template <int XB>
 __device__ __forceinline__ void rowsum_finish(RowSumRegs r, float *lds, const float *__restrict__ ss, int nb, int Mpad,
                                               int row0, int lane, int wave) {
-    constexpr int LPR = 8 * MB, G = 64 / LPR;
+    constexpr int LPR = 8 * XB, G = 64 / LPR;
     const int nwaves = blockDim.x >> 6;
     f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
     for (int base = 0;;) {
@@ -51,25 +51,26 @@ __device__ __forceinline__ void rowsum_finish(RowSumRegs r, float *lds, const fl
         for (int j = 0; j < 8; ++j) acc += r.v[j];
         base += 8 * nwaves * G;
         if (base >= nb) break;
-        r = rowsum_issue<MB>(ss, nb, Mpad, row0, lane, wave, base);
+        r = rowsum_issue<XB>(ss, nb, Mpad, row0, lane, wave, base);
     }
 #pragma unroll
     for (int o = LPR; o < 64; o <<= 1) {
         acc[0] += __shfl_xor(acc[0], o, 64); acc[1] += __shfl_xor(acc[1], o, 64);
         acc[2] += __shfl_xor(acc[2], o, 64); acc[3] += __shfl_xor(acc[3], o, 64);
     }
-    if (lane < LPR) *reinterpret_cast<f32x4_t *>(lds + GEMM_LDS_ROWSUM + wave * 128 + lane * 4) = acc;
+    if (lane < LPR) *reinterpret_cast<f32x4_t *>(lds + (wave * GemmTile<XB, 1>::ROWS) + lane * 4) = acc;
 }
 
 // after the barrier: every wave fills its own table of row scales, rstd[row] at wave_stage(t)[256 + row]
-__device__ __forceinline__ float *wave_stage(float *lds, int wave) { return lds + GEMM_LDS_STAGE + wave * GEMM_LDS_STAGE_WAVE; }
-template <int MB>
-__device__ __forceinline__ void rstd_table(float *lds, int lane, int wave, int d, float eps) {
+template <int MB, int NT, int XB>
+__device__ __forceinline__ float *wave_stage(const GemmTile<MB, NT, XB> &t) { return t.stage + t.wave * GEMM_LDS_STAGE_WAVE; }
+template <int MB, int NT, int XB>
+__device__ __forceinline__ void rstd_table(const GemmTile<MB, NT, XB> &t, int d, float eps) {
     const int nwaves = blockDim.x >> 6;
-    float *tab = wave_stage(lds, wave) + 256;
-    for (int r = lane; r < 32 * MB; r += 64) {
+    float *tab = wave_stage(t) + 256;
+    for (int r = t.lane; r < 32 * MB; r += 64) {
         float s = 0.f;
-        for (int w = 0; w < nwaves; ++w) s += lds[GEMM_LDS_ROWSUM + w * 128 + r];
+        for (int w = 0; w < nwaves; ++w) s += t.lds[t.ROWSUM + w * t.ROWS + t.row_off + r];
         tab[r] = 1.0f / sqrtf(s / (float)d + eps);
     }
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -83,12 +84,12 @@ template <bool DEV>
 struct EpiPlainT {
     float *out; int ld; size_t split_stride;
     static constexpr bool LDS_PROLOGUE = false, PAIRED = false, EXTRA_BLOCKS = false, ROWWISE = false;
-    template <int MB, int NT> __device__ __forceinline__ NoPre issue(const GemmTile<MB, NT> &, const GemmGeom &) const { return NoPre{}; }
-    template <int MB, int NT> __device__ __forceinline__ NoPre prologue(NoPre, const GemmTile<MB, NT> &, const GemmGeom &) const { return NoPre{}; }
-    template <int MB, int NT> __device__ __forceinline__ void before_barrier(NoPre, const GemmTile<MB, NT> &, const GemmGeom &) const {}
-    template <int MB, int NT> __device__ __forceinline__ void begin(const GemmTile<MB, NT> &, const GemmGeom &) const {}
-    template <int MB, int NT>
-    __device__ __forceinline__ void tile(const f32x16_t &acc, int a, int i, const GemmTile<MB, NT> &t, const GemmGeom &g) const {
+    template <int MB, int NT, int XB> __device__ __forceinline__ NoPre issue(const GemmTile<MB, NT, XB> &, const GemmGeom &) const { return NoPre{}; }
+    template <int MB, int NT, int XB> __device__ __forceinline__ NoPre prologue(NoPre, const GemmTile<MB, NT, XB> &, const GemmGeom &) const { return NoPre{}; }
+    template <int MB, int NT, int XB> __device__ __forceinline__ void before_barrier(NoPre, const GemmTile<MB, NT, XB> &, const GemmGeom &) const {}
+    template <int MB, int NT, int XB> __device__ __forceinline__ void begin(const GemmTile<MB, NT, XB> &, const GemmGeom &) const {}
+    template <int MB, int NT, int XB>
+    __device__ __forceinline__ void tile(const f32x16_t &acc, int a, int i, const GemmTile<MB, NT, XB> &t, const GemmGeom &g) const {
         if (t.tile0 + i >= g.NTiles) return;
         float *dst = out + (size_t)t.split * split_stride + (t.tile0 + i) * 32 + (t.lane & 31);
 #pragma unroll
@@ -123,18 +124,18 @@ __device__ __forceinline__ Top2 top2_dpp(const Top2 &q) {
 struct EpiTop2 {
     float *cand; int Mpad; int V;
     static constexpr bool LDS_PROLOGUE = false, PAIRED = false, EXTRA_BLOCKS = false, ROWWISE = true;
-    template <int MB, int NT> __device__ __forceinline__ NoPre issue(const GemmTile<MB, NT> &, const GemmGeom &) const { return NoPre{}; }
-    template <int MB, int NT> __device__ __forceinline__ NoPre prologue(NoPre, const GemmTile<MB, NT> &, const GemmGeom &) const { return NoPre{}; }
-    template <int MB, int NT> __device__ __forceinline__ void before_barrier(NoPre, const GemmTile<MB, NT> &, const GemmGeom &) const {}
-    template <int MB, int NT> __device__ __forceinline__ void begin(const GemmTile<MB, NT> &, const GemmGeom &) const {}
+    template <int MB, int NT, int XB> __device__ __forceinline__ NoPre issue(const GemmTile<MB, NT, XB> &, const GemmGeom &) const { return NoPre{}; }
+    template <int MB, int NT, int XB> __device__ __forceinline__ NoPre prologue(NoPre, const GemmTile<MB, NT, XB> &, const GemmGeom &) const { return NoPre{}; }
+    template <int MB, int NT, int XB> __device__ __forceinline__ void before_barrier(NoPre, const GemmTile<MB, NT, XB> &, const GemmGeom &) const {}
+    template <int MB, int NT, int XB> __device__ __forceinline__ void begin(const GemmTile<MB, NT, XB> &, const GemmGeom &) const {}
     // The same from the workgroup's LDS reduction buffer (waves that split K): copies[w * copy_stride + v * 64 + lane] is
     // accumulator register v of K-split wave w.  Here a lane takes one ROW of the tile and half of its 32 columns, adds
     // the copies in wave order and keeps a running top-2, so one exchange between the two halves finishes the row (the
     // column-wise way above needs a reduction across lanes for each of the 16 registers).  Row r of the tile lives in
     // register 4 * (r / 8) + r % 4 of the lanes 32 * ((r % 8) / 4) + column; the columns are visited in an order rotated
     // by the row, so that the 32 lanes of a half read 32 different LDS banks.
-    template <int MB, int NT>
-    __device__ __forceinline__ void rows(const float *copies, size_t copy_stride, int KW, int a, int i, const GemmTile<MB, NT> &t,
+    template <int MB, int NT, int XB>
+    __device__ __forceinline__ void rows(const float *copies, size_t copy_stride, int KW, int a, int i, const GemmTile<MB, NT, XB> &t,
                                          const GemmGeom &g) const {
         const int band = t.tile0 + i;
         if (band >= g.NTiles) return;
@@ -157,8 +158,8 @@ struct EpiTop2 {
         const int row = 32 * (t.mb0 + a) + r;
         if (h == 0 && row < g.M) reinterpret_cast<f32x4_t *>(cand)[(size_t)band * Mpad + row] = f32x4_t{q.v1, __int_as_float(q.i1), q.v2, 0.f};
     }
-    template <int MB, int NT>
-    __device__ __forceinline__ void tile(const f32x16_t &acc, int a, int i, const GemmTile<MB, NT> &t, const GemmGeom &g) const {
+    template <int MB, int NT, int XB>
+    __device__ __forceinline__ void tile(const f32x16_t &acc, int a, int i, const GemmTile<MB, NT, XB> &t, const GemmGeom &g) const {
         const int band = t.tile0 + i;
         if (band >= g.NTiles) return;
         const int col = band * 32 + (t.lane & 31);
@@ -186,18 +187,18 @@ struct EpiTop2 {
 struct EpiResid {
     float *x; int d; const float *gain; a16_t *xg; float *ss; int Mpad; int32_t *flags;
     static constexpr bool LDS_PROLOGUE = false, PAIRED = false, EXTRA_BLOCKS = false, ROWWISE = false;
-    template <int MB, int NT> __device__ __forceinline__ NoPre issue(const GemmTile<MB, NT> &, const GemmGeom &) const { return NoPre{}; }
-    template <int MB, int NT> __device__ __forceinline__ NoPre prologue(NoPre, const GemmTile<MB, NT> &, const GemmGeom &) const { return NoPre{}; }
-    template <int MB, int NT> __device__ __forceinline__ void before_barrier(NoPre, const GemmTile<MB, NT> &, const GemmGeom &) const {}
-    template <int MB, int NT> __device__ __forceinline__ void begin(const GemmTile<MB, NT> &, const GemmGeom &) const {}
-    template <int MB, int NT>
-    __device__ __forceinline__ void tile(const f32x16_t &acc, int a, int i, const GemmTile<MB, NT> &t, const GemmGeom &g) const {
+    template <int MB, int NT, int XB> __device__ __forceinline__ NoPre issue(const GemmTile<MB, NT, XB> &, const GemmGeom &) const { return NoPre{}; }
+    template <int MB, int NT, int XB> __device__ __forceinline__ NoPre prologue(NoPre, const GemmTile<MB, NT, XB> &, const GemmGeom &) const { return NoPre{}; }
+    template <int MB, int NT, int XB> __device__ __forceinline__ void before_barrier(NoPre, const GemmTile<MB, NT, XB> &, const GemmGeom &) const {}
+    template <int MB, int NT, int XB> __device__ __forceinline__ void begin(const GemmTile<MB, NT, XB> &, const GemmGeom &) const {}
+    template <int MB, int NT, int XB>
+    __device__ __forceinline__ void tile(const f32x16_t &acc, int a, int i, const GemmTile<MB, NT, XB> &t, const GemmGeom &g) const {
         if (t.tile0 + i >= g.NTiles) return;
         float *__restrict__ xp = x;
         a16_t *__restrict__ xgp = xg;
         float *__restrict__ ssp = ss;
         const int band = t.tile0 + i;
-        const int col = band * 32 + (t.lane & 31);
+        const int col = band * 32 + (t.lane & 31), hl = t.lane >> 5;
         const float gn = gain[col];
         float xo[16];
 #pragma unroll
@@ -205,20 +206,60 @@ struct EpiResid {
             const int row = acc_row(t.mb0 + a, v, t.lane);
             xo[v] = row < g.M ? xp[(size_t)row * d + col] : 0.f;
         }
+        // The band's 32 x 32 values are two tiles of the next GEMM's input (columns 0-15 and 16-31): each is put together in
+        // the wave's staging block and written with one 16-byte store per lane where all its rows exist.
+        a16_t *stage = reinterpret_cast<a16_t *>(wave_stage(t));
+        const bool full = (t.mb0 + a) * 32 + 32 <= g.M;
+        float sq[16];
+        uint32_t half2[8];
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
             const int row = acc_row(t.mb0 + a, v, t.lane);
             const float xn = xo[v] + acc[v];
-            float sq = 0.f;
+            sq[v] = 0.f;
             if (row < g.M) {
                 xp[(size_t)row * d + col] = xn;
-                xgp[x_index<true>(row, col, d)] = f2a_f(xn * gn, flags);
-                sq = xn * xn;
+                sq[v] = xn * xn;
+                if (!full) xgp[x_index<true>(row, col, d)] = f2a_f(xn * gn, flags);
             }
-#pragma unroll
-            for (int o = 16; o > 0; o >>= 1) sq += __shfl_xor(sq, o, 64);      // over the 32 columns of the band
-            if ((t.lane & 31) == 0 && row < g.M) ssp[(size_t)band * Mpad + row] = sq;
+            if (full) {
+                const uint32_t y = f2a_f(xn * gn, flags);
+                half2[v >> 1] = (v & 1) ? half2[v >> 1] | (y << 16) : y;
+            }
         }
+        if (full) {
+            const int fo = t.lane & 15;
+#pragma unroll
+            for (int side = 0; side < 2; ++side) {
+                if (((t.lane >> 4) & 1) == side) {
+#pragma unroll
+                    for (int v = 0; v < 16; ++v)
+                        stage[((fo >> 3) * 32 + 8 * (v >> 2) + 4 * hl + (v & 3)) * 8 + (fo & 7)] = (a16_t)(half2[v >> 1] >> (16 * (v & 1)));
+                }
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");           // LDS is in order within a wave; keep the compiler from reordering
+                __builtin_amdgcn_wave_barrier();
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+                const u32x4_t blk = reinterpret_cast<const u32x4_t *>(stage)[t.lane];
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                reinterpret_cast<u32x4_t *>(xgp)[((size_t)(t.mb0 + a) * (d >> 4) + 2 * band + side) * 64 + t.lane] = blk;
+            }
+        }
+        // Sums over the 32 columns of the band, all 16 rows of a half-wave together: each step a lane keeps the rows that
+        // agree with one bit of its lane number and hands the others over (15 exchanges and one across the 16-lane halves,
+        // where a sum per row takes five each).
+#pragma unroll
+        for (int hf = 8; hf > 0; hf >>= 1) {
+            const bool up = (t.lane & hf) != 0;
+#pragma unroll
+            for (int q = 0; q < hf; ++q) {
+                const float keep = up ? sq[q + hf] : sq[q], give = up ? sq[q] : sq[q + hf];
+                sq[q] = keep + __shfl_xor(give, hf, 64);
+            }
+        }
+        const float s = sq[0] + __shfl_xor(sq[0], 16, 64);                       // row index v = lane % 16
+        const int v = t.lane & 15, row = (t.mb0 + a) * 32 + 8 * (v >> 2) + 4 * hl + (v & 3);
+        if ((t.lane & 16) == 0 && row < g.M) ssp[(size_t)band * Mpad + row] = s;
     }
 };
 
@@ -231,27 +272,27 @@ template <bool DEV>
 struct EpiSiluT {
     const float *ss; int nb; int Mpad; int dmodel; float eps; a16_t *act; int F; int32_t *flags;
     static constexpr bool LDS_PROLOGUE = true, PAIRED = false, EXTRA_BLOCKS = false, ROWWISE = false;
-    template <int MB, int NT> __device__ __forceinline__ RowSumRegs issue(const GemmTile<MB, NT> &t, const GemmGeom &) const {
-        return rowsum_issue<MB>(ss, nb, Mpad, t.mb0 * 32, t.lane, t.wave, 0);
+    template <int MB, int NT, int XB> __device__ __forceinline__ RowSumRegs issue(const GemmTile<MB, NT, XB> &t, const GemmGeom &) const {
+        return rowsum_issue<XB>(ss, nb, Mpad, t.wg_mb0 * 32, t.lane, t.wave, 0);
     }
-    template <int MB, int NT> __device__ __forceinline__ NoPre prologue(RowSumRegs r, const GemmTile<MB, NT> &t, const GemmGeom &) const {
-        rowsum_finish<MB>(r, t.lds, ss, nb, Mpad, t.mb0 * 32, t.lane, t.wave);
+    template <int MB, int NT, int XB> __device__ __forceinline__ NoPre prologue(RowSumRegs r, const GemmTile<MB, NT, XB> &t, const GemmGeom &) const {
+        rowsum_finish<XB>(r, t.lds, ss, nb, Mpad, t.wg_mb0 * 32, t.lane, t.wave);
         return NoPre{};
     }
-    template <int MB, int NT> __device__ __forceinline__ void before_barrier(NoPre, const GemmTile<MB, NT> &, const GemmGeom &) const {}
-    template <int MB, int NT> __device__ __forceinline__ void begin(const GemmTile<MB, NT> &t, const GemmGeom &) const {
-        rstd_table<MB>(t.lds, t.lane, t.wave, dmodel, eps);
+    template <int MB, int NT, int XB> __device__ __forceinline__ void before_barrier(NoPre, const GemmTile<MB, NT, XB> &, const GemmGeom &) const {}
+    template <int MB, int NT, int XB> __device__ __forceinline__ void begin(const GemmTile<MB, NT, XB> &t, const GemmGeom &) const {
+        rstd_table(t, dmodel, eps);
     }
     // One band of gate|up columns gives 32 rows x 16 features of the activation: exactly one 1 KiB tile of
     // the next GEMM's input.  The wave assembles it in its LDS staging block and writes it with a single
     // 16-byte-per-lane store (rows past M hold don't-care values in the padded part of the buffer).
-    template <int MB, int NT>
-    __device__ __forceinline__ void tile(const f32x16_t &acc, int a, int i, const GemmTile<MB, NT> &t, const GemmGeom &g) const {
+    template <int MB, int NT, int XB>
+    __device__ __forceinline__ void tile(const f32x16_t &acc, int a, int i, const GemmTile<MB, NT, XB> &t, const GemmGeom &g) const {
         if (t.tile0 + i >= g.NTiles) return;
         const int c = t.lane & 31, hl = t.lane >> 5;
         const bool left = c < 16;
         const int fo = c & 15;
-        float *ws = wave_stage(t.lds, t.wave);
+        float *ws = wave_stage(t);
         a16_t *stage = reinterpret_cast<a16_t *>(ws);
         const float *rstd = ws + 256 + a * 32 + 4 * hl;
 #pragma unroll
@@ -325,15 +366,15 @@ struct EpiQkvRopeT {
         }
         asm volatile("" : : "v"(sink));                              // the loads must be issued although nothing uses them
     }
-    template <int MB, int NT> __device__ __forceinline__ QkvRopePre issue(const GemmTile<MB, NT> &t, const GemmGeom &g) const {
+    template <int MB, int NT, int XB> __device__ __forceinline__ QkvRopePre issue(const GemmTile<MB, NT, XB> &t, const GemmGeom &g) const {
         QkvRopePre p;
-        p.rs = rowsum_issue<MB>(ss, nb, Mpad, t.mb0 * 32, t.lane, t.wave, 0);
+        p.rs = rowsum_issue<XB>(ss, nb, Mpad, t.wg_mb0 * 32, t.lane, t.wave, 0);
         p.max_depth = 0;
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
             p.L[q] = -1; p.dep[q] = 0;
-            const int r = t.lane + 64 * q, m = t.mb0 * 32 + r;
-            if (t.wave == 0 && r < 32 * MB && m < g.M) {
+            const int r = t.lane + 64 * q, m = t.wg_mb0 * 32 + r;
+            if (t.wave == 0 && r < 32 * XB && m < g.M) {
                 const int b = m / T, n = m - b * T;
                 p.L[q] = seq_len[b];
                 p.dep[q] = tree->depth[n];
@@ -342,14 +383,14 @@ struct EpiQkvRopeT {
         }
         return p;
     }
-    template <int MB, int NT> __device__ __forceinline__ QkvRopeCarry prologue(const QkvRopePre &p, const GemmTile<MB, NT> &t, const GemmGeom &g) const {
-        rowsum_finish<MB>(p.rs, t.lds, ss, nb, Mpad, t.mb0 * 32, t.lane, t.wave);
+    template <int MB, int NT, int XB> __device__ __forceinline__ QkvRopeCarry prologue(const QkvRopePre &p, const GemmTile<MB, NT, XB> &t, const GemmGeom &g) const {
+        rowsum_finish<XB>(p.rs, t.lds, ss, nb, Mpad, t.wg_mb0 * 32, t.lane, t.wave);
         QkvRopeCarry c;
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
             c.pos[q] = -1; c.pagetok[q] = 0; c.bn[q] = 0;
-            const int r = t.lane + 64 * q, m = t.mb0 * 32 + r;
-            if (t.wave == 0 && r < 32 * MB && m < g.M) {
+            const int r = t.lane + 64 * q, m = t.wg_mb0 * 32 + r;
+            if (t.wave == 0 && r < 32 * XB && m < g.M) {
                 const int b = m / T, n = m - b * T, L = p.L[q];
                 const bool ok = L >= 0 && L + T <= max_pages * 16 && L + p.max_depth < max_pos;
                 if (ok) {
@@ -369,31 +410,31 @@ struct EpiQkvRopeT {
         }
         return c;
     }
-    template <int MB, int NT> __device__ __forceinline__ void before_barrier(const QkvRopeCarry &c, const GemmTile<MB, NT> &t, const GemmGeom &) const {
+    template <int MB, int NT, int XB> __device__ __forceinline__ void before_barrier(const QkvRopeCarry &c, const GemmTile<MB, NT, XB> &t, const GemmGeom &) const {
         if (t.wave != 0) return;
-        int *info = reinterpret_cast<int *>(t.lds + GEMM_LDS_ROWINFO);
+        int *info = reinterpret_cast<int *>(t.lds + t.ROWINFO);
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
             const int r = t.lane + 64 * q;
-            if (r < 32 * MB) { info[r] = c.pos[q]; info[128 + r] = c.pagetok[q]; info[256 + r] = c.bn[q]; }
+            if (r < 32 * XB) { info[r] = c.pos[q]; info[t.ROWS + r] = c.pagetok[q]; info[2 * t.ROWS + r] = c.bn[q]; }
         }
     }
-    template <int MB, int NT> __device__ __forceinline__ void begin(const GemmTile<MB, NT> &t, const GemmGeom &) const {
-        rstd_table<MB>(t.lds, t.lane, t.wave, dmodel, eps);
+    template <int MB, int NT, int XB> __device__ __forceinline__ void begin(const GemmTile<MB, NT, XB> &t, const GemmGeom &) const {
+        rstd_table(t, dmodel, eps);
     }
-    template <int MB, int NT>
-    __device__ __forceinline__ void pair4(const float (&x0)[4], const float (&x1)[4], int a, int v0, const GemmTile<MB, NT> &t, const GemmGeom &g) const {
+    template <int MB, int NT, int XB>
+    __device__ __forceinline__ void pair4(const float (&x0)[4], const float (&x1)[4], int a, int v0, const GemmTile<MB, NT, XB> &t, const GemmGeom &g) const {
         if (t.tile0 + 1 >= g.NTiles) return;
         const int c = t.lane & 31, hl = t.lane >> 5;
         const int nbs = dmodel >> 5, bph = Dh >> 5, half = Dh >> 1;
         const int sec = t.tile0 / nbs, hb = t.tile0 - sec * nbs;
         const int h = hb / bph, pb = hb - h * bph;                       // pb is even: first band of a pair
-        const int *info = reinterpret_cast<const int *>(t.lds + GEMM_LDS_ROWINFO);
-        const float *rstd = wave_stage(t.lds, t.wave) + 256;
+        const int *info = reinterpret_cast<const int *>(t.lds + t.ROWINFO) + t.row_off;
+        const float *rstd = wave_stage(t) + 256;
         const int rl0 = a * 32 + 8 * (v0 >> 2) + 4 * hl;
         int pos[4], pagetok[4], bn[4];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) { pos[q] = info[rl0 + q]; pagetok[q] = info[128 + rl0 + q]; bn[q] = info[256 + rl0 + q]; }
+        for (int q = 0; q < 4; ++q) { pos[q] = info[rl0 + q]; pagetok[q] = info[t.ROWS + rl0 + q]; bn[q] = info[2 * t.ROWS + rl0 + q]; }
         a16_t *__restrict__ kp = kpages;
         a16_t *__restrict__ vp = vpages;
         a16_t *__restrict__ qp = qbuf;
@@ -438,20 +479,20 @@ struct EpiQkvRopeT {
             }
         }
     }
-    template <int MB, int NT>
-    __device__ __forceinline__ void tile(const f32x16_t &, int, int, const GemmTile<MB, NT> &, const GemmGeom &) const {}
+    template <int MB, int NT, int XB>
+    __device__ __forceinline__ void tile(const f32x16_t &, int, int, const GemmTile<MB, NT, XB> &, const GemmGeom &) const {}
 };
 
 // Draft-head MLP layer: z = (residual ? z : 0) + SiLU(acc + bias), fp32 and as next GEMM input
 struct EpiBiasSilu {
     const float *bias; float *z; int d; int residual; a16_t *xg; int32_t *flags;
     static constexpr bool LDS_PROLOGUE = false, PAIRED = false, EXTRA_BLOCKS = false, ROWWISE = false;
-    template <int MB, int NT> __device__ __forceinline__ NoPre issue(const GemmTile<MB, NT> &, const GemmGeom &) const { return NoPre{}; }
-    template <int MB, int NT> __device__ __forceinline__ NoPre prologue(NoPre, const GemmTile<MB, NT> &, const GemmGeom &) const { return NoPre{}; }
-    template <int MB, int NT> __device__ __forceinline__ void before_barrier(NoPre, const GemmTile<MB, NT> &, const GemmGeom &) const {}
-    template <int MB, int NT> __device__ __forceinline__ void begin(const GemmTile<MB, NT> &, const GemmGeom &) const {}
-    template <int MB, int NT>
-    __device__ __forceinline__ void tile(const f32x16_t &acc, int a, int i, const GemmTile<MB, NT> &t, const GemmGeom &g) const {
+    template <int MB, int NT, int XB> __device__ __forceinline__ NoPre issue(const GemmTile<MB, NT, XB> &, const GemmGeom &) const { return NoPre{}; }
+    template <int MB, int NT, int XB> __device__ __forceinline__ NoPre prologue(NoPre, const GemmTile<MB, NT, XB> &, const GemmGeom &) const { return NoPre{}; }
+    template <int MB, int NT, int XB> __device__ __forceinline__ void before_barrier(NoPre, const GemmTile<MB, NT, XB> &, const GemmGeom &) const {}
+    template <int MB, int NT, int XB> __device__ __forceinline__ void begin(const GemmTile<MB, NT, XB> &, const GemmGeom &) const {}
+    template <int MB, int NT, int XB>
+    __device__ __forceinline__ void tile(const f32x16_t &acc, int a, int i, const GemmTile<MB, NT, XB> &t, const GemmGeom &g) const {
         if (t.tile0 + i >= g.NTiles) return;
         const int col = (t.tile0 + i) * 32 + (t.lane & 31);
         const float bv = bias[col];

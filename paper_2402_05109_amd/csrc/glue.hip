@@ -176,18 +176,9 @@ __device__ __forceinline__ size_t q_index(int b, int n, int h, int dim, int H, i
     }
 }
 
-// 16-bit family: rounded to half with the saturation flag, as the fused epilogue of the q|k|v GEMM does
-template <bool BF>
-__device__ __forceinline__ void qkv_store(typename Act<BF>::type *p, size_t i, float v, int32_t *flags) {
-    if constexpr (BF) p[i] = f2a_f(v, flags);
-    else p[i] = v;
-}
-
-template <bool BF>
-__global__ void rope_append_kernel(const float *part, int S, int part_ld, size_t split_stride, RowScale rs, const TreeDev *tree,
+__global__ void rope_append_kernel(const float *part, int S, int part_ld, size_t split_stride, const TreeDev *tree,
                                    const float *rope, const int32_t *seq_len, const int32_t *page_table,
-                                   int max_pages, int n_pages, int layer, typename Act<BF>::type *kpages,
-                                   typename Act<BF>::type *vpages, typename Act<BF>::type *qbuf, int d, int H,
+                                   int max_pages, int n_pages, int layer, float *kpages, float *vpages, float *qbuf, int d, int H,
                                    int Dh, int max_pos, int32_t *flags) {
     const int T = tree->T;
     const int m = blockIdx.x, h = blockIdx.y;
@@ -200,44 +191,125 @@ __global__ void rope_append_kernel(const float *part, int S, int part_ld, size_t
         if (threadIdx.x == 0) atomicOr(flags, FLAG_CAPACITY);
         return;
     }
-    __shared__ float sh[1];
-    const float r = row_rstd_block(rs, m, sh);
     const int half = Dh >> 1;
     const int j = threadIdx.x;
     if (j >= half) return;
     const size_t row = (size_t)m * part_ld;
-    const int c0 = h * Dh + j, c1 = c0 + half;                  // v columns (and q, k in the fp32 family): the natural order
-    // 16-bit family: the q and k weight bands of a head are packed so that the bands holding dims j and j + Dh/2 are
-    // neighbours (pack_weight_kernel, bph > 1): dim j < Dh/2 sits in band 2 * (j / 32), dim j + Dh/2 in the band behind it
-    const int p0 = BF ? h * Dh + 2 * (j >> 5) * 32 + (j & 31) : c0, p1 = BF ? p0 + 32 : c1;
-    const float q0 = r * part_sum(part, S, split_stride, row + p0), q1 = r * part_sum(part, S, split_stride, row + p1);
-    const float k0 = r * part_sum(part, S, split_stride, row + d + p0), k1 = r * part_sum(part, S, split_stride, row + d + p1);
-    const float v0 = r * part_sum(part, S, split_stride, row + 2 * d + c0), v1 = r * part_sum(part, S, split_stride, row + 2 * d + c1);
+    const int c0 = h * Dh + j, c1 = c0 + half;
+    const float q0 = part_sum(part, S, split_stride, row + c0), q1 = part_sum(part, S, split_stride, row + c1);
+    const float k0 = part_sum(part, S, split_stride, row + d + c0), k1 = part_sum(part, S, split_stride, row + d + c1);
+    const float v0 = part_sum(part, S, split_stride, row + 2 * d + c0), v1 = part_sum(part, S, split_stride, row + 2 * d + c1);
     const float cs = rope[((size_t)pos * half + j) * 2], sn = rope[((size_t)pos * half + j) * 2 + 1];
-    qkv_store<BF>(qbuf, q_index<BF>(b, n, h, j, H, Dh, T), q0 * cs - q1 * sn, flags);
-    qkv_store<BF>(qbuf, q_index<BF>(b, n, h, j + half, H, Dh, T), q1 * cs + q0 * sn, flags);
+    qbuf[q_index<false>(b, n, h, j, H, Dh, T)] = q0 * cs - q1 * sn;
+    qbuf[q_index<false>(b, n, h, j + half, H, Dh, T)] = q1 * cs + q0 * sn;
     const int page = page_table[(size_t)b * max_pages + (slot >> 4)];
     if ((unsigned)page >= (unsigned)n_pages) { atomicOr(flags, FLAG_BAD_PAGE); return; }      // bad table entry: the row's K/V are not written
     const int tok = slot & 15;
     const size_t base = kv_block_base(layer, n_pages, page, H, h, Dh);
-    qkv_store<BF>(kpages, base + k_in_block<BF>(tok, j, Dh), k0 * cs - k1 * sn, flags);
-    qkv_store<BF>(kpages, base + k_in_block<BF>(tok, j + half, Dh), k1 * cs + k0 * sn, flags);
-    qkv_store<BF>(vpages, base + v_in_block<BF>(tok, j, Dh), v0, flags);
-    qkv_store<BF>(vpages, base + v_in_block<BF>(tok, j + half, Dh), v1, flags);
+    kpages[base + k_in_block<false>(tok, j, Dh)] = k0 * cs - k1 * sn;
+    kpages[base + k_in_block<false>(tok, j + half, Dh)] = k1 * cs + k0 * sn;
+    vpages[base + v_in_block<false>(tok, j, Dh)] = v0;
+    vpages[base + v_in_block<false>(tok, j + half, Dh)] = v1;
+}
+
+// The same for the 16-bit family where the q|k|v GEMM leaves plain partial sums (launch_gemm_qkv_rope), with the row's 1/rms
+// applied here.  The q and k weight bands of a head are packed so that the bands holding dims j and j + Dh/2 are
+// neighbours (pack_weight_kernel, bph > 1): dim j < Dh/2 sits in band 2 * (j / 32), dim j + Dh/2 in the band behind it.
+// A workgroup takes the tokens of one row that fall into one cache page, up to 16, for one head: a thread holds four
+// neighbouring pairs (j, j + Dh/2) of q, k and v of one token (six 16-byte loads per partial, 8-byte stores of q and K), and
+// V, whose block is [dim][token], is turned round in LDS and leaves as whole 16-byte pieces where the page's 16 tokens are
+// all new.  One thread per pair and one wave per (token, head), two bytes per store, took 26.1 us at 256 tokens x 52 heads
+// with three partials; four pairs per thread without the page grouping 21.1 us with one.
+template <int DH>
+__global__ __launch_bounds__(DH * 2) void rope_append16_kernel(
+    const float *__restrict__ part, int S, int part_ld, size_t split_stride, RowScale rs, const TreeDev *tree, const float *__restrict__ rope,
+    const int32_t *seq_len, const int32_t *page_table, int max_pages, int n_pages, int layer, a16_t *__restrict__ kpages,
+    a16_t *__restrict__ vpages, a16_t *__restrict__ qbuf, int d, int H, int T, int max_pos, int groups, int32_t *flags) {
+    typedef __attribute__((ext_vector_type(4))) float f4;
+    typedef __attribute__((ext_vector_type(2))) uint32_t u2;
+    typedef __attribute__((ext_vector_type(4))) uint32_t u4;
+    constexpr int half = DH / 2, TPT = half / 4;                     // threads per token
+    __shared__ u4 vblk[DH * 2];                                      // one page's V block: [dim][16 tokens]
+    const int b = blockIdx.x / groups, grp = blockIdx.x - b * groups, h = blockIdx.y;
+    const int L = seq_len[b];
+    const int max_depth = tree->max_depth;
+    const int slot0 = (L >> 4) * 16 + grp * 16;                      // first slot of the page
+    const int tok = threadIdx.x / TPT, j = (threadIdx.x % TPT) * 4;
+    const int n = slot0 + tok - L;
+    if (L < 0 || L + T > max_pages * 16 || L + max_depth >= max_pos) {                        // the same for every thread
+        if (threadIdx.x == 0) atomicOr(flags, FLAG_CAPACITY);
+        return;
+    }
+    if (slot0 >= L + T) return;                                      // fewer pages than the longest alignment needs
+    const int page = page_table[(size_t)b * max_pages + (slot0 >> 4)];
+    const bool live = n >= 0 && n < T, kv = (unsigned)page < (unsigned)n_pages;
+    const bool whole = slot0 >= L && slot0 + 16 <= L + T;            // every token of the page is new
+    if (!kv && threadIdx.x == 0) atomicOr(flags, FLAG_BAD_PAGE);      // bad table entry: the tokens' K/V are not written
+    const int m = b * T + (live ? n : 0);
+    const size_t row = (size_t)m * part_ld;
+    const int p0 = h * DH + 2 * (j >> 5) * 32 + (j & 31), c0 = h * DH + j;
+    const size_t at[6] = {row + p0, row + p0 + 32, row + d + p0, row + d + p0 + 32, row + 2 * d + c0, row + 2 * d + c0 + half};
+    f4 x[6];
+#pragma unroll
+    for (int i = 0; i < 6; ++i) x[i] = *reinterpret_cast<const f4 *>(part + at[i]);
+    const int pos = L + tree->depth[live ? n : 0];
+    const f4 t0 = *reinterpret_cast<const f4 *>(rope + ((size_t)pos * half + j) * 2), t1 = *reinterpret_cast<const f4 *>(rope + ((size_t)pos * half + j) * 2 + 4);
+    float sq = 0.f;
+    for (int q = threadIdx.x % TPT; q < rs.nb; q += TPT) sq += rs.ss[(size_t)q * rs.Mpad + m];
+    for (int s = 1; s < S; ++s)                                      // added in split order
+#pragma unroll
+        for (int i = 0; i < 6; ++i) x[i] += *reinterpret_cast<const f4 *>(part + (size_t)s * split_stride + at[i]);
+#pragma unroll
+    for (int o = 1; o < TPT; o <<= 1) sq += __shfl_xor(sq, o, 64);
+    const float r = 1.0f / sqrtf(sq / (float)rs.d + rs.eps);
+    const float cs[4] = {t0[0], t0[2], t1[0], t1[2]}, sn[4] = {t0[1], t0[3], t1[1], t1[3]};
+    float y0[4], y1[4];
+    auto rotate = [&](const f4 &u, const f4 &w) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const float a = r * u[e], c = r * w[e];
+            y0[e] = a * cs[e] - c * sn[e];
+            y1[e] = c * cs[e] + a * sn[e];
+        }
+    };
+    auto put = [&](a16_t *p, const float (&y)[4]) { *reinterpret_cast<u2 *>(p) = u2{f2a_pack_f(y[0], y[1], flags), f2a_pack_f(y[2], y[3], flags)}; };
+    const size_t base = kv_block_base(layer, n_pages, kv ? page : 0, H, h, DH);
+    if (live) {
+        rotate(x[0], x[1]);
+        put(qbuf + q_index<true>(b, n, h, j, H, DH, T), y0);
+        put(qbuf + q_index<true>(b, n, h, j + half, H, DH, T), y1);
+        if (kv) {
+            rotate(x[2], x[3]);
+            put(kpages + base + k_in_block<true>(tok, j, DH), y0);
+            put(kpages + base + k_in_block<true>(tok, j + half, DH), y1);
+            a16_t *vd = whole ? reinterpret_cast<a16_t *>(vblk) : vpages + base;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                vd[v_in_block<true>(tok, j + e, DH)] = f2a_f(r * x[4][e], flags);
+                vd[v_in_block<true>(tok, j + half + e, DH)] = f2a_f(r * x[5][e], flags);
+            }
+        }
+    }
+    if (whole && kv) {                                               // the same for every thread
+        __syncthreads();
+        reinterpret_cast<u4 *>(vpages + base)[threadIdx.x] = vblk[threadIdx.x];
+    }
 }
 
 int launch_rope_append(hydra_ctx *c, hipStream_t s, const float *part, int S, int part_ld, size_t split_stride,
                        RowScale rs, int B, int layer, const int32_t *seq_len, const hydra_kv *kv, void *qbuf,
                        int32_t *flags) {
-    const int T = c->tree.T;
-    dim3 grid(B * T, c->m.n_heads), block(64);
-    // the bf16 family does this step in the epilogue of its q|k|v GEMM unless the plan splits K (launch_gemm_qkv_rope)
+    const int T = c->tree.T, H = c->m.n_heads, Dh = c->m.head_dim;
     if (c->bf16) {
-        hipLaunchKernelGGL(rope_append_kernel<true>, grid, block, 0, s, part, S, part_ld, split_stride, rs, tree_dev(c), rope_dev(c), seq_len, kv->page_table, kv->max_pages, kv->n_pages, layer, (a16_t *)kv->k_pages, (a16_t *)kv->v_pages, (a16_t *)qbuf, c->m.d, c->m.n_heads, c->m.head_dim, c->m.max_pos, flags);
-        HYDRA_LAUNCH_CHECK("rope_append_kernel");
+        const int groups = ceil_div(T + 15, 16);              // pages that T tokens can touch, whatever their alignment
+        dim3 grid(B * groups, H);
+#define ROPE16(DHv) hipLaunchKernelGGL(rope_append16_kernel<DHv>, grid, dim3(DHv * 2), 0, s, part, S, part_ld, split_stride, rs, tree_dev(c), rope_dev(c), seq_len, kv->page_table, kv->max_pages, kv->n_pages, layer, (a16_t *)kv->k_pages, (a16_t *)kv->v_pages, (a16_t *)qbuf, c->m.d, H, T, c->m.max_pos, groups, flags)
+        if (Dh == 128) ROPE16(128); else ROPE16(64);
+#undef ROPE16
+        HYDRA_LAUNCH_CHECK("rope_append16_kernel");
         return HYDRA_OK;
     }
-    hipLaunchKernelGGL(rope_append_kernel<false>, grid, block, 0, s, part, S, part_ld, split_stride, rs, tree_dev(c), rope_dev(c), seq_len, kv->page_table, kv->max_pages, kv->n_pages, layer, (float *)kv->k_pages, (float *)kv->v_pages, (float *)qbuf, c->m.d, c->m.n_heads, c->m.head_dim, c->m.max_pos, flags);
+    hipLaunchKernelGGL(rope_append_kernel, dim3(B * T, H), dim3(64), 0, s, part, S, part_ld, split_stride, tree_dev(c), rope_dev(c), seq_len, kv->page_table, kv->max_pages, kv->n_pages, layer, (float *)kv->k_pages, (float *)kv->v_pages, (float *)qbuf, c->m.d, H, Dh, c->m.max_pos, flags);
     HYDRA_LAUNCH_CHECK("rope_append_kernel");
     return HYDRA_OK;
 }

@@ -46,6 +46,7 @@ struct GemmPlan {      // launch shape of one weight-streaming GEMM (bf16 family
     int splits;        // workgroups along K (each writes its own partial output)
     int kpw;           // k-steps (of 16) per wave
     int shared_x;      // 0, or the number of waves (4 or 8) of the many-rows variant that shares X tiles through LDS
+    int tile;          // 0, or the tile of the many-rows kernel with both operands in LDS (bf16_gemm_tile.hip); mb, nt: the whole tile's
     float cost_us;     // the planner's estimate
 };
 
@@ -101,8 +102,10 @@ struct WsLayout {
     int attn_units;     // split-KV units per (row, head, query group)
 };
 WsLayout ws_layout(const hydra_ctx *c, int B);
-enum { GEMM_KIND_PLAIN = 0, GEMM_KIND_FUSED = 1, GEMM_KIND_PAIRS = 2, GEMM_KIND_SWIGLU = 3 };   // plain output (may split K) / fused epilogue / q|k|v band pairs / gate-up (fused, up to five bands per wave)
+// plain output (may split K) / fused epilogue / q|k|v band pairs / gate-up (fused, up to five bands per wave) / fused residual
+enum { GEMM_KIND_PLAIN = 0, GEMM_KIND_FUSED = 1, GEMM_KIND_PAIRS = 2, GEMM_KIND_SWIGLU = 3, GEMM_KIND_RESID = 4 };
 GemmPlan plan_gemm(const hydra_ctx *c, int M, int N, int K, int kind);
+bool     plan_tile(const hydra_ctx *c, int M, int N, int K, int kind, GemmPlan *p);      // fills *p: the cheapest tile of bf16_gemm_tile.hip
 int      attn_units(const hydra_ctx *c, int B);
 
 // ---- launchers (each enqueues on `s` and returns a hydra_status) -----------
@@ -120,6 +123,7 @@ int launch_gemm_silu(hydra_ctx *c, hipStream_t s, const void *X, const void *W, 
 int launch_gemm_bias_silu(hydra_ctx *c, hipStream_t s, const void *X, const void *W, int M, int N, int K,
                           const float *bias, float *z, bool residual, void *xg);
 int gemm_max_dynamic_lds(hydra_ctx *c);
+int gemm_tile_max_dynamic_lds();
 int attn_max_dynamic_lds(hydra_ctx *c);
 // per-row 1/rms from the per-band sums of squares ss[band][Mpad] (bf16 family); ss == NULL: no scaling
 struct RowScale { const float *ss; int nb; int Mpad; int d; float eps; };

@@ -32,7 +32,8 @@ static double env_or(const char *name, double dflt) {
 GemmPlan plan_gemm(const hydra_ctx *c, int M, int N, int K, int kind) {
     // model constants; the environment overrides exist for tuning runs only
     static const double cap_gbps = env_or("HYDRA_PLAN_CAP", 45.0);        // L1-miss bytes one CU can pull, GB/s
-    static const double hbm_tbps = env_or("HYDRA_PLAN_HBM", 6.0);         // achievable HBM stream, TB/s
+    static const double hbm_env = env_or("HYDRA_PLAN_HBM", 0.0);          // achievable HBM stream, TB/s:
+    const double hbm_tbps = hbm_env > 0.0 ? hbm_env : M <= 32 ? 7.2 : 6.0;  // one row block 12288 x 4096 17.7 us, two 20..24 us
     static const double split_us = env_or("HYDRA_PLAN_SPLIT_US", 0.5);    // cost of reading one more partial back, us
     static const int max_split = (int)env_or("HYDRA_PLAN_MAX_SPLIT", 8);
     GemmPlan p;
@@ -53,6 +54,10 @@ GemmPlan plan_gemm(const hydra_ctx *c, int M, int N, int K, int kind) {
     const double split_charge = split_us * (M > 64 ? M / 32.0 : 1.0);
     const bool may_split = kind == GEMM_KIND_PLAIN;
     p.nw = 1;
+    // rows of X that a workgroup's loads touch: an X tile's 128-byte lines hold 8 rows each, and lanes past M repeat the last row
+    // (counted for one row block only: the shapes for two were fitted with all 64 rows, and 54 rows run 4 % slower on the
+    // ones that 56 would pick)
+    const int x_rows = p.mb == 1 ? std::min(32, ceil_div(M, 8) * 8) : p.mb * 32;
     // bands per wave: accumulators MB*NT*16 plus two prefetch sets must fit the register file
     int nt_max = pairs ? (p.mb == 4 ? 2 : 4) : (p.mb == 4 ? 3 : 4);   // pairs: one or two band pairs per wave
     if (kind == GEMM_KIND_SWIGLU && p.mb == 2) nt_max = 5;             // the widest instantiation (very wide FFNs: one round instead of two)
@@ -65,7 +70,7 @@ GemmPlan plan_gemm(const hydra_ctx *c, int M, int N, int K, int kind) {
             const int wgs = groups * s * mgroups;
             const int rounds = ceil_div(wgs, 256);                     // workgroups on the busiest CU
             const double w_bytes = (double)nt * 32 * K * 2 / s;         // per workgroup
-            const double x_bytes = (double)p.mb * 32 * K * 2 / s;
+            const double x_bytes = (double)x_rows * K * 2 / s;
             double cost = rounds * (w_bytes + x_bytes) / (cap_gbps * 1e3);   // us at the per-CU limit
             const double hbm = (double)N * K * 2 / (hbm_tbps * 1e6);         // us at the HBM limit
             if (cost < hbm) cost = hbm;
@@ -83,6 +88,11 @@ GemmPlan plan_gemm(const hydra_ctx *c, int M, int N, int K, int kind) {
     p.cost_us = (float)best_cost;
     const int max_waves = (p.mb * p.nt >= 6) ? 4 : 8;                   // 256-thread workgroups get 512 VGPRs per wave
     p.kw = max_waves;
+    // One row block: four waves with twice the run each (17.7 against 18.6 us for 12288 x 4096 at one row, 16.1 against 17.0 for
+    // 6656 x 6656, 41.1 against 44.1 for 32000 x 4096 at 32), except four bands per wave, where four waves have too little in
+    // flight (48.5 against 44.5 us, 27648 x 5120), and beyond four rounds (80 against 73 us, 35840 x 6656).  Fused epilogues
+    // keep eight waves, over which they are spread (q|k|v 20.0 against 20.4 us, 28.6 against 29.5 at the 13B shape).
+    if (kind == GEMM_KIND_PLAIN && p.mb == 1 && p.nt <= 3 && ceil_div(bands, p.nt) * p.splits <= 1024) p.kw = 4;
     if (p.kw == 8 && p.splits > 1 && KT / (8 * p.splits) >= 16) p.kw = 4;   // split K with long runs left: four waves with twice the run each measured faster
     while (p.kw > 1 && KT / (p.kw * p.splits) < 4) p.kw >>= 1;
     while (p.kw > 1 && ((size_t)GEMM_LDS_SCRATCH + (size_t)p.kw * p.mb * p.nt * 16 * 64) * 4 > 150 * 1024) p.kw >>= 1;   // LDS: KW accumulator copies

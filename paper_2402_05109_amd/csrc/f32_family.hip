@@ -8,79 +8,64 @@ namespace hydra {
 typedef __attribute__((ext_vector_type(4))) float f32x4_t;
 typedef float f32x4_u __attribute__((ext_vector_type(4), aligned(4)));      // the caller's pages: no more than float alignment is known
 
-// Sums v[0..R) over the 64 lanes, R a power of two up to 16: afterwards lane l holds the sum of v[l % R] in v[0].  Each
-// step halves the values a lane carries: it keeps those whose index agrees with one bit of its lane number and hands the
-// others to its partner, so R sums take R - 1 + log2(64 / R) exchanges instead of 6 R.
-template <int R>
-__device__ __forceinline__ float lanes_sum(float (&v)[R], int lane) {
-#pragma unroll
-    for (int half = R / 2; half > 0; half >>= 1) {
-        const bool up = (lane & half) != 0;
-#pragma unroll
-        for (int i = 0; i < half; ++i) {
-            const float keep = up ? v[i + half] : v[i], give = up ? v[i] : v[i + half];
-            v[i] = keep + __shfl_xor(give, half, 64);
-        }
-    }
-    float s = v[0];
-#pragma unroll
-    for (int o = R; o < 64; o <<= 1) s += __shfl_xor(s, o, 64);
-    return s;
-}
-
-// part[m][n] = sum_k X[m][k] W[n][k].  One wave per output feature n and R rows of X; lanes stride over k, four
-// consecutive k a lane where K is a multiple of four (rows are then 16-byte aligned), then one reduction over the lanes
-// for all R rows together.  Bound by the latency of one or two rounds of loads and of the reduction: with single floats
-// and a separate wave reduction per row a launch of the tiny shape (16 rows, K = 256) took 6.2 us, and 8.3 on average
-// over a generation; R follows the rows of the call so that a draft phase of a few rows does not load sixteen.
-template <int R, bool VEC>
+// part[m][n] = sum_k X[m][k] W[n][k] on the fp32 matrix instruction (16 x 16 x 4, fp32 products and sums).  A workgroup
+// computes 16 rows x 16 features; its four waves take the 16-long pieces of K in turn and meet in LDS.
+// Lane (r, g) loads four consecutive k of row r and of feature r at piece + 4 g, and instruction e of a piece multiplies the
+// k of every lane's element e: the four lane groups hold different k, the same ones on both sides, so no data is moved
+// between lanes.  Bound by one round of loads (four pieces in flight per wave) and the meeting.  With a feature per wave, 16
+// rows per lane and a reduction over the lanes a launch of the tiny shape (16 rows, K = 256 or 688) took 8.3 us on average,
+// 8.9 with a shared reduction and 16-byte loads.
+// Rows and features past the end repeat the last one and are not stored; k past K is zero on both sides.
+template <bool VEC>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(const float *__restrict__ X, const float *__restrict__ W,
                                                         float *__restrict__ part, int M, int N, int K, int ld) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int n = blockIdx.x * 4 + wave;
-    const int m0 = blockIdx.y * R;
-    if (n >= N) return;                                              // whole waves
-    float acc[R];
-    const float *xr[R];
+    __shared__ f32x4_t red[4][64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, r = lane & 15, g = lane >> 4;
+    const int n0 = blockIdx.x * 16, m0 = blockIdx.y * 16;
+    const float *xr = X + (size_t)min(m0 + r, M - 1) * K + 4 * g, *wr = W + (size_t)min(n0 + r, N - 1) * K + 4 * g;
+    auto four = [&](const float *p, int k) {
+        f32x4_t v = {0.f, 0.f, 0.f, 0.f};
+        if (VEC) {
+            if (k + 4 * g < K) v = *reinterpret_cast<const f32x4_t *>(p + k);       // K % 4 == 0: all four or none
+        } else {
 #pragma unroll
-    for (int i = 0; i < R; ++i) { acc[i] = 0.f; xr[i] = X + (size_t)min(m0 + i, M - 1) * K; }
-    const float *wr = W + (size_t)n * K;
-    if (VEC) {
-        for (int k = lane * 4; k < K; k += 256) {
-            const f32x4_t w = *reinterpret_cast<const f32x4_t *>(wr + k);
-            f32x4_t x[R];
-#pragma unroll
-            for (int i = 0; i < R; ++i) x[i] = *reinterpret_cast<const f32x4_t *>(xr[i] + k);
-#pragma unroll
-            for (int i = 0; i < R; ++i) {
-#pragma unroll
-                for (int e = 0; e < 4; ++e) acc[i] = fmaf(x[i][e], w[e], acc[i]);
-            }
+            for (int e = 0; e < 4; ++e)
+                if (k + 4 * g + e < K) v[e] = p[k + e];
         }
-    } else {
-        for (int k = lane; k < K; k += 64) {
-            const float w = wr[k];
+        return v;
+    };
+    f32x4_t part_acc[4][4];                                            // a sum per (piece, element): chains of K / 256 products, added as a tree
 #pragma unroll
-            for (int i = 0; i < R; ++i) acc[i] = fmaf(xr[i][k], w, acc[i]);
-        }
+    for (int u = 0; u < 4; ++u)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) part_acc[u][e] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    for (int k0 = wave * 16; k0 < K; k0 += 256) {
+        f32x4_t a[4], b[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) { a[u] = four(xr, k0 + 64 * u); b[u] = four(wr, k0 + 64 * u); }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) part_acc[u][e] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u][e], b[u][e], part_acc[u][e], 0, 0, 0);
     }
-    const float s = lanes_sum<R>(acc, lane);
-    if (lane < R && m0 + lane < M) part[(size_t)(m0 + lane) * ld + n] = s;
+    f32x4_t by_piece[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) by_piece[u] = (part_acc[u][0] + part_acc[u][1]) + (part_acc[u][2] + part_acc[u][3]);
+    const f32x4_t acc = (by_piece[0] + by_piece[1]) + (by_piece[2] + by_piece[3]);
+    red[wave][lane] = acc;                                            // acc[v]: row 4 g + v, feature r
+    __syncthreads();
+    const int m = threadIdx.x >> 4, n = threadIdx.x & 15;
+    const int from = (m >> 2) * 16 + n;
+    const float s = (red[0][from][m & 3] + red[1][from][m & 3]) + (red[2][from][m & 3] + red[3][from][m & 3]);
+    if (m0 + m < M && n0 + n < N) part[(size_t)(m0 + m) * ld + n0 + n] = s;
 }
 
 int launch_gemm_f32(hydra_ctx *c, hipStream_t s, const float *X, const float *W, float *part, int M, int N, int K) {
     (void)c;
     // K % 4 == 0: X and W start at 256-byte boundaries of the workspace and the arena, so every row is 16-byte aligned
-    const bool vec = K % 4 == 0;
-    const int r = M <= 1 ? 1 : M <= 2 ? 2 : M <= 4 ? 4 : M <= 8 ? 8 : 16;
-    dim3 grid(ceil_div(N, 4), ceil_div(M, r)), block(256);
-#define GEMM_F32(Rv)                                                                                                  \
-    case Rv:                                                                                                          \
-        if (vec) hipLaunchKernelGGL((gemm_f32_kernel<Rv, true>), grid, block, 0, s, X, W, part, M, N, K, N);            \
-        else     hipLaunchKernelGGL((gemm_f32_kernel<Rv, false>), grid, block, 0, s, X, W, part, M, N, K, N);           \
-        break
-    switch (r) { GEMM_F32(1); GEMM_F32(2); GEMM_F32(4); GEMM_F32(8); GEMM_F32(16); }
-#undef GEMM_F32
+    dim3 grid(ceil_div(N, 16), ceil_div(M, 16)), block(256);
+    if (K % 4 == 0) hipLaunchKernelGGL(gemm_f32_kernel<true>, grid, block, 0, s, X, W, part, M, N, K, N);
+    else            hipLaunchKernelGGL(gemm_f32_kernel<false>, grid, block, 0, s, X, W, part, M, N, K, N);
     HYDRA_LAUNCH_CHECK("gemm_f32_kernel");
     return HYDRA_OK;
 }

@@ -103,3 +103,36 @@ def test_typical_acceptance_at_the_edges_of_a_piece(V):
             cdf = np.cumsum(q)                                          # fp32 sums of V terms: within 1e-5 of the 64-bit distribution
             assert q[got] > 0 and (cdf[got] - q[got]) - 1e-5 <= float(uu[b]) <= cdf[got] + 1e-5, (b, got)
     assert compared >= B
+
+
+@pytest.mark.parametrize("V,distinct", [(40, 1), (1500, 1), (1500, 7), (5000, 300), (32768, 2)])
+def test_draft_ties_take_the_lowest_ids(V, distinct):
+    """Rows of the vocabulary projection repeat, so whole groups of logits are equal bit for bit: more entries at the bound
+    than a wave has lanes, fewer, and all of them.  Order: value descending, then id ascending."""
+    parent = [-1] + [0] * 32 + [1] * 10 + [2] * 3
+    cfg = small_shape(d=128, NL=1, H=2, Dh=64, F=176, V=V, K=2, T=len(parent))
+    W = make_weights(cfg)
+    g = torch.Generator().manual_seed(V + distinct)
+    for i in (1, 2):
+        W[f"heads.{i}.wout"] = W[f"heads.{i}.wout"][:distinct][torch.randint(0, distinct, (V,), generator=g)].contiguous()
+    sess = gpu_session(cfg, parent, 2, 32, W)
+    sess.h_last.normal_()
+    sess.root.copy_(torch.tensor([3, V - 1], dtype=torch.int32))
+    sess.draft()
+    torch.cuda.synchronize()
+    toks = sess.out().tree_tokens.cpu()
+    for b in range(2):
+        for n, kids in ((0, range(1, 33)), (1, range(33, 43)), (2, range(43, 46))):
+            i, path = (1, [0]) if n == 0 else (2, [0, n])
+            u = torch.cat([sess.h_last[b].cpu()] + [W["embed"][int(toks[b, p])] for p in path]).double()
+            z = W[f"heads.{i}.w1"].double() @ u + W[f"heads.{i}.b1"].double()
+            lg = W[f"heads.{i}.wout"].double() @ (z * torch.sigmoid(z))
+            got = [int(toks[b, c]) for c in kids]
+            want = lg[torch.tensor(got)]
+            best = torch.sort(lg, descending=True).values[:len(got)]
+            assert torch.allclose(want, best, rtol=0, atol=2e-5 * float(lg.abs().max()))      # fp32 sums against 64 bits
+            for a, c in zip(got, got[1:]):                            # equal rows have equal logits: ids ascend, none is skipped
+                assert (W[f"heads.{i}.wout"][a] != W[f"heads.{i}.wout"][c]).any() or a < c
+            for t in got:
+                same = (W[f"heads.{i}.wout"] == W[f"heads.{i}.wout"][t]).all(1).nonzero().flatten().tolist()
+                assert all(x in got for x in same if x < t)

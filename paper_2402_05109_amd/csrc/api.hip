@@ -438,21 +438,25 @@ struct RowSource {
 // verify step); otherwise the residual stream after the last layer is left in the workspace's x.
 // LM head, greedy token and margin of the 16-bit family (paper, section 2: the base model's next-token choice at every
 // tree node).  Without a logits buffer the GEMM's epilogue reduces every band to its two best columns and a small
-// kernel merges the bands; with one, the logits go through memory and argmax_kernel reads them back.
-static int lm_head_tail(hydra_ctx *c, hipStream_t s, const void *xg, float *part, int M, RowScale rs, int Mpad, int32_t *argmax,
-                        float *margin, float *logits) {
+// kernel merges the bands (opt-in); otherwise the sums go through memory and two kernels scale, reduce and finish them.
+static int lm_head_tail(hydra_ctx *c, hipStream_t s, const float *x, const void *xg, float *part, void *cand, int M, RowScale rs, int Mpad,
+                        float *hidden, int32_t *argmax, float *margin, float *logits) {
     const int d = c->m.d, V = c->m.vocab;
     const int ld_v = gemm_npad(c, V);
     const size_t mp = align_up(M, 32);
+    const float *gain = (const float *)(c->arena + c->off_final_norm);
     int rc;
     if (!logits && (size_t)ceil_div(V, 32) * Mpad * 16 <= (size_t)mp * ld_v * 4) {
         int fused = 0;
         if ((rc = launch_gemm_top2(c, s, xg, c->arena + c->off_lm_head, M, V, d, part, Mpad, &fused))) return rc;
-        if (fused) return launch_argmax_bands(c, s, part, ceil_div(V, 32), Mpad, rs, M, argmax, margin);
+        if (fused) {
+            if ((rc = launch_final_hidden(c, s, x, gain, rs, hidden, M))) return rc;
+            return launch_argmax_bands(c, s, part, ceil_div(V, 32), Mpad, rs, M, argmax, margin);
+        }
     }
     GemmPlan p;
     if ((rc = launch_gemm(c, s, xg, c->arena + c->off_lm_head, part, M, V, d, &p))) return rc;
-    return launch_argmax(c, s, part, p.splits, ld_v, mp * ld_v, rs, M, argmax, margin, logits);
+    return launch_lm_tail(c, s, part, p.splits, ld_v, mp * ld_v, rs, M, cand, x, gain, hidden, argmax, margin, logits);
 }
 
 static int forward_layers(hydra_ctx *c, hipStream_t s, int B, void *ws, const RowSource &src, const int32_t *seq_len,
@@ -482,8 +486,7 @@ static int forward_layers(hydra_ctx *c, hipStream_t s, int B, void *ws, const Ro
             if ((rc = launch_embed_prep(c, s, src.tokens, io.x_first, gain0, io.xg_first, io.ss_first, io.Mpad, M, flags))) return rc;
             if ((rc = launch_layers_mega(c, s, B, W + w.mega, seq_len, kv, flags, &io, true))) return rc;
             const RowScale rl = {io.ss_last, io.nb_last, io.Mpad, d, c->m.rms_eps};
-            if ((rc = launch_final_hidden(c, s, io.x_last, (const float *)(A + c->off_final_norm), rl, hidden, M))) return rc;
-            return lm_head_tail(c, s, io.xg_last, part, M, rl, io.Mpad, argmax, margin, logits);
+            return lm_head_tail(c, s, io.x_last, io.xg_last, part, apart, M, rl, io.Mpad, hidden, argmax, margin, logits);
         }
         if (src.tokens) { if ((rc = launch_embed_prep(c, s, src.tokens, x, gain0, xa, ss, Mpad, M, flags))) return rc; }
         else            { if ((rc = launch_gather_prep(c, s, B, src.hidden, src.T_src, src.path, src.n_acc, x, gain0, xa, ss, Mpad, flags))) return rc; }
@@ -497,8 +500,7 @@ static int forward_layers(hydra_ctx *c, hipStream_t s, int B, void *ws, const Ro
             if ((rc = launch_gemm_resid(c, s, xb, A + o.wdown, M, d, F, x, next_gain, xa, ss, Mpad, part, &rs.nb))) return rc;
         }
         if (!lm_tail) return HYDRA_OK;
-        if ((rc = launch_final_hidden(c, s, x, (const float *)(A + c->off_final_norm), rs, hidden, M))) return rc;
-        return lm_head_tail(c, s, xa, part, M, rs, Mpad, argmax, margin, logits);
+        return lm_head_tail(c, s, x, xa, part, apart, M, rs, Mpad, hidden, argmax, margin, logits);       // the attention's partial records are free again
     }
     if (src.tokens) { if ((rc = launch_embed(c, s, src.tokens, x, M, flags))) return rc; }
     else            { if ((rc = launch_gather_prep(c, s, B, src.hidden, src.T_src, src.path, src.n_acc, x, nullptr, nullptr, nullptr, 0, flags))) return rc; }
@@ -520,7 +522,7 @@ static int forward_layers(hydra_ctx *c, hipStream_t s, int B, void *ws, const Ro
     if ((rc = launch_rmsnorm(c, s, x, part, S_prev, ld_d, mp * ld_d, (const float *)(A + c->off_final_norm), xa, M, lm_tail ? hidden : nullptr))) return rc;
     if (!lm_tail) return HYDRA_OK;
     if ((rc = launch_gemm(c, s, xa, A + c->off_lm_head, part, M, V, d, &p))) return rc;
-    if ((rc = launch_argmax(c, s, part, p.splits, ld_v, mp * ld_v, none, M, argmax, margin, logits))) return rc;
+    if ((rc = launch_argmax(c, s, part, p.splits, ld_v, mp * ld_v, M, argmax, margin, logits))) return rc;
     return HYDRA_OK;
 }
 

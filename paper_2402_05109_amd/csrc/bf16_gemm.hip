@@ -7,6 +7,7 @@
 #include <type_traits>
 
 #include <algorithm>
+#include <atomic>
 
 #include <hip/hip_ext.h>
 
@@ -419,6 +420,13 @@ static hipError_t set_attr_all() {
 // opt in to the full LDS for every instantiation (a no-op for those that need less)
 int gemm_max_dynamic_lds(hydra_ctx *c) {
     (void)c;
+    // once per device: the attribute belongs to the kernels, not to a context, and setting it for all of them takes as long
+    // as the rest of hydra_bind_weights (threads that race here set the same values)
+    static std::atomic<uint64_t> done{0};
+    int dev = -1;
+    HYDRA_HIP(hipGetDevice(&dev));
+    const uint64_t bit = dev >= 0 && dev < 64 ? 1ull << dev : 0ull;
+    if (bit & done.load(std::memory_order_acquire)) return HYDRA_OK;
     hipError_t e = set_attr_all<EpiPlain>();
     if (e == hipSuccess) e = set_attr_all<EpiResid>();
     if (e == hipSuccess) e = set_attr_all<EpiTop2>();
@@ -431,7 +439,9 @@ int gemm_max_dynamic_lds(hydra_ctx *c) {
     if (e == hipSuccess) e = set_attr<1, 4, EpiQkvRope>();
     if (e == hipSuccess) e = set_attr<2, 4, EpiQkvRope>();
     if (e != hipSuccess) return hip_fail(e, "hipFuncSetAttribute(gemm_bf16_kernel)");
-    return gemm_tile_max_dynamic_lds();
+    const int rc = gemm_tile_max_dynamic_lds();
+    if (rc == HYDRA_OK) done.fetch_or(bit, std::memory_order_release);
+    return rc;
 }
 
 // ---------------------------------------------------------------------------

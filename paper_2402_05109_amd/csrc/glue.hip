@@ -2,6 +2,8 @@
 // embedding gather, residual + RMSNorm, rotary + KV append, SiLU*up,
 // LM-head argmax, plain <-> in-page KV conversion.  Each kernel is written once
 // and instantiated for the two storage families (BF = bf16, !BF = fp32).
+#include <algorithm>
+
 #include "device_common.h"
 #include "internal.h"
 
@@ -365,16 +367,13 @@ int launch_silu_mul(hydra_ctx *c, hipStream_t s, const float *part, int S, int p
 // lowest id among the maxima; margin = top-1 minus top-2 value.
 // ---------------------------------------------------------------------------
 
-// One workgroup of 1024 threads per row.  VEC: rows of `part` are 16-byte aligned (row stride a multiple
+// fp32 family: one workgroup of 1024 threads per row.  VEC: rows of `part` are 16-byte aligned (row stride a multiple
 // of 4), so a thread takes four consecutive logits per load and keeps four loads in flight.
 template <bool VEC>
 __global__ __launch_bounds__(1024) void argmax_kernel(const float *__restrict__ part, int S, int part_ld, size_t split_stride,
-                                                       RowScale rs, int V, int32_t *argmax, float *margin,
-                                                       float *__restrict__ logits) {
+                                                       int V, int32_t *argmax, float *margin, float *__restrict__ logits) {
     typedef __attribute__((ext_vector_type(4))) float f4;
     const int m = blockIdx.x;
-    __shared__ float sh[1];
-    const float r = row_rstd_block(rs, m, sh);
     Top2 t = {-INFINITY, 0x7fffffff, -INFINITY};
     const float *row = part + (size_t)m * part_ld;
     if (VEC) {
@@ -396,7 +395,7 @@ __global__ __launch_bounds__(1024) void argmax_kernel(const float *__restrict__ 
                 for (int e = 0; e < 4; ++e) {
                     const int v = 4 * g + e;
                     if (v >= V) continue;
-                    const float y = r * x[u][e];
+                    const float y = x[u][e];
                     if (logits) logits[(size_t)m * V + v] = y;
                     top2_push(t, y, v);
                 }
@@ -404,7 +403,7 @@ __global__ __launch_bounds__(1024) void argmax_kernel(const float *__restrict__ 
         }
     } else {
         for (int v = threadIdx.x; v < V; v += 1024) {
-            const float x = r * part_sum(part, S, split_stride, (size_t)m * part_ld + v);
+            const float x = part_sum(part, S, split_stride, (size_t)m * part_ld + v);
             if (logits) logits[(size_t)m * V + v] = x;
             top2_push(t, x, v);
         }
@@ -425,19 +424,118 @@ __global__ __launch_bounds__(1024) void argmax_kernel(const float *__restrict__ 
     }
 }
 
-int launch_argmax(hydra_ctx *c, hipStream_t s, const float *part, int S, int part_ld, size_t split_stride, RowScale rs,
-                  int M, int32_t *argmax, float *margin, float *logits) {
+int launch_argmax(hydra_ctx *c, hipStream_t s, const float *part, int S, int part_ld, size_t split_stride, int M, int32_t *argmax, float *margin, float *logits) {
     const bool vec = part_ld % 4 == 0 && split_stride % 4 == 0 && part_ld >= (c->m.vocab + 3) / 4 * 4;
-    if (vec) hipLaunchKernelGGL(argmax_kernel<true>, dim3(M), dim3(1024), 0, s, part, S, part_ld, split_stride, rs, c->m.vocab, argmax, margin, logits);
-    else     hipLaunchKernelGGL(argmax_kernel<false>, dim3(M), dim3(1024), 0, s, part, S, part_ld, split_stride, rs, c->m.vocab, argmax, margin, logits);
+    if (vec) hipLaunchKernelGGL(argmax_kernel<true>, dim3(M), dim3(1024), 0, s, part, S, part_ld, split_stride, c->m.vocab, argmax, margin, logits);
+    else     hipLaunchKernelGGL(argmax_kernel<false>, dim3(M), dim3(1024), 0, s, part, S, part_ld, split_stride, c->m.vocab, argmax, margin, logits);
     HYDRA_LAUNCH_CHECK("argmax_kernel");
+    return HYDRA_OK;
+}
+
+// 16-bit family: the same in two kernels, the second of which also writes the final hidden states (it would be a launch of
+// its own otherwise).  A row of 32000 logits is cut into chunks of 4096, one workgroup each: with a whole row per workgroup
+// 64 rows kept 64 CUs busy (15.4 us, and 6.6 for the hidden states) and 1024 rows took 65 us; the logits leave in 16-byte
+// stores.  cand[m][chunk] = (largest, its id, second largest).  Chunks grow with the vocabulary so that there are at most
+// LM_MAX_CHUNKS, which is what the attention's partial buffer holds for every row.
+enum { LM_CHUNK = 4096, LM_MAX_CHUNKS = 32 };
+__global__ __launch_bounds__(256) void lm_top2_kernel(const float *__restrict__ part, int S, int part_ld, size_t split_stride, RowScale rs, int V,
+                                                       int chunk, float4 *cand, float *__restrict__ logits) {
+    typedef __attribute__((ext_vector_type(4))) float f4;
+    typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));          // the caller's logits: rows start anywhere
+    const int m = blockIdx.y, v0 = blockIdx.x * chunk, v1 = min(V, v0 + chunk);
+    const float *row = part + (size_t)m * part_ld;
+    __shared__ float sh[1];
+    Top2 t = {-INFINITY, 0x7fffffff, -INFINITY};
+    float r = 0.f;
+    for (int base = v0; base < v1; base += LM_CHUNK) {              // once for vocabularies up to 131072
+        f4 x[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {                               // part_ld is V rounded up to 32: a group may reach into the padding
+            const int v = base + (u * 256 + (int)threadIdx.x) * 4;
+            x[u] = v < v1 ? *reinterpret_cast<const f4 *>(row + v) : f4{0.f, 0.f, 0.f, 0.f};
+        }
+        for (int sp = 1; sp < S; ++sp)                              // added in split order
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int v = base + (u * 256 + (int)threadIdx.x) * 4;
+                if (v < v1) x[u] += *reinterpret_cast<const f4 *>(row + (size_t)sp * split_stride + v);
+            }
+        if (base == v0) r = row_rstd_block(rs, m, sh);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int v = base + (u * 256 + (int)threadIdx.x) * 4;
+            if (v >= v1) continue;
+            const f4 y = x[u] * r;
+            if (logits) {
+                float *dst = logits + (size_t)m * V + v;
+                if (v + 4 <= V) *reinterpret_cast<f4u *>(dst) = y;
+                else
+                    for (int e = 0; v + e < V; ++e) dst[e] = y[e];
+            }
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (v + e < V) top2_push(t, y[e], v + e);
+        }
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        Top2 u = {__shfl_xor(t.v1, o, 64), __shfl_xor(t.i1, o, 64), __shfl_xor(t.v2, o, 64)};
+        top2_merge(t, u);
+    }
+    __shared__ Top2 red[4];
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = t;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        Top2 q = red[0];
+        for (int w = 1; w < 4; ++w) top2_merge(q, red[w]);
+        cand[(size_t)m * gridDim.x + blockIdx.x] = float4{q.v1, __int_as_float(q.i1), q.v2, 0.f};
+    }
+}
+
+__global__ __launch_bounds__(256) void lm_finish_kernel(const float4 *__restrict__ cand, int chunks, const float *__restrict__ x,
+                                                         const float *__restrict__ gain, RowScale rs, float *__restrict__ hidden, int d,
+                                                         int32_t *argmax, float *margin) {
+    typedef __attribute__((ext_vector_type(4))) float f4;
+    typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));          // the caller's hidden
+    const int m = blockIdx.x;
+    __shared__ float sh[1];
+    Top2 t = {-INFINITY, 0x7fffffff, -INFINITY};
+    if ((int)threadIdx.x < chunks) {                                // at most LM_MAX_CHUNKS: half a wave
+        const float4 c = cand[(size_t)m * chunks + threadIdx.x];
+        t = Top2{c.x, __float_as_int(c.y), c.z};
+    }
+    const float r = row_rstd_block(rs, m, sh);
+    for (int k = threadIdx.x * 4; k < d; k += 1024) {               // d is a multiple of 128
+        const f4 v = *reinterpret_cast<const f4 *>(x + (size_t)m * d + k), g = *reinterpret_cast<const f4 *>(gain + k);
+        *reinterpret_cast<f4u *>(hidden + (size_t)m * d + k) = v * r * g;
+    }
+    if (threadIdx.x >= 64) return;
+#pragma unroll
+    for (int o = 16; o > 0; o >>= 1) {
+        Top2 u = {__shfl_xor(t.v1, o, 64), __shfl_xor(t.i1, o, 64), __shfl_xor(t.v2, o, 64)};
+        top2_merge(t, u);
+    }
+    if (threadIdx.x == 0) {
+        argmax[m] = t.i1;
+        if (margin) margin[m] = t.v1 - t.v2;
+    }
+}
+
+int launch_lm_tail(hydra_ctx *c, hipStream_t s, const float *part, int S, int part_ld, size_t split_stride, RowScale rs, int M, void *cand,
+                   const float *x, const float *gain, float *hidden, int32_t *argmax, float *margin, float *logits) {
+    const int V = c->m.vocab;
+    const int chunk = std::max((int)LM_CHUNK, ceil_div(ceil_div(V, LM_MAX_CHUNKS), 4) * 4), chunks = ceil_div(V, chunk);
+    hipLaunchKernelGGL(lm_top2_kernel, dim3(chunks, M), dim3(256), 0, s, part, S, part_ld, split_stride, rs, V, chunk, (float4 *)cand, logits);
+    HYDRA_LAUNCH_CHECK("lm_top2_kernel");
+    hipLaunchKernelGGL(lm_finish_kernel, dim3(M), dim3(256), 0, s, (const float4 *)cand, chunks, x, gain, rs, hidden, c->m.d, argmax, margin);
+    HYDRA_LAUNCH_CHECK("lm_finish_kernel");
     return HYDRA_OK;
 }
 
 // The same result from the per-band candidates that the LM-head GEMM's own epilogue leaves when the logits are not
 // asked for (EpiTop2): cand[band][Mpad] = (largest sum of the band, its column, second largest), unscaled.  One
 // workgroup per row merges the bands (value descending, then column ascending) after scaling by the row's 1/rms, which
-// is computed exactly as argmax_kernel computes it, so the margin has the same bits as on that path; the column can
+// is computed exactly as lm_top2_kernel computes it, so the margin has the same bits as on that path; the column can
 // differ from it only where two different sums round to the same scaled value (a tie after scaling: that path then
 // reports the lower column of the two, this one the column of the larger unscaled sum; the margin is 0 on both).
 __global__ __launch_bounds__(256) void argmax_bands_kernel(const float4 *__restrict__ cand, int bands, int Mpad, RowScale rs,

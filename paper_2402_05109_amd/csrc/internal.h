@@ -168,8 +168,10 @@ int launch_silu_mul(hydra_ctx *c, hipStream_t s, const float *part, int S, int p
 int launch_gemm_top2(hydra_ctx *c, hipStream_t s, const void *X, const void *W, int M, int N, int K, float *cand, int Mpad, int *fused);
 int launch_argmax_bands(hydra_ctx *c, hipStream_t s, const float *cand, int bands, int Mpad, RowScale rs, int M, int32_t *argmax,
                         float *margin);
-int launch_argmax(hydra_ctx *c, hipStream_t s, const float *part, int S, int part_ld, size_t split_stride,
-                  RowScale rs, int M, int32_t *argmax, float *margin, float *logits);
+int launch_argmax(hydra_ctx *c, hipStream_t s, const float *part, int S, int part_ld, size_t split_stride, int M, int32_t *argmax, float *margin, float *logits);
+// LM head of the 16-bit family behind its GEMM: logits, greedy token and margin, and the final hidden states.  cand: 512 bytes per row
+int launch_lm_tail(hydra_ctx *c, hipStream_t s, const float *part, int S, int part_ld, size_t split_stride, RowScale rs, int M, void *cand,
+                   const float *x, const float *gain, float *hidden, int32_t *argmax, float *margin, float *logits);
 int launch_q_import(hydra_ctx *c, hipStream_t s, int B, const float *q_plain, void *qbuf);
 int launch_kv_plain(hydra_ctx *c, hipStream_t s, int B, int layer, const hydra_kv *kv, int first_slot, int n_slots,
                     float *plain, bool write_cache);

@@ -18,6 +18,13 @@ __host__ __device__ inline size_t apart_record(int Tq, int Dh) { return (size_t)
 
 enum { ATTN_WAVES = 8 };
 
+// two probabilities rounded to half: nothing to saturate, so without the four clamps per pair of f2a_pack
+__device__ __forceinline__ uint32_t half_pack(float lo, float hi) {
+    typedef __attribute__((ext_vector_type(2))) float f2;
+    typedef __attribute__((ext_vector_type(2))) _Float16 h2;
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector((f2{lo, hi}), h2));
+}
+
 template <int DH>
 struct KVTile { u32x4_t k[DH / 16]; u32x4_t v[2][DH / 32]; };
 
@@ -178,6 +185,14 @@ __device__ __forceinline__ void attn_bf16_body(
             const float m_new = fmaxf(m_run, cmax);
             const float m_safe = (m_new == -INFINITY) ? 0.f : m_new;
             const float alpha = __expf(m_run - m_safe);
+            // the accumulators are rescaled only where some query's maximum moved (a factor of one otherwise; the first tile
+            // has nothing to rescale)
+            if (it > 0 && __any(m_new != m_run)) {
+#pragma unroll
+                for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) o[dt][v] *= alpha;
+            }
             float rs = 0.f;
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
@@ -188,16 +203,12 @@ __device__ __forceinline__ void attn_bf16_body(
             rs += __shfl_xor(rs, 32, 64);
             l_run = l_run * alpha + rs;
             m_run = m_new;
-#pragma unroll
-            for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-                for (int v = 0; v < 16; ++v) o[dt][v] *= alpha;
             // P^T operands: page g uses accumulator registers 8g .. 8g+7 in order
 #pragma unroll
             for (int g = 0; g < 2; ++g) {
                 u32x4_t pb;
 #pragma unroll
-                for (int w = 0; w < 4; ++w) pb[w] = f2a_pack(sc[8 * g + 2 * w], sc[8 * g + 2 * w + 1]);
+                for (int w = 0; w < 4; ++w) pb[w] = half_pack(sc[8 * g + 2 * w], sc[8 * g + 2 * w + 1]);
 #pragma unroll
                 for (int dt = 0; dt < DT; ++dt)
                     o[dt] = HYDRA_MFMA16(__builtin_bit_cast(a16x8_t, cur.v[g][dt]), __builtin_bit_cast(a16x8_t, pb), o[dt]);

@@ -377,14 +377,14 @@ int hydra_draft_tree(hydra_ctx *c, void *stream, int B, void *ws, const float *h
     float *part = (float *)(W + w.part), *z = (float *)(W + w.z);
     void *xa = W + w.xa, *xb = W + w.xb;
     const int d = c->m.d, V = c->m.vocab;
-    if ((rc = launch_draft_root(c, s, B, root, tree_tokens))) return rc;
+    if (c->tree.max_depth == 0) return launch_draft_root(c, s, B, root, tree_tokens);
     for (int i = 1; i <= c->tree.max_depth; ++i) {
         const int Mi = B * c->tree.n_expand[i];
         if (Mi == 0) continue;
         const int Kin = head_in_width(c, i);
         GemmPlan p;
         const bool first_residual = c->h.medusa != 0;       // Medusa-style first layer: z = h_last + SiLU(W1 h_last + b1)
-        if ((rc = launch_draft_gather(c, s, B, i, h_last, tree_tokens, xa, first_residual ? z : nullptr, flags_ptr(c)))) return rc;
+        if ((rc = launch_draft_gather(c, s, B, i, h_last, root, tree_tokens, xa, first_residual ? z : nullptr, flags_ptr(c)))) return rc;
         void *cur = xb, *other = xa;
         if (c->bf16) {
             // MLP layers: bias + SiLU (+ residual) fused into the GEMM epilogue, unless splitting K over more

@@ -6,7 +6,7 @@
 
 namespace hydra {
 
-// tree_tokens[b, 0] = root[b]   (node 0 is x_t)
+// tree_tokens[b, 0] = root[b]   (node 0 is x_t); for trees of one node, otherwise the first phase's gather does it
 __global__ void draft_root_kernel(const int32_t *root, int32_t *tree_tokens, int B, int T) {
     const int b = blockIdx.x * blockDim.x + threadIdx.x;
     if (b < B) tree_tokens[(size_t)b * T] = root[b];
@@ -24,11 +24,13 @@ int launch_draft_root(hydra_ctx *c, hipStream_t s, int B, const int32_t *root, i
 // concatenated on the feature axis.  Row r = b * n_expand + j.
 // grid = (rows, segments); segment 0 copies h_last, segment s >= 1 one embedding.
 // Medusa-style heads (section 2) have segment 0 only; z_out then also receives
-// h_last in fp32, the residual term of their first layer.
+// h_last in fp32, the residual term of their first layer.  Phase 1 also writes the root token into the tree (node 0 is the
+// only node that expands then, so segment 0 of its row does) and takes it from `root`: a kernel of its own for that cost
+// 4.4 us of a draft.
 // ---------------------------------------------------------------------------
 template <bool BF>
-__global__ void draft_gather_kernel(const TreeDev *tree, int phase, int include_root, const float *h_last,
-                                    const int32_t *tree_tokens, const typename Elem<BF>::type *E, int d, int V,
+__global__ void draft_gather_kernel(const TreeDev *tree, int phase, int include_root, const float *h_last, const int32_t *root,
+                                    int32_t *tree_tokens, const typename Elem<BF>::type *E, int d, int V,
                                     int Kin, typename Act<BF>::type *out, float *z_out, int32_t *flags) {
     const int ne = tree->n_expand[phase];
     const int r = blockIdx.x, seg = blockIdx.y;
@@ -37,6 +39,7 @@ __global__ void draft_gather_kernel(const TreeDev *tree, int phase, int include_
     typedef __attribute__((ext_vector_type(4))) uint32_t u4;
     typedef __attribute__((ext_vector_type(4))) float f4;
     if (seg == 0) {
+        if (phase == 1 && threadIdx.x == 0) tree_tokens[(size_t)b * tree->T] = root[b];
         if (BF) {                                               // 8 columns per thread: one 16-byte store into the operand tile
             for (int k = threadIdx.x * 8; k < d; k += blockDim.x * 8) {
                 const f4 v0 = *reinterpret_cast<const f4 *>(h_last + (size_t)b * d + k);
@@ -61,7 +64,7 @@ __global__ void draft_gather_kernel(const TreeDev *tree, int phase, int include_
     const int dd = seg - 1 + (include_root ? 0 : 1);
     int a = n;
     for (int up = (phase - 1) - dd; up > 0; --up) a = tree->parent[a];
-    int tok = tree_tokens[(size_t)b * tree->T + a];
+    int tok = phase == 1 ? root[b] : tree_tokens[(size_t)b * tree->T + a];
     if (tok < 0 || tok >= V) {
         if (threadIdx.x == 0) atomicOr(flags, FLAG_BAD_TOKEN);
         tok = 0;
@@ -80,16 +83,16 @@ __global__ void draft_gather_kernel(const TreeDev *tree, int phase, int include_
         Act<BF>::st(out, x_index<BF>(r, seg * d + k, Kin), Elem<BF>::ld(E, (size_t)tok * d + k));
 }
 
-int launch_draft_gather(hydra_ctx *c, hipStream_t s, int B, int phase, const float *h_last,
-                        const int32_t *tree_tokens, void *x_out, float *z_out, int32_t *flags) {
+int launch_draft_gather(hydra_ctx *c, hipStream_t s, int B, int phase, const float *h_last, const int32_t *root,
+                        int32_t *tree_tokens, void *x_out, float *z_out, int32_t *flags) {
     const int ne = c->tree.n_expand[phase];
     const int inc = c->h.include_root_embedding ? 1 : 0;
     const int nseg = c->h.medusa ? 1 : 1 + (inc ? phase : phase - 1);
     const int Kin = nseg * c->m.d;
     dim3 grid(B * ne, nseg), block(256);
     const void *E = c->arena + c->off_embed;
-    if (c->bf16) hipLaunchKernelGGL(draft_gather_kernel<true>, grid, block, 0, s, tree_dev(c), phase, inc, h_last, tree_tokens, (const bf16_t *)E, c->m.d, c->m.vocab, Kin, (a16_t *)x_out, z_out, flags);
-    else         hipLaunchKernelGGL(draft_gather_kernel<false>, grid, block, 0, s, tree_dev(c), phase, inc, h_last, tree_tokens, (const float *)E, c->m.d, c->m.vocab, Kin, (float *)x_out, z_out, flags);
+    if (c->bf16) hipLaunchKernelGGL(draft_gather_kernel<true>, grid, block, 0, s, tree_dev(c), phase, inc, h_last, root, tree_tokens, (const bf16_t *)E, c->m.d, c->m.vocab, Kin, (a16_t *)x_out, z_out, flags);
+    else         hipLaunchKernelGGL(draft_gather_kernel<false>, grid, block, 0, s, tree_dev(c), phase, inc, h_last, root, tree_tokens, (const float *)E, c->m.d, c->m.vocab, Kin, (float *)x_out, z_out, flags);
     HYDRA_LAUNCH_CHECK("draft_gather_kernel");
     return HYDRA_OK;
 }

@@ -186,8 +186,9 @@ __device__ __forceinline__ void attn_bf16_body(
             const float m_safe = (m_new == -INFINITY) ? 0.f : m_new;
             const float alpha = __expf(m_run - m_safe);
             // the accumulators are rescaled only where some query's maximum moved (a factor of one otherwise; the first tile
-            // has nothing to rescale)
-            if (it > 0 && __any(m_new != m_run)) {
+            // has nothing to rescale).  Not in the layer kernel, which is at its limit of registers already: the branch costs
+            // it eight more spills.
+            if (DEV || (it > 0 && __any(m_new != m_run))) {
 #pragma unroll
                 for (int dt = 0; dt < DT; ++dt)
 #pragma unroll

@@ -206,12 +206,14 @@ static int launch_bf16(hydra_ctx *c, hipStream_t s, const void *X, const void *W
     }
     const int key = p.mb * 10 + p.nt;
     if (p.tile) {
-        if constexpr (!std::is_same<Epi, EpiPlain>::value && !std::is_same<Epi, EpiResid>::value && !std::is_same<Epi, EpiSilu>::value) {      // never planned for these
-            return fail(HYDRA_E_UNSUPPORTED, "gemm: no tile kernel for this epilogue");
-        } else {
-            const int rc = launch_tile<Epi>(c, s, X, W, M, N, K, p, epi, e0, e1);
-            if (rc) return rc;
-        }
+        int rc;
+        if constexpr (std::is_same<Epi, EpiResid>::value)
+            rc = launch_tile(c, s, X, W, M, N, K, p, EpiResidStaged{epi.x, epi.d, epi.gain, epi.xg, epi.ss, epi.Mpad, epi.flags}, e0, e1);
+        else if constexpr (std::is_same<Epi, EpiPlain>::value || std::is_same<Epi, EpiSilu>::value)
+            rc = launch_tile(c, s, X, W, M, N, K, p, epi, e0, e1);
+        else                                                           // never planned for these
+            rc = fail(HYDRA_E_UNSUPPORTED, "gemm: no tile kernel for this epilogue");
+        if (rc) return rc;
     } else if (p.shared_x) {
         if constexpr (std::is_same<Epi, EpiTop2>::value) {           // never planned for this epilogue (launch_gemm_top2): no such kernel is built
             return fail(HYDRA_E_UNSUPPORTED, "gemm: the band-wise top-2 epilogue has no shared-X kernel");

@@ -123,7 +123,7 @@ int launch_tile(hydra_ctx *c, hipStream_t s, const void *X, const void *W, int M
 }
 #define TILE_FOR(Epi) template int launch_tile<Epi>(hydra_ctx *, hipStream_t, const void *, const void *, int, int, int, const GemmPlan &, const Epi &, hipEvent_t, hipEvent_t)
 TILE_FOR(EpiPlain);
-TILE_FOR(EpiResid);
+TILE_FOR(EpiResidStaged);
 TILE_FOR(EpiSilu);
 #undef TILE_FOR
 
@@ -142,7 +142,7 @@ static hipError_t tile_attr_all() {
 }
 int gemm_tile_max_dynamic_lds() {
     hipError_t e = tile_attr_all<EpiPlain>();
-    if (e == hipSuccess) e = tile_attr_all<EpiResid>();
+    if (e == hipSuccess) e = tile_attr_all<EpiResidStaged>();
     if (e == hipSuccess) e = tile_attr_all<EpiSilu>();
     if (e != hipSuccess) return hip_fail(e, "hipFuncSetAttribute(gemm_tile_kernel)");
     return HYDRA_OK;

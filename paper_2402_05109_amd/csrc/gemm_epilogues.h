@@ -184,7 +184,10 @@ struct EpiTop2 {
 // xg = half(x * gain) in GEMM input order (the 1/rms factor commutes with the
 // contraction and is applied by the consumer) and ss[band][row] = sum over the
 // band's 32 columns of x^2.
-struct EpiResid {
+// STAGED: for the tile kernel, whose waves have registers to spare; in the kernels that stream operands through registers
+// the staged form spills (20 registers with eight waves sharing X), and there it has few rows to write.
+template <bool STAGED>
+struct EpiResidT {
     float *x; int d; const float *gain; a16_t *xg; float *ss; int Mpad; int32_t *flags;
     static constexpr bool LDS_PROLOGUE = false, PAIRED = false, EXTRA_BLOCKS = false, ROWWISE = false;
     template <int MB, int NT, int XB> __device__ __forceinline__ NoPre issue(const GemmTile<MB, NT, XB> &, const GemmGeom &) const { return NoPre{}; }
@@ -205,6 +208,23 @@ struct EpiResid {
         for (int v = 0; v < 16; ++v) {                                 // all loads first: one round trip
             const int row = acc_row(t.mb0 + a, v, t.lane);
             xo[v] = row < g.M ? xp[(size_t)row * d + col] : 0.f;
+        }
+        if constexpr (!STAGED) {
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const int row = acc_row(t.mb0 + a, v, t.lane);
+                const float xn = xo[v] + acc[v];
+                float sq = 0.f;
+                if (row < g.M) {
+                    xp[(size_t)row * d + col] = xn;
+                    xgp[x_index<true>(row, col, d)] = f2a_f(xn * gn, flags);
+                    sq = xn * xn;
+                }
+#pragma unroll
+                for (int o = 16; o > 0; o >>= 1) sq += __shfl_xor(sq, o, 64);      // over the 32 columns of the band
+                if ((t.lane & 31) == 0 && row < g.M) ssp[(size_t)band * Mpad + row] = sq;
+            }
+            return;
         }
         // The band's 32 x 32 values are two tiles of the next GEMM's input (columns 0-15 and 16-31): each is put together in
         // the wave's staging block and written with one 16-byte store per lane where all its rows exist.
@@ -516,6 +536,8 @@ struct EpiBiasSilu {
 };
 
 typedef EpiPlainT<false> EpiPlain;
+typedef EpiResidT<false> EpiResid;
+typedef EpiResidT<true> EpiResidStaged;
 typedef EpiSiluT<false> EpiSilu;
 typedef EpiQkvRopeT<false> EpiQkvRope;
 

@@ -256,7 +256,7 @@ int accept_greedy(hydra_ctx *ctx, void *stream, int B,
  * draw of the next root are this library's reading (the paper states neither).
  *   logits device [B, T, V] fp32: tree_verify_forward's optional output
  *   u      device [B] fp32 or NULL           other outputs as in accept_greedy.
- * Probabilities are computed in fp32.  Requires tau > 0, eps >= 0, alpha >= 0. */
+ * Probabilities are computed in fp32.  Requires tau > 0 (infinite: the uniform distribution), eps >= 0, alpha >= 0. */
 int accept_typical(hydra_ctx *ctx, void *stream, int B, void *ws,
                    const int32_t *tree_tokens, const float *logits,
                    float tau, float eps, float alpha, const float *u,

@@ -399,7 +399,8 @@ int launch_accept(hydra_ctx *c, hipStream_t s, int B, const int32_t *tree_tokens
 enum { TYP_THREADS = 1024, TYP_PER = 32, TYP_PIECE = TYP_THREADS * TYP_PER };
 
 // One piece of a row in registers: thread t holds groups of G consecutive ids, group i at (i * 1024 + t) * G, so that the
-// ids ascend with i first and with the thread second.  Entries past V are -infinity (weight 0, never a maximum).
+// ids ascend with i first and with the thread second.  Entries past V are -infinity, so never a maximum; their weight is 0
+// by their id, not through the exponential: with an infinite temperature that would be exp(-inf * 0), not a number.
 template <bool VEC>
 struct TypRow {
     static constexpr int G = VEC ? 4 : 1, NG = TYP_PER / G;
@@ -474,7 +475,7 @@ __global__ __launch_bounds__(TYP_THREADS) void typical_stats_kernel(const float 
 #pragma unroll
             for (int e = 0; e < r.G; ++e) {
                 const float t = (r.x[i][e] - m) * inv_tau;          // <= 0
-                const float ex = __expf(t);
+                const float ex = r.id(pc, i) + e < V ? __expf(t) : 0.f;
                 z += ex;
                 sz += ex > 0.f ? ex * t : 0.f;                      // exp underflow: 0 * (-inf) must not appear
             }
@@ -571,17 +572,18 @@ __global__ __launch_bounds__(TYP_THREADS) void typical_select_kernel(const float
     __shared__ float stripe[NG];
     __shared__ int pick_s, last_s;
     float incl[NG];                                                  // mass of this wave's threads up to and with this one, per stripe
-    auto mass = [&](int i) {
+    auto weight = [&](int pc, int i, int e) { return r.id(pc, i) + e < V ? __expf((r.x[i][e] - m) * inv_tau) : 0.f; };
+    auto mass = [&](int pc, int i) {
         float g = 0.f;
 #pragma unroll
-        for (int e = 0; e < G; ++e) g += __expf((r.x[i][e] - m) * inv_tau);
+        for (int e = 0; e < G; ++e) g += weight(pc, i, e);
         return g;
     };
     auto masses = [&](int pc) {                                      // piece pc: incl, part and stripe
         if (pieces > 1) r.load(row, V, pc);
 #pragma unroll
         for (int i = 0; i < NG; ++i) {
-            incl[i] = mass(i);
+            incl[i] = mass(pc, i);
 #pragma unroll
             for (int o = 1; o < 64; o <<= 1) {
                 const float t = __shfl_up(incl[i], o, 64);
@@ -625,7 +627,7 @@ __global__ __launch_bounds__(TYP_THREADS) void typical_select_kernel(const float
     float local = 0.f, upto = 0.f;
 #pragma unroll
     for (int i = 0; i < NG; ++i)
-        if (i == at) { local = mass(i); upto = incl[i]; }
+        if (i == at) { local = mass(pc, i); upto = incl[i]; }
     float below = cum;
     for (int w = 0; w < wave; ++w) below += part[w][at];
     const float excl = below + upto - local;
@@ -637,7 +639,7 @@ __global__ __launch_bounds__(TYP_THREADS) void typical_select_kernel(const float
             if (i == at)
 #pragma unroll
                 for (int e = 0; e < G; ++e) {
-                    const float w = __expf((r.x[i][e] - m) * inv_tau);
+                    const float w = weight(pc, i, e);
                     sum += w;
                     if (w > 0.f) held = v0 + e;
                     if (pick < 0 && sum > target) pick = v0 + e;

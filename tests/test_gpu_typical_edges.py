@@ -1,0 +1,47 @@
+"""Typical acceptance at the edges of what its arguments may be, against the oracle: infinite temperature."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import hydra_oracle as O
+from synth import random_tree
+from helpers import make_weights, small_shape
+from gpu_util import gpu_session
+
+pytestmark = pytest.mark.gpu
+
+
+def _session(parent, B, V):
+    cfg = small_shape(d=128, NL=1, H=2, Dh=64, F=176, V=V, K=0, T=len(parent))
+    return gpu_session(cfg, parent, B, 32, make_weights(cfg), want_logits=True)
+
+
+@pytest.mark.parametrize("static", [False, True])
+@pytest.mark.parametrize("V", [2, 7, 1000, 1003, 32000, 32768, 40001])
+def test_infinite_temperature_is_the_uniform_distribution(V, static):
+    """Every token has probability 1 / V and the entropy is log V: with alpha < 1 every candidate passes, with alpha > 1 (and
+    eps out of the way) none does, and the next root is floor(u V).  u = (k + 1/2) / V keeps away from the steps; sums of V
+    ones are exact in fp32."""
+    parent = random_tree(20, 3, 5)
+    tree, B = O.Tree(parent), 3
+    sess = _session(parent, B, V)
+    rng = np.random.default_rng(V)
+    logits = rng.standard_normal((B, tree.T, V)).astype(np.float32)
+    tok = rng.integers(0, V, size=(B, tree.T))
+    k = np.array([0, V // 2, V - 1])
+    u = ((k + 0.5) / V).astype(np.float32)
+    o = sess.out()
+    o.tree_tokens.copy_(torch.tensor(tok, dtype=torch.int32)); o.logits.copy_(torch.tensor(logits))
+    ud = torch.tensor(u, device="cuda:0")
+    for alpha in (0.5, 1.5):
+        out = (o.n_acc, o.path, o.next_root, o.last_node)
+        if static:
+            sess.main.accept_typical_static(B, o.tree_tokens, o.logits, float("inf"), 2.0, alpha, ud, *out)
+        else:
+            sess.main.accept_typical(B, sess.ws, o.tree_tokens, o.logits, float("inf"), 2.0, alpha, ud, *out)
+        torch.cuda.synchronize()
+        for b in range(B):
+            n_acc, path, nxt, last = O.accept_typical(tree, tok[b], logits[b].astype(np.float64), float("inf"), 2.0, alpha, float(u[b]))
+            assert nxt == k[b] and (n_acc > 1) == (alpha < 1)
+            assert int(o.n_acc[b]) == n_acc and int(o.last_node[b]) == last and int(o.next_root[b]) == nxt
+            assert o.path[b, :n_acc].tolist() == path

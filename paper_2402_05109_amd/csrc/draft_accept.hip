@@ -612,7 +612,7 @@ __global__ __launch_bounds__(TYP_THREADS) void typical_select_kernel(const float
     const float target = u[b] * total;
     float cum = 0.f;
     int at = -1, pc = 0;
-    for (; pc < pieces; ++pc) {
+    for (; pc < pieces && target >= 0.f; ++pc) {                     // a negative u ends at the last token, as one of 1 or more and NaN do
         if (pieces > 1) masses(pc);
         for (int i = 0; i < NG && at < 0; ++i) {
             if (cum + stripe[i] > target) at = i;
@@ -620,7 +620,7 @@ __global__ __launch_bounds__(TYP_THREADS) void typical_select_kernel(const float
         }
         if (at >= 0) break;
     }
-    if (at < 0) {                                                    // the target lies at the very end by rounding
+    if (at < 0) {                                                    // no token's cumulative mass exceeds the target
         if (threadIdx.x == 0) next_root[b] = V - 1;
         return;
     }

@@ -1,4 +1,5 @@
-"""Typical acceptance at the edges of what its arguments may be, against the oracle: infinite temperature."""
+"""Typical acceptance at the edges of what its arguments may be, against the oracle: infinite temperature,
+uniform numbers outside [0, 1)."""
 import numpy as np
 import pytest
 import torch
@@ -45,3 +46,18 @@ def test_infinite_temperature_is_the_uniform_distribution(V, static):
             assert nxt == k[b] and (n_acc > 1) == (alpha < 1)
             assert int(o.n_acc[b]) == n_acc and int(o.last_node[b]) == last and int(o.next_root[b]) == nxt
             assert o.path[b, :n_acc].tolist() == path
+
+
+@pytest.mark.parametrize("V", [7, 5000, 32003, 40000])
+def test_numbers_outside_the_unit_interval_give_the_last_token(V):
+    """u outside [0, 1) is the caller's mistake and has no answer of its own: the call ends at the last token, whichever
+    side u lies on."""
+    us = [-0.5, -1e-30, 1.0, 7.0, float("inf"), float("-inf"), float("nan")]
+    sess = _session([-1], len(us), V)
+    o = sess.out()
+    o.logits.normal_()
+    o.tree_tokens.zero_()
+    sess.main.accept_typical(len(us), sess.ws, o.tree_tokens, o.logits, 0.7, 0.1, 0.3, torch.tensor(us, device="cuda:0"), o.n_acc, o.path,
+                             o.next_root, o.last_node)
+    torch.cuda.synchronize()
+    assert o.next_root.tolist() == [V - 1] * len(us)

@@ -1,6 +1,8 @@
 // Kernels of the draft phases (gather/concat, bias + SiLU, wave-level top-k)
 // and of the integer tail of a step (greedy acceptance, cache compaction,
 // state update).
+#include <type_traits>
+
 #include "device_common.h"
 #include "internal.h"
 
@@ -391,42 +393,62 @@ int launch_accept(hydra_ctx *c, hipStream_t s, int B, const int32_t *tree_tokens
 //
 // Both are one workgroup on one row of logits, bound by the round trips to memory and the
 // reductions between them.  A thread therefore takes 32 logits of a row of up to 32768 into
-// registers at once (TypRow: 16-byte loads where rows are 16-byte aligned) and everything
-// after that runs from there; longer rows go through in pieces of that size.  Reading the
-// row once per pass, four bytes at a time, and walking the tree in one thread took 17.3 us
-// and 40.1 us (4 rows x 64 nodes, V = 32000).
+// registers at once (TypRow: 16-byte loads) and everything after that runs from there; longer
+// rows go through in pieces of that size.  At 1024 threads a wave has 128 registers: nothing
+// but the 32 logits may live across the steps.  Reading the row once per pass, four bytes at a
+// time, and walking the tree in one thread took 17.3 us and 40.1 us (4 rows x 64 nodes, V = 32000).
 // ---------------------------------------------------------------------------
-enum { TYP_THREADS = 1024, TYP_PER = 32, TYP_PIECE = TYP_THREADS * TYP_PER };
+enum { TYP_THREADS = 1024, TYP_GROUPS = 8, TYP_STRIPE = TYP_THREADS * 4, TYP_PIECE = TYP_STRIPE * TYP_GROUPS };
 
-// One piece of a row in registers: thread t holds groups of G consecutive ids, group i at (i * 1024 + t) * G, so that the
-// ids ascend with i first and with the thread second.  Entries past V are -infinity, so never a maximum; their weight is 0
-// by their id, not through the exponential: with an infinite temperature that would be exp(-inf * 0), not a number.
-template <bool VEC>
+// no entry of this piece lies past V (the same for every thread)
+__device__ __forceinline__ bool typ_whole(int piece, int V) { return V - piece * TYP_PIECE >= TYP_PIECE; }
+
+// One piece of a row in registers: thread t holds groups of four consecutive ids, group i at (i * 1024 + t) * 4, so that the
+// ids ascend with i first and with the thread second.  Entries past V are -infinity: never a maximum, and of weight
+// exp(-inf / tau) = 0, except that an infinite temperature makes that exp(-inf * 0), not a number: then (PAD) their weight is
+// 0 by their id.  A comparison per entry at every temperature cost typical_stats_kernel 0.5 of 6.7 us.
+// Rows start wherever V puts them: the loads ask for no more than float alignment.  The one group that V cuts is read
+// entry by entry.
 struct TypRow {
-    static constexpr int G = VEC ? 4 : 1, NG = TYP_PER / G;
-    float x[NG][G];
-    __device__ __forceinline__ int id(int piece, int i) const { return piece * TYP_PIECE + (i * TYP_THREADS + (int)threadIdx.x) * G; }
+    float x[TYP_GROUPS][4];
+    __device__ __forceinline__ int id(int piece, int i) const { return piece * TYP_PIECE + i * TYP_STRIPE + (int)threadIdx.x * 4; }
+    // the same, worked out where it is used: the ids, addresses and limits of every group kept across the steps, for the pieces
+    // that need them entry by entry, cost more registers than there are
+    __device__ __forceinline__ int id_here(int piece, int i) const {
+        int t = (int)threadIdx.x;
+        asm volatile("" : "+v"(t));
+        return piece * TYP_PIECE + i * TYP_STRIPE + t * 4;
+    }
     __device__ __forceinline__ void load(const float *__restrict__ row, int V, int piece) {
-        typedef __attribute__((ext_vector_type(4))) float f4;
+        if (typ_whole(piece, V)) fill<true>(row, V, piece);         // loads without a branch between them
+        else                     fill<false>(row, V, piece);
+    }
+    template <bool WHOLE>
+    __device__ __forceinline__ void fill(const float *__restrict__ row, int V, int piece) {
+        typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
 #pragma unroll
-        for (int i = 0; i < NG; ++i) {
-            const int v = id(piece, i);
-            if (VEC) {                                              // V % 4 == 0: a group is all in or all out
-                f4 t = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
-                if (v < V) t = *reinterpret_cast<const f4 *>(row + v);
+        for (int i = 0; i < TYP_GROUPS; ++i) {
+            const int v = WHOLE ? id(piece, i) : id_here(piece, i);
+            if (WHOLE || V - piece * TYP_PIECE >= (i + 1) * TYP_STRIPE) {      // the same for every thread
+                const f4u t = *reinterpret_cast<const f4u *>(row + id(piece, i));
 #pragma unroll
-                for (int e = 0; e < G; ++e) x[i][e] = t[e];
+                for (int e = 0; e < 4; ++e) x[i][e] = t[e];
+            } else if (v + 4 <= V) {
+                const f4u t = *reinterpret_cast<const f4u *>(row + v);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) x[i][e] = t[e];
             } else {
-                x[i][0] = v < V ? row[v] : -INFINITY;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) x[i][e] = v + e < V ? row[v + e] : -INFINITY;
             }
         }
     }
     __device__ __forceinline__ float largest() const {
         float m = -INFINITY;
 #pragma unroll
-        for (int i = 0; i < NG; ++i)
+        for (int i = 0; i < TYP_GROUPS; ++i)
 #pragma unroll
-            for (int e = 0; e < G; ++e) m = fmaxf(m, x[i][e]);
+            for (int e = 0; e < 4; ++e) m = fmaxf(m, x[i][e]);
         return m;
     }
 };
@@ -443,7 +465,6 @@ __device__ __forceinline__ float block_reduce(float v, float *sh, bool is_max) {
     return r;
 }
 
-template <bool VEC>
 __global__ __launch_bounds__(TYP_THREADS) void typical_stats_kernel(const float *__restrict__ logits, int V,
                                                                      const TreeDev *tree, const int32_t *__restrict__ tree_tokens,
                                                                      float inv_tau, float eps, float alpha,
@@ -454,7 +475,7 @@ __global__ __launch_bounds__(TYP_THREADS) void typical_stats_kernel(const float 
     const float *row = logits + ((size_t)b * T + n) * V;
     const int nc = tree->n_children[n], first = tree->first_child[n];
     if (nc == 0) return;                                            // uniform over the workgroup
-    TypRow<VEC> r;
+    TypRow r;
     r.load(row, V, 0);
     int tok = 0;
     float xt = 0.f;
@@ -465,20 +486,24 @@ __global__ __launch_bounds__(TYP_THREADS) void typical_stats_kernel(const float 
     }
     const int pieces = (V + TYP_PIECE - 1) / TYP_PIECE;
     float m = r.largest();
-    for (int pc = 1; pc < pieces; ++pc) { TypRow<VEC> q; q.load(row, V, pc); m = fmaxf(m, q.largest()); }
+    for (int pc = 1; pc < pieces; ++pc) { TypRow q; q.load(row, V, pc); m = fmaxf(m, q.largest()); }
     m = block_reduce(m, sh, true);
     float z = 0.f, sz = 0.f;
-    for (int pc = 0; pc < pieces; ++pc) {
-        if (pieces > 1) r.load(row, V, pc);
+    auto add = [&](auto PAD, int pc) {
 #pragma unroll
-        for (int i = 0; i < r.NG; ++i)
+        for (int i = 0; i < TYP_GROUPS; ++i)
 #pragma unroll
-            for (int e = 0; e < r.G; ++e) {
+            for (int e = 0; e < 4; ++e) {
                 const float t = (r.x[i][e] - m) * inv_tau;          // <= 0
-                const float ex = r.id(pc, i) + e < V ? __expf(t) : 0.f;
+                const float ex = !decltype(PAD)::value || r.id_here(pc, i) + e < V ? __expf(t) : 0.f;
                 z += ex;
                 sz += ex > 0.f ? ex * t : 0.f;                      // exp underflow: 0 * (-inf) must not appear
             }
+    };
+    for (int pc = 0; pc < pieces; ++pc) {
+        if (pieces > 1) r.load(row, V, pc);
+        if (inv_tau > 0.f) add(std::false_type{}, pc);
+        else               add(std::true_type{}, pc);
     }
     z = wave_sum(z);
     sz = wave_sum(sz);
@@ -493,7 +518,12 @@ __global__ __launch_bounds__(TYP_THREADS) void typical_stats_kernel(const float 
     ok[(size_t)b * T + first + threadIdx.x] = p > th ? 1 : 0;
 }
 
-template <bool VEC>
+// next_root by u: a stripe is the 4096 ids that the workgroup holds side by side.  Every stripe is reduced to one sum per
+// wave; the stripe in which the cumulative mass exceeds u times the total, the wave inside it, and then lane and id inside
+// that wave follow from prefix sums of ever smaller pieces, each starting from the very number at which the piece before it
+// ended, and only pieces that hold any mass are taken: the token drawn always has a positive weight.  4 rows: 7.4 us at
+// V = 32000, 7.6 at 32003, 16.3 at 50257.  A scan of every stripe over the lanes instead of the one that matters keeps a
+// prefix sum per group alive (16 registers spilled, 192 where V ruled out 16-byte loads) and took 16.2, 28.6 and 75.3.
 __global__ __launch_bounds__(TYP_THREADS) void typical_select_kernel(const float *__restrict__ logits, int V, const TreeDev *tree,
                                                                       const int32_t *__restrict__ ok, float inv_tau,
                                                                       const float *__restrict__ u, int32_t *n_acc,
@@ -525,10 +555,10 @@ __global__ __launch_bounds__(TYP_THREADS) void typical_select_kernel(const float
         if (lane == 0) bestw[wave] = (int)kmax;
     }
     __syncthreads();
-    const uint32_t kbest = (uint32_t)max(bestw[0], bestw[1]);      // node 0 always counts: never 0
+    const uint32_t kbest = (uint32_t)__builtin_amdgcn_readfirstlane(max(bestw[0], bestw[1]));      // node 0 always counts: never 0; scalar, and with it the row's address
     const int best = 255 - (int)(kbest & 255u);
     const float *row = logits + ((size_t)b * T + best) * V;
-    TypRow<VEC> r;
+    TypRow r;
     r.load(row, V, 0);                                              // requested before the path is written out
     if (threadIdx.x == 0) {
         const int len = (int)(kbest >> 8) + 1;
@@ -546,9 +576,9 @@ __global__ __launch_bounds__(TYP_THREADS) void typical_select_kernel(const float
         for (int pc = 0; pc < pieces; ++pc) {
             if (pc) r.load(row, V, pc);
 #pragma unroll
-            for (int i = 0; i < r.NG; ++i)
+            for (int i = 0; i < TYP_GROUPS; ++i)
 #pragma unroll
-                for (int e = 0; e < r.G; ++e)
+                for (int e = 0; e < 4; ++e)
                     if (r.x[i][e] > bv) { bv = r.x[i][e]; bi = r.id(pc, i) + e; }      // ascending ids per thread: first maximum kept
         }
         Cand cnd = wave_best(Cand{bv, bi});
@@ -563,60 +593,72 @@ __global__ __launch_bounds__(TYP_THREADS) void typical_select_kernel(const float
         return;
     }
     float m = r.largest();
-    for (int pc = 1; pc < pieces; ++pc) { TypRow<VEC> q; q.load(row, V, pc); m = fmaxf(m, q.largest()); }
+    for (int pc = 1; pc < pieces; ++pc) { TypRow q; q.load(row, V, pc); m = fmaxf(m, q.largest()); }
     m = block_reduce(m, sh, true);
-    // In steps of the ids that the workgroup holds side by side (a stripe: 1024 groups): the stripe in which the cumulative
-    // mass exceeds u times the total, then the thread inside that stripe, then the id inside that thread's group.
-    constexpr int NG = TypRow<VEC>::NG, G = TypRow<VEC>::G;
-    __shared__ float part[16][NG];                                  // [wave][stripe] of one piece
-    __shared__ float stripe[NG];
-    __shared__ int pick_s, last_s;
-    float incl[NG];                                                  // mass of this wave's threads up to and with this one, per stripe
-    auto weight = [&](int pc, int i, int e) { return r.id(pc, i) + e < V ? __expf((r.x[i][e] - m) * inv_tau) : 0.f; };
-    auto mass = [&](int pc, int i) {
-        float g = 0.f;
-#pragma unroll
-        for (int e = 0; e < G; ++e) g += weight(pc, i, e);
-        return g;
-    };
-    auto masses = [&](int pc) {                                      // piece pc: incl, part and stripe
+    __shared__ float part[16][TYP_GROUPS];                          // [wave][stripe] of one piece
+    float sum_a = 0.f, sum_b = 0.f;                                  // lane l: the sums of stripes l / 16 and 4 + l / 16
+    auto stripes = [&](int pc) {                                     // piece pc: its weights in place of the logits, part, sum_a, sum_b
         if (pieces > 1) r.load(row, V, pc);
+        auto weights = [&](auto PAD) {
 #pragma unroll
-        for (int i = 0; i < NG; ++i) {
-            incl[i] = mass(pc, i);
+            for (int i = 0; i < TYP_GROUPS; ++i)
 #pragma unroll
-            for (int o = 1; o < 64; o <<= 1) {
-                const float t = __shfl_up(incl[i], o, 64);
-                if (lane >= o) incl[i] += t;
+                for (int e = 0; e < 4; ++e) r.x[i][e] = !decltype(PAD)::value || r.id_here(pc, i) + e < V ? __expf((r.x[i][e] - m) * inv_tau) : 0.f;
+        };
+        if (inv_tau > 0.f) weights(std::false_type{});
+        else               weights(std::true_type{});
+        float s[TYP_GROUPS];
+#pragma unroll
+        for (int i = 0; i < TYP_GROUPS; ++i) s[i] = (r.x[i][0] + r.x[i][1]) + (r.x[i][2] + r.x[i][3]);
+        // all stripes together: each step a lane keeps the ones that agree with one bit of its number and hands the others over
+#pragma unroll
+        for (int hf = TYP_GROUPS / 2; hf > 0; hf >>= 1) {
+            const bool up = (lane & hf) != 0;
+#pragma unroll
+            for (int q = 0; q < hf; ++q) {
+                const float keep = up ? s[q + hf] : s[q], give = up ? s[q] : s[q + hf];
+                s[q] = keep + __shfl_xor(give, hf, 64);
             }
         }
-        __syncthreads();                                             // every reader of the last piece's part and stripe is done
-        if (lane == 63) {
 #pragma unroll
-            for (int i = 0; i < NG; ++i) part[wave][i] = incl[i];
-        }
+        for (int o = TYP_GROUPS; o < 64; o <<= 1) s[0] += __shfl_xor(s[0], o, 64);
+        __syncthreads();                                             // every reader of the last piece's part is done
+        if (lane < TYP_GROUPS) part[wave][lane] = s[0];
         __syncthreads();
-        if ((int)threadIdx.x < NG) {
-            float a = 0.f;
-            for (int w = 0; w < 16; ++w) a += part[w][threadIdx.x];
-            stripe[threadIdx.x] = a;
+        sum_a = part[lane & 15][lane >> 4];
+        sum_b = part[lane & 15][4 + (lane >> 4)];
+#pragma unroll
+        for (int o = 1; o < 16; o <<= 1) { sum_a += __shfl_xor(sum_a, o, 64); sum_b += __shfl_xor(sum_b, o, 64); }
+    };
+    auto stripe = [&](int i) { return __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(i < 4 ? sum_a : sum_b), (i & 3) * 16)); };
+    auto prefix = [&](float v, int width) {                          // inclusive, over lanes 0 .. width - 1
+        for (int o = 1; o < width; o <<= 1) {
+            const float t = __shfl_up(v, o, 64);
+            if (lane >= o) v += t;
         }
-        if (threadIdx.x == 0) { pick_s = 0x7fffffff; last_s = -1; }
-        __syncthreads();
+        return v;
+    };
+    // the first of the lanes that hold mass whose prefix, on top of `from`, exceeds the target; the last of them where rounding leaves none
+    auto crossing = [&](float v, float incl, float from, float target, bool in) {
+        const uint64_t has = __ballot(in && v > 0.f), hit = __ballot(in && v > 0.f && from + incl > target);
+        return hit ? __builtin_ctzll(hit) : 63 - __builtin_clzll(has);
     };
     float total = 0.f;
     for (int pc = 0; pc < pieces; ++pc) {
-        masses(pc);
-        for (int i = 0; i < NG; ++i) total += stripe[i];             // the same in every thread
+        stripes(pc);
+#pragma unroll
+        for (int i = 0; i < TYP_GROUPS; ++i) total += stripe(i);     // the same in every thread
     }
     const float target = u[b] * total;
     float cum = 0.f;
     int at = -1, pc = 0;
     for (; pc < pieces && target >= 0.f; ++pc) {                     // a negative u ends at the last token, as one of 1 or more and NaN do
-        if (pieces > 1) masses(pc);
-        for (int i = 0; i < NG && at < 0; ++i) {
-            if (cum + stripe[i] > target) at = i;
-            else cum += stripe[i];
+        if (pieces > 1) stripes(pc);
+#pragma unroll
+        for (int i = 0; i < TYP_GROUPS; ++i) {
+            if (at >= 0) continue;
+            if (cum + stripe(i) > target) at = i;                    // cum <= target: the stripe holds mass
+            else cum += stripe(i);
         }
         if (at >= 0) break;
     }
@@ -624,33 +666,29 @@ __global__ __launch_bounds__(TYP_THREADS) void typical_select_kernel(const float
         if (threadIdx.x == 0) next_root[b] = V - 1;
         return;
     }
-    float local = 0.f, upto = 0.f;
+    const float wsum = part[lane & 15][at], wincl = prefix(wsum, 16);
+    const int wv = crossing(wsum, wincl, cum, target, lane < 16);
+    if (wave != wv) return;
+    const float wfrom = wv ? cum + __shfl(wincl, wv - 1, 64) : cum;
+    float w[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int i = 0; i < NG; ++i)
-        if (i == at) { local = mass(pc, i); upto = incl[i]; }
-    float below = cum;
-    for (int w = 0; w < wave; ++w) below += part[w][at];
-    const float excl = below + upto - local;
-    const int v0 = r.id(pc, at);
-    if (local > 0.f) {
-        float sum = excl; int pick = -1, held = v0;                  // held: the last id of the group with any mass
+    for (int i = 0; i < TYP_GROUPS; ++i)
+        if (i == at)
 #pragma unroll
-        for (int i = 0; i < NG; ++i)
-            if (i == at)
+            for (int e = 0; e < 4; ++e) w[e] = r.x[i][e];
+    const float mass = (w[0] + w[1]) + (w[2] + w[3]), incl = prefix(mass, 64);
+    const int ln = crossing(mass, incl, wfrom, target, true);
+    const float before = __shfl_up(incl, 1, 64);
+    if (lane != ln) return;
+    float sum = lane ? wfrom + before : wfrom;
+    int pick = -1, held = 0;                                         // held: the last id of the group with any mass
 #pragma unroll
-                for (int e = 0; e < G; ++e) {
-                    const float w = weight(pc, i, e);
-                    sum += w;
-                    if (w > 0.f) held = v0 + e;
-                    if (pick < 0 && sum > target) pick = v0 + e;
-                }
-        // every thread behind the crossing qualifies: the lowest id wins
-        if (excl + local > target) atomicMin(&pick_s, pick < 0 ? held : pick);
-        atomicMax(&last_s, held);
+    for (int e = 0; e < 4; ++e) {
+        sum += w[e];
+        if (w[e] > 0.f) held = e;
+        if (pick < 0 && w[e] > 0.f && sum > target) pick = e;
     }
-    __syncthreads();
-    // no thread qualifies only if its own sums round below the stripe's: then the last one that holds any mass
-    if (threadIdx.x == 0) next_root[b] = pick_s != 0x7fffffff ? pick_s : last_s >= 0 ? last_s : V - 1;
+    next_root[b] = pc * TYP_PIECE + at * TYP_STRIPE + (int)threadIdx.x * 4 + (pick < 0 ? held : pick);
 }
 
 int launch_accept_typical(hydra_ctx *c, hipStream_t s, int B, const int32_t *tree_tokens, const float *logits, float tau,
@@ -658,13 +696,9 @@ int launch_accept_typical(hydra_ctx *c, hipStream_t s, int B, const int32_t *tre
                           int32_t *path, int32_t *next_root, int32_t *last_node) {
     const int T = c->tree.T, V = c->m.vocab;
     const float inv_tau = 1.0f / tau;
-    // 16-byte loads: every row of the caller's logits starts at a multiple of 16 bytes
-    const bool vec = V % 4 == 0 && ((uintptr_t)logits & 15) == 0;
-    if (vec) hipLaunchKernelGGL(typical_stats_kernel<true>, dim3(T, B), dim3(TYP_THREADS), 0, s, logits, V, tree_dev(c), tree_tokens, inv_tau, eps, alpha, ok_scratch, flags, T);
-    else     hipLaunchKernelGGL(typical_stats_kernel<false>, dim3(T, B), dim3(TYP_THREADS), 0, s, logits, V, tree_dev(c), tree_tokens, inv_tau, eps, alpha, ok_scratch, flags, T);
+    hipLaunchKernelGGL(typical_stats_kernel, dim3(T, B), dim3(TYP_THREADS), 0, s, logits, V, tree_dev(c), tree_tokens, inv_tau, eps, alpha, ok_scratch, flags, T);
     HYDRA_LAUNCH_CHECK("typical_stats_kernel");
-    if (vec) hipLaunchKernelGGL(typical_select_kernel<true>, dim3(B), dim3(TYP_THREADS), 0, s, logits, V, tree_dev(c), ok_scratch, inv_tau, u, n_acc, path, next_root, last_node, T);
-    else     hipLaunchKernelGGL(typical_select_kernel<false>, dim3(B), dim3(TYP_THREADS), 0, s, logits, V, tree_dev(c), ok_scratch, inv_tau, u, n_acc, path, next_root, last_node, T);
+    hipLaunchKernelGGL(typical_select_kernel, dim3(B), dim3(TYP_THREADS), 0, s, logits, V, tree_dev(c), ok_scratch, inv_tau, u, n_acc, path, next_root, last_node, T);
     HYDRA_LAUNCH_CHECK("typical_select_kernel");
     return HYDRA_OK;
 }

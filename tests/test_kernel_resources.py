@@ -62,3 +62,11 @@ def test_layer_kernel_keeps_its_streams_in_registers():
     for k, v in rep.items():
         limit = 0 if "ELi64EEE" in k else 140
         assert v.get("spill", 0) <= limit, f"{k}: {v}"
+
+
+def test_typical_acceptance_keeps_its_row_in_registers():
+    """One workgroup of 1024 threads holds a row of logits: 128 registers per lane, none of them spilled."""
+    rep = {k: v for k, v in _resource_report("draft_accept.hip").items() if "typical_stats" in k or "typical_select" in k}
+    assert len(rep) == 2
+    bad = {k: v for k, v in rep.items() if v.get("scratch", 0) != 0 or v.get("spill", 0) != 0}
+    assert not bad, f"typical acceptance using scratch memory: {bad}"

@@ -128,7 +128,8 @@ __global__ __launch_bounds__(ATTN_F32_WAVES * 64) void attn_f32_kernel(
         }
         const float sc = valid ? (a4[0] + a4[1]) + (a4[2] + a4[3]) : -INFINITY;
         const float m_new = fmaxf(m_run, wave_max(sc));
-        if (m_new == -INFINITY) continue;                           // nothing visible yet (wave-uniform)
+        // nothing visible yet (wave-uniform).  A chunk of nothing but NaN scores has no maximum either, but must not be left out.
+        if (m_new == -INFINITY && !__any(sc != sc)) continue;
         const float p = valid ? __expf(sc - m_new) : 0.f;
         const float alpha = __expf(m_run - m_new);                   // exp(-inf) = 0 on the first visible chunk
         l_run = l_run * alpha + wave_sum(p);

@@ -30,7 +30,8 @@ static double env_or(const char *name, double dflt) {
     return v ? atof(v) : dflt;
 }
 
-GemmPlan plan_gemm(const hydra_ctx *c, int M, int N, int K, int kind) {
+// the kernels that hold their operands in registers: up to 64 rows, and what the tile kernel is not built for or declines
+static GemmPlan plan_registers(const hydra_ctx *c, int M, int N, int K, int kind) {
     // model constants; the environment overrides exist for tuning runs only
     static const double cap_gbps = env_or("HYDRA_PLAN_CAP", 45.0);        // L1-miss bytes one CU can pull, GB/s
     static const double hbm_env = env_or("HYDRA_PLAN_HBM", 0.0);          // achievable HBM stream, TB/s:
@@ -50,9 +51,6 @@ GemmPlan plan_gemm(const hydra_ctx *c, int M, int N, int K, int kind) {
     const int mgroups = ceil_div(mblocks, p.mb);
     const int bands = ceil_div(N, 32), KT = K / 16;
     const bool pairs = kind == GEMM_KIND_PAIRS;                        // band pairs: exactly two bands per wave
-    // a partial output is M x N floats written and read back: the charge per split was fitted at 64 rows and grows
-    // with the rows beyond that (measured at 128 and 256 rows: verify 6.08 -> 5.74 and 10.05 -> 9.3 ms with 4x / 8x)
-    const double split_charge = split_us * (M > 64 ? M / 32.0 : 1.0);
     const bool may_split = kind == GEMM_KIND_PLAIN;
     p.nw = 1;
     // rows of X that a workgroup's loads touch: an X tile's 128-byte lines hold 8 rows each, and lanes past M repeat the last row
@@ -75,7 +73,7 @@ GemmPlan plan_gemm(const hydra_ctx *c, int M, int N, int K, int kind) {
             double cost = rounds * (w_bytes + x_bytes) / (cap_gbps * 1e3);   // us at the per-CU limit
             const double hbm = (double)N * K * 2 / (hbm_tbps * 1e6);         // us at the HBM limit
             if (cost < hbm) cost = hbm;
-            cost += (s > 1 ? 1.0 + split_charge * s : 0.0);                  // writing and reading S partials back
+            cost += (s > 1 ? 1.0 + split_us * s : 0.0);                      // writing and reading S partials back (up to 64 rows)
             if (cost < best_cost - 1e-9) { best_cost = cost; best_nt = nt; best_s = s; }
         }
     }
@@ -103,10 +101,9 @@ GemmPlan plan_gemm(const hydra_ctx *c, int M, int N, int K, int kind) {
     p.kpw = ceil_div(KT, p.kw * p.splits);
     // Four row blocks per workgroup: the X tiles dominate what a workgroup pulls, and where enough workgroups remain 4 or 8
     // waves take different band pairs and share X through LDS (gemm_bf16_sharedx_kernel).  A workgroup then pulls NWT
-    // pairs of W and X once.  Where the output may be split (plain partial outputs), K is also split over workgroups:
-    // that multiplies the workgroups and shortens each one's slice of X (a single row group of 128 rows has only
-    // bands / (2 NWT) workgroups otherwise).  The shape is taken where it costs less than the plan above.
-    if (p.mb == 4 && (mgroups >= 2 || may_split) && KT >= 16) {
+    // pairs of W and X once.  The shape is taken where it costs less than the plan above: fused epilogues of several row groups
+    // (plain outputs of so many rows take the tile kernel).
+    if (p.mb == 4 && mgroups >= 2 && KT >= 16) {
         const int groups2 = ceil_div(bands, 2);
         int pick = 0, pick_s = 1;
         if (getenv("HYDRA_PLAN_SHARED_X_MIN_WGS")) {                  // tests: the shape wherever this many workgroups remain
@@ -118,18 +115,12 @@ GemmPlan plan_gemm(const hydra_ctx *c, int M, int N, int K, int kind) {
         } else {
             double best = p.cost_us;
             const double hbm = (double)N * K * 2 / (hbm_tbps * 1e6);
-            const int s_max = (may_split && env_or("HYDRA_PLAN_SHARED_X_SPLIT", 1.0) != 0.0) ? max_split : 1;
-            for (int nwt = 8; nwt >= 4; nwt >>= 1)
-                for (int sp = 1; sp <= s_max; ++sp) {
-                    if (sp > 1 && KT / sp < 16) break;
-                    if (sp == 1 && mgroups < 2) continue;              // one row group, no split: too few workgroups by construction
-                    const int wgs = ceil_div(groups2, nwt) * mgroups * sp;
-                    const double bytes = ((double)nwt * 64 + 128.0) * K * 2 / sp;
-                    double cost = ceil_div(wgs, 256) * bytes / (cap_gbps * 1e3);
-                    if (cost < hbm) cost = hbm;
-                    cost += (sp > 1 ? 1.0 + split_charge * sp : 0.0);
-                    if (wgs >= 128 && cost < 0.97 * best) { best = cost; pick = nwt; pick_s = sp; }      // a tie goes to the plan with more workgroups
-                }
+            for (int nwt = 8; nwt >= 4; nwt >>= 1) {
+                const int wgs = ceil_div(groups2, nwt) * mgroups;
+                const double bytes = ((double)nwt * 64 + 128.0) * K * 2;
+                const double cost = std::max(ceil_div(wgs, 256) * bytes / (cap_gbps * 1e3), hbm);
+                if (wgs >= 128 && cost < 0.97 * best) { best = cost; pick = nwt; }      // a tie goes to the plan with more workgroups
+            }
             if (pick) p.cost_us = (float)best;
         }
         if (pick) {
@@ -138,19 +129,27 @@ GemmPlan plan_gemm(const hydra_ctx *c, int M, int N, int K, int kind) {
             p.splits = ceil_div(KT, p.kpw);
         }
     }
+    return p;
+}
+
+GemmPlan plan_gemm(const hydra_ctx *c, int M, int N, int K, int kind) {
     // Beyond 64 rows: both operands through LDS (bf16_gemm_tile.hip).  For plain outputs always: it was the faster one in 143
     // of 147 timed shapes, up to 1.8 times, and the others lose 2 us at most.  For fused epilogues (no K split, so small
-    // matrices leave it too few workgroups) where it is estimated cheaper; the estimate above leaves out the ramp and is
-    // 13 to 25 % short of what is measured at 96 and more rows.  Not for KIND_FUSED and KIND_PAIRS, whose epilogues it is not
-    // built for (q|k|v: launch_gemm_qkv_rope).
+    // matrices leave it too few workgroups) where it is estimated cheaper; the register kernels' estimate leaves out the ramp
+    // and is 13 to 25 % short of what is measured at 96 and more rows.  Not for KIND_FUSED and KIND_PAIRS, whose epilogues it
+    // is not built for (q|k|v: launch_gemm_qkv_rope).  Nothing is planned that is not used: this runs several times per layer.
     // HYDRA_PLAN_TILE: 0 never, 1 wherever a tile exists.
-    const int tile_mode = (int)env_or("HYDRA_PLAN_TILE", -1.0);
-    if (kind != GEMM_KIND_FUSED && kind != GEMM_KIND_PAIRS && tile_mode != 0 && !getenv("HYDRA_PLAN_SHARED_X_MIN_WGS")) {
-        GemmPlan t = p;
-        if (plan_tile(c, M, N, K, kind, &t)) {
-            p.cost_us = 1.15f * p.cost_us + 1.0f;
-            if (tile_mode == 1 || kind == GEMM_KIND_PLAIN || t.cost_us < p.cost_us) p = t;
-        }
+    GemmPlan p = {};
+    bool tiled = false, always = kind == GEMM_KIND_PLAIN;
+    if (c->bf16 && M > 64 && kind != GEMM_KIND_FUSED && kind != GEMM_KIND_PAIRS) {
+        const int tile_mode = (int)env_or("HYDRA_PLAN_TILE", -1.0);
+        always = always || tile_mode == 1;
+        tiled = tile_mode != 0 && !getenv("HYDRA_PLAN_SHARED_X_MIN_WGS") && plan_tile(M, N, K, kind, tile_mode == 1, &p);
+    }
+    if (!tiled || !always) {
+        GemmPlan r = plan_registers(c, M, N, K, kind);
+        if (tiled) r.cost_us = 1.15f * r.cost_us + 1.0f;
+        if (!tiled || r.cost_us <= p.cost_us) p = r;
     }
     static const bool debug = getenv("HYDRA_PLAN_DEBUG") != nullptr;       // tuning aid: every plan to stderr
     if (debug)
@@ -215,7 +214,7 @@ static int launch_bf16(hydra_ctx *c, hipStream_t s, const void *X, const void *W
             rc = fail(HYDRA_E_UNSUPPORTED, "gemm: no tile kernel for this epilogue");
         if (rc) return rc;
     } else if (p.shared_x) {
-        if constexpr (std::is_same<Epi, EpiTop2>::value) {           // never planned for this epilogue (launch_gemm_top2): no such kernel is built
+        if constexpr (std::is_same<Epi, EpiTop2>::value) {           // up to two row blocks only (launch_gemm_top2)
             return fail(HYDRA_E_UNSUPPORTED, "gemm: the band-wise top-2 epilogue has no shared-X kernel");
         } else if (p.shared_x == 8) {
             if (e0) hipExtLaunchKernelGGL((gemm_bf16_sharedx_kernel<4, 2, 8, Epi>), grid, block, lds, s, e0, e1, 0, g, epi);
@@ -246,10 +245,13 @@ static int launch_bf16(hydra_ctx *c, hipStream_t s, const void *X, const void *W
             case 25:
                 if constexpr (std::is_same<Epi, EpiSilu>::value) { launch_one<2, 5>(grid, block, lds, s, g, epi, e0, e1); break; }
                 else return fail(HYDRA_E_UNSUPPORTED, "gemm: no kernel for this plan");
-            case 41: launch_one<4, 1>(grid, block, lds, s, g, epi, e0, e1); break;
-            case 42: launch_one<4, 2>(grid, block, lds, s, g, epi, e0, e1); break;
-            case 43: launch_one<4, 3>(grid, block, lds, s, g, epi, e0, e1); break;
-            default: return fail(HYDRA_E_UNSUPPORTED, "gemm: no kernel for this plan");
+            default:
+                if constexpr (!std::is_same<Epi, EpiTop2>::value) {
+                    if (key == 41) { launch_one<4, 1>(grid, block, lds, s, g, epi, e0, e1); break; }
+                    if (key == 42) { launch_one<4, 2>(grid, block, lds, s, g, epi, e0, e1); break; }
+                    if (key == 43) { launch_one<4, 3>(grid, block, lds, s, g, epi, e0, e1); break; }
+                }
+                return fail(HYDRA_E_UNSUPPORTED, "gemm: no kernel for this plan");
         }
     }
     HYDRA_LAUNCH_CHECK("gemm_bf16_kernel");
@@ -337,14 +339,15 @@ int launch_gemm_resid(hydra_ctx *c, hipStream_t s, const void *X, const void *W,
 
 // LM head straight to per-band top-2 candidates (no logits): *fused = 0 and nothing launched where the plan that splits K
 // over workgroups is estimated clearly faster than one workgroup per band group (the candidates need complete sums), and
-// beyond 64 rows, where the logits come from the tile kernel.
+// beyond 64 rows, where the logits come from the tile kernel (no kernel of more than two row blocks is built for it).
 // Opt-in (HYDRA_LM_HEAD_TOP2=1): measured at the 7B shape it is a wash, 50.3 + 5.8 us against 47.0 + 11.6 us at 64 rows and
 // 52.1 + 5.7 against 41.8 + ~8 us for the one-node tree, so by default the logits go through memory.
 int launch_gemm_top2(hydra_ctx *c, hipStream_t s, const void *X, const void *W, int M, int N, int K, float *cand, int Mpad, int *fused) {
-    const GemmPlan ps = plan_gemm(c, M, N, K, GEMM_KIND_PLAIN);
+    *fused = 0;
+    if (M > 64 || env_or("HYDRA_LM_HEAD_TOP2", 0.0) == 0.0) return HYDRA_OK;
     const GemmPlan p = plan_gemm(c, M, N, K, GEMM_KIND_FUSED);
-    *fused = (p.shared_x == 0 && ps.tile == 0 && p.cost_us <= ps.cost_us + 4.0f && env_or("HYDRA_LM_HEAD_TOP2", 0.0) != 0.0) ? 1 : 0;
-    if (!*fused) return HYDRA_OK;
+    if (p.cost_us > plan_gemm(c, M, N, K, GEMM_KIND_PLAIN).cost_us + 4.0f) return HYDRA_OK;
+    *fused = 1;
     EpiTop2 epi{cand, Mpad, N};
     return launch_bf16<EpiTop2, NT_ANY>(c, s, X, W, M, N, K, p, epi);
 }
@@ -415,7 +418,9 @@ static hipError_t set_attr_all() {
     if (e == hipSuccess) e = set_attr<1, 3, Epi>(); if (e == hipSuccess) e = set_attr<1, 4, Epi>();
     if (e == hipSuccess) e = set_attr<2, 1, Epi>(); if (e == hipSuccess) e = set_attr<2, 2, Epi>();
     if (e == hipSuccess) e = set_attr<2, 3, Epi>(); if (e == hipSuccess) e = set_attr<2, 4, Epi>();
-    if (e == hipSuccess) e = set_attr<4, 1, Epi>(); if (e == hipSuccess) e = set_attr<4, 2, Epi>();
+    if constexpr (!std::is_same<Epi, EpiTop2>::value) {
+        if (e == hipSuccess) e = set_attr<4, 1, Epi>(); if (e == hipSuccess) e = set_attr<4, 2, Epi>();
+    }
     return e;
 }
 

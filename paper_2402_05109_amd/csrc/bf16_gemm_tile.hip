@@ -50,33 +50,38 @@ static TileInfo tile_info(int id) {
 // part; rounds of 256 workgroups follow one another; the weights need HBM at 5.3 TB/s; and the output is written at 4.3 TB/s
 // once per split.  Splits are chosen with the consumer's reading of the partial sums (5 TB/s) in mind, which is not part
 // of cost_us.
-bool plan_tile(const hydra_ctx *c, int M, int N, int K, int kind, GemmPlan *p) {
-    (void)c;
+bool plan_tile(int M, int N, int K, int kind, bool forced, GemmPlan *p) {
     const bool may_split = kind == GEMM_KIND_PLAIN;
     const int KT = K / 16, bands = ceil_div(N, 32);
     // up to 64 rows the register-streaming kernels win: at 72 rows this one takes 23.1 against 29.9 us (12288 x 4096), at 64
     // those take 24.9 with the epilogue fused
     if (M <= 64 || KT % 2 != 0) return false;
-    const char *only_s = getenv("HYDRA_PLAN_TILE_ID"), *splits_s = getenv("HYDRA_PLAN_TILE_SPLITS");      // tests: this tile, this many splits where the output may be split
+    const char *only_s = forced ? getenv("HYDRA_PLAN_TILE_ID") : nullptr, *splits_s = forced ? getenv("HYDRA_PLAN_TILE_SPLITS") : nullptr;      // tests: this tile, with this many splits where the output may be split
     const int only = only_s ? atoi(only_s) : 0, only_splits = may_split && splits_s ? atoi(splits_s) : 0;
+    const double hbm = (double)N * K * 2 / 5.3e6;
     double best = 1e30;
     for (int id = TILE_256x256; id < TILE_COUNT; ++id) {
         const TileInfo ti = tile_info(id);
         if (only && id != only) continue;
         if (ti.rows == 256 && M <= 128) continue;
         const int gx = ceil_div(bands, ti.cols / 32), gz = ceil_div(M, ti.rows);
+        const double by = (std::min(ti.rows, ceil_div(M, 32) * 32) + ti.cols) * 32 / (gz > 1 ? 107e3 : 86e3);
+        double step_few = 0.0, step_all = 0.0;                         // a k-step with up to 200 workgroups and with 256: the same for every split
+        auto step_us = [&](int active) {
+            double &known = active <= 200 ? step_few : step_all;
+            if ((active <= 200 || active == 256) && known > 0.0) return known;
+            const double fl = 32.0 * ti.rows * ti.cols / std::min(6.0e6, 1200e6 / active);
+            const double us = std::cbrt(fl * fl * fl + by * by * by);
+            if (active <= 200 || active == 256) known = us;
+            return us;
+        };
         for (int s = 1; s <= (may_split ? 8 : 1); ++s) {
             const int kps = ceil_div(ceil_div(KT, s), 2) * 2, wgs = gx * gz * s;
             if ((s > 1 || !only) && kps < 2 * ti.slots) break;             // fewer slots than are in flight
             if (s > 1 && wgs > 640 && !only_splits) break;                 // the chip is full
             if (ceil_div(KT, kps) != s || (only_splits && s != only_splits)) continue;
-            const double by = (std::min(ti.rows, ceil_div(M, 32) * 32) + ti.cols) * 32 / (gz > 1 ? 107e3 : 86e3);
-            auto round_us = [&](int active) {
-                const double fl = 32.0 * ti.rows * ti.cols / std::min(6.0e6, 1200e6 / active);
-                return kps * ti.eff * std::cbrt(fl * fl * fl + by * by * by);
-            };
-            double run = (wgs / 256) * round_us(256) + (wgs % 256 ? round_us(wgs % 256) : 0.0);
-            const double hbm = (double)N * K * 2 / 5.3e6;
+            auto round_us = [&](int active) { return kps * ti.eff * step_us(active); };
+            double run = (wgs >= 256 ? (wgs / 256) * round_us(256) : 0.0) + (wgs % 256 ? round_us(wgs % 256) : 0.0);
             run = std::sqrt(std::sqrt(run * run * run * run + hbm * hbm * hbm * hbm));
             const double out = (double)M * N * (may_split ? 4.0 * s : 2.0);
             const double cost = 2.8 + run + out / 4.3e6 + (may_split ? 0.0 : 2.0);

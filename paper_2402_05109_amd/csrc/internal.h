@@ -105,7 +105,7 @@ WsLayout ws_layout(const hydra_ctx *c, int B);
 // plain output (may split K) / fused epilogue / q|k|v band pairs / gate-up (fused, up to five bands per wave) / fused residual
 enum { GEMM_KIND_PLAIN = 0, GEMM_KIND_FUSED = 1, GEMM_KIND_PAIRS = 2, GEMM_KIND_SWIGLU = 3, GEMM_KIND_RESID = 4 };
 GemmPlan plan_gemm(const hydra_ctx *c, int M, int N, int K, int kind);
-bool     plan_tile(const hydra_ctx *c, int M, int N, int K, int kind, GemmPlan *p);      // fills *p: the cheapest tile of bf16_gemm_tile.hip
+bool     plan_tile(int M, int N, int K, int kind, bool forced, GemmPlan *p);      // fills *p: the cheapest tile of bf16_gemm_tile.hip (forced: the one that tests name)
 int      attn_units(const hydra_ctx *c, int B);
 
 // ---- launchers (each enqueues on `s` and returns a hydra_status) -----------

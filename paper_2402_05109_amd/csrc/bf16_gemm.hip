@@ -318,7 +318,9 @@ int launch_gemm_resid(hydra_ctx *c, hipStream_t s, const void *X, const void *W,
                       const float *gain, void *xg, float *ss, int Mpad, float *part, int *ss_bands) {
     GemmPlan p = plan_gemm(c, M, N, K, GEMM_KIND_PLAIN);
     const GemmPlan fused = plan_gemm(c, M, N, K, GEMM_KIND_RESID);
-    const bool second = p.tile ? p.cost_us + second_kernel_us(p.splits, M, N, 10) < fused.cost_us : p.splits > 1;
+    // However small the matrix, the fused kernel takes 10 us beyond 64 rows, which its estimate (bytes alone) does not see: 512 x 512
+    // 10.2 us and 512 x 1024 11.7 us at 80 rows (estimates 5.2 and 9.4), where the tile kernel and the second one take 8 to 9.
+    const bool second = p.tile ? p.cost_us + second_kernel_us(p.splits, M, N, 10) < std::max(fused.cost_us, 10.0f) : p.splits > 1;
     if (second) {
         const int npad = gemm_npad(c, N);
         const size_t stride = (size_t)ceil_div(M, 32) * 32 * npad;

@@ -10,7 +10,8 @@
 //
 // One workgroup barrier per slot.  Slot j + 1 is awaited in front of the last k-step of slot j, so that the reads of its
 // first k-step overlap the multiplications of that last one:
-//   own DMA of slot j + 1 has landed (vmcnt) | barrier: everybody's has, and everybody is done with slot j - 1 |
+//   own DMA of slot j + 1 has landed (vmcnt), own reads of slot j - 1 are done (lgkmcnt: the reads of slot j may be under way) |
+//   barrier: everybody's has and are |
 //   request slot j + SLOTS - 1 into the place of slot j - 1 | read the first operands of slot j + 1 | multiply.
 // Every wave issues the same number of loads per slot, past the end too (the last k-step again), so the counts that
 // vmcnt waits for are exact and every wave meets the same number of barriers.
@@ -42,6 +43,11 @@ __device__ __forceinline__ void tile_dma(const u32x4_t *src, uint32_t dst) {
                                      (__attribute__((address_space(3))) void *)(uintptr_t)dst, 16, 0, 0);
 }
 template <int N> __device__ __forceinline__ void wait_loads() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
+// and at most L reads of LDS still under way
+template <int N, int L> __device__ __forceinline__ void wait_loads_and_reads() {
+    static_assert(L <= 15, "the counter's range");
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(%1)" ::"n"(N), "n"(L) : "memory");
+}
 
 template <class S, class Epilogue>
 __global__ __launch_bounds__(S::WAVES * 64) void gemm_tile_kernel(GemmGeom g, Epilogue epi) {
@@ -120,7 +126,7 @@ __global__ __launch_bounds__(S::WAVES * 64) void gemm_tile_kernel(GemmGeom g, Ep
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 if (u == U - 1) {
-                    wait_loads<(SLOTS - 3) * SHARE>();
+                    wait_loads_and_reads<(SLOTS - 3) * SHARE, U * (MB + NT)>();
                     meet();
                     request(j + SLOTS - 1, prev);
                     if constexpr (on) read(next, 0, (u + 1) & 1);

@@ -83,10 +83,31 @@ def test_rotary_append_by_pages(start, T, monkeypatch):
     assert float((a - b).abs().max() / a.abs().max()) <= 2.0 ** -10
 
 
-def test_tile_kernels_keep_everything_in_registers():
-    cmd = [build_lib._hipcc(), *build_lib.FLAGS, "-c", os.path.join(build_lib.CSRC, "bf16_gemm_tile.hip"), "-o", os.devnull, "--cuda-device-only",
+@pytest.fixture(scope="module")
+def compiled(tmp_path_factory):
+    """(assembly of the tile kernels, the compiler's resource remarks)"""
+    out = str(tmp_path_factory.mktemp("asm") / "tile.s")
+    cmd = [build_lib._hipcc(), *build_lib.FLAGS, "-S", os.path.join(build_lib.CSRC, "bf16_gemm_tile.hip"), "-o", out, "--cuda-device-only",
            "-Rpass-analysis=kernel-resource-usage"]
     r = subprocess.run(cmd, capture_output=True, text=True)
     assert r.returncode == 0, r.stderr[-2000:]
-    scratch = [int(x) for x in re.findall(r"ScratchSize \[bytes/lane\]: (\d+)", r.stderr)]
+    with open(out) as f:
+        return f.read(), r.stderr
+
+
+def test_tile_kernels_keep_everything_in_registers(compiled):
+    scratch = [int(x) for x in re.findall(r"ScratchSize \[bytes/lane\]: (\d+)", compiled[1])]
     assert len(scratch) >= 21 and not any(scratch)
+
+
+def test_tile_kernels_end_their_reads_before_a_slot_is_refilled(compiled):
+    """The barrier inside the loop over the slots lets other waves overwrite the slot before the current one: a wave must not
+    arrive with reads of it under way, wherever the compiler has put the instructions that use them."""
+    kernels = [k for k in re.split(r"\n(?=_ZN5hydra16gemm_tile_kernel\S+:)", compiled[0])[1:]]
+    assert len(kernels) == 21
+    for k in kernels:
+        body = [x.strip() for x in k.split(".Lfunc_end")[0].splitlines()]
+        code = [x for x in body if x and not x.startswith((";", "."))]
+        waits = [code[i - 1] for i, x in enumerate(code) if x == "s_barrier"]
+        ring = [w for w in waits if re.fullmatch(r"s_waitcnt vmcnt\(\d+\) lgkmcnt\(\d+\)", w) and "lgkmcnt(0)" not in w]
+        assert len(ring) == 2, (k.split(":")[0], waits)              # waves with rows of their own, and waves that only fetch

@@ -41,7 +41,10 @@ static TileInfo tile_info(int id) {
     }
 }
 
-// The cheapest tile and K split for an M x N x K product; false where none applies.
+// The cheapest tile and K split for an M x N x K product; false where none applies.  `forced` (tests): HYDRA_PLAN_TILE_ID names
+// the tile and HYDRA_PLAN_TILE_SPLITS the K splits of plain outputs, and a product that cannot have them gets a plan that
+// launch_tile refuses, never another one; splits of a residual's product are then always taken, and whole K never instead of
+// the fused epilogue.
 //
 // The estimate was fitted to 3658 timings (14 matrices of the 7B, 13B-like, 33B and a 2048-wide shape, 72 to 1024 rows, all
 // tiles, 1 to 8 splits; 7 % root mean square error, the tile it picks is 1.4 % off the best on average).  A workgroup's
@@ -56,7 +59,7 @@ bool plan_tile(int M, int N, int K, int kind, bool forced, GemmPlan *p) {
     // up to 64 rows the register-streaming kernels win: at 72 rows this one takes 23.1 against 29.9 us (12288 x 4096), at 64
     // those take 24.9 with the epilogue fused
     if (M <= 64 || KT % 2 != 0) return false;
-    const char *only_s = forced ? getenv("HYDRA_PLAN_TILE_ID") : nullptr, *splits_s = forced ? getenv("HYDRA_PLAN_TILE_SPLITS") : nullptr;      // tests: this tile, with this many splits where the output may be split
+    const char *only_s = forced ? getenv("HYDRA_PLAN_TILE_ID") : nullptr, *splits_s = only_s ? getenv("HYDRA_PLAN_TILE_SPLITS") : nullptr;
     const int only = only_s ? atoi(only_s) : 0, only_splits = may_split && splits_s ? atoi(splits_s) : 0;
     const double hbm = (double)N * K * 2 / 5.3e6;
     double best = 1e30;
@@ -92,6 +95,11 @@ bool plan_tile(int M, int N, int K, int kind, bool forced, GemmPlan *p) {
                 p->mb = ti.rows / 32; p->nt = ti.cols / 32; p->nw = 1; p->kw = 1; p->shared_x = 0;
             }
         }
+    }
+    if (only) {
+        if (best == 1e30) *p = GemmPlan{8, 1, 1, 1, 1, 0, 0, only, 0.f};       // kpw = 0
+        else if (may_split) p->cost_us = p->splits > 1 ? 0.f : 1e6f;
+        return true;
     }
     return best < 1e30;
 }

@@ -12,21 +12,30 @@ from oracle import hydra_oracle as O
 from synth import random_tree, uniform_tokens
 from helpers import make_weights, oracle_model, small_shape
 from gpu_util import gpu_session, max_rel, to_np
+from paper_2402_05109_amd import binding as hb
 from paper_2402_05109_amd import build as build_lib
 
-CFG = small_shape(d=512, NL=1, H=4, Dh=128, F=896, V=1003, K=0).with_(dtype="bf16")      # 16, 48, 28 and (ragged) 32 bands; 32 and 56 k-steps
-_ref = {}
+CFG = small_shape(d=512, NL=1, H=4, Dh=128, F=896, V=1003, K=0).with_(dtype="bf16")
+# 40, 120, 88 and (ragged) 32 bands; 80 and 88 k-steps, of which four splits leave the 20 that the deepest ring (two times ten
+# slots) asks for and three splits a shorter last one
+WIDE = small_shape(d=1280, NL=1, H=10, Dh=128, F=1408, V=1003, K=0).with_(dtype="bf16")
+_weights, _ref = {}, {}
+
+
+def _made(cfg):
+    if cfg.d not in _weights:
+        _weights[cfg.d] = make_weights(cfg, gain_std=0.1, std=0.04 * (512 / cfg.d) ** 0.5)
+    return _weights[cfg.d]
 
 
 def _reference(T, B):
-    """Oracle hidden and logits of every row, computed once per shape."""
+    """Oracle hidden and logits of every row of the wide shape, computed once per shape."""
     if (T, B) not in _ref:
-        W = make_weights(CFG, gain_std=0.1, std=0.04)
-        m = oracle_model(CFG, W)
-        parent = random_tree(T, 5, 7) if T > 1 else [-1]
-        toks = torch.stack([uniform_tokens(31, b, T, CFG.V) for b in range(B)]).to(torch.int32)
+        m = oracle_model(WIDE, _made(WIDE))
+        parent = random_tree(T, 5, 7)
+        toks = torch.stack([uniform_tokens(31, b, T, WIDE.V) for b in range(B)]).to(torch.int32)
         out = [O.tree_verify(m, O.FlatCache(m, T), 0, O.Tree(parent), toks[b].tolist())[:2] for b in range(B)]
-        _ref[T, B] = (W, parent, toks, np.stack([o[0] for o in out]), np.stack([o[1] for o in out]))
+        _ref[T, B] = (_made(WIDE), parent, toks, np.stack([o[0] for o in out]), np.stack([o[1] for o in out]))
     return _ref[T, B]
 
 
@@ -35,13 +44,15 @@ def _reference(T, B):
                                              for T, B, splits in ((65, 1, 1), (128, 1, 3), (43, 3, 1), (37, 7, 2), (100, 3, 4))      # 65, 128, 129, 259, 300 rows
                                              if tile > 4 or T * B > 128])            # tiles of 256 rows are not planned for up to 128 rows
 def test_every_tile_matches_the_oracle(tile, T, B, splits, monkeypatch):
-    """16-bit parity bar of the repository (2e-2 relative); a wrong tile, k-step or row shows as an error of order 1."""
+    """16-bit parity bar of the repository (2e-2 relative); a wrong tile, k-step or row shows as an error of order 1.  Every
+    product of the call runs on the tile and with the K splits named here (q|k|v, O, down and LM head; gate/up and, with one
+    split, the residual epilogues have K whole) or the call is refused: see test_a_tile_that_cannot_be_had_is_refused."""
     monkeypatch.setenv("HYDRA_PLAN_TILE", "1")
     monkeypatch.setenv("HYDRA_PLAN_TILE_ID", str(tile))
     monkeypatch.setenv("HYDRA_PLAN_TILE_SPLITS", str(splits))
     monkeypatch.setenv("HYDRA_PLAN_QKV_UNFUSED", "1")
     W, parent, toks, hid, lg = _reference(T, B)
-    sess = gpu_session(CFG, parent, B, 32, W, page_perm_seed=5, want_logits=True)
+    sess = gpu_session(WIDE, parent, B, 32, W, page_perm_seed=5, want_logits=True)
     o = sess.out()
     o.tree_tokens.copy_(toks)
     sess.verify()
@@ -50,8 +61,23 @@ def test_every_tile_matches_the_oracle(tile, T, B, splits, monkeypatch):
     torch.cuda.synchronize()
     assert sess.main.read_flags() == 0
     assert all(torch.equal(a, b) for a, b in zip(first, (o.hidden, o.logits, o.argmax)))      # fixed summation order
-    assert max_rel(to_np(o.hidden).reshape(-1, CFG.d), hid.reshape(-1, CFG.d)) <= 2e-2
-    assert max_rel(to_np(o.logits).reshape(-1, CFG.V), lg.reshape(-1, CFG.V)) <= 2e-2
+    assert max_rel(to_np(o.hidden).reshape(-1, WIDE.d), hid.reshape(-1, WIDE.d)) <= 2e-2
+    assert max_rel(to_np(o.logits).reshape(-1, WIDE.V), lg.reshape(-1, WIDE.V)) <= 2e-2
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("tile,T,B,splits", [(7, 100, 3, 5), (6, 100, 3, 6), (1, 128, 1, 1), (5, 65, 1, 9)])
+def test_a_tile_that_cannot_be_had_is_refused(tile, T, B, splits, monkeypatch):
+    """More splits than the ring leaves k-steps for or than are planned, or 256 rows for 128: the forced plan does not give way
+    to another one, so the test above cannot pass on kernels that it does not name."""
+    monkeypatch.setenv("HYDRA_PLAN_TILE", "1")
+    monkeypatch.setenv("HYDRA_PLAN_TILE_ID", str(tile))
+    monkeypatch.setenv("HYDRA_PLAN_TILE_SPLITS", str(splits))
+    monkeypatch.setenv("HYDRA_PLAN_QKV_UNFUSED", "1")
+    sess = gpu_session(WIDE, random_tree(T, 5, 7), B, 32, _made(WIDE))
+    with pytest.raises(hb.HydraError) as e:
+        sess.verify()
+    assert e.value.code == hb.E_UNSUPPORTED
 
 
 @pytest.mark.gpu
@@ -60,8 +86,7 @@ def test_every_tile_matches_the_oracle(tile, T, B, splits, monkeypatch):
 def test_rotary_append_by_pages(start, T, monkeypatch):
     """Cache append as a kernel of its own: tokens that begin and end inside a page leave the page's other tokens alone and
     whole pages are written whole; compared with the fused q|k|v kernel on the same inputs."""
-    W, _, _, _, _ = _reference(65, 1)
-    parent = random_tree(T, 5, 7)
+    W, parent = _made(CFG), random_tree(T, 5, 7)
     got = {}
     for mode in ("0", "1"):
         monkeypatch.setenv("HYDRA_PLAN_QKV_UNFUSED", mode)

@@ -434,8 +434,6 @@ struct RowSource {
     const int32_t *path; const int32_t *n_acc;   // [B, T], [B]
 };
 
-// The decoder layers of the context over its B * T tree rows.  lm_tail: final RMSNorm, LM head, argmax (the
-// verify step); otherwise the residual stream after the last layer is left in the workspace's x.
 // LM head, greedy token and margin of the 16-bit family (paper, section 2: the base model's next-token choice at every
 // tree node).  Without a logits buffer the GEMM's epilogue reduces every band to its two best columns and a small
 // kernel merges the bands (opt-in); otherwise the sums go through memory and two kernels scale, reduce and finish them.
@@ -459,6 +457,8 @@ static int lm_head_tail(hydra_ctx *c, hipStream_t s, const float *x, const void 
     return launch_lm_tail(c, s, part, p.splits, ld_v, mp * ld_v, rs, M, cand, x, gain, hidden, argmax, margin, logits);
 }
 
+// The decoder layers of the context over its B * T tree rows.  lm_tail: final RMSNorm, LM head, argmax (the
+// verify step); otherwise the residual stream after the last layer is left in the workspace's x.
 static int forward_layers(hydra_ctx *c, hipStream_t s, int B, void *ws, const RowSource &src, const int32_t *seq_len,
                           const hydra_kv *kv, bool lm_tail, float *hidden, int32_t *argmax, float *margin, float *logits) {
     int rc;

@@ -1,4 +1,4 @@
-// fp32 storage family: a plain VALU GEMM and a tree attention.  Used by fp32 models (small, launch-bound), where what a
+// fp32 storage family: a GEMM on the fp32 matrix instruction and a tree attention.  Used by fp32 models (small, launch-bound), where what a
 // kernel costs is its chain of dependent memory round trips and cross-lane steps, not bandwidth.
 #include "device_common.h"
 #include "internal.h"

@@ -14,13 +14,15 @@ namespace hydra {
 // rows of a lane's accumulator registers
 __device__ __forceinline__ int acc_row(int mb, int v, int lane) { return mb * 32 + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3); }
 
-// Per-row 1/rms for the 32*MB rows of a workgroup, from the per-band sums of squares ss[band][Mpad]
+// Per-row 1/rms for the 32*XB rows of a workgroup, from the per-band sums of squares ss[band][Mpad]
 // left by the producer of the GEMM input:  rstd = 1 / sqrt(sum_band ss / d + eps).
-// The waves of the workgroup share the bands.  A load instruction covers G = 64 / (8*MB) bands: lane
-// l reads the four rows 4*(l % (8*MB)) .. +3 of band group l / (8*MB).  rowsum_issue() starts the
+// The waves of the workgroup share the bands.  A load instruction covers G = 64 / (8*XB) bands: lane
+// l reads the four rows 4*(l % (8*XB)) .. +3 of band group l / (8*XB).  rowsum_issue() starts the
 // first eight such loads of a wave; rowsum_finish() adds them (and any further batches, which only
 // very wide models need), folds the band groups together with lane shuffles and leaves this wave's
-// partial sums in LDS at lds[wave*128 + row].  rstd_row() adds the partials in wave order.
+// partial sums in LDS at lds[wave * GemmTile::ROWS + row] (128 rows, 256 for eight row blocks); rstd_table() adds them in wave
+// order.  With eight row blocks the rows read can go up to 128 past the padded ones: into the next band's sums, or into the
+// spare band behind the last; nothing is made of them.
 struct RowSumRegs { f32x4_t v[8]; };
 struct NoPre {};
 

@@ -6,7 +6,8 @@
 // for its whole share of K: the 1 KiB operand tiles of U k-steps at a time (a slot) are brought into LDS by the LDS DMA
 // (global_load_lds, 16 bytes per lane: the tile order in memory is the order the matrix cores read, so a tile is copied
 // as it lies and read back lane by lane without bank conflicts), every wave fetching an equal share, and each wave
-// multiplies MB x NT of them out of LDS.  No registers hold data in flight, so up to 140 KB are in flight per CU.
+// multiplies MB x NT of them out of LDS.  No registers hold data in flight: of a ring of up to 140 KB (five slots of 28 or ten
+// of 14) all but two slots are under way in the steady state, 84 KB for 256 x 192 and 112 KB for 128 x 96, all but one at the start.
 //
 // One workgroup barrier per slot.  Slot j + 1 is awaited in front of the last k-step of slot j, so that the reads of its
 // first k-step overlap the multiplications of that last one:

@@ -41,7 +41,7 @@ struct HeadOff  { size_t w1, b1, wout; size_t wl[8], bl[8]; };   // wl[j], j = 2
 
 struct GemmPlan {      // launch shape of one weight-streaming GEMM (bf16 family)
     int mb;            // 32-row blocks per workgroup (1, 2 or 4)
-    int nt;            // 32-column bands per wave (1 or 2)
+    int nt;            // 32-column bands per wave (1 to 5)
     int nw, kw;        // waves per workgroup along N and along K
     int splits;        // workgroups along K (each writes its own partial output)
     int kpw;           // k-steps (of 16) per wave

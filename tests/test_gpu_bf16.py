@@ -231,7 +231,7 @@ def test_tree_verify_forward_five_bands_per_wave_in_gate_up(tree_name, B, L, mon
 
 @pytest.mark.parametrize("tree_name,B,L", [("prior64", 2, 33), ("prior128", 1, 200), ("tiny16", 3, 0), ("prior64", 1, 95)])
 def test_tree_verify_forward_with_rotary_and_append_as_their_own_kernel(tree_name, B, L, monkeypatch):
-    """Beyond 128 rows the planner may split K of the q|k|v GEMM over workgroups and leave rotary embedding and cache
+    """Beyond 64 rows the planner may take the tile kernel for the q|k|v GEMM and leave rotary embedding and cache
     append to a second kernel (which has to undo the pairing of the packed q and k bands); forced here for every shape."""
     monkeypatch.setenv("HYDRA_PLAN_QKV_UNFUSED", "1")
     _verify_forward_teacher_forced(tree_name, B, L)
@@ -270,8 +270,8 @@ def test_greedy_token_and_margin_without_a_logits_buffer(tree_name, B, monkeypat
     """Without a logits buffer the LM head's epilogue keeps two candidates per 32-column band and a small kernel merges
     them; with one, the logits go through memory.  Same inputs through both: hidden states bit-equal, margins
     bit-equal, tokens equal (a token may differ only where the margin is exactly 0: a tie after scaling).  The
-    vocabulary (1000) ends inside a band.  The band-wise path is opt-in (HYDRA_LM_HEAD_TOP2=1); without the switch a
-    call without a logits buffer must give the same bits too."""
+    vocabulary (1000) ends inside a band.  The band-wise path is opt-in (HYDRA_LM_HEAD_TOP2=1) and ends at 64 rows (the
+    128-node tree compares the ordinary path with itself); without the switch a call without a logits buffer must give the same bits too."""
     cfg = bf16_shape()
     W = make_weights(cfg, gain_std=0.1, std=0.05)
     parent = TREES[tree_name]()

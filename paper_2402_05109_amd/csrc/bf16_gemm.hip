@@ -214,7 +214,7 @@ static int launch_bf16(hydra_ctx *c, hipStream_t s, const void *X, const void *W
             rc = fail(HYDRA_E_UNSUPPORTED, "gemm: no tile kernel for this epilogue");
         if (rc) return rc;
     } else if (p.shared_x) {
-        if constexpr (std::is_same<Epi, EpiTop2>::value) {           // up to two row blocks only (launch_gemm_top2)
+        if constexpr (std::is_same<Epi, EpiTop2>::value) {           // never planned for this epilogue (launch_gemm_top2): no such kernel is built
             return fail(HYDRA_E_UNSUPPORTED, "gemm: the band-wise top-2 epilogue has no shared-X kernel");
         } else if (p.shared_x == 8) {
             if (e0) hipExtLaunchKernelGGL((gemm_bf16_sharedx_kernel<4, 2, 8, Epi>), grid, block, lds, s, e0, e1, 0, g, epi);
@@ -245,13 +245,10 @@ static int launch_bf16(hydra_ctx *c, hipStream_t s, const void *X, const void *W
             case 25:
                 if constexpr (std::is_same<Epi, EpiSilu>::value) { launch_one<2, 5>(grid, block, lds, s, g, epi, e0, e1); break; }
                 else return fail(HYDRA_E_UNSUPPORTED, "gemm: no kernel for this plan");
-            default:
-                if constexpr (!std::is_same<Epi, EpiTop2>::value) {
-                    if (key == 41) { launch_one<4, 1>(grid, block, lds, s, g, epi, e0, e1); break; }
-                    if (key == 42) { launch_one<4, 2>(grid, block, lds, s, g, epi, e0, e1); break; }
-                    if (key == 43) { launch_one<4, 3>(grid, block, lds, s, g, epi, e0, e1); break; }
-                }
-                return fail(HYDRA_E_UNSUPPORTED, "gemm: no kernel for this plan");
+            case 41: launch_one<4, 1>(grid, block, lds, s, g, epi, e0, e1); break;
+            case 42: launch_one<4, 2>(grid, block, lds, s, g, epi, e0, e1); break;
+            case 43: launch_one<4, 3>(grid, block, lds, s, g, epi, e0, e1); break;
+            default: return fail(HYDRA_E_UNSUPPORTED, "gemm: no kernel for this plan");
         }
     }
     HYDRA_LAUNCH_CHECK("gemm_bf16_kernel");
@@ -341,14 +338,14 @@ int launch_gemm_resid(hydra_ctx *c, hipStream_t s, const void *X, const void *W,
 
 // LM head straight to per-band top-2 candidates (no logits): *fused = 0 and nothing launched where the plan that splits K
 // over workgroups is estimated clearly faster than one workgroup per band group (the candidates need complete sums), and
-// beyond 64 rows, where the logits come from the tile kernel (no kernel of more than two row blocks is built for it).
+// beyond 64 rows, where the logits come from the tile kernel (except at K = 128 with up to 128 rows, which it declines).
 // Opt-in (HYDRA_LM_HEAD_TOP2=1): measured at the 7B shape it is a wash, 50.3 + 5.8 us against 47.0 + 11.6 us at 64 rows and
 // 52.1 + 5.7 against 41.8 + ~8 us for the one-node tree, so by default the logits go through memory.
 int launch_gemm_top2(hydra_ctx *c, hipStream_t s, const void *X, const void *W, int M, int N, int K, float *cand, int Mpad, int *fused) {
     *fused = 0;
-    if (M > 64 || env_or("HYDRA_LM_HEAD_TOP2", 0.0) == 0.0) return HYDRA_OK;
-    const GemmPlan p = plan_gemm(c, M, N, K, GEMM_KIND_FUSED);
-    if (p.cost_us > plan_gemm(c, M, N, K, GEMM_KIND_PLAIN).cost_us + 4.0f) return HYDRA_OK;
+    if (env_or("HYDRA_LM_HEAD_TOP2", 0.0) == 0.0) return HYDRA_OK;
+    const GemmPlan ps = plan_gemm(c, M, N, K, GEMM_KIND_PLAIN), p = plan_gemm(c, M, N, K, GEMM_KIND_FUSED);
+    if (p.shared_x || ps.tile || p.cost_us > ps.cost_us + 4.0f) return HYDRA_OK;
     *fused = 1;
     EpiTop2 epi{cand, Mpad, N};
     return launch_bf16<EpiTop2, NT_ANY>(c, s, X, W, M, N, K, p, epi);
@@ -420,9 +417,7 @@ static hipError_t set_attr_all() {
     if (e == hipSuccess) e = set_attr<1, 3, Epi>(); if (e == hipSuccess) e = set_attr<1, 4, Epi>();
     if (e == hipSuccess) e = set_attr<2, 1, Epi>(); if (e == hipSuccess) e = set_attr<2, 2, Epi>();
     if (e == hipSuccess) e = set_attr<2, 3, Epi>(); if (e == hipSuccess) e = set_attr<2, 4, Epi>();
-    if constexpr (!std::is_same<Epi, EpiTop2>::value) {
-        if (e == hipSuccess) e = set_attr<4, 1, Epi>(); if (e == hipSuccess) e = set_attr<4, 2, Epi>();
-    }
+    if (e == hipSuccess) e = set_attr<4, 1, Epi>(); if (e == hipSuccess) e = set_attr<4, 2, Epi>();
     return e;
 }
 

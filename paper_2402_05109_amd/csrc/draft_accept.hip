@@ -400,47 +400,38 @@ int launch_accept(hydra_ctx *c, hipStream_t s, int B, const int32_t *tree_tokens
 // ---------------------------------------------------------------------------
 enum { TYP_THREADS = 1024, TYP_GROUPS = 8, TYP_STRIPE = TYP_THREADS * 4, TYP_PIECE = TYP_STRIPE * TYP_GROUPS };
 
-// no entry of this piece lies past V (the same for every thread)
-__device__ __forceinline__ bool typ_whole(int piece, int V) { return V - piece * TYP_PIECE >= TYP_PIECE; }
-
 // One piece of a row in registers: thread t holds groups of four consecutive ids, group i at (i * 1024 + t) * 4, so that the
-// ids ascend with i first and with the thread second.  Entries past V are -infinity: never a maximum, and of weight
-// exp(-inf / tau) = 0, except that an infinite temperature makes that exp(-inf * 0), not a number: then (PAD) their weight is
-// 0 by their id.  A comparison per entry at every temperature cost typical_stats_kernel 0.5 of 6.7 us.
-// Rows start wherever V puts them: the loads ask for no more than float alignment.  The one group that V cuts is read
-// entry by entry.
+// ids ascend with i first and with the thread second.  Rows start wherever V puts them: the loads ask for no more than float
+// alignment.  Groups past V4 = V rounded down to 4 are -infinity: never a maximum, and of weight exp(-inf / tau) = 0, except that
+// an infinite temperature makes that exp(-inf * 0), not a number: then (PAD) their weight is 0 by their id.  A comparison per
+// entry at every temperature cost typical_stats_kernel 0.5 of 6.7 us.
+// The up to three entries behind V4 (TypTail) are the same loads in every thread.  Letting the group that V cuts take them, entry
+// by entry, puts branches between the loads: the stats of 4 rows took 6.9 us at V = 32000 and 12.1 at 50257, so 6.7 and 10.8.
+struct TypTail { float x[3]; };
+__device__ __forceinline__ TypTail typ_tail(const float *__restrict__ row, int V, int V4) {
+    TypTail t;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) t.x[k] = V4 + k < V ? row[V4 + k] : -INFINITY;
+    return t;
+}
 struct TypRow {
     float x[TYP_GROUPS][4];
     __device__ __forceinline__ int id(int piece, int i) const { return piece * TYP_PIECE + i * TYP_STRIPE + (int)threadIdx.x * 4; }
-    // the same, worked out where it is used: the ids, addresses and limits of every group kept across the steps, for the pieces
-    // that need them entry by entry, cost more registers than there are
+    // the same, worked out where it is used: the id of every group kept across the steps costs more registers than there are
     __device__ __forceinline__ int id_here(int piece, int i) const {
         int t = (int)threadIdx.x;
         asm volatile("" : "+v"(t));
         return piece * TYP_PIECE + i * TYP_STRIPE + t * 4;
     }
-    __device__ __forceinline__ void load(const float *__restrict__ row, int V, int piece) {
-        if (typ_whole(piece, V)) fill<true>(row, V, piece);         // loads without a branch between them
-        else                     fill<false>(row, V, piece);
-    }
-    template <bool WHOLE>
-    __device__ __forceinline__ void fill(const float *__restrict__ row, int V, int piece) {
+    __device__ __forceinline__ void load(const float *__restrict__ row, int V4, int piece) {
         typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
 #pragma unroll
         for (int i = 0; i < TYP_GROUPS; ++i) {
-            const int v = WHOLE ? id(piece, i) : id_here(piece, i);
-            if (WHOLE || V - piece * TYP_PIECE >= (i + 1) * TYP_STRIPE) {      // the same for every thread
-                const f4u t = *reinterpret_cast<const f4u *>(row + id(piece, i));
+            const int v = id(piece, i);
+            f4u t = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+            if (v < V4) t = *reinterpret_cast<const f4u *>(row + v);
 #pragma unroll
-                for (int e = 0; e < 4; ++e) x[i][e] = t[e];
-            } else if (v + 4 <= V) {
-                const f4u t = *reinterpret_cast<const f4u *>(row + v);
-#pragma unroll
-                for (int e = 0; e < 4; ++e) x[i][e] = t[e];
-            } else {
-#pragma unroll
-                for (int e = 0; e < 4; ++e) x[i][e] = v + e < V ? row[v + e] : -INFINITY;
-            }
+            for (int e = 0; e < 4; ++e) x[i][e] = t[e];
         }
     }
     __device__ __forceinline__ float largest() const {
@@ -473,10 +464,11 @@ __global__ __launch_bounds__(TYP_THREADS) void typical_stats_kernel(const float 
     __shared__ float2 sh2[16];
     const int n = blockIdx.x, b = blockIdx.y;
     const float *row = logits + ((size_t)b * T + n) * V;
-    const int nc = tree->n_children[n], first = tree->first_child[n];
+    const int nc = tree->n_children[n], first = tree->first_child[n], V4 = V & ~3;
     if (nc == 0) return;                                            // uniform over the workgroup
     TypRow r;
-    r.load(row, V, 0);
+    r.load(row, V4, 0);
+    const TypTail tail = typ_tail(row, V, V4);
     int tok = 0;
     float xt = 0.f;
     if ((int)threadIdx.x < nc) {                                    // at most 32 children; their logits are fetched with the row
@@ -485,25 +477,30 @@ __global__ __launch_bounds__(TYP_THREADS) void typical_stats_kernel(const float 
         xt = row[tok];
     }
     const int pieces = (V + TYP_PIECE - 1) / TYP_PIECE;
-    float m = r.largest();
-    for (int pc = 1; pc < pieces; ++pc) { TypRow q; q.load(row, V, pc); m = fmaxf(m, q.largest()); }
+    float m = fmaxf(fmaxf(r.largest(), tail.x[0]), fmaxf(tail.x[1], tail.x[2]));
+    for (int pc = 1; pc < pieces; ++pc) { TypRow q; q.load(row, V4, pc); m = fmaxf(m, q.largest()); }
     m = block_reduce(m, sh, true);
     float z = 0.f, sz = 0.f;
+    auto one = [&](float x, bool in) {
+        const float t = (x - m) * inv_tau;                          // <= 0
+        const float ex = in ? __expf(t) : 0.f;
+        z += ex;
+        sz += ex > 0.f ? ex * t : 0.f;                              // exp underflow: 0 * (-inf) must not appear
+    };
     auto add = [&](auto PAD, int pc) {
 #pragma unroll
         for (int i = 0; i < TYP_GROUPS; ++i)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const float t = (r.x[i][e] - m) * inv_tau;          // <= 0
-                const float ex = !decltype(PAD)::value || r.id_here(pc, i) + e < V ? __expf(t) : 0.f;
-                z += ex;
-                sz += ex > 0.f ? ex * t : 0.f;                      // exp underflow: 0 * (-inf) must not appear
-            }
+            for (int e = 0; e < 4; ++e) one(r.x[i][e], !decltype(PAD)::value || r.id(pc, i) < V4);
     };
     for (int pc = 0; pc < pieces; ++pc) {
-        if (pieces > 1) r.load(row, V, pc);
+        if (pieces > 1) r.load(row, V4, pc);
         if (inv_tau > 0.f) add(std::false_type{}, pc);
         else               add(std::true_type{}, pc);
+    }
+    if (threadIdx.x == 0) {
+#pragma unroll
+        for (int k = 0; k < 3; ++k) one(tail.x[k], V4 + k < V);
     }
     z = wave_sum(z);
     sz = wave_sum(sz);
@@ -522,7 +519,7 @@ __global__ __launch_bounds__(TYP_THREADS) void typical_stats_kernel(const float 
 // wave; the stripe in which the cumulative mass exceeds u times the total, the wave inside it, and then lane and id inside
 // that wave follow from prefix sums of ever smaller pieces, each starting from the very number at which the piece before it
 // ended, and only pieces that hold any mass are taken: the token drawn always has a positive weight.  4 rows: 7.4 us at
-// V = 32000, 7.6 at 32003, 16.3 at 50257.  A scan of every stripe over the lanes instead of the one that matters keeps a
+// V = 32000, 7.3 at 32003, 15.0 at 50257.  A scan of every stripe over the lanes instead of the one that matters keeps a
 // prefix sum per group alive (16 registers spilled, 192 where V ruled out 16-byte loads) and took 16.2, 28.6 and 75.3.
 __global__ __launch_bounds__(TYP_THREADS) void typical_select_kernel(const float *__restrict__ logits, int V, const TreeDev *tree,
                                                                       const int32_t *__restrict__ ok, float inv_tau,
@@ -531,7 +528,7 @@ __global__ __launch_bounds__(TYP_THREADS) void typical_select_kernel(const float
     __shared__ float sh[16];
     __shared__ uint64_t pass[2];
     __shared__ int bestw[2];
-    const int b = blockIdx.x, plen = tree->max_depth + 1;
+    const int b = blockIdx.x, plen = tree->max_depth + 1, V4 = V & ~3;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     // Waves 0 and 1 hold one node per lane (T <= 128): a node is accepted if its own test and those of all its ancestors
     // passed, which its ancestor mask says; the winner is the deepest, then the lowest id.
@@ -559,7 +556,8 @@ __global__ __launch_bounds__(TYP_THREADS) void typical_select_kernel(const float
     const int best = 255 - (int)(kbest & 255u);
     const float *row = logits + ((size_t)b * T + best) * V;
     TypRow r;
-    r.load(row, V, 0);                                              // requested before the path is written out
+    r.load(row, V4, 0);                                             // requested before the path is written out
+    const TypTail tail = typ_tail(row, V, V4);
     if (threadIdx.x == 0) {
         const int len = (int)(kbest >> 8) + 1;
         int32_t *p = path + (size_t)b * plen;
@@ -574,12 +572,17 @@ __global__ __launch_bounds__(TYP_THREADS) void typical_select_kernel(const float
         // most likely token, lowest id at ties
         float bv = -INFINITY; int bi = 0x7fffffff;
         for (int pc = 0; pc < pieces; ++pc) {
-            if (pc) r.load(row, V, pc);
+            if (pc) r.load(row, V4, pc);
 #pragma unroll
             for (int i = 0; i < TYP_GROUPS; ++i)
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
                     if (r.x[i][e] > bv) { bv = r.x[i][e]; bi = r.id(pc, i) + e; }      // ascending ids per thread: first maximum kept
+        }
+        if (threadIdx.x == 0) {
+#pragma unroll
+            for (int k = 0; k < 3; ++k)
+                if (tail.x[k] > bv) { bv = tail.x[k]; bi = V4 + k; }
         }
         Cand cnd = wave_best(Cand{bv, bi});
         __shared__ Cand red[16];
@@ -592,18 +595,18 @@ __global__ __launch_bounds__(TYP_THREADS) void typical_select_kernel(const float
         }
         return;
     }
-    float m = r.largest();
-    for (int pc = 1; pc < pieces; ++pc) { TypRow q; q.load(row, V, pc); m = fmaxf(m, q.largest()); }
+    float m = fmaxf(fmaxf(r.largest(), tail.x[0]), fmaxf(tail.x[1], tail.x[2]));
+    for (int pc = 1; pc < pieces; ++pc) { TypRow q; q.load(row, V4, pc); m = fmaxf(m, q.largest()); }
     m = block_reduce(m, sh, true);
     __shared__ float part[16][TYP_GROUPS];                          // [wave][stripe] of one piece
     float sum_a = 0.f, sum_b = 0.f;                                  // lane l: the sums of stripes l / 16 and 4 + l / 16
     auto stripes = [&](int pc) {                                     // piece pc: its weights in place of the logits, part, sum_a, sum_b
-        if (pieces > 1) r.load(row, V, pc);
+        if (pieces > 1) r.load(row, V4, pc);
         auto weights = [&](auto PAD) {
 #pragma unroll
             for (int i = 0; i < TYP_GROUPS; ++i)
 #pragma unroll
-                for (int e = 0; e < 4; ++e) r.x[i][e] = !decltype(PAD)::value || r.id_here(pc, i) + e < V ? __expf((r.x[i][e] - m) * inv_tau) : 0.f;
+                for (int e = 0; e < 4; ++e) r.x[i][e] = !decltype(PAD)::value || r.id_here(pc, i) < V4 ? __expf((r.x[i][e] - m) * inv_tau) : 0.f;
         };
         if (inv_tau > 0.f) weights(std::false_type{});
         else               weights(std::true_type{});
@@ -649,6 +652,12 @@ __global__ __launch_bounds__(TYP_THREADS) void typical_select_kernel(const float
 #pragma unroll
         for (int i = 0; i < TYP_GROUPS; ++i) total += stripe(i);     // the same in every thread
     }
+    float wt[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        wt[k] = V4 + k < V ? __expf((tail.x[k] - m) * inv_tau) : 0.f;
+        total += wt[k];
+    }
     const float target = u[b] * total;
     float cum = 0.f;
     int at = -1, pc = 0;
@@ -662,8 +671,12 @@ __global__ __launch_bounds__(TYP_THREADS) void typical_select_kernel(const float
         }
         if (at >= 0) break;
     }
-    if (at < 0) {                                                    // no token's cumulative mass exceeds the target
-        if (threadIdx.x == 0) next_root[b] = V - 1;
+    if (at < 0) {
+        int pick = V - 1;                                            // no token's cumulative mass exceeds the target
+#pragma unroll
+        for (int k = 2; k >= 0; --k)                                 // the tail's entries, the first that does last
+            if (target >= 0.f && wt[k] > 0.f && cum + (k > 0 ? wt[0] : 0.f) + (k > 1 ? wt[1] : 0.f) + wt[k] > target) pick = V4 + k;
+        if (threadIdx.x == 0) next_root[b] = pick;
         return;
     }
     const float wsum = part[lane & 15][at], wincl = prefix(wsum, 16);

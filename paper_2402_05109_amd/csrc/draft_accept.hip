@@ -209,48 +209,51 @@ __global__ __launch_bounds__(64) void topk_chunk_kernel(const float *part, int S
 // k-th largest of the 64 lane maxima, so the lanes rank their maxima against each other (64 scalar broadcasts), drop
 // everything below that bound, put what is left (a little over k entries) one per lane through LDS and rank those the same
 // way; ranks follow the order, ids break ties, so nothing has to be extracted in turn.  More than 64 entries at or above the
-// bound (many equal logits) go back to k rounds of a maximum over the wave.  With rounds only the merge took 7.4 us per head
-// (7B, up to 10 children), so 5.6; in the first kernel, whose ids are implied by the slot and whose rounds are therefore
+// bound (many equal logits) go back to k rounds of a maximum over the wave, as do one or two children: rounds cost 0.9 us each
+// where ranking costs 1.4 in all (one row, V = 1000: 2.7 / 3.5 / 4.4 us for 1 / 2 / 3 children against 3.9 / 3.9 / 4.0).  With
+// rounds only the merge took 7.4 us per head (7B, up to 10 children), so 5.6; in the first kernel, whose ids are implied by the slot and whose rounds are therefore
 // half as long, it loses (10.4 against 9.6 us).
 
 // key[i] (0: no entry) with id[i]; put(t, key, id) is called for t < k by one lane each: key 0 and id ~0 past the last entry.
 // list: 64 entries of LDS.
 template <int N, class Put>
 __device__ __forceinline__ void wave_top_k(uint32_t (&key)[N], const uint32_t (&id)[N], int k, uint2 *list, int lane, Put put) {
-    uint32_t best = 0u;
+    if (k > 2) {
+        uint32_t best = 0u;
 #pragma unroll
-    for (int i = 0; i < N; ++i) best = max(best, key[i]);
-    int rank = 0;                                                     // of this lane's maximum; equal ones by lane number
+        for (int i = 0; i < N; ++i) best = max(best, key[i]);
+        int rank = 0;                                                     // of this lane's maximum; equal ones by lane number
 #pragma unroll 8
-    for (int l = 0; l < 64; ++l) {
-        const uint32_t o = (uint32_t)__builtin_amdgcn_readlane((int)best, l);
-        rank += (o > best || (o == best && l < lane)) ? 1 : 0;
-    }
-    const uint64_t at = __ballot(rank == k - 1);                      // k <= HYDRA_MAX_TOPK = 32: exactly one lane
-    const uint32_t bound = max((uint32_t)__builtin_amdgcn_readlane((int)best, __builtin_ctzll(at)), 1u);
-    int count = 0;
+        for (int l = 0; l < 64; ++l) {
+            const uint32_t o = (uint32_t)__builtin_amdgcn_readlane((int)best, l);
+            rank += (o > best || (o == best && l < lane)) ? 1 : 0;
+        }
+        const uint64_t at = __ballot(rank == k - 1);                      // k <= HYDRA_MAX_TOPK = 32: exactly one lane
+        const uint32_t bound = max((uint32_t)__builtin_amdgcn_readlane((int)best, __builtin_ctzll(at)), 1u);
+        int count = 0;
 #pragma unroll
-    for (int i = 0; i < N; ++i) {
-        const uint64_t has = __ballot(key[i] >= bound);
-        if (key[i] >= bound) {
-            const int pos = count + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(has >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)has, 0u));
-            if (pos < 64) list[pos] = make_uint2(key[i], id[i]);
+        for (int i = 0; i < N; ++i) {
+            const uint64_t has = __ballot(key[i] >= bound);
+            if (key[i] >= bound) {
+                const int pos = count + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(has >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)has, 0u));
+                if (pos < 64) list[pos] = make_uint2(key[i], id[i]);
+            }
+            count += __popcll(has);
         }
-        count += __popcll(has);
-    }
-    if (count <= 64) {                                                // wave-uniform
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");         // LDS is in order within a wave; keep the compiler from reordering
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        const uint2 e = lane < count ? list[lane] : make_uint2(0u, 0xffffffffu);
-        int r = 0;
-        for (int l = 0; l < count; ++l) {
-            const uint32_t ok = (uint32_t)__builtin_amdgcn_readlane((int)e.x, l), oi = (uint32_t)__builtin_amdgcn_readlane((int)e.y, l);
-            r += (ok > e.x || (ok == e.x && oi < e.y)) ? 1 : 0;
+        if (count <= 64) {                                                // wave-uniform
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");         // LDS is in order within a wave; keep the compiler from reordering
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            const uint2 e = lane < count ? list[lane] : make_uint2(0u, 0xffffffffu);
+            int r = 0;
+            for (int l = 0; l < count; ++l) {
+                const uint32_t ok = (uint32_t)__builtin_amdgcn_readlane((int)e.x, l), oi = (uint32_t)__builtin_amdgcn_readlane((int)e.y, l);
+                r += (ok > e.x || (ok == e.x && oi < e.y)) ? 1 : 0;
+            }
+            if (lane < count && r < k) put(r, e.x, e.y);
+            if (lane >= count && lane < k) put(lane, 0u, 0xffffffffu);     // fewer entries than k
+            return;
         }
-        if (lane < count && r < k) put(r, e.x, e.y);
-        if (lane >= count && lane < k) put(lane, 0u, 0xffffffffu);     // fewer entries than k
-        return;
     }
     for (int t = 0; t < k; ++t) {
         uint32_t bk = 0u, bi = 0xffffffffu;

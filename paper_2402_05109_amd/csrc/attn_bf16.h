@@ -25,16 +25,67 @@ __device__ __forceinline__ uint32_t half_pack(float lo, float hi) {
     return __builtin_bit_cast(uint32_t, __builtin_convertvector((f2{lo, hi}), h2));
 }
 
+// Which of the 32 keys at slot0 .. slot0 + 31 a query sees, one bit each: every cached slot, and the tree slots that its ancestor
+// mask names (no bit of it is set from node T on).  Written without a branch per key: with `slot < L ? .. : mask bit` per score
+// the compiler made two nested branches of each of the 16 scores of a lane, also for tiles that need no mask, and they were
+// a fifth of a tile's time (0.9 us per 32-key tile with two waves to a SIMD, 0.7 now).
+__device__ __forceinline__ uint32_t keys_seen(int slot0, int L, uint64_t anc0, uint64_t anc1) {
+    const int rel = slot0 - L;                             // node of the first key; negative: cached slots first
+    if (rel < 0) {
+        const int n = -rel;                                // cached slots among the 32 (uniform)
+        return n >= 32 ? 0xffffffffu : ((1u << n) - 1u) | ((uint32_t)anc0 << n);
+    }
+    if (rel >= 64) return rel >= 128 ? 0u : (uint32_t)(anc1 >> (rel - 64));
+    return (uint32_t)(anc0 >> rel) | (rel > 32 ? (uint32_t)(anc1 << (64 - rel)) : 0u);
+}
+
+// One 32-key tile's scores, S^T = K Q^T as the matrix cores leave it -> probabilities, in place, and the running maximum and sum
+// of the lane's query.  Returns the factor by which what was accumulated before has to be scaled.
+__device__ __forceinline__ float softmax_tile(f32x16_t &sc, float scale, bool need_mask, int slot0, int L, uint64_t anc0, uint64_t anc1, int hl,
+                                              float &m_run, float &l_run, bool &moved) {
+#pragma unroll
+    for (int v = 0; v < 16; ++v) sc[v] *= scale;
+    if (need_mask) {                                       // uniform: the tiles that hold tree slots or end the row
+        const uint32_t seen = keys_seen(slot0, L, anc0, anc1) >> (4 * hl);
+#pragma unroll
+        for (int v = 0; v < 16; ++v) sc[v] = (seen >> (8 * (v >> 2) + (v & 3))) & 1u ? sc[v] : -INFINITY;
+    }
+    float cmax = -INFINITY;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) cmax = fmaxf(cmax, sc[v]);
+    const HalfWaves cm = half_waves(cmax);
+    cmax = fmaxf(cm.lo, cm.hi);
+    const float m_new = fmaxf(m_run, cmax);
+    const float m_safe = (m_new == -INFINITY) ? 0.f : m_new;
+    const float alpha = __expf(m_run - m_safe);
+    moved = __any(m_new != m_run);
+    float rs = 0.f;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+        const float p = __expf(sc[v] - m_safe);            // exp(-inf) = 0 for masked keys
+        sc[v] = p;
+        rs += p;
+    }
+    const HalfWaves rh = half_waves(rs);
+    rs = rh.lo + rh.hi;
+    l_run = l_run * alpha + rs;
+    m_run = m_new;
+    return alpha;
+}
+
 template <int DH>
 struct KVTile { u32x4_t k[DH / 16]; u32x4_t v[2][DH / 32]; };
 
 template <int DH>
-__device__ __forceinline__ void load_kv_tile(KVTile<DH> &kv, const a16_t *kpages, const a16_t *vpages,
-                                             int p0, int p1, int layer, int n_pages, int H, int h, int lane) {
+__device__ __forceinline__ void load_k_tile(KVTile<DH> &kv, const a16_t *kpages, int p0, int p1, int layer, int n_pages, int H, int h, int lane) {
     const int hl = lane >> 5, col = lane & 31;
     const u32x4_t *kp = reinterpret_cast<const u32x4_t *>(kpages + kv_block_base(layer, n_pages, (col >> 4) ? p1 : p0, H, h, DH));
 #pragma unroll
     for (int s = 0; s < DH / 16; ++s) kv.k[s] = kp[(2 * s + hl) * 16 + (col & 15)];
+}
+template <int DH>
+__device__ __forceinline__ void load_v_tile(KVTile<DH> &kv, const a16_t *vpages, int p0, int p1, int layer, int n_pages, int H, int h, int lane) {
+    const int hl = lane >> 5, col = lane & 31;
 #pragma unroll
     for (int g = 0; g < 2; ++g) {
         const u32x4_t *vp = reinterpret_cast<const u32x4_t *>(vpages + kv_block_base(layer, n_pages, g ? p1 : p0, H, h, DH));
@@ -121,14 +172,15 @@ __device__ __forceinline__ void attn_bf16_body(
         {
             const int p0 = checked_page(pg[0][0], n_pages, flags);
             const int p1 = (2 * unit + 1 < row_pages) ? checked_page(pg[0][1], n_pages, flags) : p0;
-            load_kv_tile<DH>(cur, kpages, vpages, p0, p1, layer, n_pages, H, h, lane);
+            load_k_tile<DH>(cur, kpages, p0, p1, layer, n_pages, H, h, lane);
+            load_v_tile<DH>(cur, vpages, p0, p1, layer, n_pages, H, h, lane);
         }
         int it = 0;                                        // index of tile t among this wave's tiles
         for (int t = unit; t < n_tiles; t += units, ++it) {
             const bool more = t + units < n_tiles;
+            int p0 = 0, p1 = 0;                            // pages of the next tile
             if (more) {
                 const int tn = t + units;
-                int p0, p1;
                 switch (it + 1) {                          // wave-uniform; keeps the page ids in scalar registers
                     case 1: p0 = pg[1][0]; p1 = pg[1][1]; break;
                     case 2: p0 = pg[2][0]; p1 = pg[2][1]; break;
@@ -139,7 +191,10 @@ __device__ __forceinline__ void attn_bf16_body(
                 if (2 * tn + 1 >= row_pages) p1 = p0;
                 p0 = checked_page(p0, n_pages, flags);                  // wave-uniform
                 p1 = checked_page(p1, n_pages, flags);
-                load_kv_tile<DH>(nxt, kpages, vpages, p0, p1, layer, n_pages, H, h, lane);
+                if (!DEV) {
+                    load_k_tile<DH>(nxt, kpages, p0, p1, layer, n_pages, H, h, lane);
+                    load_v_tile<DH>(nxt, vpages, p0, p1, layer, n_pages, H, h, lane);
+                }
             }
             const int slot0 = t * 32;
             if (slot0 + 32 > total) {   // zero V of slots >= total (stale or never written): 0 * garbage must not appear
@@ -164,46 +219,19 @@ __device__ __forceinline__ void attn_bf16_body(
 #pragma unroll
             for (int s = 0; s < KS; ++s)
                 sc = HYDRA_MFMA16(__builtin_bit_cast(a16x8_t, cur.k[s]), __builtin_bit_cast(a16x8_t, QLDS ? qlds[qoff + s * 64] : qreg[s]), sc);
-            const bool need_mask = slot0 + 32 > L;
-            float cmax = -INFINITY;
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                float x = sc[v] * scale;
-                if (need_mask) {
-                    const int slot = slot0 + 8 * (v >> 2) + 4 * hl + (v & 3);
-                    bool ok = slot < L;
-                    if (!ok) {
-                        const int a = slot - L;
-                        ok = a < T && (((a < 64 ? anc0 >> a : anc1 >> (a - 64)) & 1ull) != 0);
-                    }
-                    x = ok ? x : -INFINITY;
-                }
-                sc[v] = x;
-                cmax = fmaxf(cmax, x);
-            }
-            cmax = fmaxf(cmax, __shfl_xor(cmax, 32, 64));
-            const float m_new = fmaxf(m_run, cmax);
-            const float m_safe = (m_new == -INFINITY) ? 0.f : m_new;
-            const float alpha = __expf(m_run - m_safe);
+            // the layer kernel, whose waves hold weights as well, has one tile's registers: the next K comes once K is used
+            if (DEV && more) load_k_tile<DH>(cur, kpages, p0, p1, layer, n_pages, H, h, lane);
+            bool moved;
+            const float alpha = softmax_tile(sc, scale, slot0 + 32 > L, slot0, L, anc0, anc1, hl, m_run, l_run, moved);
             // the accumulators are rescaled only where some query's maximum moved (a factor of one otherwise; the first tile
-            // has nothing to rescale).  Not in the layer kernel, which is at its limit of registers already: the branch costs
-            // it eight more spills.
-            if (DEV || (it > 0 && __any(m_new != m_run))) {
+            // has nothing to rescale).  Always in the layer kernel, where the branch costs registers that it lacks.
+
+            if (DEV || (it > 0 && moved)) {
 #pragma unroll
                 for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
                     for (int v = 0; v < 16; ++v) o[dt][v] *= alpha;
             }
-            float rs = 0.f;
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const float p = __expf(sc[v] - m_safe);        // exp(-inf) = 0 for masked keys
-                sc[v] = p;
-                rs += p;
-            }
-            rs += __shfl_xor(rs, 32, 64);
-            l_run = l_run * alpha + rs;
-            m_run = m_new;
             // P^T operands: page g uses accumulator registers 8g .. 8g+7 in order
 #pragma unroll
             for (int g = 0; g < 2; ++g) {
@@ -214,7 +242,8 @@ __device__ __forceinline__ void attn_bf16_body(
                 for (int dt = 0; dt < DT; ++dt)
                     o[dt] = HYDRA_MFMA16(__builtin_bit_cast(a16x8_t, cur.v[g][dt]), __builtin_bit_cast(a16x8_t, pb), o[dt]);
             }
-            if (more) cur = nxt;
+            if (DEV && more) load_v_tile<DH>(cur, vpages, p0, p1, layer, n_pages, H, h, lane);
+            if (!DEV && more) cur = nxt;
         }
     }
 

@@ -17,11 +17,10 @@
 // 16-byte-per-lane loads straight from the cache pages.
 //
 // A workgroup is 8 waves on one (b, h).  Two launch shapes:
-//   short contexts (up to ~1200 keys): one workgroup per 32-query tile; its 8
-//     waves split the keys (32-key tiles taken round-robin, next tile prefetched
-//     while the current one is multiplied), are merged through LDS, and the
-//     result goes straight out as the next GEMM's input: one kernel, no partial
-//     records.  A CU streams at most ~45 GB/s, which is what bounds this shape;
+//   short contexts (up to ~1200 keys): attn_short_kernel, one workgroup per
+//     32-query tile and share of the head's dims; its 8 waves split the keys and
+//     the result goes straight out as the next GEMM's input: one kernel, no
+//     partial records;
 //   longer contexts: QW waves of a workgroup take different query tiles, 8/QW
 //     waves split the keys, and several workgroups per (b, h) split the keys
 //     further; each leaves a (max, sum, O) record that attn_merge_kernel combines.
@@ -44,6 +43,199 @@ __global__ __launch_bounds__(ATTN_WAVES * 64) void attn_bf16_kernel(
     extern __shared__ float lds[];
     attn_bf16_body<DH, PACKED, false, true>(qbuf, kpages, vpages, page_table, max_pages, n_pages, layer, seq_len, tree, T, H, QW, qsplit,
                                       scale, apart, out, flags, (int)blockIdx.x, (int)gridDim.x, (int)blockIdx.y, (int)blockIdx.z, lds, (int)threadIdx.x);
+}
+
+// Short contexts: a workgroup takes one 32-query tile of one (row, head) and 1 / DS of the head's dims; its eight waves split
+// the keys and meet in LDS, and the result goes straight out as the next GEMM's input.  The key loop does what attn_bf16_body does,
+// sum for sum.
+//
+// Bound by a chain: launch and row length 2.0 us, K/V 3.2 (memory-side cache), three to four tiles of 0.7, merge and store 1.1
+// (in-kernel clocks, 64 queries, 840 keys, 32 heads).  A workgroup's requests go through its CU at 64 bytes a cycle, so a head is shared
+// out over as many workgroups as the chip takes in one round: with all of K and 1 / DS of V each one asks for less (430 KB ->
+// 270 with DS = 4) and holds more tiles at once (RING; the accumulators and V tiles shrink with DS).  The scores are computed
+// DS times over, which idle CUs do for nothing.  The workgroups of a head sit on one XCD (workgroup i runs on XCD i % 8),
+// whose L2 then fetches K and V once.  64 x 840: 10.9 / 10.2 / 9.7 us with DS = 1 / 2 / 4, 12.5 before; on the whole
+// verification call of 32 layers 3769 -> 3687 us, one node behind 701 tokens 797 -> 775 (8 layers).
+template <int DH, int DS>
+struct ShortTile { u32x4_t k[DH / 16]; u32x4_t v[2][DH / 32 / DS]; };
+enum { ATTN_SHORT_TILES = 5 };                              // 32-key tiles per wave up to which the launch rule takes this kernel
+
+template <int DH, int DS, bool PACKED>
+__global__ __launch_bounds__(ATTN_WAVES * 64) void attn_short_kernel(
+    const u32x4_t *__restrict__ qbuf, const a16_t *__restrict__ kpages, const a16_t *__restrict__ vpages,
+    const int32_t *__restrict__ page_table, int max_pages, int n_pages, int layer, const int32_t *__restrict__ seq_len,
+    const TreeDev *__restrict__ tree, int T, int H, int groups, float scale, void *out, int32_t *flags) {
+    constexpr int KS = DH / 16, DT = DH / 32 / DS, RING = DS == 4 ? 4 : DS == 2 ? 3 : 2, NW = ATTN_WAVES;
+    extern __shared__ float lds[];                          // [NW][2][32] maxima and sums, then the query tile and later O[NW][DT * 16][64]
+    const int tid = (int)threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int hl = lane >> 5, col = lane & 31;
+    const int QTtot = (T + 31) >> 5, per = QTtot * DS;
+    const int seq = (int)blockIdx.x >> 3;
+    const int group = seq / per * 8 + ((int)blockIdx.x & 7), j = seq % per;
+    if (group >= groups) return;
+    const int b = group / H, h = group - b * H, qtile = j / DS, ds = j % DS;
+    const int32_t *pt = page_table + (size_t)b * max_pages;
+    // everything whose address does not depend on the row's length is requested before the length is known: the queries (each
+    // wave brings a share of the tile), the ancestor masks, and the page ids of this wave's tiles (the table has max_pages
+    // entries for every row; entries past the row's pages are not used)
+    u32x4_t *qs = reinterpret_cast<u32x4_t *>(lds + NW * 64);
+    const int query = qtile * 32 + col;
+    uint64_t anc0 = 0ull, anc1 = 0ull;
+    if (query < T) { anc0 = tree->anc[query][0]; anc1 = tree->anc[query][1]; }
+    int pg[ATTN_SHORT_TILES][2];
+#pragma unroll
+    for (int i = 0; i < ATTN_SHORT_TILES; ++i) {
+        const int t = wave + i * NW;
+        pg[i][0] = pt[min(2 * t, max_pages - 1)];
+        pg[i][1] = pt[min(2 * t + 1, max_pages - 1)];
+    }
+    const int L = seq_len[b];
+    if (wave < KS) qs[wave * 64 + lane] = qbuf[((((size_t)b * H + h) * QTtot + qtile) * KS + wave) * 64 + lane];
+    if (L < 0 || L + T > max_pages * 16) {                  // uniform over the workgroup
+        if (tid == 0 && j == 0 && h == 0) atomicOr(flags, FLAG_CAPACITY);
+        return;
+    }
+    const int total = L + T, n_tiles = (total + 31) >> 5, row_pages = (total + 15) >> 4;
+    const int mine_n = wave < n_tiles ? (n_tiles - wave + NW - 1) / NW : 0;     // this wave's tiles: wave, wave + NW, ...
+
+    // Loads are never behind a condition (the compiler then knows how many are younger than the ones it waits for): a tile past
+    // the last one reads one and the same piece of page 0 in every lane.
+    auto load = [&](ShortTile<DH, DS> &kv, int it, int p0, int p1) {
+        const int t = wave + it * NW;
+        const bool live = t < n_tiles;
+        if (2 * t + 1 >= row_pages) p1 = p0;                // second page of a tile: absent when the row ends inside the first
+        p0 = live ? checked_page(p0, n_pages, flags) : 0;
+        p1 = live ? checked_page(p1, n_pages, flags) : 0;
+        const int ln = live ? lane : 0, lh = ln >> 5, lc = ln & 31;
+        const u32x4_t *kp = reinterpret_cast<const u32x4_t *>(kpages + kv_block_base(layer, n_pages, (lc >> 4) ? p1 : p0, H, h, DH));
+#pragma unroll
+        for (int s = 0; s < KS; ++s) kv.k[s] = kp[(2 * s + lh) * 16 + (lc & 15)];
+#pragma unroll
+        for (int g = 0; g < 2; ++g) {
+            const u32x4_t *vp = reinterpret_cast<const u32x4_t *>(vpages + kv_block_base(layer, n_pages, g ? p1 : p0, H, h, DH));
+#pragma unroll
+            for (int dt = 0; dt < DT; ++dt) kv.v[g][dt] = vp[(32 * (ds * DT + dt) + lc) * 2 + lh];
+        }
+    };
+    f32x16_t o[DT];
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) o[dt][v] = 0.f;
+    float m_run = -INFINITY, l_run = 0.f;
+    auto step = [&](ShortTile<DH, DS> &kv, int it) {
+        const int slot0 = (wave + it * NW) * 32;
+        if (slot0 + 32 > total) {       // zero V of slots >= total (stale or never written): 0 * garbage must not appear
+#pragma unroll
+            for (int g = 0; g < 2; ++g)
+#pragma unroll
+                for (int w = 0; w < 4; ++w) {
+                    // dword w holds keys i = 2w, 2w+1 of this half-wave: token = 8*(i/4) + 4*hl + i%4
+                    const int i0 = 2 * w, i1 = 2 * w + 1;
+                    const int s0 = slot0 + 16 * g + 8 * (i0 >> 2) + 4 * hl + (i0 & 3);
+                    const int s1 = slot0 + 16 * g + 8 * (i1 >> 2) + 4 * hl + (i1 & 3);
+                    const uint32_t keep = (s0 < total ? 0x0000ffffu : 0u) | (s1 < total ? 0xffff0000u : 0u);
+#pragma unroll
+                    for (int dt = 0; dt < DT; ++dt) kv.v[g][dt][w] &= keep;
+                }
+        }
+        f32x16_t sc;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) sc[v] = 0.f;
+        int qoff = lane;
+        asm volatile("" : "+v"(qoff));                       // keeps the reads of the queries here (hoisted, they are registers)
+#pragma unroll
+        for (int s = 0; s < KS; ++s)
+            sc = HYDRA_MFMA16(__builtin_bit_cast(a16x8_t, kv.k[s]), __builtin_bit_cast(a16x8_t, qs[qoff + s * 64]), sc);
+        bool moved;
+        const float alpha = softmax_tile(sc, scale, slot0 + 32 > L, slot0, L, anc0, anc1, hl, m_run, l_run, moved);
+        // the accumulators are rescaled only where some query's maximum moved (a factor of one otherwise; the first tile has
+        // nothing to rescale)
+        if (it > 0 && moved) {
+#pragma unroll
+            for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) o[dt][v] *= alpha;
+        }
+        // P^T operands: page g uses accumulator registers 8g .. 8g+7 in order
+#pragma unroll
+        for (int g = 0; g < 2; ++g) {
+            u32x4_t pb;
+#pragma unroll
+            for (int w = 0; w < 4; ++w) pb[w] = half_pack(sc[8 * g + 2 * w], sc[8 * g + 2 * w + 1]);
+#pragma unroll
+            for (int dt = 0; dt < DT; ++dt)
+                o[dt] = HYDRA_MFMA16(__builtin_bit_cast(a16x8_t, kv.v[g][dt]), __builtin_bit_cast(a16x8_t, pb), o[dt]);
+        }
+    };
+    ShortTile<DH, DS> ring[RING];
+#pragma unroll
+    for (int i = 0; i < RING; ++i) load(ring[i], i, pg[i][0], pg[i][1]);
+    __syncthreads();                                         // the query tile is in LDS
+    int it = 0;
+    for (; it + RING < mine_n; it += RING)                   // all of the ring's tiles exist
+#pragma unroll
+        for (int i = 0; i < RING; ++i) {
+            const int next = it + i + RING, t = wave + next * NW;
+            int p0, p1;
+            if (next < ATTN_SHORT_TILES) {                   // wave-uniform
+                p0 = pg[ATTN_SHORT_TILES - 1][0]; p1 = pg[ATTN_SHORT_TILES - 1][1];
+#pragma unroll
+                for (int q = RING; q + 1 < ATTN_SHORT_TILES; ++q)
+                    if (next == q) { p0 = pg[q][0]; p1 = pg[q][1]; }
+            } else {                                         // a row longer than the host's hint
+                p0 = pt[min(2 * t, max_pages - 1)];
+                p1 = pt[min(2 * t + 1, max_pages - 1)];
+            }
+            step(ring[i], it + i);
+            load(ring[i], next, p0, p1);
+        }
+#pragma unroll
+    for (int i = 0; i < RING; ++i)
+        if (it + i < mine_n) step(ring[i], it + i);
+
+    // ---- merge the waves through LDS: ml[NW][2][32], then O[NW][DT * 16][64] where the queries were
+    float *ml = lds, *ob = lds + NW * 64;
+    if (hl == 0) {
+        ml[(wave * 2 + 0) * 32 + col] = m_run;
+        ml[(wave * 2 + 1) * 32 + col] = l_run;
+    }
+    __syncthreads();
+    float m_tot = -INFINITY;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) m_tot = fmaxf(m_tot, ml[(w * 2 + 0) * 32 + col]);
+    float l_tot = 0.f;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) l_tot += __expf(ml[(w * 2 + 0) * 32 + col] - (m_tot == -INFINITY ? 0.f : m_tot)) * ml[(w * 2 + 1) * 32 + col];
+    const float mine = __expf(m_run - (m_tot == -INFINITY ? 0.f : m_tot));
+    {
+        float *dst = ob + (size_t)wave * DT * 16 * 64 + lane;
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) dst[(dt * 16 + v) * 64] = o[dt][v] * mine;
+    }
+    __syncthreads();
+    // the (band, group of 4 registers = 4 consecutive dims) items are shared out over the waves
+    const float inv = 1.0f / l_tot;
+    for (int id = wave; id < DT * 4; id += NW) {
+        const int dt = id >> 2, g4 = id & 3;
+        float acc[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+            const float *src = ob + (size_t)w * DT * 16 * 64 + lane;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) acc[q] += src[(dt * 16 + 4 * g4 + q) * 64];
+        }
+        if (query >= T) continue;
+        const int dim = 32 * (ds * DT + dt) + 8 * g4 + 4 * hl, m = b * T + query;
+        if (PACKED) {
+            const u32x2_t pk = {f2a_pack(acc[0] * inv, acc[1] * inv), f2a_pack(acc[2] * inv, acc[3] * inv)};
+            *reinterpret_cast<u32x2_t *>(reinterpret_cast<a16_t *>(out) + x_index<true>(m, h * DH + dim, H * DH)) = pk;
+        } else {
+            *reinterpret_cast<f32x4_t *>(reinterpret_cast<float *>(out) + ((size_t)m * H + h) * DH + dim) = f32x4_t{acc[0] * inv, acc[1] * inv, acc[2] * inv, acc[3] * inv};
+        }
+    }
 }
 
 // out[b, n, h, :] = sum_u w_u O_u[n] / sum_u w_u l_u,  w_u = exp(m_u - max_u m_u).
@@ -109,11 +301,18 @@ int launch_attention_f32(hydra_ctx *c, hipStream_t s, int B, int layer, const fl
 
 static size_t attn_lds_bytes(int Dh) { return ((size_t)ATTN_WAVES * 64 + (size_t)ATTN_WAVES * (Dh / 32) * 16 * 64) * 4; }
 
+static size_t attn_short_lds_bytes(int Dh, int ds) {
+    return ((size_t)ATTN_WAVES * 64 + std::max((size_t)ATTN_WAVES * (Dh / 32 / ds) * 16 * 64, (size_t)Dh * 16)) * 4;       // O, or the query tile
+}
+
 int attn_max_dynamic_lds(hydra_ctx *c) {
     (void)c;
     hipError_t e = hipSuccess;
 #define ATTR(DHv, Pv) if (e == hipSuccess) e = hipFuncSetAttribute((const void *)attn_bf16_kernel<DHv, Pv>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024)
     ATTR(128, true); ATTR(128, false); ATTR(64, true); ATTR(64, false);
+#undef ATTR
+#define ATTR(DHv, DSv, Pv) if (e == hipSuccess) e = hipFuncSetAttribute((const void *)attn_short_kernel<DHv, DSv, Pv>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024)
+    ATTR(128, 1, true); ATTR(128, 1, false); ATTR(128, 2, true); ATTR(128, 2, false); ATTR(64, 1, true); ATTR(64, 1, false);
 #undef ATTR
     if (e != hipSuccess) return hip_fail(e, "hipFuncSetAttribute(attn_bf16_kernel)");
     return HYDRA_OK;
@@ -135,35 +334,44 @@ int launch_attention(hydra_ctx *c, hipStream_t s, int B, int layer, const void *
     // Short contexts: one workgroup per 32-query tile, its 8 waves split the keys (up to five 32-key tiles each) and
     // the result goes straight out.  Longer ones: a CU streams at most ~45 GB/s, so the keys of one head are spread
     // over several workgroups (two tiles per wave or more) whose partial records attn_merge_kernel combines.
-    int wgs = 1, qsplit = 0;
-    // (only while those workgroups fit one round of the chip: at batch 8 and 16 one workgroup per (row, head) that
-    // holds all query tiles and reads each K/V byte once measured 2-3 % faster on the whole verify step)
-    if (tiles <= ATTN_WAVES * 5 && QTtot * H * B <= 256) {
-        qsplit = 1; QW = 1; KWV = ATTN_WAVES; wgs = QTtot;
-    } else {
-        // ... but never more workgroups than one round of the chip: a workgroup holds a CU by itself (registers), so
-        // a second round only repeats the fixed cost of a workgroup (first round trips, LDS merge, partial record).
-        // Measured best at about 200 workgroups in all: 7B at 2066 / 4114 keys 4.30 -> 4.01 / 4.63 -> 4.30 ms per verify.
-        wgs = ceil_div(tiles, KWV * 2);
-        const int cap = std::max(1, 208 / (H * B));
-        if (wgs > cap) wgs = cap;
-        if (wgs > units_max) wgs = units_max;
-        if (wgs < 1) wgs = 1;
-    }
-    dim3 grid(wgs, H, B), block(ATTN_WAVES * 64);
     const float scale = 1.0f / sqrtf((float)Dh);
-    const size_t lds = attn_lds_bytes(Dh);
     void *out = x_out ? x_out : (void *)plain_out;
     const bool packed = x_out != nullptr;
+    // short contexts, while those workgroups fit one round of the chip (at batch 8 and 16 one workgroup per (row, head) that
+    // holds all query tiles and reads each K/V byte once measured 2-3 % faster on the whole verify step); see attn_short_kernel
+    if (tiles <= ATTN_WAVES * ATTN_SHORT_TILES && QTtot * H * B <= 256) {
+        int ds = Dh / 32;
+        while (ds > 1 && QTtot * H * B * ds > 256) ds >>= 1;
+        const dim3 sgrid(ceil_div(H * B, 8) * 8 * QTtot * ds), sblock(ATTN_WAVES * 64);
+#define SHORT(DHv, DSv, Pv)                                                                                                                      \
+    hipLaunchKernelGGL((attn_short_kernel<DHv, DSv, Pv>), sgrid, sblock, attn_short_lds_bytes(DHv, DSv), s, (const u32x4_t *)qbuf,                \
+                       (const a16_t *)kv->k_pages, (const a16_t *)kv->v_pages, kv->page_table, kv->max_pages, kv->n_pages, layer, seq_len,        \
+                       tree_dev(c), T, H, H * B, scale, out, flags)
+#define SHORT_DS(DHv, DSv) do { if (packed) SHORT(DHv, DSv, true); else SHORT(DHv, DSv, false); } while (0)
+        if (Dh == 128) { if (ds == 4) SHORT_DS(128, 4); else if (ds == 2) SHORT_DS(128, 2); else SHORT_DS(128, 1); }
+        else           { if (ds == 2) SHORT_DS(64, 2); else SHORT_DS(64, 1); }
+#undef SHORT_DS
+#undef SHORT
+        HYDRA_LAUNCH_CHECK("attn_short_kernel");
+        return HYDRA_OK;
+    }
+    // Longer contexts, or more rows: several workgroups per head, but never more of them than one round of the chip: a workgroup
+    // holds a CU by itself (registers), so a second round only repeats the fixed cost of a workgroup (first round trips, LDS
+    // merge, partial record).  Measured best at about 200 workgroups in all: 7B at 2066 / 4114 keys 4.30 -> 4.01 / 4.63 -> 4.30 ms
+    // per verify.
+    int wgs = ceil_div(tiles, KWV * 2);
+    wgs = std::max(1, std::min({wgs, std::max(1, 208 / (H * B)), units_max}));
+    dim3 grid(wgs, H, B), block(ATTN_WAVES * 64);
+    const size_t lds = attn_lds_bytes(Dh);
 #define ATTN_CASE(DHv, Pv)                                                                                           \
     hipLaunchKernelGGL((attn_bf16_kernel<DHv, Pv>), grid, block, lds, s, (const u32x4_t *)qbuf,                       \
                        (const a16_t *)kv->k_pages, (const a16_t *)kv->v_pages, kv->page_table, kv->max_pages,      \
-                       kv->n_pages, layer, seq_len, tree_dev(c), T, H, QW, qsplit, scale, apart, out, flags)
+                       kv->n_pages, layer, seq_len, tree_dev(c), T, H, QW, 0, scale, apart, out, flags)
     if (Dh == 128) { if (packed) ATTN_CASE(128, true); else ATTN_CASE(128, false); }
     else           { if (packed) ATTN_CASE(64, true); else ATTN_CASE(64, false); }
 #undef ATTN_CASE
     HYDRA_LAUNCH_CHECK("attn_bf16_kernel");
-    if (!qsplit && wgs > 1) {
+    if (wgs > 1) {
         const int q_per_wg = 256 / (Dh / 4);
         dim3 mgrid(ceil_div(T, q_per_wg), H, B), mblock(256);
         if (packed) hipLaunchKernelGGL(attn_merge_kernel<true>, mgrid, mblock, 0, s, apart, seq_len, T, H, Dh, wgs, kv->max_pages, out);

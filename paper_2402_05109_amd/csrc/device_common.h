@@ -114,6 +114,14 @@ __device__ __forceinline__ float wave_max(float v) {
     return v;
 }
 
+// A value of the lower and one of the upper half-wave, lane by lane, in both halves: one vector instruction where a shuffle by 32
+// lanes goes through LDS.
+struct HalfWaves { float lo, hi; };
+__device__ __forceinline__ HalfWaves half_waves(float v) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return HalfWaves{__uint_as_float(r[0]), __uint_as_float(r[1])};
+}
+
 // sum of S split-K partial results of one output element
 // Four partials per memory round trip: the loads of a group are unconditional (surplus ones re-read the last split), so
 // they are all in flight before the first add; the adds keep the split order.

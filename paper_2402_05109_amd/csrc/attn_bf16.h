@@ -76,21 +76,28 @@ __device__ __forceinline__ float softmax_tile(f32x16_t &sc, float scale, bool ne
 template <int DH>
 struct KVTile { u32x4_t k[DH / 16]; u32x4_t v[2][DH / 32]; };
 
-template <int DH>
+// STREAM: nontemporal, for K and V that one workgroup alone reads (16 rows x 64 queries, 1000 keys: 58.8 -> 54.8 us; where the
+// workgroups of two query tiles read the same bytes it costs time)
+template <bool STREAM>
+__device__ __forceinline__ u32x4_t load_kv(const u32x4_t *p) {
+    if (STREAM) return __builtin_nontemporal_load(p);
+    return *p;
+}
+template <int DH, bool STREAM>
 __device__ __forceinline__ void load_k_tile(KVTile<DH> &kv, const a16_t *kpages, int p0, int p1, int layer, int n_pages, int H, int h, int lane) {
     const int hl = lane >> 5, col = lane & 31;
     const u32x4_t *kp = reinterpret_cast<const u32x4_t *>(kpages + kv_block_base(layer, n_pages, (col >> 4) ? p1 : p0, H, h, DH));
 #pragma unroll
-    for (int s = 0; s < DH / 16; ++s) kv.k[s] = kp[(2 * s + hl) * 16 + (col & 15)];
+    for (int s = 0; s < DH / 16; ++s) kv.k[s] = load_kv<STREAM>(kp + (2 * s + hl) * 16 + (col & 15));
 }
-template <int DH>
+template <int DH, bool STREAM>
 __device__ __forceinline__ void load_v_tile(KVTile<DH> &kv, const a16_t *vpages, int p0, int p1, int layer, int n_pages, int H, int h, int lane) {
     const int hl = lane >> 5, col = lane & 31;
 #pragma unroll
     for (int g = 0; g < 2; ++g) {
         const u32x4_t *vp = reinterpret_cast<const u32x4_t *>(vpages + kv_block_base(layer, n_pages, g ? p1 : p0, H, h, DH));
 #pragma unroll
-        for (int dt = 0; dt < DH / 32; ++dt) kv.v[g][dt] = vp[(32 * dt + col) * 2 + hl];
+        for (int dt = 0; dt < DH / 32; ++dt) kv.v[g][dt] = load_kv<STREAM>(vp + (32 * dt + col) * 2 + hl);
     }
 }
 
@@ -172,8 +179,8 @@ __device__ __forceinline__ void attn_bf16_body(
         {
             const int p0 = checked_page(pg[0][0], n_pages, flags);
             const int p1 = (2 * unit + 1 < row_pages) ? checked_page(pg[0][1], n_pages, flags) : p0;
-            load_k_tile<DH>(cur, kpages, p0, p1, layer, n_pages, H, h, lane);
-            load_v_tile<DH>(cur, vpages, p0, p1, layer, n_pages, H, h, lane);
+            load_k_tile<DH, !DEV>(cur, kpages, p0, p1, layer, n_pages, H, h, lane);
+            load_v_tile<DH, !DEV>(cur, vpages, p0, p1, layer, n_pages, H, h, lane);
         }
         int it = 0;                                        // index of tile t among this wave's tiles
         for (int t = unit; t < n_tiles; t += units, ++it) {
@@ -192,8 +199,8 @@ __device__ __forceinline__ void attn_bf16_body(
                 p0 = checked_page(p0, n_pages, flags);                  // wave-uniform
                 p1 = checked_page(p1, n_pages, flags);
                 if (!DEV) {
-                    load_k_tile<DH>(nxt, kpages, p0, p1, layer, n_pages, H, h, lane);
-                    load_v_tile<DH>(nxt, vpages, p0, p1, layer, n_pages, H, h, lane);
+                    load_k_tile<DH, !DEV>(nxt, kpages, p0, p1, layer, n_pages, H, h, lane);
+                    load_v_tile<DH, !DEV>(nxt, vpages, p0, p1, layer, n_pages, H, h, lane);
                 }
             }
             const int slot0 = t * 32;
@@ -220,7 +227,7 @@ __device__ __forceinline__ void attn_bf16_body(
             for (int s = 0; s < KS; ++s)
                 sc = HYDRA_MFMA16(__builtin_bit_cast(a16x8_t, cur.k[s]), __builtin_bit_cast(a16x8_t, QLDS ? qlds[qoff + s * 64] : qreg[s]), sc);
             // the layer kernel, whose waves hold weights as well, has one tile's registers: the next K comes once K is used
-            if (DEV && more) load_k_tile<DH>(cur, kpages, p0, p1, layer, n_pages, H, h, lane);
+            if (DEV && more) load_k_tile<DH, !DEV>(cur, kpages, p0, p1, layer, n_pages, H, h, lane);
             bool moved;
             const float alpha = softmax_tile(sc, scale, slot0 + 32 > L, slot0, L, anc0, anc1, hl, m_run, l_run, moved);
             // the accumulators are rescaled only where some query's maximum moved (a factor of one otherwise; the first tile
@@ -242,7 +249,7 @@ __device__ __forceinline__ void attn_bf16_body(
                 for (int dt = 0; dt < DT; ++dt)
                     o[dt] = HYDRA_MFMA16(__builtin_bit_cast(a16x8_t, cur.v[g][dt]), __builtin_bit_cast(a16x8_t, pb), o[dt]);
             }
-            if (DEV && more) load_v_tile<DH>(cur, vpages, p0, p1, layer, n_pages, H, h, lane);
+            if (DEV && more) load_v_tile<DH, !DEV>(cur, vpages, p0, p1, layer, n_pages, H, h, lane);
             if (!DEV && more) cur = nxt;
         }
     }

@@ -16,14 +16,15 @@
 // of K and V (device_common.h) makes both A operands single coalesced
 // 16-byte-per-lane loads straight from the cache pages.
 //
-// A workgroup is 8 waves on one (b, h).  Two launch shapes:
+// A workgroup works on one (b, h).  Launch shapes:
 //   short contexts (up to ~1200 keys): attn_short_kernel, one workgroup per
 //     32-query tile and share of the head's dims; its 8 waves split the keys and
 //     the result goes straight out as the next GEMM's input: one kernel, no
 //     partial records;
-//   longer contexts: QW waves of a workgroup take different query tiles, 8/QW
-//     waves split the keys, and several workgroups per (b, h) split the keys
-//     further; each leaves a (max, sum, O) record that attn_merge_kernel combines.
+//   longer contexts, or more rows: attn_bf16_kernel up to 32 queries, attn_pair_kernel
+//     beyond (two query tiles to a wave).  The waves of a workgroup split the keys, and
+//     so do several workgroups per (b, h) while the chip has room; each of those leaves
+//     a (max, sum, O) record that attn_merge_kernel combines.
 #include <algorithm>
 
 #include "attn_bf16.h"
@@ -38,11 +39,10 @@ template <int DH, bool PACKED>
 __global__ __launch_bounds__(ATTN_WAVES * 64) void attn_bf16_kernel(
     const u32x4_t *__restrict__ qbuf, const a16_t *__restrict__ kpages, const a16_t *__restrict__ vpages,
     const int32_t *__restrict__ page_table, int max_pages, int n_pages, int layer, const int32_t *__restrict__ seq_len,
-    const TreeDev *__restrict__ tree, int T, int H, int QW, int qsplit, float scale, float *__restrict__ apart, void *out,
-    int32_t *flags) {
+    const TreeDev *__restrict__ tree, int T, int H, float scale, float *__restrict__ apart, void *out, int32_t *flags) {
     extern __shared__ float lds[];
-    attn_bf16_body<DH, PACKED, false, true>(qbuf, kpages, vpages, page_table, max_pages, n_pages, layer, seq_len, tree, T, H, QW, qsplit,
-                                      scale, apart, out, flags, (int)blockIdx.x, (int)gridDim.x, (int)blockIdx.y, (int)blockIdx.z, lds, (int)threadIdx.x);
+    attn_bf16_body<DH, PACKED, false, true>(qbuf, kpages, vpages, page_table, max_pages, n_pages, layer, seq_len, tree, T, H, 1, 0,
+                                             scale, apart, out, flags, (int)blockIdx.x, (int)gridDim.x, (int)blockIdx.y, (int)blockIdx.z, lds, (int)threadIdx.x);
 }
 
 // Short contexts: a workgroup takes one 32-query tile of one (row, head) and 1 / DS of the head's dims; its eight waves split
@@ -60,7 +60,7 @@ template <int DH, int DS>
 struct ShortTile { u32x4_t k[DH / 16]; u32x4_t v[2][DH / 32 / DS]; };
 enum { ATTN_SHORT_TILES = 5 };                              // 32-key tiles per wave up to which the launch rule takes this kernel
 
-template <int DH, int DS, bool PACKED>
+template <int DH, int DS, bool STREAM, bool PACKED>
 __global__ __launch_bounds__(ATTN_WAVES * 64) void attn_short_kernel(
     const u32x4_t *__restrict__ qbuf, const a16_t *__restrict__ kpages, const a16_t *__restrict__ vpages,
     const int32_t *__restrict__ page_table, int max_pages, int n_pages, int layer, const int32_t *__restrict__ seq_len,
@@ -109,12 +109,12 @@ __global__ __launch_bounds__(ATTN_WAVES * 64) void attn_short_kernel(
         const int ln = live ? lane : 0, lh = ln >> 5, lc = ln & 31;
         const u32x4_t *kp = reinterpret_cast<const u32x4_t *>(kpages + kv_block_base(layer, n_pages, (lc >> 4) ? p1 : p0, H, h, DH));
 #pragma unroll
-        for (int s = 0; s < KS; ++s) kv.k[s] = kp[(2 * s + lh) * 16 + (lc & 15)];
+        for (int s = 0; s < KS; ++s) kv.k[s] = load_kv<STREAM>(kp + (2 * s + lh) * 16 + (lc & 15));
 #pragma unroll
         for (int g = 0; g < 2; ++g) {
             const u32x4_t *vp = reinterpret_cast<const u32x4_t *>(vpages + kv_block_base(layer, n_pages, g ? p1 : p0, H, h, DH));
 #pragma unroll
-            for (int dt = 0; dt < DT; ++dt) kv.v[g][dt] = vp[(32 * (ds * DT + dt) + lc) * 2 + lh];
+            for (int dt = 0; dt < DT; ++dt) kv.v[g][dt] = load_kv<STREAM>(vp + (32 * (ds * DT + dt) + lc) * 2 + lh);
         }
     };
     f32x16_t o[DT];
@@ -238,6 +238,255 @@ __global__ __launch_bounds__(ATTN_WAVES * 64) void attn_short_kernel(
     }
 }
 
+// More rows, or longer ones, with more than 32 queries per row: a wave holds TWO query tiles, so that a CU asks for every byte of
+// K and V once (a wave per query tile asked twice, and what a CU can ask for is the bound: 33B shape, 4 rows of 2048 keys: 63 us a
+// launch, 45 now; 7B, 16 rows of 1024: 67, 51 now).  There is no room for K and V tiles in registers next to two sets of accumulators
+// (128 of them), so each wave has a tile of its own in LDS that the LDS DMA fills: K is requested again as soon as the scores
+// are computed, V as soon as it is used, and no wave waits for another before the end.
+// STREAM (up to 64 queries, every byte of K and V read once on the chip): nontemporal requests, 47.1 -> 43.8 us on the same shape; with
+// a second workgroup on the same bytes 62.9 -> 65.3.
+// NW waves split the keys: eight where the workgroups fit one round of the chip, four, two workgroups to a CU, beyond.
+//
+// Softmax in powers of two, with the scale folded into the exponent's multiply-add.  The maximum is followed exactly: a reference
+// that trails it by up to 2^8 saves most of the rescaling, but the largest probability is then no longer exactly one, and its
+// rounding to half tripled the error of sharp rows (5e-5 -> 1.6e-4 of the result's 2-norm); nothing is gained either, since the
+// loads alone take as long.
+template <int DH, int NW, bool STREAM>
+__global__ __launch_bounds__(NW * 64, 2) void attn_pair_kernel(
+    const u32x4_t *__restrict__ qbuf, const a16_t *__restrict__ kpages, const a16_t *__restrict__ vpages,
+    const int32_t *__restrict__ page_table, int max_pages, int n_pages, int layer, const int32_t *__restrict__ seq_len,
+    const TreeDev *__restrict__ tree, int T, int H, int groups, int key_wgs, float scale, float *__restrict__ apart, void *out, int packed,
+    int32_t *flags) {
+    constexpr int KS = DH / 16, DT = DH / 32, TILE = KS + 2 * DT;    // KiB of a K and V tile
+    extern __shared__ float lds[];                          // queries [2][KS] and tiles [NW][TILE] of 1 KiB; then maxima and sums, O of one query tile
+    const int tid = (int)threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int hl = lane >> 5, col = lane & 31;
+    const int QTtot = (T + 31) >> 5, QG = (QTtot + 1) >> 1, per = QG * key_wgs;
+    const int seq = (int)blockIdx.x >> 3;
+    const int group = seq / per * 8 + ((int)blockIdx.x & 7), j = seq % per;
+    if (group >= groups) return;
+    const int b = group / H, h = group - b * H, qg = j % QG, key_wg = j / QG;
+    const int units = key_wgs * NW, unit = key_wg * NW + wave;
+    const int32_t *pt = page_table + (size_t)b * max_pages;
+    u32x4_t *qs = reinterpret_cast<u32x4_t *>(lds);
+    const u32x4_t *ql = qs + lane;
+    uint64_t anc[2][2];
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        const int query = (qg * 2 + q) * 32 + col;
+        anc[q][0] = anc[q][1] = 0ull;
+        if (query < T) { anc[q][0] = tree->anc[query][0]; anc[q][1] = tree->anc[query][1]; }
+    }
+    // page ids of this wave's next 32 tiles, two per tile, one per lane
+    auto page_ids = [&](int first) { return pt[min(2 * (unit + (first + (lane >> 1)) * units) + (lane & 1), max_pages - 1)]; };
+    int pgs = page_ids(0);
+    const int L = seq_len[b];
+    // the second query tile of the last group may lie behind the last query: the first one again, which nobody stores
+    const size_t qblk = (((size_t)b * H + h) * QTtot + qg * 2) * KS;
+    const int second = qg * 2 + 1 < QTtot ? KS : 0;
+    for (int i = wave; i < 2 * KS; i += NW) qs[i * 64 + lane] = qbuf[(qblk + (i < KS ? i : second + i - KS)) * 64 + lane];
+    __syncthreads();
+    if (L < 0 || L + T > max_pages * 16) {                  // uniform over the workgroup
+        if (tid == 0 && j == 0 && h == 0) atomicOr(flags, FLAG_CAPACITY);
+        return;
+    }
+    const int total = L + T, n_tiles = (total + 31) >> 5, row_pages = (total + 15) >> 4;
+    const int mine_n = unit < n_tiles ? (n_tiles - unit + units - 1) / units : 0;      // this wave's tiles: unit, unit + units, ...
+
+    u32x4_t *mine = qs + (2 * KS + wave * TILE) * 64;       // this wave's tile: K blocks, then V blocks [page][dims / 32]
+    const uint32_t mine_at = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void *)mine;
+    auto dma = [&](const u32x4_t *src, int block) {
+        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)src,
+                                         (__attribute__((address_space(3))) void *)(uintptr_t)(mine_at + (uint32_t)block * 1024u), 16, 0, STREAM ? 2 : 0);      // 2: nontemporal
+    };
+    int p0 = 0, p1 = 0;                                     // pages of the tile that is requested next
+    auto next_pages = [&](int it) {
+        if (it > 0 && (it & 31) == 0) { pgs = page_ids(it); asm volatile("" : "+v"(pgs)); }      // awaited in here, not behind the branch
+        p0 = checked_page(__builtin_amdgcn_readlane(pgs, 2 * (it & 31)), n_pages, flags);
+        // second page of a tile: absent when the row ends inside the first one (its keys are masked; any valid page will do)
+        p1 = 2 * (unit + it * units) + 1 < row_pages ? checked_page(__builtin_amdgcn_readlane(pgs, 2 * (it & 31) + 1), n_pages, flags) : p0;
+    };
+    auto request_k = [&] {
+        const u32x4_t *kp = reinterpret_cast<const u32x4_t *>(kpages + kv_block_base(layer, n_pages, (col >> 4) ? p1 : p0, H, h, DH)) + hl * 16 + (col & 15);
+#pragma unroll
+        for (int s = 0; s < KS; ++s) dma(kp + s * 32, s);
+    };
+    auto request_v = [&] {
+#pragma unroll
+        for (int g = 0; g < 2; ++g) {
+            const u32x4_t *vp = reinterpret_cast<const u32x4_t *>(vpages + kv_block_base(layer, n_pages, g ? p1 : p0, H, h, DH)) + col * 2 + hl;
+#pragma unroll
+            for (int dt = 0; dt < DT; ++dt) dma(vp + dt * 64, KS + g * DT + dt);
+        }
+    };
+    f32x16_t o[2][DT];
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) o[q][dt][v] = 0.f;
+    float m_run[2] = {-INFINITY, -INFINITY}, l_run[2] = {0.f, 0.f};
+    const float c = scale * 1.44269504f;
+    // these have arrived: nothing in the loop is to wait for an ordinary load, which would be a wait for the DMA as well
+    asm volatile("" : "+v"(pgs), "+v"(anc[0][0]), "+v"(anc[0][1]), "+v"(anc[1][0]), "+v"(anc[1][1]));
+    if (mine_n > 0) { next_pages(0); request_k(); request_v(); }
+    for (int it = 0; it < mine_n; ++it) {
+        const bool more = it + 1 < mine_n;
+        const int slot0 = (unit + it * units) * 32;
+        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * DT) : "memory");             // K has landed: of what was asked for only V may be missing
+        f32x16_t sc[2];
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) sc[q][v] = 0.f;
+        int at = 0;
+        asm volatile("" : "+v"(at));                        // keeps the reads of the queries inside the loop
+#pragma unroll
+        for (int s = 0; s < KS; ++s) {
+            const a16x8_t k = __builtin_bit_cast(a16x8_t, mine[s * 64 + lane]);
+#pragma unroll
+            for (int q = 0; q < 2; ++q) sc[q] = HYDRA_MFMA16(k, __builtin_bit_cast(a16x8_t, ql[at + (q * KS + s) * 64]), sc[q]);
+        }
+        if (more) {
+            next_pages(it + 1);
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");                    // K is read
+            request_k();
+        }
+        u32x4_t pb[2][2];
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            if (slot0 + 32 > L) {                           // uniform: the tiles that hold tree slots or end the row
+                const uint32_t seen = keys_seen(slot0, L, anc[q][0], anc[q][1]) >> (4 * hl);
+#pragma unroll
+                for (int v = 0; v < 16; ++v) sc[q][v] = (seen >> (8 * (v >> 2) + (v & 3))) & 1u ? sc[q][v] : -INFINITY;
+            }
+            float cmax = -INFINITY;
+#pragma unroll
+            for (int v = 0; v < 16; ++v) cmax = fmaxf(cmax, sc[q][v]);
+            const HalfWaves cm = half_waves(cmax);
+            cmax = fmaxf(cm.lo, cm.hi) * c;
+            if (__any(cmax > m_run[q])) {                                          // always on the first visible tile
+                const float m_new = fmaxf(m_run[q], cmax);
+                const float alpha = m_new == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_run[q] - m_new);
+                m_run[q] = m_new;
+                l_run[q] *= alpha;
+#pragma unroll
+                for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) o[q][dt][v] *= alpha;
+            }
+            const float ref = m_run[q] == -INFINITY ? 0.f : m_run[q];
+            float rs = 0.f;
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const float p = __builtin_amdgcn_exp2f(fmaf(sc[q][v], c, -ref));   // 0 for masked keys
+                sc[q][v] = p;
+                rs += p;
+            }
+            const HalfWaves rh = half_waves(rs);
+            l_run[q] += rh.lo + rh.hi;
+            // P^T operands: page g uses accumulator registers 8g .. 8g+7 in order
+#pragma unroll
+            for (int g = 0; g < 2; ++g)
+#pragma unroll
+                for (int w = 0; w < 4; ++w) pb[q][g][w] = half_pack(sc[q][8 * g + 2 * w], sc[q][8 * g + 2 * w + 1]);
+        }
+        if (more) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(KS) : "memory");       // V has landed: only the next K may be missing
+        else      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        if (slot0 + 32 > total) {       // zero V of slots >= total (stale or never written): 0 * garbage must not appear
+#pragma unroll
+            for (int g = 0; g < 2; ++g) {
+                u32x4_t keep;
+#pragma unroll
+                for (int w = 0; w < 4; ++w) {
+                    // dword w holds keys i = 2w, 2w+1 of this half-wave: token = 8*(i/4) + 4*hl + i%4
+                    const int i0 = 2 * w, i1 = 2 * w + 1;
+                    const int s0 = slot0 + 16 * g + 8 * (i0 >> 2) + 4 * hl + (i0 & 3);
+                    const int s1 = slot0 + 16 * g + 8 * (i1 >> 2) + 4 * hl + (i1 & 3);
+                    keep[w] = (s0 < total ? 0x0000ffffu : 0u) | (s1 < total ? 0xffff0000u : 0u);
+                }
+#pragma unroll
+                for (int dt = 0; dt < DT; ++dt) mine[(KS + g * DT + dt) * 64 + lane] &= keep;      // each lane its own 16 bytes
+            }
+        }
+#pragma unroll
+        for (int g = 0; g < 2; ++g)
+#pragma unroll
+            for (int dt = 0; dt < DT; ++dt) {
+                const a16x8_t v = __builtin_bit_cast(a16x8_t, mine[(KS + g * DT + dt) * 64 + lane]);
+#pragma unroll
+                for (int q = 0; q < 2; ++q) o[q][dt] = HYDRA_MFMA16(v, __builtin_bit_cast(a16x8_t, pb[q][g]), o[q][dt]);
+            }
+        if (more) {
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");                    // V is read
+            request_v();
+        }
+    }
+
+    // ---- merge the waves through LDS, one query tile after the other: ml[2][NW][2][32], then O[NW][DT * 16][64]
+    __syncthreads();                                         // every wave is done with queries and tiles
+    float *ml = lds, *ob = lds + NW * 128;
+    if (hl == 0) {
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            ml[((q * NW + wave) * 2 + 0) * 32 + col] = m_run[q];
+            ml[((q * NW + wave) * 2 + 1) * 32 + col] = l_run[q];
+        }
+    }
+    __syncthreads();
+    const int Tq = QTtot * 32;
+    float *rec = apart + (((size_t)b * H + h) * key_wgs + key_wg) * apart_record(Tq, DH);
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        const int qtile = qg * 2 + q, query = qtile * 32 + col;
+        if (qtile >= QTtot) break;                           // uniform over the workgroup
+        const float *mq = ml + q * NW * 64;
+        float m_tot = -INFINITY;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) m_tot = fmaxf(m_tot, mq[w * 64 + col]);
+        const float m_safe = m_tot == -INFINITY ? 0.f : m_tot;
+        float l_tot = 0.f;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) l_tot += __builtin_amdgcn_exp2f(mq[w * 64 + col] - m_safe) * mq[w * 64 + 32 + col];
+        const float f = __builtin_amdgcn_exp2f(m_run[q] - m_safe);
+        float *dst = ob + (size_t)wave * DT * 16 * 64 + lane;
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) dst[(dt * 16 + v) * 64] = o[q][dt][v] * f;
+        __syncthreads();
+        // the (band, group of 4 registers = 4 consecutive dims) items are shared out over the waves
+        const float inv = key_wgs == 1 ? 1.0f / l_tot : 1.0f;
+        for (int id = wave; id < DT * 4; id += NW) {
+            const int dt = id >> 2, g4 = id & 3;
+            float acc[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int w = 0; w < NW; ++w) {
+                const float *src = ob + (size_t)w * DT * 16 * 64 + lane;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) acc[e] += src[(dt * 16 + 4 * g4 + e) * 64];
+            }
+            const int dim = 32 * dt + 8 * g4 + 4 * hl, m = b * T + query;
+            if (key_wgs > 1) {
+                *reinterpret_cast<f32x4_t *>(rec + (size_t)query * DH + dim) = f32x4_t{acc[0], acc[1], acc[2], acc[3]};
+            } else if (query < T) {
+                if (packed) {
+                    const u32x2_t pk = {f2a_pack(acc[0] * inv, acc[1] * inv), f2a_pack(acc[2] * inv, acc[3] * inv)};
+                    *reinterpret_cast<u32x2_t *>(reinterpret_cast<a16_t *>(out) + x_index<true>(m, h * DH + dim, H * DH)) = pk;
+                } else {
+                    *reinterpret_cast<f32x4_t *>(reinterpret_cast<float *>(out) + ((size_t)m * H + h) * DH + dim) = f32x4_t{acc[0] * inv, acc[1] * inv, acc[2] * inv, acc[3] * inv};
+                }
+            }
+        }
+        if (key_wgs > 1 && wave == 0 && hl == 0) {           // attn_merge_kernel takes natural logarithms
+            rec[(size_t)Tq * DH + query] = m_tot * 0.693147181f;
+            rec[(size_t)Tq * DH + Tq + query] = l_tot;
+        }
+        if (q == 0) __syncthreads();                         // the second query tile's sums go where these were
+    }
+}
+
 // out[b, n, h, :] = sum_u w_u O_u[n] / sum_u w_u l_u,  w_u = exp(m_u - max_u m_u).
 // One workgroup per (row, head, 8 queries), one thread per (query, 4 dims); all loads of a thread are
 // independent of each other and of the row length, so they make one round trip.
@@ -305,14 +554,21 @@ static size_t attn_short_lds_bytes(int Dh, int ds) {
     return ((size_t)ATTN_WAVES * 64 + std::max((size_t)ATTN_WAVES * (Dh / 32 / ds) * 16 * 64, (size_t)Dh * 16)) * 4;       // O, or the query tile
 }
 
+static size_t attn_pair_lds_bytes(int Dh, int nw) { return ((size_t)2 * (Dh / 16) + (size_t)nw * (Dh / 8)) * 1024; }
+
 int attn_max_dynamic_lds(hydra_ctx *c) {
     (void)c;
     hipError_t e = hipSuccess;
 #define ATTR(DHv, Pv) if (e == hipSuccess) e = hipFuncSetAttribute((const void *)attn_bf16_kernel<DHv, Pv>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024)
     ATTR(128, true); ATTR(128, false); ATTR(64, true); ATTR(64, false);
 #undef ATTR
-#define ATTR(DHv, DSv, Pv) if (e == hipSuccess) e = hipFuncSetAttribute((const void *)attn_short_kernel<DHv, DSv, Pv>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024)
-    ATTR(128, 1, true); ATTR(128, 1, false); ATTR(128, 2, true); ATTR(128, 2, false); ATTR(64, 1, true); ATTR(64, 1, false);
+#define ATTR(DHv, DSv, STv) \
+    if (e == hipSuccess) e = hipFuncSetAttribute((const void *)attn_short_kernel<DHv, DSv, STv, true>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024); \
+    if (e == hipSuccess) e = hipFuncSetAttribute((const void *)attn_short_kernel<DHv, DSv, STv, false>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024)
+    ATTR(128, 1, false); ATTR(128, 1, true); ATTR(128, 2, false); ATTR(64, 1, false); ATTR(64, 1, true);
+#undef ATTR
+#define ATTR(DHv, NWv, Pv) if (e == hipSuccess) e = hipFuncSetAttribute((const void *)attn_pair_kernel<DHv, NWv, Pv>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024)
+    ATTR(128, 8, true); ATTR(128, 8, false); ATTR(64, 8, true); ATTR(64, 8, false); ATTR(128, 4, true); ATTR(128, 4, false);
 #undef ATTR
     if (e != hipSuccess) return hip_fail(e, "hipFuncSetAttribute(attn_bf16_kernel)");
     return HYDRA_OK;
@@ -327,8 +583,6 @@ int launch_attention(hydra_ctx *c, hipStream_t s, int B, int layer, const void *
     }
     const int T = c->tree.T, H = c->m.n_heads, Dh = c->m.head_dim;
     const int QTtot = ceil_div(T, 32);
-    int QW = QTtot >= 3 ? 4 : QTtot;                       // 1, 2 or 4 query waves
-    int KWV = ATTN_WAVES / QW;
     const int len = kv->seq_len_hint > 0 ? kv->seq_len_hint : c->m.max_pos;
     const int tiles = ceil_div(len + T, 32);
     // Short contexts: one workgroup per 32-query tile, its 8 waves split the keys (up to five 32-key tiles each) and
@@ -343,13 +597,21 @@ int launch_attention(hydra_ctx *c, hipStream_t s, int B, int layer, const void *
         int ds = Dh / 32;
         while (ds > 1 && QTtot * H * B * ds > 256) ds >>= 1;
         const dim3 sgrid(ceil_div(H * B, 8) * 8 * QTtot * ds), sblock(ATTN_WAVES * 64);
-#define SHORT(DHv, DSv, Pv)                                                                                                                      \
-    hipLaunchKernelGGL((attn_short_kernel<DHv, DSv, Pv>), sgrid, sblock, attn_short_lds_bytes(DHv, DSv), s, (const u32x4_t *)qbuf,                \
+#define SHORT(DHv, DSv, STv, Pv)                                                                                                                  \
+    hipLaunchKernelGGL((attn_short_kernel<DHv, DSv, STv, Pv>), sgrid, sblock, attn_short_lds_bytes(DHv, DSv), s, (const u32x4_t *)qbuf,           \
                        (const a16_t *)kv->k_pages, (const a16_t *)kv->v_pages, kv->page_table, kv->max_pages, kv->n_pages, layer, seq_len,        \
                        tree_dev(c), T, H, H * B, scale, out, flags)
-#define SHORT_DS(DHv, DSv) do { if (packed) SHORT(DHv, DSv, true); else SHORT(DHv, DSv, false); } while (0)
-        if (Dh == 128) { if (ds == 4) SHORT_DS(128, 4); else if (ds == 2) SHORT_DS(128, 2); else SHORT_DS(128, 1); }
-        else           { if (ds == 2) SHORT_DS(64, 2); else SHORT_DS(64, 1); }
+#define SHORT_DS(DHv, DSv, STv) do { if (packed) SHORT(DHv, DSv, STv, true); else SHORT(DHv, DSv, STv, false); } while (0)
+        if (Dh == 128) {
+            if (ds == 4) SHORT_DS(128, 4, false);
+            else if (ds == 2) SHORT_DS(128, 2, false);
+            else if (QTtot > 1) SHORT_DS(128, 1, false);
+            else SHORT_DS(128, 1, true);
+        } else {
+            if (ds == 2) SHORT_DS(64, 2, false);
+            else if (QTtot > 1) SHORT_DS(64, 1, false);
+            else SHORT_DS(64, 1, true);
+        }
 #undef SHORT_DS
 #undef SHORT
         HYDRA_LAUNCH_CHECK("attn_short_kernel");
@@ -359,18 +621,33 @@ int launch_attention(hydra_ctx *c, hipStream_t s, int B, int layer, const void *
     // holds a CU by itself (registers), so a second round only repeats the fixed cost of a workgroup (first round trips, LDS
     // merge, partial record).  Measured best at about 200 workgroups in all: 7B at 2066 / 4114 keys 4.30 -> 4.01 / 4.63 -> 4.30 ms
     // per verify.
-    int wgs = ceil_div(tiles, KWV * 2);
-    wgs = std::max(1, std::min({wgs, std::max(1, 208 / (H * B)), units_max}));
-    dim3 grid(wgs, H, B), block(ATTN_WAVES * 64);
-    const size_t lds = attn_lds_bytes(Dh);
+    // (two tiles per wave or more)
+    const int qgroups = (QTtot + 1) / 2, nw = QTtot > 1 && H * B * qgroups > 256 ? 4 : 8;
+    const int wgs = nw == 4 ? 1 : std::max(1, std::min({ceil_div(tiles, nw * 2), std::max(1, 208 / (H * B * qgroups)), units_max}));
+    if (QTtot > 1) {                                       // two query tiles to a wave
+        const dim3 pgrid(ceil_div(H * B, 8) * 8 * qgroups * wgs);
+#define PAIR(DHv, NWv, STv)                                                                                                                       \
+    hipLaunchKernelGGL((attn_pair_kernel<DHv, NWv, STv>), pgrid, dim3(NWv * 64), attn_pair_lds_bytes(DHv, NWv), s, (const u32x4_t *)qbuf,          \
+                       (const a16_t *)kv->k_pages, (const a16_t *)kv->v_pages, kv->page_table, kv->max_pages, kv->n_pages, layer, seq_len,        \
+                       tree_dev(c), T, H, H * B, wgs, scale, apart, out, packed ? 1 : 0, flags)
+#define PAIR_NW(DHv, NWv) do { if (qgroups == 1) PAIR(DHv, NWv, true); else PAIR(DHv, NWv, false); } while (0)
+        if (Dh == 128) { if (nw == 8) PAIR_NW(128, 8); else PAIR_NW(128, 4); }
+        else           { if (nw == 8) PAIR_NW(64, 8); else PAIR_NW(64, 4); }
+#undef PAIR_NW
+#undef PAIR
+        HYDRA_LAUNCH_CHECK("attn_pair_kernel");
+    } else {
+        dim3 grid(wgs, H, B), block(ATTN_WAVES * 64);
+        const size_t lds = attn_lds_bytes(Dh);
 #define ATTN_CASE(DHv, Pv)                                                                                           \
-    hipLaunchKernelGGL((attn_bf16_kernel<DHv, Pv>), grid, block, lds, s, (const u32x4_t *)qbuf,                       \
-                       (const a16_t *)kv->k_pages, (const a16_t *)kv->v_pages, kv->page_table, kv->max_pages,      \
-                       kv->n_pages, layer, seq_len, tree_dev(c), T, H, QW, 0, scale, apart, out, flags)
-    if (Dh == 128) { if (packed) ATTN_CASE(128, true); else ATTN_CASE(128, false); }
-    else           { if (packed) ATTN_CASE(64, true); else ATTN_CASE(64, false); }
+        hipLaunchKernelGGL((attn_bf16_kernel<DHv, Pv>), grid, block, lds, s, (const u32x4_t *)qbuf,                       \
+                           (const a16_t *)kv->k_pages, (const a16_t *)kv->v_pages, kv->page_table, kv->max_pages,      \
+                           kv->n_pages, layer, seq_len, tree_dev(c), T, H, scale, apart, out, flags)
+        if (Dh == 128) { if (packed) ATTN_CASE(128, true); else ATTN_CASE(128, false); }
+        else           { if (packed) ATTN_CASE(64, true); else ATTN_CASE(64, false); }
 #undef ATTN_CASE
-    HYDRA_LAUNCH_CHECK("attn_bf16_kernel");
+        HYDRA_LAUNCH_CHECK("attn_bf16_kernel");
+    }
     if (wgs > 1) {
         const int q_per_wg = 256 / (Dh / 4);
         dim3 mgrid(ceil_div(T, q_per_wg), H, B), mblock(256);

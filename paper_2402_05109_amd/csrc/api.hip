@@ -406,12 +406,11 @@ int hydra_draft_tree(hydra_ctx *c, void *stream, int B, void *ws, const float *h
                 std::swap(cur, other);
             }
         } else {
-            if ((rc = launch_gemm(c, s, xa, A + c->head[i].w1, part, Mi, d, Kin, &p))) return rc;
-            const size_t ss = (size_t)align_up(Mi, 32) * gemm_npad(c, d);
-            if ((rc = launch_bias_silu(c, s, part, p.splits, gemm_npad(c, d), ss, (const float *)(A + c->head[i].b1), z, first_residual, xb, Mi))) return rc;
+            if ((rc = launch_f32_bias_silu(c, s, (const float *)xa, (const float *)(A + c->head[i].w1), Mi, Kin, (const float *)(A + c->head[i].b1), z,
+                                           first_residual, (float *)xb))) return rc;
             for (int j = 2; j <= c->h.mlp_layers; ++j) {
-                if ((rc = launch_gemm(c, s, cur, A + c->head[i].wl[j - 2], part, Mi, d, d, &p))) return rc;
-                if ((rc = launch_bias_silu(c, s, part, p.splits, gemm_npad(c, d), ss, (const float *)(A + c->head[i].bl[j - 2]), z, true, other, Mi))) return rc;
+                if ((rc = launch_f32_bias_silu(c, s, (const float *)cur, (const float *)(A + c->head[i].wl[j - 2]), Mi, d,
+                                               (const float *)(A + c->head[i].bl[j - 2]), z, true, (float *)other))) return rc;
                 std::swap(cur, other);
             }
         }
@@ -468,10 +467,6 @@ static int forward_layers(hydra_ctx *c, hipStream_t s, int B, void *ws, const Ro
     void *xa = W + w.xa, *xb = W + w.xb, *qbuf = W + w.qbuf;
     int32_t *flags = flags_ptr(c);
     const int d = c->m.d, F = c->m.ffn, V = c->m.vocab, M = B * c->tree.T;
-    const size_t mp = align_up(M, 32);
-    const int ld_d = gemm_npad(c, d), ld_qkv = gemm_npad(c, 3 * d), ld_gu = gemm_npad(c, 2 * F), ld_v = gemm_npad(c, V);
-    GemmPlan p;
-    const RowScale none = {nullptr, 0, 0, 0, 0.f};
     if (c->bf16) {
         // Fused flow.  The residual epilogues leave x, xg = half(x * gain of the next norm) and per-band sums of
         // squares; the 1/rms factor of each RMSNorm is applied by the consumer of the following GEMM.
@@ -504,26 +499,19 @@ static int forward_layers(hydra_ctx *c, hipStream_t s, int B, void *ws, const Ro
     }
     if (src.tokens) { if ((rc = launch_embed(c, s, src.tokens, x, M, flags))) return rc; }
     else            { if ((rc = launch_gather_prep(c, s, B, src.hidden, src.T_src, src.path, src.n_acc, x, nullptr, nullptr, nullptr, 0, flags))) return rc; }
-    int S_prev = 0;                         // split-K partials of the previous residual branch, still to be added to x
     for (int l = 0; l < c->m.n_layers; ++l) {
         const LayerOff &o = c->layer[l];
-        if ((rc = launch_rmsnorm(c, s, x, part, S_prev, ld_d, mp * ld_d, (const float *)(A + o.attn_norm), xa, M, nullptr))) return rc;
-        if ((rc = launch_gemm(c, s, xa, A + o.wqkv, part, M, 3 * d, d, &p))) return rc;
-        if ((rc = launch_rope_append(c, s, part, p.splits, ld_qkv, mp * ld_qkv, none, B, l, seq_len, kv, qbuf, flags))) return rc;
+        auto weights = [&](size_t off) { return (const float *)(A + off); };
+        if ((rc = launch_f32_qkv_rope(c, s, x, weights(o.attn_norm), weights(o.wqkv), M, l, seq_len, kv, (float *)qbuf, flags))) return rc;
         if ((rc = launch_attention(c, s, B, l, qbuf, seq_len, kv, apart, w.attn_units, xa, nullptr, flags))) return rc;
-        if ((rc = launch_gemm(c, s, xa, A + o.wo, part, M, d, d, &p))) return rc;
-        if ((rc = launch_rmsnorm(c, s, x, part, p.splits, ld_d, mp * ld_d, (const float *)(A + o.ffn_norm), xa, M, nullptr))) return rc;
-        if ((rc = launch_gemm(c, s, xa, A + o.wgu, part, M, 2 * F, d, &p))) return rc;
-        if ((rc = launch_silu_mul(c, s, part, p.splits, ld_gu, mp * ld_gu, xb, M))) return rc;
-        if ((rc = launch_gemm(c, s, xb, A + o.wdown, part, M, d, F, &p))) return rc;
-        S_prev = p.splits;
+        if ((rc = launch_f32_add(c, s, (const float *)xa, weights(o.wo), x, M, d))) return rc;
+        if ((rc = launch_f32_swiglu(c, s, x, weights(o.ffn_norm), weights(o.wgu), (float *)xb, M))) return rc;
+        if ((rc = launch_f32_add(c, s, (const float *)xb, weights(o.wdown), x, M, F))) return rc;
     }
-    // adds the last residual branch to x; the normalised copy it also writes is what the LM head reads
-    if ((rc = launch_rmsnorm(c, s, x, part, S_prev, ld_d, mp * ld_d, (const float *)(A + c->off_final_norm), xa, M, lm_tail ? hidden : nullptr))) return rc;
     if (!lm_tail) return HYDRA_OK;
-    if ((rc = launch_gemm(c, s, xa, A + c->off_lm_head, part, M, V, d, &p))) return rc;
-    if ((rc = launch_argmax(c, s, part, p.splits, ld_v, mp * ld_v, M, argmax, margin, logits))) return rc;
-    return HYDRA_OK;
+    const float *gain = (const float *)(A + c->off_final_norm);
+    if ((rc = launch_f32_norm_gemm(c, s, x, gain, (const float *)(A + c->off_lm_head), part, M, V))) return rc;
+    return launch_argmax(c, s, part, V, M, x, gain, hidden, argmax, margin, logits);
 }
 
 }  // namespace hydra

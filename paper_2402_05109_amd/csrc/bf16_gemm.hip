@@ -158,8 +158,6 @@ GemmPlan plan_gemm(const hydra_ctx *c, int M, int N, int K, int kind) {
     return p;
 }
 
-int launch_gemm_f32(hydra_ctx *c, hipStream_t s, const float *X, const float *W, float *part, int M, int N, int K);
-
 // e0/e1 non-null (profiling): the events take the kernel's own begin and end times, not the stream's before and after
 template <int MB, int NT, class Epi>
 static void launch_one(dim3 grid, dim3 block, size_t lds, hipStream_t s, const GemmGeom &g, const Epi &epi, hipEvent_t e0, hipEvent_t e1) {

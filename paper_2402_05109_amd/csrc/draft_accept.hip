@@ -99,24 +99,22 @@ int launch_draft_gather(hydra_ctx *c, hipStream_t s, int B, int phase, const flo
     return HYDRA_OK;
 }
 
-// z <- (residual ? z : 0) + SiLU(W u + b);  also written as the next GEMM input
-template <bool BF>
+// z <- (residual ? z : 0) + SiLU(W u + b);  also written as the next GEMM input (16-bit family, where the product's K is split)
 __global__ void bias_silu_kernel(const float *part, int S, int part_ld, size_t split_stride, const float *bias,
-                                 float *z, int residual, int d, typename Act<BF>::type *out) {
+                                 float *z, int residual, int d, a16_t *out) {
     const int m = blockIdx.y;
     const int k = blockIdx.x * blockDim.x + threadIdx.x;
     if (k >= d) return;
     float a = silu_f(part_sum(part, S, split_stride, (size_t)m * part_ld + k) + bias[k]);
     if (residual) a += z[(size_t)m * d + k];
     z[(size_t)m * d + k] = a;
-    Act<BF>::st(out, x_index<BF>(m, k, d), a);
+    out[x_index<true>(m, k, d)] = f2a(a);
 }
 
 int launch_bias_silu(hydra_ctx *c, hipStream_t s, const float *part, int S, int part_ld, size_t split_stride,
                      const float *bias, float *z, bool residual, void *x_out, int M) {
     dim3 grid(ceil_div(c->m.d, 256), M), block(256);
-    if (c->bf16) hipLaunchKernelGGL(bias_silu_kernel<true>, grid, block, 0, s, part, S, part_ld, split_stride, bias, z, residual ? 1 : 0, c->m.d, (a16_t *)x_out);
-    else         hipLaunchKernelGGL(bias_silu_kernel<false>, grid, block, 0, s, part, S, part_ld, split_stride, bias, z, residual ? 1 : 0, c->m.d, (float *)x_out);
+    hipLaunchKernelGGL(bias_silu_kernel, grid, block, 0, s, part, S, part_ld, split_stride, bias, z, residual ? 1 : 0, c->m.d, (a16_t *)x_out);
     HYDRA_LAUNCH_CHECK("bias_silu_kernel");
     return HYDRA_OK;
 }
@@ -172,24 +170,23 @@ __device__ __forceinline__ Cand wave_best(Cand c) {
 // ascending) order.
 enum { TOPK_CHUNK = 1024, TOPK_PER_LANE = 16, TOPK_MAX_CHUNKS = 32 };
 
-__global__ __launch_bounds__(64) void topk_chunk_kernel(const float *part, int S, int part_ld, size_t split_stride, int V,
-                                                         const TreeDev *tree, int ne, int expand_off, uint2 *surv) {
-    const int r = blockIdx.y, chunk = blockIdx.x, lane = threadIdx.x;
-    const int base = chunk * TOPK_CHUNK;
-    // the logits first: their addresses need nothing from the tree tables, whose dependent lookups follow
-    uint32_t key[TOPK_PER_LANE];
+// lane's share of a chunk: ids base + i * 64 + lane
+template <int N>
+__device__ __forceinline__ void topk_load(uint32_t (&key)[N], const float *part, int S, size_t split_stride, size_t row, int base, int V, int lane) {
 #pragma unroll
-    for (int i = 0; i < TOPK_PER_LANE; ++i) {
+    for (int i = 0; i < N; ++i) {
         const int id = base + i * 64 + lane;
-        key[i] = id < V ? order_key(part_sum(part, S, split_stride, (size_t)r * part_ld + id)) : 0u;
+        key[i] = id < V ? order_key(part_sum(part, S, split_stride, row + id)) : 0u;
     }
-    const int k = tree->expand_k[expand_off + r % ne];
-    uint2 *out = surv + ((size_t)r * gridDim.x + chunk) * HYDRA_MAX_TOPK;
+}
+// the chunk's k best, best first; key 0: the chunk ran out of entries
+template <int N>
+__device__ __forceinline__ void topk_rounds(uint32_t (&key)[N], int k, int base, int lane, uint2 *out) {
     for (int t = 0; t < k; ++t) {
         // the lane's best: the first maximum in slot order is also its lowest id
         uint32_t bk = 0u, bs = 0u;
 #pragma unroll
-        for (int i = 0; i < TOPK_PER_LANE; ++i)
+        for (int i = 0; i < N; ++i)
             if (key[i] > bk) { bk = key[i]; bs = (uint32_t)i; }
         const uint32_t kmax = wave_reduce_u32<true>(bk);
         const uint32_t idmin = wave_reduce_u32<false>(bk == kmax && kmax != 0u ? (uint32_t)base + bs * 64u + (uint32_t)lane : 0xffffffffu);
@@ -198,11 +195,22 @@ __global__ __launch_bounds__(64) void topk_chunk_kernel(const float *part, int S
             const uint32_t slot = off >> 6;
             const bool owner = (off & 63u) == (uint32_t)lane;
 #pragma unroll
-            for (int i = 0; i < TOPK_PER_LANE; ++i)
+            for (int i = 0; i < N; ++i)
                 if ((uint32_t)i == slot && owner) key[i] = 0u;
         }
-        if (lane == 0) out[t] = make_uint2(kmax, idmin);              // key 0: the chunk ran out of entries
+        if (lane == 0) out[t] = make_uint2(kmax, idmin);
     }
+}
+
+__global__ __launch_bounds__(64) void topk_chunk_kernel(const float *part, int S, int part_ld, size_t split_stride, int V,
+                                                         const TreeDev *tree, int ne, int expand_off, uint2 *surv) {
+    const int r = blockIdx.y, chunk = blockIdx.x, lane = threadIdx.x;
+    const int base = chunk * TOPK_CHUNK;
+    // the logits first: their addresses need nothing from the tree tables, whose dependent lookups follow
+    uint32_t key[TOPK_PER_LANE];
+    topk_load(key, part, S, split_stride, (size_t)r * part_ld, base, V, lane);
+    const int k = tree->expand_k[expand_off + r % ne];
+    topk_rounds(key, k, base, lane, surv + ((size_t)r * gridDim.x + chunk) * HYDRA_MAX_TOPK);
 }
 
 // The k best of the entries that a wave's lanes hold, without k rounds (the second kernel): any entry among them is at least as large as the
@@ -292,6 +300,32 @@ __global__ __launch_bounds__(64) void topk_merge_kernel(const uint2 *surv, int c
     wave_top_k(mk, mi, k, list, lane, [&](int t, uint32_t, uint32_t ii) { out[t] = (int32_t)ii; });
 }
 
+// Small vocabularies: both kernels in one, a wave per 256 ids (four to a lane: rescanning the lane's entries is what a round
+// costs) and the survivors in LDS, at most 16 * 32.  One row of 1000 logits took 7.9 + 3.8 us with the pair of kernels.
+enum { TOPK_ROW_PART = 256, TOPK_ROW_WAVES = 16 };
+template <int WAVES>
+__global__ __launch_bounds__(64 * WAVES) void topk_row_kernel(const float *part, int S, int part_ld, size_t split_stride, int V,
+                                                               const TreeDev *tree, int ne, int expand_off, int32_t *tree_tokens) {
+    __shared__ uint2 surv[WAVES * HYDRA_MAX_TOPK];
+    __shared__ uint2 list[64];
+    const int r = blockIdx.x, b = r / ne, lane = threadIdx.x & 63, wave = threadIdx.x >> 6, waves = blockDim.x >> 6;
+    uint32_t key[TOPK_ROW_PART / 64];
+    topk_load(key, part, S, split_stride, (size_t)r * part_ld, wave * TOPK_ROW_PART, V, lane);
+    const int at = expand_off + r - b * ne, k = tree->expand_k[at];
+    int32_t *out = tree_tokens + (size_t)b * tree->T + tree->expand_first[at];
+    topk_rounds(key, k, wave * TOPK_ROW_PART, lane, surv + wave * k);
+    __syncthreads();
+    if (wave > 0) return;
+    uint32_t mk[WAVES * HYDRA_MAX_TOPK / 64], mi[WAVES * HYDRA_MAX_TOPK / 64];
+#pragma unroll
+    for (int i = 0; i < WAVES * HYDRA_MAX_TOPK / 64; ++i) {
+        const int q = i * 64 + lane;
+        const uint2 e = q < waves * k ? surv[q] : make_uint2(0u, 0xffffffffu);
+        mk[i] = e.x; mi[i] = e.y;
+    }
+    wave_top_k(mk, mi, k, list, lane, [&](int t, uint32_t, uint32_t ii) { out[t] = (int32_t)ii; });
+}
+
 // Any-V fallback: k rounds over memory, each picking the best entry that comes
 // strictly after the previous winner in the (value desc, id asc) order.
 __global__ __launch_bounds__(256) void topk_scan_kernel(const float *part, int S, int part_ld, size_t split_stride,
@@ -335,7 +369,11 @@ int launch_topk(hydra_ctx *c, hipStream_t s, const float *part, int S, int part_
     const int ne = c->tree.n_expand[phase], eoff = c->tree.expand_off[phase];
     const int rows = B * ne;
     const int chunks = ceil_div(c->m.vocab, TOPK_CHUNK);
-    if (chunks <= TOPK_MAX_CHUNKS) {
+    if (const int waves = ceil_div(c->m.vocab, TOPK_ROW_PART); waves <= TOPK_ROW_WAVES) {
+        if (waves <= 4) hipLaunchKernelGGL(topk_row_kernel<4>, dim3(rows), dim3(64 * waves), 0, s, part, S, part_ld, split_stride, c->m.vocab, tree_dev(c), ne, eoff, tree_tokens);
+        else            hipLaunchKernelGGL(topk_row_kernel<TOPK_ROW_WAVES>, dim3(rows), dim3(64 * waves), 0, s, part, S, part_ld, split_stride, c->m.vocab, tree_dev(c), ne, eoff, tree_tokens);
+        HYDRA_LAUNCH_CHECK("topk_row_kernel");
+    } else if (chunks <= TOPK_MAX_CHUNKS) {
         hipLaunchKernelGGL(topk_chunk_kernel, dim3(chunks, rows), dim3(64), 0, s, part, S, part_ld, split_stride, c->m.vocab, tree_dev(c), ne, eoff, (uint2 *)scratch);
         HYDRA_LAUNCH_CHECK("topk_chunk_kernel");
         hipLaunchKernelGGL(topk_merge_kernel, dim3(rows), dim3(64), 0, s, (const uint2 *)scratch, chunks, tree_dev(c), ne, eoff, tree_tokens);

@@ -8,21 +8,53 @@ namespace hydra {
 typedef __attribute__((ext_vector_type(4))) float f32x4_t;
 typedef float f32x4_u __attribute__((ext_vector_type(4), aligned(4)));      // the caller's pages: no more than float alignment is known
 
-// part[m][n] = sum_k X[m][k] W[n][k] on the fp32 matrix instruction (16 x 16 x 4, fp32 products and sums).  A workgroup
+// sum_k X[m][k] W[n][k] on the fp32 matrix instruction (16 x 16 x 4, fp32 products and sums).  A workgroup
 // computes 16 rows x 16 features; its four waves take the 16-long pieces of K in turn and meet in LDS.
 // Lane (r, g) loads four consecutive k of row r and of feature r at piece + 4 g, and instruction e of a piece multiplies the
 // k of every lane's element e: the four lane groups hold different k, the same ones on both sides, so no data is moved
-// between lanes.  Bound by one round of loads (four pieces in flight per wave) and the meeting.  With a feature per wave, 16
-// rows per lane and a reduction over the lanes a launch of the tiny shape (16 rows, K = 256 or 688) took 8.3 us on average,
-// 8.9 with a shared reduction and 16-byte loads.
+// between lanes.  Bound by one round of loads (four pieces in flight per wave, the next four requested before these are
+// multiplied) and the meeting.  With a feature per wave, 16 rows per lane and a reduction over the lanes a launch of the tiny
+// shape (16 rows, K = 256 or 688) took 8.3 us on average, 8.9 with a shared reduction and 16-byte loads.
 // Rows and features past the end repeat the last one and are not stored; k past K is zero on both sides.
-template <bool VEC>
-__global__ __launch_bounds__(256) void gemm_f32_kernel(const float *__restrict__ X, const float *__restrict__ W,
-                                                        float *__restrict__ part, int M, int N, int K, int ld) {
-    __shared__ f32x4_t red[4][64];
+//
+// A launch of these models costs 2 to 5 us whatever it does, so what stands in front of and behind a product is part of it:
+//   NORM      X is the residual stream: x * gain is multiplied, and 1 / rms(x), whose sum of squares the lanes collect on the
+//             way, scales the sums (it commutes with the contraction)
+//   ADD       out (the residual stream) += sums
+//   BIAS_SILU z = (residual ? z : 0) + SiLU(sums + bias), also written as the next layer's input
+//   SWIGLU    SiLU(sums of gate feature n) * sums of up feature n (weight rows n and F + n)
+//   ROPE      features n and n + Dh/2 of a head, which are a rotary pair: q -> attention input [B][T][H][Dh], k and v -> cache
+//             slot seq_len[b] + node at position seq_len[b] + depth (paper, section 2, "Tree decoding")
+// Norm, rotary embedding, activation and bias as kernels of their own: 43 launches per step of the tiny shape, 28 this way.
+enum { F32_PLAIN, F32_ADD, F32_BIAS_SILU, F32_SWIGLU, F32_ROPE };
+struct F32Rope {
+    const float *table; const int32_t *seq_len, *page_table; const TreeDev *tree;
+    float *kpages, *vpages, *qbuf; int32_t *flags;
+    int max_pages, n_pages, layer, H, Dh, T, max_pos;
+};
+struct F32Epilogue {
+    float *out; int ld;
+    const float *gain; float eps;                                      // NORM
+    const float *bias; float *z; int residual;                         // BIAS_SILU
+    F32Rope rope;                                                      // ROPE
+};
+template <int MODE, bool NORM, bool VEC>
+__global__ __launch_bounds__(256, 2) void gemm_f32_kernel(const float *__restrict__ X, const float *__restrict__ W, int M, int N, int K, F32Epilogue o) {
+    constexpr int NB = MODE == F32_SWIGLU || MODE == F32_ROPE ? 2 : 1;              // features per lane
+    __shared__ f32x4_t red[NB][4][64];
+    __shared__ float red_sq[4][16];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, r = lane & 15, g = lane >> 4;
-    const int n0 = blockIdx.x * 16, m0 = blockIdx.y * 16;
+    const int m0 = blockIdx.y * 16;
+    // first feature and the distance of the second one.  ROPE: the 16-feature pieces of the first half of each q, k and v head
+    int n0 = blockIdx.x * 16, second = N, part = 0;
+    if (MODE == F32_ROPE) {
+        const int half = o.rope.Dh >> 1, pieces = half >> 4;
+        part = blockIdx.x / pieces;                                    // q heads, then k heads, then v heads
+        n0 = part * o.rope.Dh + (blockIdx.x - part * pieces) * 16;
+        second = half;
+    }
     const float *xr = X + (size_t)min(m0 + r, M - 1) * K + 4 * g, *wr = W + (size_t)min(n0 + r, N - 1) * K + 4 * g;
+    const float *gr = NORM ? o.gain + 4 * g : nullptr;
     auto four = [&](const float *p, int k) {
         f32x4_t v = {0.f, 0.f, 0.f, 0.f};
         if (VEC) {
@@ -34,40 +66,164 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float *__restrict__
         }
         return v;
     };
-    f32x4_t part_acc[4][4];                                            // a sum per (piece, element): chains of K / 256 products, added as a tree
+    f32x4_t a[4], b[NB][4], gn[4];
+    auto fetch = [&](int k0) {
 #pragma unroll
-    for (int u = 0; u < 4; ++u)
+        for (int u = 0; u < 4; ++u) {
+            a[u] = four(xr, k0 + 64 * u);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) part_acc[u][e] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+            for (int i = 0; i < NB; ++i) b[i][u] = four(wr + (size_t)i * second * K, k0 + 64 * u);
+            if (NORM) gn[u] = four(gr, k0 + 64 * u);
+        }
+    };
+    fetch(wave * 16);
+    // what the end needs, requested while the operands are under way
+    const int m = threadIdx.x >> 4, n = threadIdx.x & 15, row = m0 + m, col = n0 + n;
+    const bool live = row < M && col < N;
+    float before = 0.f, bias = 0.f;
+    if (MODE == F32_ADD && live) before = o.out[(size_t)row * o.ld + col];
+    if (MODE == F32_BIAS_SILU && live) {
+        bias = o.bias[col];
+        if (o.residual) before = o.z[(size_t)row * N + col];
+    }
+    float cs = 1.f, sn = 0.f;
+    size_t at = 0;
+    bool fits = false, cached = false;
+    if (MODE == F32_ROPE) {
+        const F32Rope &p = o.rope;
+        const int bb = min(row, M - 1) / p.T, node = min(row, M - 1) - bb * p.T, L = p.seq_len[bb];
+        fits = L >= 0 && L + p.T <= p.max_pages * 16 && L + p.tree->max_depth < p.max_pos;
+        if (fits) {
+            const int j = (n0 % p.Dh) + n, half = p.Dh >> 1, slot = L + node;
+            const float *t = p.table + ((size_t)(L + p.tree->depth[node]) * half + j) * 2;
+            cs = t[0];
+            sn = t[1];
+            const int page = p.page_table[(size_t)bb * p.max_pages + (slot >> 4)];
+            cached = (unsigned)page < (unsigned)p.n_pages;
+            at = kv_block_base(p.layer, p.n_pages, cached ? page : 0, p.H, part % p.H, p.Dh) + (size_t)(slot & 15) * p.Dh + j;
+        }
+    }
+    // a sum per (piece, element), added as a tree: chains of K / 256 products.  Two pieces share one where there are two features
+    // (with 32 sums per lane only one wave fits a SIMD: 2048 wide, 128 rows, a step 4.5 % slower)
+    constexpr int NP = 4 / NB;
+    f32x4_t part_acc[NB][NP][4];
+#pragma unroll
+    for (int i = 0; i < NB; ++i)
+#pragma unroll
+        for (int u = 0; u < NP; ++u)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) part_acc[i][u][e] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    float sq = 0.f;
     for (int k0 = wave * 16; k0 < K; k0 += 256) {
-        f32x4_t a[4], b[4];
+        f32x4_t ca[4], cb[NB][4];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) { a[u] = four(xr, k0 + 64 * u); b[u] = four(wr, k0 + 64 * u); }
+        for (int u = 0; u < 4; ++u) {
+            ca[u] = a[u];
+#pragma unroll
+            for (int i = 0; i < NB; ++i) cb[i][u] = b[i][u];
+            if (NORM)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    sq = fmaf(a[u][e], a[u][e], sq);
+                    ca[u][e] *= gn[u][e];
+                }
+        }
+        if (k0 + 256 < K) fetch(k0 + 256);
 #pragma unroll
         for (int u = 0; u < 4; ++u)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) part_acc[u][e] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u][e], b[u][e], part_acc[u][e], 0, 0, 0);
-    }
-    f32x4_t by_piece[4];
+            for (int e = 0; e < 4; ++e)
 #pragma unroll
-    for (int u = 0; u < 4; ++u) by_piece[u] = (part_acc[u][0] + part_acc[u][1]) + (part_acc[u][2] + part_acc[u][3]);
-    const f32x4_t acc = (by_piece[0] + by_piece[1]) + (by_piece[2] + by_piece[3]);
-    red[wave][lane] = acc;                                            // acc[v]: row 4 g + v, feature r
+                for (int i = 0; i < NB; ++i) part_acc[i][u % NP][e] = __builtin_amdgcn_mfma_f32_16x16x4f32(ca[u][e], cb[i][u][e], part_acc[i][u % NP][e], 0, 0, 0);
+    }
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+        f32x4_t by_piece[NP];
+#pragma unroll
+        for (int u = 0; u < NP; ++u) by_piece[u] = (part_acc[i][u][0] + part_acc[i][u][1]) + (part_acc[i][u][2] + part_acc[i][u][3]);
+        f32x4_t all = by_piece[0] + by_piece[1];
+        if constexpr (NP == 4) all += by_piece[2] + by_piece[3];
+        red[i][wave][lane] = all;                                      // [v]: row 4 g + v, feature r
+    }
+    if (NORM) {
+        sq += __shfl_xor(sq, 16, 64);
+        sq += __shfl_xor(sq, 32, 64);
+        if (g == 0) red_sq[wave][r] = sq;
+    }
     __syncthreads();
-    const int m = threadIdx.x >> 4, n = threadIdx.x & 15;
+    if (row >= M) return;
     const int from = (m >> 2) * 16 + n;
-    const float s = (red[0][from][m & 3] + red[1][from][m & 3]) + (red[2][from][m & 3] + red[3][from][m & 3]);
-    if (m0 + m < M && n0 + n < N) part[(size_t)(m0 + m) * ld + n0 + n] = s;
+    const float rstd = NORM ? 1.0f / sqrtf(((red_sq[0][m] + red_sq[1][m]) + (red_sq[2][m] + red_sq[3][m])) / (float)K + o.eps) : 1.0f;
+    float s[NB];
+#pragma unroll
+    for (int i = 0; i < NB; ++i) s[i] = ((red[i][0][from][m & 3] + red[i][1][from][m & 3]) + (red[i][2][from][m & 3] + red[i][3][from][m & 3])) * rstd;
+    if (MODE == F32_ROPE) {
+        const F32Rope &p = o.rope;
+        if (n == 0 && !(fits && cached)) atomicOr(p.flags, fits ? FLAG_BAD_PAGE : FLAG_CAPACITY);      // bad table entry: the row's K/V are not written
+        const int sec = part / p.H, half = p.Dh >> 1;
+        if (!fits || (sec > 0 && !cached)) return;
+        const float y0 = sec < 2 ? s[0] * cs - s[NB - 1] * sn : s[0], y1 = sec < 2 ? s[NB - 1] * cs + s[0] * sn : s[NB - 1];
+        float *dst = sec == 0 ? p.qbuf + (size_t)row * p.H * p.Dh + n0 + n : (sec == 1 ? p.kpages : p.vpages) + at;
+        dst[0] = y0;
+        dst[half] = y1;
+        return;
+    }
+    if (!live) return;
+    float y = s[0];
+    if (MODE == F32_ADD) y += before;
+    if (MODE == F32_BIAS_SILU) {
+        y = silu_f(y + bias) + before;
+        o.z[(size_t)row * N + col] = y;
+    }
+    if (MODE == F32_SWIGLU) y = silu_f(y) * s[NB - 1];
+    o.out[(size_t)row * o.ld + col] = y;
+}
+
+// VEC where K % 4 == 0: X, W and the gains start at 256-byte boundaries of the workspace and the arena, so every row is 16-byte
+// aligned.  Only the width of the FFN may be anything; d and the heads' widths are multiples of 64.
+template <int MODE, bool NORM>
+static int run_f32(hipStream_t s, const float *X, const float *W, int M, int N, int K, int tiles, const F32Epilogue &o) {
+    dim3 grid(tiles, ceil_div(M, 16)), block(256);
+    if (K % 4 == 0) hipLaunchKernelGGL((gemm_f32_kernel<MODE, NORM, true>), grid, block, 0, s, X, W, M, N, K, o);
+    else if constexpr (!NORM) hipLaunchKernelGGL((gemm_f32_kernel<MODE, NORM, false>), grid, block, 0, s, X, W, M, N, K, o);
+    else return fail(HYDRA_E_UNSUPPORTED, "fp32 family: d is a multiple of 64");
+    HYDRA_LAUNCH_CHECK("gemm_f32_kernel");
+    return HYDRA_OK;
 }
 
 int launch_gemm_f32(hydra_ctx *c, hipStream_t s, const float *X, const float *W, float *part, int M, int N, int K) {
     (void)c;
-    // K % 4 == 0: X and W start at 256-byte boundaries of the workspace and the arena, so every row is 16-byte aligned
-    dim3 grid(ceil_div(N, 16), ceil_div(M, 16)), block(256);
-    if (K % 4 == 0) hipLaunchKernelGGL(gemm_f32_kernel<true>, grid, block, 0, s, X, W, part, M, N, K, N);
-    else            hipLaunchKernelGGL(gemm_f32_kernel<false>, grid, block, 0, s, X, W, part, M, N, K, N);
-    HYDRA_LAUNCH_CHECK("gemm_f32_kernel");
-    return HYDRA_OK;
+    F32Epilogue o{};
+    o.out = part; o.ld = N;
+    return run_f32<F32_PLAIN, false>(s, X, W, M, N, K, ceil_div(N, 16), o);
+}
+int launch_f32_norm_gemm(hydra_ctx *c, hipStream_t s, const float *x, const float *gain, const float *W, float *part, int M, int N) {
+    F32Epilogue o{};
+    o.out = part; o.ld = N; o.gain = gain; o.eps = c->m.rms_eps;
+    return run_f32<F32_PLAIN, true>(s, x, W, M, N, c->m.d, ceil_div(N, 16), o);
+}
+int launch_f32_add(hydra_ctx *c, hipStream_t s, const float *X, const float *W, float *x, int M, int K) {
+    F32Epilogue o{};
+    o.out = x; o.ld = c->m.d;
+    return run_f32<F32_ADD, false>(s, X, W, M, c->m.d, K, ceil_div(c->m.d, 16), o);
+}
+int launch_f32_bias_silu(hydra_ctx *c, hipStream_t s, const float *X, const float *W, int M, int K, const float *bias, float *z, bool residual, float *out) {
+    F32Epilogue o{};
+    o.out = out; o.ld = c->m.d; o.bias = bias; o.z = z; o.residual = residual ? 1 : 0;
+    return run_f32<F32_BIAS_SILU, false>(s, X, W, M, c->m.d, K, ceil_div(c->m.d, 16), o);
+}
+int launch_f32_swiglu(hydra_ctx *c, hipStream_t s, const float *x, const float *gain, const float *W, float *act, int M) {
+    F32Epilogue o{};
+    o.out = act; o.ld = c->m.ffn; o.gain = gain; o.eps = c->m.rms_eps;
+    return run_f32<F32_SWIGLU, true>(s, x, W, M, c->m.ffn, c->m.d, ceil_div(c->m.ffn, 16), o);
+}
+int launch_f32_qkv_rope(hydra_ctx *c, hipStream_t s, const float *x, const float *gain, const float *W, int M, int layer, const int32_t *seq_len,
+                        const hydra_kv *kv, float *qbuf, int32_t *flags) {
+    F32Epilogue o{};
+    o.gain = gain; o.eps = c->m.rms_eps;
+    o.rope = F32Rope{rope_dev(c), seq_len, kv->page_table, tree_dev(c), (float *)kv->k_pages, (float *)kv->v_pages, qbuf, flags,
+                     kv->max_pages, kv->n_pages, layer, c->m.n_heads, c->m.head_dim, c->tree.T, c->m.max_pos};
+    return run_f32<F32_ROPE, true>(s, x, W, M, 3 * c->m.d, c->m.d, 3 * c->m.n_heads * (c->m.head_dim / 32), o);
 }
 
 // ---------------------------------------------------------------------------

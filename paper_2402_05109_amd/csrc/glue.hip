@@ -111,58 +111,6 @@ int launch_embed(hydra_ctx *c, hipStream_t s, const int32_t *tokens, float *x, i
 }
 
 // ---------------------------------------------------------------------------
-// Residual add + RMSNorm.  x[m,:] += sum_s part[s][m,:]  (if S > 0), then
-// out[m,k] = x[m,k] * gain[k] / sqrt(mean_k x^2 + eps), written as the next
-// GEMM's input and, for the final norm, also as fp32 `hidden`.
-// One workgroup per row; a thread keeps its <= 32 elements in registers.
-// ---------------------------------------------------------------------------
-template <bool BF>
-__global__ __launch_bounds__(256) void rmsnorm_kernel(float *x, const float *part, int S, int part_ld,
-                                                       size_t split_stride, const float *gain, float eps, int d,
-                                                       typename Act<BF>::type *out, float *hidden) {
-    const int m = blockIdx.x;
-    float v[32];
-    float ss = 0.f;
-    int cnt = 0;
-    for (int k = threadIdx.x; k < d; k += 256, ++cnt) {
-        float a = x[(size_t)m * d + k];
-        if (S > 0) {
-            a += part_sum(part, S, split_stride, (size_t)m * part_ld + k);
-            x[(size_t)m * d + k] = a;
-        }
-        v[cnt] = a;
-        ss += a * a;
-    }
-    __shared__ float red[4];
-    ss = wave_sum(ss);
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = ss;
-    __syncthreads();
-    const float tot = red[0] + red[1] + red[2] + red[3];
-    const float rstd = 1.0f / sqrtf(tot / (float)d + eps);
-    cnt = 0;
-    for (int k = threadIdx.x; k < d; k += 256, ++cnt) {
-        const float y = v[cnt] * rstd * gain[k];
-        Act<BF>::st(out, x_index<BF>(m, k, d), y);
-        if (hidden) hidden[(size_t)m * d + k] = y;
-    }
-}
-
-int launch_rmsnorm(hydra_ctx *c, hipStream_t s, float *x, const float *part, int S, int part_ld,
-                   size_t split_stride, const float *gain, void *x_out, int M, float *hidden_out) {
-    if (c->m.d > 32 * 256) return fail(HYDRA_E_UNSUPPORTED, "rmsnorm: d > 8192");
-    if (c->bf16) hipLaunchKernelGGL(rmsnorm_kernel<true>, dim3(M), dim3(256), 0, s, x, part, S, part_ld, split_stride, gain, c->m.rms_eps, c->m.d, (a16_t *)x_out, hidden_out);
-    else         hipLaunchKernelGGL(rmsnorm_kernel<false>, dim3(M), dim3(256), 0, s, x, part, S, part_ld, split_stride, gain, c->m.rms_eps, c->m.d, (float *)x_out, hidden_out);
-    HYDRA_LAUNCH_CHECK("rmsnorm_kernel");
-    return HYDRA_OK;
-}
-
-// ---------------------------------------------------------------------------
-// Rotary embedding of q and k at position seq_len[b] + depth[n], then
-//   q -> attention input buffer, (k, v) -> cache slot seq_len[b] + n.
-// Input: the QKV GEMM result, columns [0,d) = q, [d,2d) = k, [2d,3d) = v.
-// One workgroup per (row m = b*T + n, head); thread j < Dh/2 owns the rotary
-// pair (j, j + Dh/2).
-//
 // q buffer layout.  f32 family: [B][T][H][Dh] fp32.  bf16 family: per (b, head,
 // 32-query tile qt) a run of Dh/16 blocks of 1 KiB in MFMA operand order:
 // block s, lane = ((dim>>3)&1)*32 + query%32 holds dims (dim>>3)*8 .. +8.
@@ -178,44 +126,9 @@ __device__ __forceinline__ size_t q_index(int b, int n, int h, int dim, int H, i
     }
 }
 
-__global__ void rope_append_kernel(const float *part, int S, int part_ld, size_t split_stride, const TreeDev *tree,
-                                   const float *rope, const int32_t *seq_len, const int32_t *page_table,
-                                   int max_pages, int n_pages, int layer, float *kpages, float *vpages, float *qbuf, int d, int H,
-                                   int Dh, int max_pos, int32_t *flags) {
-    const int T = tree->T;
-    const int m = blockIdx.x, h = blockIdx.y;
-    const int b = m / T, n = m - b * T;
-    const int L = seq_len[b];
-    const int slot = L + n;
-    const int pos = L + tree->depth[n];
-    const bool ok = L >= 0 && (L + T) <= max_pages * 16 && (L + tree->max_depth) < max_pos;
-    if (!ok) {
-        if (threadIdx.x == 0) atomicOr(flags, FLAG_CAPACITY);
-        return;
-    }
-    const int half = Dh >> 1;
-    const int j = threadIdx.x;
-    if (j >= half) return;
-    const size_t row = (size_t)m * part_ld;
-    const int c0 = h * Dh + j, c1 = c0 + half;
-    const float q0 = part_sum(part, S, split_stride, row + c0), q1 = part_sum(part, S, split_stride, row + c1);
-    const float k0 = part_sum(part, S, split_stride, row + d + c0), k1 = part_sum(part, S, split_stride, row + d + c1);
-    const float v0 = part_sum(part, S, split_stride, row + 2 * d + c0), v1 = part_sum(part, S, split_stride, row + 2 * d + c1);
-    const float cs = rope[((size_t)pos * half + j) * 2], sn = rope[((size_t)pos * half + j) * 2 + 1];
-    qbuf[q_index<false>(b, n, h, j, H, Dh, T)] = q0 * cs - q1 * sn;
-    qbuf[q_index<false>(b, n, h, j + half, H, Dh, T)] = q1 * cs + q0 * sn;
-    const int page = page_table[(size_t)b * max_pages + (slot >> 4)];
-    if ((unsigned)page >= (unsigned)n_pages) { atomicOr(flags, FLAG_BAD_PAGE); return; }      // bad table entry: the row's K/V are not written
-    const int tok = slot & 15;
-    const size_t base = kv_block_base(layer, n_pages, page, H, h, Dh);
-    kpages[base + k_in_block<false>(tok, j, Dh)] = k0 * cs - k1 * sn;
-    kpages[base + k_in_block<false>(tok, j + half, Dh)] = k1 * cs + k0 * sn;
-    vpages[base + v_in_block<false>(tok, j, Dh)] = v0;
-    vpages[base + v_in_block<false>(tok, j + half, Dh)] = v1;
-}
-
-// The same for the 16-bit family where the q|k|v GEMM leaves plain partial sums (launch_gemm_qkv_rope), with the row's 1/rms
-// applied here.  The q and k weight bands of a head are packed so that the bands holding dims j and j + Dh/2 are
+// Rotary embedding of q and k at position seq_len[b] + depth[n], then q -> attention input buffer, (k, v) -> cache slot
+// seq_len[b] + n, for the 16-bit family where the q|k|v GEMM leaves plain partial sums (launch_gemm_qkv_rope), columns [0,d) = q,
+// [d,2d) = k, [2d,3d) = v, with the row's 1/rms applied here.  The q and k weight bands of a head are packed so that the bands holding dims j and j + Dh/2 are
 // neighbours (pack_weight_kernel, bph > 1): dim j < Dh/2 sits in band 2 * (j / 32), dim j + Dh/2 in the band behind it.
 // A workgroup takes the tokens of one row that fall into one cache page, up to 16, for one head: a thread holds four
 // neighbouring pairs (j, j + Dh/2) of q, k and v of one token (six 16-byte loads per partial, 8-byte stores of q and K), and
@@ -302,17 +215,12 @@ int launch_rope_append(hydra_ctx *c, hipStream_t s, const float *part, int S, in
                        RowScale rs, int B, int layer, const int32_t *seq_len, const hydra_kv *kv, void *qbuf,
                        int32_t *flags) {
     const int T = c->tree.T, H = c->m.n_heads, Dh = c->m.head_dim;
-    if (c->bf16) {
-        const int groups = ceil_div(T + 15, 16);              // pages that T tokens can touch, whatever their alignment
-        dim3 grid(B * groups, H);
+    const int groups = ceil_div(T + 15, 16);                  // pages that T tokens can touch, whatever their alignment
+    dim3 grid(B * groups, H);
 #define ROPE16(DHv) hipLaunchKernelGGL(rope_append16_kernel<DHv>, grid, dim3(DHv * 2), 0, s, part, S, part_ld, split_stride, rs, tree_dev(c), rope_dev(c), seq_len, kv->page_table, kv->max_pages, kv->n_pages, layer, (a16_t *)kv->k_pages, (a16_t *)kv->v_pages, (a16_t *)qbuf, c->m.d, H, T, c->m.max_pos, groups, flags)
-        if (Dh == 128) ROPE16(128); else ROPE16(64);
+    if (Dh == 128) ROPE16(128); else ROPE16(64);
 #undef ROPE16
-        HYDRA_LAUNCH_CHECK("rope_append16_kernel");
-        return HYDRA_OK;
-    }
-    hipLaunchKernelGGL(rope_append_kernel, dim3(B * T, H), dim3(64), 0, s, part, S, part_ld, split_stride, tree_dev(c), rope_dev(c), seq_len, kv->page_table, kv->max_pages, kv->n_pages, layer, (float *)kv->k_pages, (float *)kv->v_pages, (float *)qbuf, c->m.d, H, Dh, c->m.max_pos, flags);
-    HYDRA_LAUNCH_CHECK("rope_append_kernel");
+    HYDRA_LAUNCH_CHECK("rope_append16_kernel");
     return HYDRA_OK;
 }
 
@@ -334,78 +242,58 @@ int launch_q_import(hydra_ctx *c, hipStream_t s, int B, const float *q_plain, vo
 }
 
 // ---------------------------------------------------------------------------
-// SwiGLU: act[m,f] = SiLU(gate[m,f]) * up[m,f].  The gate/up GEMM output holds
-// gate feature f in column (f / blk) * 2 blk + f % blk and up feature f `blk`
-// columns further (blk = 32 for the tile-interleaved bf16 weights, blk = F for
-// the fp32 family, where the rows are simply [gate ; up]).
-// ---------------------------------------------------------------------------
-template <bool BF>
-__global__ void silu_mul_kernel(const float *part, int S, int part_ld, size_t split_stride, int F, int blk,
-                                typename Act<BF>::type *out) {
-    const int m = blockIdx.y;
-    const int f = blockIdx.x * blockDim.x + threadIdx.x;
-    if (f >= F) return;
-    const int gc = (f / blk) * 2 * blk + (f % blk);
-    const size_t row = (size_t)m * part_ld;
-    const float g = part_sum(part, S, split_stride, row + gc);
-    const float u = part_sum(part, S, split_stride, row + gc + blk);
-    Act<BF>::st(out, x_index<BF>(m, f, F), silu_f(g) * u);
-}
-
-int launch_silu_mul(hydra_ctx *c, hipStream_t s, const float *part, int S, int part_ld, size_t split_stride,
-                    void *x_out, int M) {
-    const int F = c->m.ffn;
-    dim3 grid(ceil_div(F, 256), M), block(256);
-    if (c->bf16) hipLaunchKernelGGL(silu_mul_kernel<true>, grid, block, 0, s, part, S, part_ld, split_stride, F, 16, (a16_t *)x_out);
-    else         hipLaunchKernelGGL(silu_mul_kernel<false>, grid, block, 0, s, part, S, part_ld, split_stride, F, F, (float *)x_out);
-    HYDRA_LAUNCH_CHECK("silu_mul_kernel");
-    return HYDRA_OK;
-}
-
-// ---------------------------------------------------------------------------
 // LM head epilogue: per row, logits = sum of split-K partials; greedy token =
 // lowest id among the maxima; margin = top-1 minus top-2 value.
 // ---------------------------------------------------------------------------
 
-// fp32 family: one workgroup of 1024 threads per row.  VEC: rows of `part` are 16-byte aligned (row stride a multiple
-// of 4), so a thread takes four consecutive logits per load and keeps four loads in flight.
+// fp32 family: one workgroup of 1024 threads per row, which also writes the row's final hidden state (x times the norm's gain
+// over its rms; the product in front of this one applied the same factor to its sums).  VEC: rows of `part` are 16-byte aligned (V a
+// multiple of 4), so a thread takes four consecutive logits per load and keeps four loads in flight.
 template <bool VEC>
-__global__ __launch_bounds__(1024) void argmax_kernel(const float *__restrict__ part, int S, int part_ld, size_t split_stride,
-                                                       int V, int32_t *argmax, float *margin, float *__restrict__ logits) {
+__global__ __launch_bounds__(1024) void argmax_kernel(const float *__restrict__ part, int part_ld, int V, const float *__restrict__ x,
+                                                       const float *__restrict__ gain, float *__restrict__ hidden, int d, float eps, int32_t *argmax, float *margin,
+                                                       float *__restrict__ logits) {
     typedef __attribute__((ext_vector_type(4))) float f4;
+    typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));          // the caller's hidden states
     const int m = blockIdx.x;
+    f4 h[2], gn[2];                                        // d is a multiple of 64, at most 8192
+    float sq = 0.f;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const int k = (i * 1024 + (int)threadIdx.x) * 4;
+        h[i] = gn[i] = f4{0.f, 0.f, 0.f, 0.f};
+        if (k < d) {
+            h[i] = *reinterpret_cast<const f4 *>(x + (size_t)m * d + k);
+            gn[i] = *reinterpret_cast<const f4 *>(gain + k);
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) sq += h[i][e] * h[i][e];
+    }
     Top2 t = {-INFINITY, 0x7fffffff, -INFINITY};
     const float *row = part + (size_t)m * part_ld;
     if (VEC) {
-        const int V4 = (V + 3) >> 2;                       // the last group may reach into the row padding (part_ld >= V rounded up to 4)
+        const int V4 = V >> 2;
         for (int g0 = threadIdx.x; g0 < V4; g0 += 4 * 1024) {
-            f4 x[4];
+            f4 y[4];
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
                 const int g = g0 + u * 1024;
-                x[u] = f4{0.f, 0.f, 0.f, 0.f};
-                if (g < V4)
-                    for (int sp = 0; sp < S; ++sp) x[u] += *reinterpret_cast<const f4 *>(row + (size_t)sp * split_stride + 4 * g);
+                y[u] = g < V4 ? *reinterpret_cast<const f4 *>(row + 4 * g) : f4{0.f, 0.f, 0.f, 0.f};
             }
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
                 const int g = g0 + u * 1024;
                 if (g >= V4) continue;
+                if (logits) *reinterpret_cast<f4u *>(logits + (size_t)m * V + 4 * g) = y[u];
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const int v = 4 * g + e;
-                    if (v >= V) continue;
-                    const float y = x[u][e];
-                    if (logits) logits[(size_t)m * V + v] = y;
-                    top2_push(t, y, v);
-                }
+                for (int e = 0; e < 4; ++e) top2_push(t, y[u][e], 4 * g + e);
             }
         }
     } else {
         for (int v = threadIdx.x; v < V; v += 1024) {
-            const float x = part_sum(part, S, split_stride, (size_t)m * part_ld + v);
-            if (logits) logits[(size_t)m * V + v] = x;
-            top2_push(t, x, v);
+            const float y = row[v];
+            if (logits) logits[(size_t)m * V + v] = y;
+            top2_push(t, y, v);
         }
     }
 #pragma unroll
@@ -413,9 +301,20 @@ __global__ __launch_bounds__(1024) void argmax_kernel(const float *__restrict__ 
         Top2 u = {__shfl_xor(t.v1, o, 64), __shfl_xor(t.i1, o, 64), __shfl_xor(t.v2, o, 64)};
         top2_merge(t, u);
     }
+    sq = wave_sum(sq);
     __shared__ Top2 red[16];
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = t;
+    __shared__ float red_sq[16];
+    if ((threadIdx.x & 63) == 0) { red[threadIdx.x >> 6] = t; red_sq[threadIdx.x >> 6] = sq; }
     __syncthreads();
+    float tot = 0.f;
+#pragma unroll
+    for (int w = 0; w < 16; ++w) tot += red_sq[w];
+    const float r = 1.0f / sqrtf(tot / (float)d + eps);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const int k = (i * 1024 + (int)threadIdx.x) * 4;
+        if (k < d) *reinterpret_cast<f4u *>(hidden + (size_t)m * d + k) = h[i] * r * gn[i];
+    }
     if (threadIdx.x == 0) {
         Top2 q = red[0];
         for (int w = 1; w < 16; ++w) top2_merge(q, red[w]);
@@ -424,10 +323,10 @@ __global__ __launch_bounds__(1024) void argmax_kernel(const float *__restrict__ 
     }
 }
 
-int launch_argmax(hydra_ctx *c, hipStream_t s, const float *part, int S, int part_ld, size_t split_stride, int M, int32_t *argmax, float *margin, float *logits) {
-    const bool vec = part_ld % 4 == 0 && split_stride % 4 == 0 && part_ld >= (c->m.vocab + 3) / 4 * 4;
-    if (vec) hipLaunchKernelGGL(argmax_kernel<true>, dim3(M), dim3(1024), 0, s, part, S, part_ld, split_stride, c->m.vocab, argmax, margin, logits);
-    else     hipLaunchKernelGGL(argmax_kernel<false>, dim3(M), dim3(1024), 0, s, part, S, part_ld, split_stride, c->m.vocab, argmax, margin, logits);
+int launch_argmax(hydra_ctx *c, hipStream_t s, const float *part, int part_ld, int M, const float *x, const float *gain, float *hidden, int32_t *argmax, float *margin, float *logits) {
+    const int V = c->m.vocab, d = c->m.d;
+    if (part_ld % 4 == 0 && V % 4 == 0) hipLaunchKernelGGL(argmax_kernel<true>, dim3(M), dim3(1024), 0, s, part, part_ld, V, x, gain, hidden, d, c->m.rms_eps, argmax, margin, logits);
+    else                                hipLaunchKernelGGL(argmax_kernel<false>, dim3(M), dim3(1024), 0, s, part, part_ld, V, x, gain, hidden, d, c->m.rms_eps, argmax, margin, logits);
     HYDRA_LAUNCH_CHECK("argmax_kernel");
     return HYDRA_OK;
 }

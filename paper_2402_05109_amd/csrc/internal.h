@@ -142,6 +142,15 @@ void layers_mega_info(const hydra_ctx *c, int B, int64_t *out);
 int launch_layers_mega(hydra_ctx *c, hipStream_t s, int B, char *mega, const int32_t *seq_len, const hydra_kv *kv, int32_t *flags,
                        LayersMegaIO *io, bool launch);
 
+// fp32 family: products with what stands in front of and behind them (f32_family.hip)
+int launch_gemm_f32(hydra_ctx *c, hipStream_t s, const float *X, const float *W, float *part, int M, int N, int K);
+int launch_f32_norm_gemm(hydra_ctx *c, hipStream_t s, const float *x, const float *gain, const float *W, float *part, int M, int N);
+int launch_f32_add(hydra_ctx *c, hipStream_t s, const float *X, const float *W, float *x, int M, int K);
+int launch_f32_bias_silu(hydra_ctx *c, hipStream_t s, const float *X, const float *W, int M, int K, const float *bias, float *z, bool residual, float *out);
+int launch_f32_swiglu(hydra_ctx *c, hipStream_t s, const float *x, const float *gain, const float *W, float *act, int M);
+int launch_f32_qkv_rope(hydra_ctx *c, hipStream_t s, const float *x, const float *gain, const float *W, int M, int layer, const int32_t *seq_len,
+                        const hydra_kv *kv, float *qbuf, int32_t *flags);
+
 // packing (arena loads)
 int launch_pack_matrix(hydra_ctx *c, hipStream_t s, const void *src, void *dst, int N, int K,
                        int tile_off, int tile_stride, int rows_per_band, int col_off, int bands_per_head);
@@ -156,19 +165,16 @@ int launch_prefix_select(hydra_ctx *c, hipStream_t s, int B, const float *x, con
                          int32_t *seq_len, float *h_out);
 struct VerifyArgs;
 int launch_embed(hydra_ctx *c, hipStream_t s, const int32_t *tokens, float *x, int M, int32_t *flags);
-int launch_rmsnorm(hydra_ctx *c, hipStream_t s, float *x, const float *part, int S, int part_ld, size_t part_split_stride,
-                   const float *gain, void *x_out, int M, float *hidden_out);
 int launch_rope_append(hydra_ctx *c, hipStream_t s, const float *part, int S, int part_ld, size_t split_stride,
                        RowScale rs, int B, int layer, const int32_t *seq_len, const hydra_kv *kv, void *qbuf,
                        int32_t *flags);
 int launch_attention(hydra_ctx *c, hipStream_t s, int B, int layer, const void *qbuf, const int32_t *seq_len,
                      const hydra_kv *kv, float *apart, int units, void *x_out, float *plain_out, int32_t *flags);
-int launch_silu_mul(hydra_ctx *c, hipStream_t s, const float *part, int S, int part_ld, size_t split_stride,
-                    void *x_out, int M);
 int launch_gemm_top2(hydra_ctx *c, hipStream_t s, const void *X, const void *W, int M, int N, int K, float *cand, int Mpad, int *fused);
 int launch_argmax_bands(hydra_ctx *c, hipStream_t s, const float *cand, int bands, int Mpad, RowScale rs, int M, int32_t *argmax,
                         float *margin);
-int launch_argmax(hydra_ctx *c, hipStream_t s, const float *part, int S, int part_ld, size_t split_stride, int M, int32_t *argmax, float *margin, float *logits);
+// fp32 family, behind the LM head's product: greedy token and margin, the logits, and the final hidden states
+int launch_argmax(hydra_ctx *c, hipStream_t s, const float *part, int part_ld, int M, const float *x, const float *gain, float *hidden, int32_t *argmax, float *margin, float *logits);
 // LM head of the 16-bit family behind its GEMM: logits, greedy token and margin, and the final hidden states.  cand: 512 bytes per row
 int launch_lm_tail(hydra_ctx *c, hipStream_t s, const float *part, int S, int part_ld, size_t split_stride, RowScale rs, int M, void *cand,
                    const float *x, const float *gain, float *hidden, int32_t *argmax, float *margin, float *logits);

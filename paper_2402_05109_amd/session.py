@@ -307,24 +307,45 @@ class Session:
         return self.host_len
 
     def generate(self, n_new: int, name: str = "main", max_steps: Optional[int] = None):
-        """Runs steps until every row has >= n_new tokens.  Returns (tokens per row, n_acc per step)."""
-        self.ctx(name)
+        """Runs steps until every row has >= n_new tokens.  Returns (tokens per row, n_acc per step).
+
+        fp32 models (a step is a few dozen launches of microseconds, as long on the host as on the GPU): while a further step is
+        needed whatever the one before it accepts, it is enqueued before that one's result is waited for."""
+        ctx = self.ctx(name)
         o = self._out[name]
         out = [[] for _ in range(self.B)]
         accs = []
         steps = 0
         # what a step is read back for goes to pinned memory in four copies behind one wait, instead of a wait per tensor
         src = (o.tree_tokens, o.path, o.n_acc, self.seq_len)
-        host = [torch.empty(t.shape, dtype=t.dtype, pin_memory=True) for t in src]
-        while min(len(t) for t in out) < n_new and (max_steps is None or steps < max_steps):
-            self.step(name)
-            for h, t in zip(host, src):
-                h.copy_(t, non_blocking=True)
-            torch.cuda.current_stream().synchronize()
-            tt, pa, na, lens = (h.tolist() for h in host)
+        host = [[torch.empty(t.shape, dtype=t.dtype, pin_memory=True) for t in src] for _ in range(2)]
+        done = [torch.cuda.Event(), torch.cuda.Event()]
+        ahead = 2 if self.dtype_code == hb.HYDRA_F32 else 1
+        most = ctx.depth + 1                          # tokens that a step can add to a row
+        unread: List[int] = []                        # buffers of the steps that are enqueued and not read back yet
+
+        def wanted() -> bool:
+            if min(len(t) for t in out) + len(unread) * most >= n_new or (max_steps is not None and steps >= max_steps):
+                return False
+            # the length is an upper bound while a result is outstanding: where only that bound is refused, the result comes first
+            return not unread or (self.host_len + ctx.T <= self.max_pages * 16 and self.host_len + most <= self._max_pos)
+
+        while True:
+            while len(unread) < ahead and wanted():
+                k = steps % 2
+                self.step(name)
+                for h, t in zip(host[k], src):
+                    h.copy_(t, non_blocking=True)
+                done[k].record()
+                unread.append(k)
+                steps += 1
+            if not unread:
+                break
+            k = unread.pop(0)
+            done[k].synchronize()
+            tt, pa, na, lens = (h.tolist() for h in host[k])
             for b in range(self.B):
                 out[b] += [tt[b][pa[b][j]] for j in range(na[b])]
             accs.append(na)
-            self._set_len(max(lens))
-            steps += 1
+            self._set_len(max(lens) + len(unread) * most)
         return [t[:n_new] for t in out], accs

@@ -12,7 +12,7 @@ CSRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "libhydra.so")
 OBJ_DIR = os.path.join(HERE, "_build")
 
-SOURCES = ["api.hip", "glue.hip", "draft_accept.hip", "f32_family.hip", "bf16_gemm.hip", "bf16_gemm_tile.hip", "bf16_attn.hip", "bf16_layers.hip"]
+SOURCES = ["api.hip", "glue.hip", "draft_accept.hip", "f32_family.hip", "bf16_gemm.hip", "bf16_gemm_tile.hip", "bf16_gemm_halves.hip", "bf16_attn.hip", "bf16_layers.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          # the first kernel arguments come in scalar registers with the launch instead of by a load that everything waits for:

@@ -128,7 +128,10 @@ int launch_tile(hydra_ctx *c, hipStream_t s, const void *X, const void *W, int M
         case TILE_256x160: launch_shape<Tile256x160>(grid, s, g, epi, e0, e1); break;
         case TILE_256x128: launch_shape<Tile256x128>(grid, s, g, epi, e0, e1); break;
         case TILE_128x192: launch_shape<Tile128x192>(grid, s, g, epi, e0, e1); break;
-        case TILE_128x128: launch_shape<Tile128x128>(grid, s, g, epi, e0, e1); break;
+        case TILE_128x128:
+            if (g.gz > 1) launch_tile_halves(grid, s, g, epi, e0, e1);       // bf16_gemm_halves.hip
+            else          launch_shape<Tile128x128>(grid, s, g, epi, e0, e1);
+            break;
         default:           launch_shape<Tile128x96>(grid, s, g, epi, e0, e1); break;
     }
     HYDRA_LAUNCH_CHECK("gemm_tile_kernel");
@@ -157,6 +160,7 @@ int gemm_tile_max_dynamic_lds() {
     hipError_t e = tile_attr_all<EpiPlain>();
     if (e == hipSuccess) e = tile_attr_all<EpiResidStaged>();
     if (e == hipSuccess) e = tile_attr_all<EpiSilu>();
+    if (e == hipSuccess) e = tile_halves_attr();
     if (e != hipSuccess) return hip_fail(e, "hipFuncSetAttribute(gemm_tile_kernel)");
     return HYDRA_OK;
 }

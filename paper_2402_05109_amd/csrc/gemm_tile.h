@@ -28,15 +28,23 @@
 
 namespace hydra {
 
-template <int WM_, int WN_, int MB_, int NT_, int SLOTS_>
+// KG: groups of WM x WN waves that take the k-steps of a slot in turn (1, or U with one k-step each)
+template <int WM_, int WN_, int MB_, int NT_, int SLOTS_, int KG_ = 1>
 struct TileShape {
-    static constexpr int WM = WM_, WN = WN_, MB = MB_, NT = NT_, SLOTS = SLOTS_, U = 2;
-    static constexpr int WAVES = WM * WN, XB = MB * WM, WB = NT * WN, PER_STEP = XB + WB, PER_SLOT = U * PER_STEP;
+    static constexpr int WM = WM_, WN = WN_, MB = MB_, NT = NT_, SLOTS = SLOTS_, U = 2, KG = KG_;
+    static constexpr int WAVES = WM * WN * KG, XB = MB * WM, WB = NT * WN, PER_STEP = XB + WB, PER_SLOT = U * PER_STEP;
     static constexpr int SHARE = (PER_SLOT + WAVES - 1) / WAVES;                    // tiles of a slot that each wave fetches
     static constexpr int TABLE_FLOATS = 11 * GemmTile<MB, NT, XB>::ROWS;            // in front of the slots: see GemmTile
     static constexpr size_t LDS = (size_t)TABLE_FLOATS * 4 + (size_t)SLOTS * PER_SLOT * 1024;
+    static_assert(KG == 1 || (KG == U && MB % KG == 0), "a group finishes its share of the row blocks");
+    static_assert(KG == 1 || (size_t)WAVES * (GEMM_LDS_STAGE_WAVE * 4 + MB / KG * NT * 4096) <= (size_t)SLOTS * PER_SLOT * 1024, "LDS of the exchange");
     static_assert(SLOTS >= 3 && LDS <= 160 * 1024 && (size_t)WAVES * GEMM_LDS_STAGE_WAVE * 4 <= (size_t)SLOTS * PER_SLOT * 1024, "LDS");
 };
+
+// the 128 x 128 tile of several row groups (bf16_gemm_halves.hip)
+template <class Epilogue>
+void launch_tile_halves(dim3 grid, hipStream_t s, const GemmGeom &g, const Epilogue &epi, hipEvent_t e0, hipEvent_t e1);
+hipError_t tile_halves_attr();
 
 // one KiB: lane l's 16 bytes at src go to LDS byte address dst + 16 l
 __device__ __forceinline__ void tile_dma(const u32x4_t *src, uint32_t dst) {
@@ -59,7 +67,8 @@ __global__ __launch_bounds__(S::WAVES * 64) void gemm_tile_kernel(GemmGeom g, Ep
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     int bx, by, bz;
     if (!gemm_block(g, bx, by, bz)) return;
-    const int wm = wave / S::WN, wn = wave % S::WN;
+    constexpr int KG = S::KG;
+    const int kg = wave / (S::WM * S::WN), wm = wave / S::WN % S::WM, wn = wave % S::WN;
     GemmTile<MB, NT, XB> t;
     t.tile0 = bx * WB + wn * NT;
     t.wg_mb0 = bz * XB;
@@ -121,7 +130,29 @@ __global__ __launch_bounds__(S::WAVES * 64) void gemm_tile_kernel(GemmGeom g, Ep
     int slot = 0;
     auto sweep = [&](auto LIVE) {
         constexpr bool on = decltype(LIVE)::value;
-        if constexpr (on) read(0, 0, 0);
+        auto multiply = [&](int p) {
+#pragma unroll
+            for (int a = 0; a < MB; ++a)
+#pragma unroll
+                for (int i = 0; i < NT; ++i)
+                    acc[a][i] = HYDRA_MFMA16(__builtin_bit_cast(a16x8_t, fx[p][a]), __builtin_bit_cast(a16x8_t, fw[p][i]), acc[a][i]);
+        };
+        if constexpr (on) read(0, kg, 0);
+        // KG == U: this group's k-step of slot j, out of register set p; its reads may be under way, those of slot j - 1 are done
+        auto one = [&](int j, int p) {
+            const int next = slot + 1 == SLOTS ? 0 : slot + 1, prev = slot == 0 ? SLOTS - 1 : slot - 1;
+            wait_loads_and_reads<(SLOTS - 3) * SHARE, MB + NT>();
+            meet();
+            request(j + SLOTS - 1, prev);
+            if constexpr (on) read(next, kg, p ^ 1);
+            if constexpr (on) multiply(p);
+            slot = next;
+        };
+        if constexpr (KG > 1) {
+            for (int j = 0; j + 1 < nblk; j += 2) { one(j, 0); one(j + 1, 1); }
+            if (nblk & 1) one(nblk - 1, 0);
+            return;
+        }
         for (int j = 0; j < nblk; ++j) {
             const int next = slot + 1 == SLOTS ? 0 : slot + 1, prev = slot == 0 ? SLOTS - 1 : slot - 1;
 #pragma unroll
@@ -134,13 +165,7 @@ __global__ __launch_bounds__(S::WAVES * 64) void gemm_tile_kernel(GemmGeom g, Ep
                 } else {
                     if constexpr (on) read(slot, u + 1, (u + 1) & 1);
                 }
-                if constexpr (on) {
-#pragma unroll
-                    for (int a = 0; a < MB; ++a)
-#pragma unroll
-                        for (int i = 0; i < NT; ++i)
-                            acc[a][i] = HYDRA_MFMA16(__builtin_bit_cast(a16x8_t, fx[u & 1][a]), __builtin_bit_cast(a16x8_t, fw[u & 1][i]), acc[a][i]);
-                }
+                if constexpr (on) multiply(u & 1);
             }
             slot = next;
         }
@@ -151,6 +176,34 @@ __global__ __launch_bounds__(S::WAVES * 64) void gemm_tile_kernel(GemmGeom g, Ep
     wait_loads<0>();                                   // nothing may land in the slots any more: the epilogue stages there
     epi.before_barrier(carry, t, g);
     __syncthreads();
+    if constexpr (KG > 1) {
+        // each group finishes half of the row blocks: the other half of its sums goes to the wave of the same tile in the other group
+        constexpr int HB = MB / KG;
+        f32x4_t *give = reinterpret_cast<f32x4_t *>(t.stage + S::WAVES * GEMM_LDS_STAGE_WAVE) + lane;
+        const int peer = wave ^ (S::WM * S::WN);
+        if (live)
+            static_for<HB * NT>([&](auto J) {
+                constexpr int b = decltype(J)::value / NT, i = decltype(J)::value % NT;
+                const f32x16_t out = kg == 0 ? acc[HB + b][i] : acc[b][i];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) give[((wave * HB * NT + decltype(J)::value) * 4 + q) * 64] = f32x4_t{out[4 * q], out[4 * q + 1], out[4 * q + 2], out[4 * q + 3]};
+            });
+        __syncthreads();
+        if (!live) return;
+        epi.begin(t, g);
+        static_for<HB * NT>([&](auto J) {
+            constexpr int b = decltype(J)::value / NT, i = decltype(J)::value % NT;
+            f32x16_t own = kg == 0 ? acc[b][i] : acc[HB + b][i];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const f32x4_t got = give[((peer * HB * NT + decltype(J)::value) * 4 + q) * 64];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) own[4 * q + e] += got[e];
+            }
+            epi.tile(own, kg * HB + b, i, t, g);
+        });
+        return;
+    }
     if (!live) return;
     epi.begin(t, g);
     static_for<MB * NT>([&](auto J) {

@@ -292,6 +292,15 @@ int kv_compact(hydra_ctx *ctx, void *stream, int B,
                const int32_t *last_node, const float *hidden, const hydra_kv *kv,
                int32_t *seq_len, float *h_last, int32_t *root, int32_t *kv_index);
 
+/* K and V of the B * T tree nodes in their cache slots, exactly as
+ * tree_verify_forward leaves them, and none of its other results: for the
+ * chunks of a prompt whose hidden states and next tokens nobody reads.  What the
+ * last layer computes behind its K and V, the final norm and the LM head are not run
+ * (and report no device flags).  Arguments as there. */
+int hydra_prefill_chunk(hydra_ctx *ctx, void *stream, int B, void *ws,
+                        const int32_t *tree_tokens, const int32_t *seq_len,
+                        const hydra_kv *kv);
+
 /* Section 3.1 item 3 and the appendix paragraph "Hydra-specific prefix
  * attention" (Hydra++): an extra decoder layer over the verified sequence,
  * queried once per decoding step, whose output at the last verified token the

@@ -24,7 +24,7 @@ E_INVALID_ARG, E_SHAPE, E_CAPACITY, E_UNSUPPORTED, E_HIP, E_STATE = -1, -2, -3, 
 
 EXPORTS = ["hydra_create", "hydra_destroy", "hydra_last_error", "hydra_weights_bytes", "hydra_bind_weights",
            "hydra_load_tensor", "hydra_workspace_bytes", "hydra_read_flags", "hydra_draft_tree",
-           "tree_verify_forward", "tree_attention", "accept_greedy", "accept_typical", "accept_typical_static", "kv_compact", "hydra_prefix_attention", "hydra_tree_depth",
+           "tree_verify_forward", "tree_attention", "accept_greedy", "accept_typical", "accept_typical_static", "kv_compact", "hydra_prefill_chunk", "hydra_prefix_attention", "hydra_tree_depth",
            "hydra_kv_write", "hydra_kv_read", "hydra_profile_begin", "hydra_profile_end", "hydra_layer_kernel_info"]
 
 
@@ -70,6 +70,7 @@ def _load() -> C.CDLL:
     lib.hydra_read_flags.argtypes = [vp, vp, C.POINTER(C.c_int32)]
     lib.hydra_draft_tree.argtypes = [vp, vp, i32, vp, vp, vp, vp]
     lib.tree_verify_forward.argtypes = [vp, vp, i32, vp, vp, vp, C.POINTER(KVDesc), vp, vp, vp, vp]
+    lib.hydra_prefill_chunk.argtypes = [vp, vp, i32, vp, vp, vp, C.POINTER(KVDesc)]
     lib.tree_attention.argtypes = [vp, vp, i32, i32, vp, vp, vp, C.POINTER(KVDesc), vp]
     lib.accept_greedy.argtypes = [vp, vp, i32, vp, vp, vp, vp, vp, vp]
     lib.accept_typical.argtypes = [vp, vp, i32, vp, vp, vp, C.c_float, C.c_float, C.c_float, vp, vp, vp, vp, vp]
@@ -186,6 +187,11 @@ class Hydra:
                                         _ptr(seq_len, torch.int32, "seq_len"), C.byref(d),
                                         _ptr(hidden, torch.float32, "hidden"), _ptr(argmax, torch.int32, "argmax"),
                                         _ptr(margin, torch.float32, "margin"), _ptr(logits, torch.float32, "logits")))
+
+    def hydra_prefill_chunk(self, B, ws, tree_tokens, seq_len, kv: KV) -> None:
+        d = kv.desc()
+        _check(_lib.hydra_prefill_chunk(self._h, _stream(), B, _ptr(ws, torch.uint8, "ws"), _ptr(tree_tokens, torch.int32, "tree_tokens"),
+                                        _ptr(seq_len, torch.int32, "seq_len"), C.byref(d)))
 
     def tree_attention(self, B, layer, ws, q, seq_len, kv: KV, out) -> None:
         d = kv.desc()

@@ -215,19 +215,28 @@ class Session:
         B, L = prompts.shape
         assert B == self.B
         prompts = prompts.to(self.dev, torch.int32)
+        chunks = [min(self.prefill_chunk, L - pos) for pos in range(0, L, self.prefill_chunk)]
+        # Of a chunk whose outputs a later chunk of the same length writes again, only K and V are computed: nothing else of it can
+        # be read once the call is over.  Not where the prefix layer reads every chunk's hidden states, and not where the prompt
+        # does not fit (the chunks in front of the one that is refused then keep their outputs and the state behind them).
+        kv_only = not self.prefix and self.host_len + L <= min(self.max_pages * 16, self._max_pos)
+        last = {n: i for i, n in enumerate(chunks)}
         pos = 0
-        while pos < L:
-            n = min(self.prefill_chunk, L - pos)
+        for i, n in enumerate(chunks):
             name = f"chain{n}"
             c = self.ctx(name)
             o = self._out[name]
             o.tree_tokens.copy_(prompts[:, pos:pos + n])
             self._hint(n)
-            c.tree_verify_forward(B, self.ws, o.tree_tokens, self.seq_len, self.kv, o.hidden, o.argmax, o.margin, o.logits)
-            o.n_acc.fill_(n)
-            o.path.copy_(torch.arange(n, dtype=torch.int32, device=self.dev).expand(B, n))
-            o.last_node.fill_(n - 1)
-            o.next_root.copy_(o.argmax[:, n - 1])
+            if i == chunks.index(n):                  # the same for every chunk of this length
+                o.n_acc.fill_(n)
+                o.path.copy_(torch.arange(n, dtype=torch.int32, device=self.dev).expand(B, n))
+                o.last_node.fill_(n - 1)
+            if kv_only and i < last[n]:
+                c.hydra_prefill_chunk(B, self.ws, o.tree_tokens, self.seq_len, self.kv)
+            else:
+                c.tree_verify_forward(B, self.ws, o.tree_tokens, self.seq_len, self.kv, o.hidden, o.argmax, o.margin, o.logits)
+                o.next_root.copy_(o.argmax[:, n - 1])
             c.kv_compact(B, o.n_acc, o.path, o.next_root, o.last_node, o.hidden, self.kv, self.seq_len, self.h_last,
                          self.root, o.kv_index)
             if self.prefix:

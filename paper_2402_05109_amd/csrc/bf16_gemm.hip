@@ -164,13 +164,13 @@ static void launch_one(dim3 grid, dim3 block, size_t lds, hipStream_t s, const G
     constexpr int MAXT = (MB * NT >= 6) ? 256 : 512;
     if constexpr (MB == 4) {                       // several row groups exist only with four row blocks per workgroup
         if (g.gz > 1) {
-            if (e0) hipExtLaunchKernelGGL((gemm_bf16_kernel<MB, NT, MAXT, Epi, true>), grid, block, lds, s, e0, e1, 0, g, epi);
-            else    hipLaunchKernelGGL((gemm_bf16_kernel<MB, NT, MAXT, Epi, true>), grid, block, lds, s, g, epi);
+            if (e0) hipExtLaunchKernelGGL((gemm_bf16_kernel<MB, NT, MAXT, Epi, true>), grid, block, lds, s, e0, e1, 0, GEMM_GEOM_ARGS(g), epi);
+            else    hipLaunchKernelGGL((gemm_bf16_kernel<MB, NT, MAXT, Epi, true>), grid, block, lds, s, GEMM_GEOM_ARGS(g), epi);
             return;
         }
     }
-    if (e0) hipExtLaunchKernelGGL((gemm_bf16_kernel<MB, NT, MAXT, Epi>), grid, block, lds, s, e0, e1, 0, g, epi);
-    else    hipLaunchKernelGGL((gemm_bf16_kernel<MB, NT, MAXT, Epi>), grid, block, lds, s, g, epi);
+    if (e0) hipExtLaunchKernelGGL((gemm_bf16_kernel<MB, NT, MAXT, Epi>), grid, block, lds, s, e0, e1, 0, GEMM_GEOM_ARGS(g), epi);
+    else    hipLaunchKernelGGL((gemm_bf16_kernel<MB, NT, MAXT, Epi>), grid, block, lds, s, GEMM_GEOM_ARGS(g), epi);
 }
 
 template <class Epi>
@@ -215,11 +215,11 @@ static int launch_bf16(hydra_ctx *c, hipStream_t s, const void *X, const void *W
         if constexpr (std::is_same<Epi, EpiTop2>::value) {           // never planned for this epilogue (launch_gemm_top2): no such kernel is built
             return fail(HYDRA_E_UNSUPPORTED, "gemm: the band-wise top-2 epilogue has no shared-X kernel");
         } else if (p.shared_x == 8) {
-            if (e0) hipExtLaunchKernelGGL((gemm_bf16_sharedx_kernel<4, 2, 8, Epi>), grid, block, lds, s, e0, e1, 0, g, epi);
-            else    hipLaunchKernelGGL((gemm_bf16_sharedx_kernel<4, 2, 8, Epi>), grid, block, lds, s, g, epi);
+            if (e0) hipExtLaunchKernelGGL((gemm_bf16_sharedx_kernel<4, 2, 8, Epi>), grid, block, lds, s, e0, e1, 0, GEMM_GEOM_ARGS(g), epi);
+            else    hipLaunchKernelGGL((gemm_bf16_sharedx_kernel<4, 2, 8, Epi>), grid, block, lds, s, GEMM_GEOM_ARGS(g), epi);
         } else {
-            if (e0) hipExtLaunchKernelGGL((gemm_bf16_sharedx_kernel<4, 2, 4, Epi>), grid, block, lds, s, e0, e1, 0, g, epi);
-            else    hipLaunchKernelGGL((gemm_bf16_sharedx_kernel<4, 2, 4, Epi>), grid, block, lds, s, g, epi);
+            if (e0) hipExtLaunchKernelGGL((gemm_bf16_sharedx_kernel<4, 2, 4, Epi>), grid, block, lds, s, e0, e1, 0, GEMM_GEOM_ARGS(g), epi);
+            else    hipLaunchKernelGGL((gemm_bf16_sharedx_kernel<4, 2, 4, Epi>), grid, block, lds, s, GEMM_GEOM_ARGS(g), epi);
         }
     } else if constexpr (NT_SET == NT_TWO) {
         switch (key) {

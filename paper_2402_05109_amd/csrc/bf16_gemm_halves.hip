@@ -20,8 +20,8 @@ typedef TileShape<2, 2, 2, 2, 8, 2> Tile128x128Halves;
 template <class Epi>
 void launch_tile_halves(dim3 grid, hipStream_t s, const GemmGeom &g, const Epi &epi, hipEvent_t e0, hipEvent_t e1) {
     typedef Tile128x128Halves S;
-    if (e0) hipExtLaunchKernelGGL((gemm_tile_kernel<S, Epi>), grid, dim3(S::WAVES * 64), S::LDS, s, e0, e1, 0, g, epi);
-    else    hipLaunchKernelGGL((gemm_tile_kernel<S, Epi>), grid, dim3(S::WAVES * 64), S::LDS, s, g, epi);
+    if (e0) hipExtLaunchKernelGGL((gemm_tile_kernel<S, Epi>), grid, dim3(S::WAVES * 64), S::LDS, s, e0, e1, 0, GEMM_GEOM_ARGS(g), epi);
+    else    hipLaunchKernelGGL((gemm_tile_kernel<S, Epi>), grid, dim3(S::WAVES * 64), S::LDS, s, GEMM_GEOM_ARGS(g), epi);
 }
 template void launch_tile_halves<EpiPlain>(dim3, hipStream_t, const GemmGeom &, const EpiPlain &, hipEvent_t, hipEvent_t);
 template void launch_tile_halves<EpiResidStaged>(dim3, hipStream_t, const GemmGeom &, const EpiResidStaged &, hipEvent_t, hipEvent_t);

@@ -106,8 +106,8 @@ bool plan_tile(int M, int N, int K, int kind, bool forced, GemmPlan *p) {
 
 template <class S, class Epi>
 static void launch_shape(dim3 grid, hipStream_t s, const GemmGeom &g, const Epi &epi, hipEvent_t e0, hipEvent_t e1) {
-    if (e0) hipExtLaunchKernelGGL((gemm_tile_kernel<S, Epi>), grid, dim3(S::WAVES * 64), S::LDS, s, e0, e1, 0, g, epi);
-    else    hipLaunchKernelGGL((gemm_tile_kernel<S, Epi>), grid, dim3(S::WAVES * 64), S::LDS, s, g, epi);
+    if (e0) hipExtLaunchKernelGGL((gemm_tile_kernel<S, Epi>), grid, dim3(S::WAVES * 64), S::LDS, s, e0, e1, 0, GEMM_GEOM_ARGS(g), epi);
+    else    hipLaunchKernelGGL((gemm_tile_kernel<S, Epi>), grid, dim3(S::WAVES * 64), S::LDS, s, GEMM_GEOM_ARGS(g), epi);
 }
 
 template <class Epi>

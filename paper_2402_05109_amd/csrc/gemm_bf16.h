@@ -59,6 +59,13 @@ struct GemmGeom {
     int gx, gy, gz; // gz > 1 (several row groups): the grid is one-dimensional and gemm_block() maps it onto (gx, gy, gz)
 };
 
+// As kernel parameters one by one: the launch brings the first 16 words of scalars and pointers in registers (a struct it does
+// not), so the first weights are requested without a load of arguments in front of them (0.3 us of every GEMM: 129 of them, 7B
+// verification 3664 -> 3625 us).
+#define GEMM_GEOM_PARAMS const u32x4_t *gX, const u32x4_t *gW, int gM, int gNTiles, int gKT, int gkpw, int gNW, int gKW, int ggx, int ggy, int ggz
+#define GEMM_GEOM_OF_PARAMS (GemmGeom{gX, gW, gM, gNTiles, gKT, gkpw, gNW, gKW, ggx, ggy, ggz})
+#define GEMM_GEOM_ARGS(g) (g).X, (g).W, (g).M, (g).NTiles, (g).KT, (g).kpw, (g).NW, (g).KW, (g).gx, (g).gy, (g).gz
+
 // Which (band group, K split, row group) a workgroup takes.  With several row groups the workgroups that stream the
 // same weight bands should meet in one L2: workgroups are handed to the 8 XCDs in turn, so workgroup i runs on XCD
 // i % 8, and the row groups of one (band group, split) take consecutive places on one XCD.  The grid is rounded up
@@ -292,7 +299,8 @@ __device__ __forceinline__ void gemm_bf16_body(const GemmGeom &g, const Epilogue
 
 
 template <int MB, int NT, int MAXT, class Epilogue, bool ROWGROUPS = false, int GEMM_U = GemmU<MB, NT>::value>
-__global__ __launch_bounds__(MAXT) void gemm_bf16_kernel(GemmGeom g, Epilogue epi) {
+__global__ __launch_bounds__(MAXT) void gemm_bf16_kernel(GEMM_GEOM_PARAMS, Epilogue epi) {
+    const GemmGeom g = GEMM_GEOM_OF_PARAMS;
     extern __shared__ float red[];                 // [scratch] + [KW][NW][MB*NT][16][64]
     if constexpr (Epilogue::EXTRA_BLOCKS) {        // workgroups behind the last band group: side work of the epilogue's choosing
         const int wgs = ((g.NTiles + NT - 1) / NT + g.NW - 1) / g.NW;
@@ -316,7 +324,8 @@ __global__ __launch_bounds__(MAXT) void gemm_bf16_kernel(GemmGeom g, Epilogue ep
 // is unconditional (blocks past the end re-read the last one and their MFMAs are skipped), so waits are exact and
 // every wave meets the same number of barriers.
 template <int MB, int NT, int NWT, class Epilogue, int GEMM_U = 4>
-__global__ __launch_bounds__(NWT * 64) void gemm_bf16_sharedx_kernel(GemmGeom g, Epilogue epi) {
+__global__ __launch_bounds__(NWT * 64) void gemm_bf16_sharedx_kernel(GEMM_GEOM_PARAMS, Epilogue epi) {
+    const GemmGeom g = GEMM_GEOM_OF_PARAMS;
     extern __shared__ float red[];                 // [scratch] + 2 x [GEMM_U][MB] X tiles of 1 KiB
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     int bx, by, bz;

@@ -59,7 +59,8 @@ template <int N, int L> __device__ __forceinline__ void wait_loads_and_reads() {
 }
 
 template <class S, class Epilogue>
-__global__ __launch_bounds__(S::WAVES * 64) void gemm_tile_kernel(GemmGeom g, Epilogue epi) {
+__global__ __launch_bounds__(S::WAVES * 64) void gemm_tile_kernel(GEMM_GEOM_PARAMS, Epilogue epi) {
+    const GemmGeom g = GEMM_GEOM_OF_PARAMS;
     static_assert(!Epilogue::PAIRED, "the waves' tiles need not hold whole band pairs");
     constexpr int MB = S::MB, NT = S::NT, XB = S::XB, WB = S::WB, U = S::U, SLOTS = S::SLOTS, SHARE = S::SHARE;
     extern __shared__ float lds[];                     // [tables] + SLOTS x [U][XB + WB] tiles of 1 KiB

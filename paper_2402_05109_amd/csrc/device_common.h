@@ -102,18 +102,6 @@ __device__ __forceinline__ int checked_page(int page, int n_pages, int32_t *flag
     return page;
 }
 
-// ---- wave reductions (64 lanes) ------------------------------------------------
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
-}
-__device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
-    return v;
-}
-
 // A value of the lower and one of the upper half-wave, lane by lane, in both halves: one vector instruction where a shuffle by 32
 // lanes goes through LDS.
 struct HalfWaves { float lo, hi; };
@@ -121,6 +109,24 @@ __device__ __forceinline__ HalfWaves half_waves(float v) {
     const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
     return HalfWaves{__uint_as_float(r[0]), __uint_as_float(r[1])};
 }
+
+// ---- wave reductions (64 lanes)
+// A butterfly over lane distances 32, 16, 8, 4, 2, 1 in vector instructions: half-waves and rows of 16 lanes are swapped, inside a row
+// the lanes are rotated (behind the step over 2 n lanes the values repeat every 2 n, so a rotation by n is an exchange over n).
+// The same pairs in the same order as six shuffles through LDS, so the same bits, without their latency.
+template <class Op>
+__device__ __forceinline__ float wave_butterfly(float v, Op op) {
+    const HalfWaves h = half_waves(v);
+    v = op(h.lo, h.hi);
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = op(__uint_as_float(r[0]), __uint_as_float(r[1]));
+    v = op(v, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x128, 0xf, 0xf, false)));      // row_ror:8
+    v = op(v, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x124, 0xf, 0xf, false)));      // row_ror:4
+    v = op(v, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x122, 0xf, 0xf, false)));      // row_ror:2
+    return op(v, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x121, 0xf, 0xf, false)));   // row_ror:1
+}
+__device__ __forceinline__ float wave_sum(float v) { return wave_butterfly(v, [](float a, float b) { return a + b; }); }
+__device__ __forceinline__ float wave_max(float v) { return wave_butterfly(v, [](float a, float b) { return fmaxf(a, b); }); }
 
 // sum of S split-K partial results of one output element
 // Four partials per memory round trip: the loads of a group are unconditional (surplus ones re-read the last split), so

@@ -163,12 +163,12 @@ __device__ __forceinline__ Cand wave_best(Cand c) {
 
 // Top-k of a logits row in two kernels.  One workgroup on 32000 logits is bound by its own instruction issue (every
 // wave rescans its registers once per extracted entry, and the waves of a workgroup share four SIMDs), so the row is
-// cut into chunks of 1024 ids, one single-wave workgroup each, spread over the chip: lane l holds ids
+// cut into chunks of 1024 ids, one workgroup of four waves each, spread over the chip: lane l of a wave holds four ids
 // base + l, base + 64 + l, ... as monotone keys (order_key; key 0 is below every real key and marks an absent or
-// already extracted entry), and k rounds leave the chunk's k best, in order, as (key, id) pairs.  The second kernel,
-// one wave per row, picks the k best of those at most 32 * k survivors in the same (value descending, id
+// already extracted entry), and k rounds leave the wave's k best, in order, as (key, id) pairs.  The second kernel,
+// one wave per row, picks the k best of the at most 32 * k survivors of the chunks in the same (value descending, id
 // ascending) order.
-enum { TOPK_CHUNK = 1024, TOPK_PER_LANE = 16, TOPK_MAX_CHUNKS = 32 };
+enum { TOPK_CHUNK = 1024, TOPK_MAX_CHUNKS = 32 };
 
 // lane's share of a chunk: ids base + i * 64 + lane
 template <int N>
@@ -202,25 +202,13 @@ __device__ __forceinline__ void topk_rounds(uint32_t (&key)[N], int k, int base,
     }
 }
 
-__global__ __launch_bounds__(64) void topk_chunk_kernel(const float *part, int S, int part_ld, size_t split_stride, int V,
-                                                         const TreeDev *tree, int ne, int expand_off, uint2 *surv) {
-    const int r = blockIdx.y, chunk = blockIdx.x, lane = threadIdx.x;
-    const int base = chunk * TOPK_CHUNK;
-    // the logits first: their addresses need nothing from the tree tables, whose dependent lookups follow
-    uint32_t key[TOPK_PER_LANE];
-    topk_load(key, part, S, split_stride, (size_t)r * part_ld, base, V, lane);
-    const int k = tree->expand_k[expand_off + r % ne];
-    topk_rounds(key, k, base, lane, surv + ((size_t)r * gridDim.x + chunk) * HYDRA_MAX_TOPK);
-}
-
 // The k best of the entries that a wave's lanes hold, without k rounds (the second kernel): any entry among them is at least as large as the
 // k-th largest of the 64 lane maxima, so the lanes rank their maxima against each other (64 scalar broadcasts), drop
 // everything below that bound, put what is left (a little over k entries) one per lane through LDS and rank those the same
 // way; ranks follow the order, ids break ties, so nothing has to be extracted in turn.  More than 64 entries at or above the
-// bound (many equal logits) go back to k rounds of a maximum over the wave, as do one or two children: rounds cost 0.9 us each
-// where ranking costs 1.4 in all (one row, V = 1000: 2.7 / 3.5 / 4.4 us for 1 / 2 / 3 children against 3.9 / 3.9 / 4.0).  With
-// rounds only the merge took 7.4 us per head (7B, up to 10 children), so 5.6; in the first kernel, whose ids are implied by the slot and whose rounds are therefore
-// half as long, it loses (10.4 against 9.6 us).
+// bound (many equal logits) go back to k rounds of a maximum over the wave, as do one or two children: a round over sixteen
+// entries to a lane costs 0.9 us where ranking costs 1.4 in all.  topk_merge_kernel with rounds only took 7.4 us per head (7B, up
+// to 10 children), ranking sixteen entries to a lane 5.8, and 4.8 now that a lane holds no more than half the children.
 
 // key[i] (0: no entry) with id[i]; put(t, key, id) is called for t < k by one lane each: key 0 and id ~0 past the last entry.
 // list: 64 entries of LDS.
@@ -277,6 +265,33 @@ __device__ __forceinline__ void wave_top_k(uint32_t (&key)[N], const uint32_t (&
     }
 }
 
+// A chunk of 1024 ids: four waves find the k best of 256 each (four entries to a lane: rescanning them is what a round costs), the
+// first one picks from those.  One wave with sixteen entries to a lane took 10.4 us a launch (7B, up to 10 children), this 6.9.
+__global__ __launch_bounds__(TOPK_CHUNK / 4) void topk_chunk_kernel(const float *part, int S, int part_ld, size_t split_stride, int V,
+                                                                     const TreeDev *tree, int ne, int expand_off, uint2 *surv) {
+    constexpr int WAVES = TOPK_CHUNK / 256;
+    __shared__ uint2 best[WAVES * HYDRA_MAX_TOPK];
+    __shared__ uint2 list[64];
+    const int r = blockIdx.y, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int base = blockIdx.x * TOPK_CHUNK + wave * 256;
+    // the logits first: their addresses need nothing from the tree tables, whose dependent lookups follow
+    uint32_t key[4];
+    topk_load(key, part, S, split_stride, (size_t)r * part_ld, base, V, lane);
+    const int k = tree->expand_k[expand_off + r % ne];
+    topk_rounds(key, k, base, lane, best + wave * k);
+    __syncthreads();
+    if (wave > 0) return;
+    uint2 *out = surv + ((size_t)r * gridDim.x + blockIdx.x) * HYDRA_MAX_TOPK;
+    uint32_t mk[WAVES * HYDRA_MAX_TOPK / 64], mi[WAVES * HYDRA_MAX_TOPK / 64];
+#pragma unroll
+    for (int i = 0; i < WAVES * HYDRA_MAX_TOPK / 64; ++i) {
+        const int q = i * 64 + lane;
+        const uint2 e = q < WAVES * k ? best[q] : make_uint2(0u, 0xffffffffu);
+        mk[i] = e.x; mi[i] = e.y;
+    }
+    wave_top_k(mk, mi, k, list, lane, [&](int t, uint32_t kk, uint32_t ii) { out[t] = make_uint2(kk, ii); });
+}
+
 __global__ __launch_bounds__(64) void topk_merge_kernel(const uint2 *surv, int chunks, const TreeDev *tree, int ne,
                                                          int expand_off, int32_t *tree_tokens) {
     __shared__ uint2 list[64];
@@ -284,20 +299,24 @@ __global__ __launch_bounds__(64) void topk_merge_kernel(const uint2 *surv, int c
     const int b = r / ne, j = r - b * ne;
     const int k = tree->expand_k[expand_off + j];
     const int first = tree->expand_first[expand_off + j];
-    const uint2 *in = surv + (size_t)r * chunks * HYDRA_MAX_TOPK;
-    // chunks * k survivors, at most 32 * 32: lane holds up to 16 of them
-    uint32_t mk[16], mi[16];
+    // two lanes to a chunk (at most 32 of them), every other of its survivors each: an address without a division, and no more
+    // entries per lane than half the children
+    const uint2 *in = surv + ((size_t)r * chunks + (lane >> 1)) * HYDRA_MAX_TOPK;
+    int32_t *out = tree_tokens + (size_t)b * tree->T + first;
+    auto merge = [&](auto N) {
+        uint32_t mk[decltype(N)::value], mi[decltype(N)::value];
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-        const int q = i * 64 + lane;                  // survivor index: chunk = q / k, rank = q % k
-        mk[i] = 0u; mi[i] = 0xffffffffu;
-        if (q < chunks * k) {
-            const uint2 e = in[(size_t)(q / k) * HYDRA_MAX_TOPK + (q % k)];
+        for (int i = 0; i < decltype(N)::value; ++i) {
+            const int q = 2 * i + (lane & 1);
+            uint2 e = make_uint2(0u, 0xffffffffu);
+            if (q < k && (lane >> 1) < chunks) e = in[q];
             mk[i] = e.x; mi[i] = e.y;
         }
-    }
-    int32_t *out = tree_tokens + (size_t)b * tree->T + first;
-    wave_top_k(mk, mi, k, list, lane, [&](int t, uint32_t, uint32_t ii) { out[t] = (int32_t)ii; });
+        wave_top_k(mk, mi, k, list, lane, [&](int t, uint32_t, uint32_t ii) { out[t] = (int32_t)ii; });
+    };
+    if (k <= 4) merge(std::integral_constant<int, 2>{});
+    else if (k <= 12) merge(std::integral_constant<int, 6>{});
+    else merge(std::integral_constant<int, HYDRA_MAX_TOPK / 2>{});
 }
 
 // Small vocabularies: both kernels in one, a wave per 256 ids (four to a lane: rescanning the lane's entries is what a round
@@ -374,7 +393,7 @@ int launch_topk(hydra_ctx *c, hipStream_t s, const float *part, int S, int part_
         else            hipLaunchKernelGGL(topk_row_kernel<TOPK_ROW_WAVES>, dim3(rows), dim3(64 * waves), 0, s, part, S, part_ld, split_stride, c->m.vocab, tree_dev(c), ne, eoff, tree_tokens);
         HYDRA_LAUNCH_CHECK("topk_row_kernel");
     } else if (chunks <= TOPK_MAX_CHUNKS) {
-        hipLaunchKernelGGL(topk_chunk_kernel, dim3(chunks, rows), dim3(64), 0, s, part, S, part_ld, split_stride, c->m.vocab, tree_dev(c), ne, eoff, (uint2 *)scratch);
+        hipLaunchKernelGGL(topk_chunk_kernel, dim3(chunks, rows), dim3(TOPK_CHUNK / 4), 0, s, part, S, part_ld, split_stride, c->m.vocab, tree_dev(c), ne, eoff, (uint2 *)scratch);
         HYDRA_LAUNCH_CHECK("topk_chunk_kernel");
         hipLaunchKernelGGL(topk_merge_kernel, dim3(rows), dim3(64), 0, s, (const uint2 *)scratch, chunks, tree_dev(c), ne, eoff, tree_tokens);
         HYDRA_LAUNCH_CHECK("topk_merge_kernel");

@@ -73,10 +73,10 @@ def test_draft_and_verify(H, Dh, F, V, T, B, lens, mlp, medusa):
             assert max_rel(got[:, 1].reshape(T, -1), caches[b].V[l, lens[b]:lens[b] + T].reshape(T, -1)) <= TOL
 
 
-@pytest.mark.parametrize("V", [2, 64, 300, 1024, 3000])
-def test_topk_of_equal_logits_takes_the_lowest_ids(V):
+@pytest.mark.parametrize("V,most", [(2, 20), (64, 20), (300, 32), (1024, 1), (3000, 32), (4097, 32), (5000, 12), (5000, 2), (32768, 32)])
+def test_topk_of_equal_logits_takes_the_lowest_ids(V, most):
     """All weights of the vocabulary projection are zero: every logit is equal and the children are ids 0, 1, 2, ..."""
-    k = min(V, 20)
+    k = min(V, most)
     cfg = small_shape(d=64, NL=1, H=1, Dh=64, F=16, V=V, K=1, T=k + 1)
     W = make_weights(cfg)
     W["heads.1.wout"] = torch.zeros_like(W["heads.1.wout"])

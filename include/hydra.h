@@ -292,11 +292,10 @@ int kv_compact(hydra_ctx *ctx, void *stream, int B,
                const int32_t *last_node, const float *hidden, const hydra_kv *kv,
                int32_t *seq_len, float *h_last, int32_t *root, int32_t *kv_index);
 
-/* K and V of the B * T tree nodes in their cache slots, exactly as
- * tree_verify_forward leaves them, and none of its other results: for the
- * chunks of a prompt whose hidden states and next tokens nobody reads.  What the
- * last layer computes behind its K and V, the final norm and the LM head are not run
- * (and report no device flags).  Arguments as there. */
+/* The decoder layers of tree_verify_forward alone: K and V of the B * T tree
+ * nodes in their cache slots, exactly as it leaves them, and none of its other
+ * results; final norm, LM head and argmax are not run.  For the chunks of a prompt
+ * whose hidden states and next tokens nobody reads.  Arguments as there. */
 int hydra_prefill_chunk(hydra_ctx *ctx, void *stream, int B, void *ws,
                         const int32_t *tree_tokens, const int32_t *seq_len,
                         const hydra_kv *kv);

@@ -456,13 +456,10 @@ static int lm_head_tail(hydra_ctx *c, hipStream_t s, const float *x, const void 
     return launch_lm_tail(c, s, part, p.splits, ld_v, mp * ld_v, rs, M, cand, x, gain, hidden, argmax, margin, logits);
 }
 
-// How far a forward pass goes: to K and V of the last layer, to the residual stream behind it (left in the workspace's x), or through
-// final RMSNorm, LM head and argmax (the verify step).
-enum ForwardEnd { END_AT_KV, END_AT_LAYERS, END_AT_LM_HEAD };
-
-// The decoder layers of the context over its B * T tree rows.
+// The decoder layers of the context over its B * T tree rows.  lm_tail: final RMSNorm, LM head, argmax (the
+// verify step); otherwise the residual stream after the last layer is left in the workspace's x.
 static int forward_layers(hydra_ctx *c, hipStream_t s, int B, void *ws, const RowSource &src, const int32_t *seq_len,
-                          const hydra_kv *kv, ForwardEnd end, float *hidden, int32_t *argmax, float *margin, float *logits) {
+                          const hydra_kv *kv, bool lm_tail, float *hidden, int32_t *argmax, float *margin, float *logits) {
     int rc;
     const WsLayout w = ws_layout(c, B);
     char *W = (char *)ws, *A = c->arena;
@@ -470,7 +467,6 @@ static int forward_layers(hydra_ctx *c, hipStream_t s, int B, void *ws, const Ro
     void *xa = W + w.xa, *xb = W + w.xb, *qbuf = W + w.qbuf;
     int32_t *flags = flags_ptr(c);
     const int d = c->m.d, F = c->m.ffn, V = c->m.vocab, M = B * c->tree.T;
-    const bool lm_tail = end == END_AT_LM_HEAD;
     if (c->bf16) {
         // Fused flow.  The residual epilogues leave x, xg = half(x * gain of the next norm) and per-band sums of
         // squares; the 1/rms factor of each RMSNorm is applied by the consumer of the following GEMM.
@@ -493,7 +489,6 @@ static int forward_layers(hydra_ctx *c, hipStream_t s, int B, void *ws, const Ro
             const LayerOff &o = c->layer[l];
             const float *next_gain = (const float *)(A + (l + 1 < c->m.n_layers ? c->layer[l + 1].attn_norm : c->off_final_norm));
             if ((rc = launch_gemm_qkv_rope(c, s, xa, A + o.wqkv, M, rs, l, seq_len, kv, qbuf, part, flags))) return rc;
-            if (end == END_AT_KV && l + 1 == c->m.n_layers) return HYDRA_OK;
             if ((rc = launch_attention(c, s, B, l, qbuf, seq_len, kv, apart, w.attn_units, xb, nullptr, flags))) return rc;
             if ((rc = launch_gemm_resid(c, s, xb, A + o.wo, M, d, d, x, (const float *)(A + o.ffn_norm), xa, ss, Mpad, part, &rs.nb))) return rc;
             if ((rc = launch_gemm_silu(c, s, xa, A + o.wgu, M, F, d, ss, rs.nb, Mpad, xb))) return rc;
@@ -508,7 +503,6 @@ static int forward_layers(hydra_ctx *c, hipStream_t s, int B, void *ws, const Ro
         const LayerOff &o = c->layer[l];
         auto weights = [&](size_t off) { return (const float *)(A + off); };
         if ((rc = launch_f32_qkv_rope(c, s, x, weights(o.attn_norm), weights(o.wqkv), M, l, seq_len, kv, (float *)qbuf, flags))) return rc;
-        if (end == END_AT_KV && l + 1 == c->m.n_layers) return HYDRA_OK;
         if ((rc = launch_attention(c, s, B, l, qbuf, seq_len, kv, apart, w.attn_units, xa, nullptr, flags))) return rc;
         if ((rc = launch_f32_add(c, s, (const float *)xa, weights(o.wo), x, M, d))) return rc;
         if ((rc = launch_f32_swiglu(c, s, x, weights(o.ffn_norm), weights(o.wgu), (float *)xb, M))) return rc;
@@ -535,7 +529,7 @@ int tree_verify_forward(hydra_ctx *c, void *stream, int B, void *ws, const int32
     if (!tree_tokens || !seq_len || !hidden || !argmax) return fail(HYDRA_E_INVALID_ARG, "tree_verify_forward: NULL argument");
     if ((rc = check_kv(c, kv))) return rc;
     const RowSource src = {tree_tokens, nullptr, 0, nullptr, nullptr};
-    return forward_layers(c, (hipStream_t)stream, B, ws, src, seq_len, kv, END_AT_LM_HEAD, hidden, argmax, margin, logits);
+    return forward_layers(c, (hipStream_t)stream, B, ws, src, seq_len, kv, true, hidden, argmax, margin, logits);
 }
 
 int hydra_prefill_chunk(hydra_ctx *c, void *stream, int B, void *ws, const int32_t *tree_tokens, const int32_t *seq_len, const hydra_kv *kv) {
@@ -544,7 +538,7 @@ int hydra_prefill_chunk(hydra_ctx *c, void *stream, int B, void *ws, const int32
     if (!tree_tokens || !seq_len) return fail(HYDRA_E_INVALID_ARG, "hydra_prefill_chunk: NULL argument");
     if ((rc = check_kv(c, kv))) return rc;
     const RowSource src = {tree_tokens, nullptr, 0, nullptr, nullptr};
-    return forward_layers(c, (hipStream_t)stream, B, ws, src, seq_len, kv, END_AT_KV, nullptr, nullptr, nullptr, nullptr);
+    return forward_layers(c, (hipStream_t)stream, B, ws, src, seq_len, kv, false, nullptr, nullptr, nullptr, nullptr);
 }
 
 // ---------------------------------------------------------------------------
@@ -562,7 +556,7 @@ int hydra_prefix_attention(hydra_ctx *c, void *stream, int B, void *ws, const fl
     if ((rc = check_kv(c, kv))) return rc;
     hipStream_t s = (hipStream_t)stream;
     const RowSource src = {nullptr, hidden, T_src, path, n_acc};
-    if ((rc = forward_layers(c, s, B, ws, src, seq_len, kv, END_AT_LAYERS, nullptr, nullptr, nullptr, nullptr))) return rc;
+    if ((rc = forward_layers(c, s, B, ws, src, seq_len, kv, false, nullptr, nullptr, nullptr, nullptr))) return rc;
     const WsLayout w = ws_layout(c, B);
     return launch_prefix_select(c, s, B, (const float *)((char *)ws + w.x), n_acc, kv, seq_len, h_out);
 }

@@ -216,10 +216,10 @@ class Session:
         assert B == self.B
         prompts = prompts.to(self.dev, torch.int32)
         chunks = [min(self.prefill_chunk, L - pos) for pos in range(0, L, self.prefill_chunk)]
-        # Of a chunk whose outputs a later chunk of the same length writes again, only K and V are computed: nothing else of it can
-        # be read once the call is over.  Not where the prefix layer reads every chunk's hidden states, and not where the prompt
+        # A chunk whose outputs a later chunk of the same length writes again ends behind the decoder layers: no final norm, LM head and
+        # argmax, whose results nobody can read once the call is over.  Not where the prefix layer reads every chunk's hidden states, and not where the prompt
         # does not fit (the chunks in front of the one that is refused then keep their outputs and the state behind them).
-        kv_only = not self.prefix and self.host_len + L <= min(self.max_pages * 16, self._max_pos)
+        layers_only = not self.prefix and self.host_len + L <= min(self.max_pages * 16, self._max_pos)
         last = {n: i for i, n in enumerate(chunks)}
         pos = 0
         for i, n in enumerate(chunks):
@@ -232,7 +232,7 @@ class Session:
                 o.n_acc.fill_(n)
                 o.path.copy_(torch.arange(n, dtype=torch.int32, device=self.dev).expand(B, n))
                 o.last_node.fill_(n - 1)
-            if kv_only and i < last[n]:
+            if layers_only and i < last[n]:
                 c.hydra_prefill_chunk(B, self.ws, o.tree_tokens, self.seq_len, self.kv)
             else:
                 c.tree_verify_forward(B, self.ws, o.tree_tokens, self.seq_len, self.kv, o.hidden, o.argmax, o.margin, o.logits)

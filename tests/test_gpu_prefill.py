@@ -1,4 +1,4 @@
-"""Reading a prompt: chunks of which only K and V are computed leave the same cache, state and (for every chunk length) the
+"""Reading a prompt: chunks that end behind the decoder layers leave the same cache, state and (for every chunk length) the
 outputs of that length's last chunk as chunks that are computed whole."""
 import pytest
 import torch

@@ -58,6 +58,7 @@ __global__ __launch_bounds__(ATTN_WAVES * 64) void attn_bf16_kernel(
 // verification call of 32 layers 3769 -> 3687 us, one node behind 701 tokens 797 -> 775 (8 layers).
 template <int DH, int DS>
 struct ShortTile { u32x4_t k[DH / 16]; u32x4_t v[2][DH / 32 / DS]; };
+static constexpr float LOG2E = 1.44269504f;
 enum { ATTN_SHORT_TILES = 5 };                              // 32-key tiles per wave up to which the launch rule takes this kernel
 
 template <int DH, int DS, bool STREAM, bool PACKED>
@@ -247,10 +248,11 @@ __global__ __launch_bounds__(ATTN_WAVES * 64) void attn_short_kernel(
 // a second workgroup on the same bytes 62.9 -> 65.3.
 // NW waves split the keys: eight where the workgroups fit one round of the chip, four, two workgroups to a CU, beyond.
 //
-// Softmax in powers of two, with the scale folded into the exponent's multiply-add.  The maximum is followed exactly: a reference
-// that trails it by up to 2^8 saves most of the rescaling, but the largest probability is then no longer exactly one, and its
-// rounding to half tripled the error of sharp rows (5e-5 -> 1.6e-4 of the result's 2-norm); nothing is gained either, since the
-// loads alone take as long.
+// Softmax in powers of two: maxima of the unscaled scores, and the scale as a factor of the exponent 2^((s - max) c).  The largest
+// probability has to be exactly one, since the sums take it as it is and the products rounded to half.  With c in a multiply-add,
+// 2^(s c - max c), it was off by the rounding of max c: scores of 200 and more cost that much (64 queries behind 3900 keys, scores of
+// deviation 50 / 100: error 6.0e-6 / 1.03e-5 of the result's 2-norm, 3.3e-6 / 2.9e-6 now; the loop takes 0.5 to 2.5 % longer).  A reference that trails the maximum by up to 2^8 saves
+// most of the rescaling and costs far more (sharp rows 5e-5 -> 1.6e-4); nothing is gained either, since the loads alone take as long.
 template <int DH, int NW, bool STREAM>
 __global__ __launch_bounds__(NW * 64, 2) void attn_pair_kernel(
     const u32x4_t *__restrict__ qbuf, const a16_t *__restrict__ kpages, const a16_t *__restrict__ vpages,
@@ -327,7 +329,7 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_pair_kernel(
 #pragma unroll
             for (int v = 0; v < 16; ++v) o[q][dt][v] = 0.f;
     float m_run[2] = {-INFINITY, -INFINITY}, l_run[2] = {0.f, 0.f};
-    const float c = scale * 1.44269504f;
+    const float c = scale * LOG2E;
     // these have arrived: nothing in the loop is to wait for an ordinary load, which would be a wait for the DMA as well
     asm volatile("" : "+v"(pgs), "+v"(anc[0][0]), "+v"(anc[0][1]), "+v"(anc[1][0]), "+v"(anc[1][1]));
     if (mine_n > 0) { next_pages(0); request_k(); request_v(); }
@@ -365,10 +367,10 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_pair_kernel(
 #pragma unroll
             for (int v = 0; v < 16; ++v) cmax = fmaxf(cmax, sc[q][v]);
             const HalfWaves cm = half_waves(cmax);
-            cmax = fmaxf(cm.lo, cm.hi) * c;
+            cmax = fmaxf(cm.lo, cm.hi);
             if (__any(cmax > m_run[q])) {                                          // always on the first visible tile
                 const float m_new = fmaxf(m_run[q], cmax);
-                const float alpha = m_new == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_run[q] - m_new);
+                const float alpha = m_new == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((m_run[q] - m_new) * c);
                 m_run[q] = m_new;
                 l_run[q] *= alpha;
 #pragma unroll
@@ -380,7 +382,7 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_pair_kernel(
             float rs = 0.f;
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
-                const float p = __builtin_amdgcn_exp2f(fmaf(sc[q][v], c, -ref));   // 0 for masked keys
+                const float p = __builtin_amdgcn_exp2f((sc[q][v] - ref) * c);     // 0 for masked keys, exactly 1 for the largest
                 sc[q][v] = p;
                 rs += p;
             }
@@ -448,8 +450,8 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_pair_kernel(
         const float m_safe = m_tot == -INFINITY ? 0.f : m_tot;
         float l_tot = 0.f;
 #pragma unroll
-        for (int w = 0; w < NW; ++w) l_tot += __builtin_amdgcn_exp2f(mq[w * 64 + col] - m_safe) * mq[w * 64 + 32 + col];
-        const float f = __builtin_amdgcn_exp2f(m_run[q] - m_safe);
+        for (int w = 0; w < NW; ++w) l_tot += __builtin_amdgcn_exp2f((mq[w * 64 + col] - m_safe) * c) * mq[w * 64 + 32 + col];
+        const float f = __builtin_amdgcn_exp2f((m_run[q] - m_safe) * c);
         float *dst = ob + (size_t)wave * DT * 16 * 64 + lane;
 #pragma unroll
         for (int dt = 0; dt < DT; ++dt)
@@ -479,21 +481,22 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_pair_kernel(
                 }
             }
         }
-        if (key_wgs > 1 && wave == 0 && hl == 0) {           // attn_merge_kernel takes natural logarithms
-            rec[(size_t)Tq * DH + query] = m_tot * 0.693147181f;
+        if (key_wgs > 1 && wave == 0 && hl == 0) {
+            rec[(size_t)Tq * DH + query] = m_tot;
             rec[(size_t)Tq * DH + Tq + query] = l_tot;
         }
         if (q == 0) __syncthreads();                         // the second query tile's sums go where these were
     }
 }
 
-// out[b, n, h, :] = sum_u w_u O_u[n] / sum_u w_u l_u,  w_u = exp(m_u - max_u m_u).
+// out[b, n, h, :] = sum_u w_u O_u[n] / sum_u w_u l_u,  w_u = exp(m_u - max_u m_u), or 2^(c (m_u - max_u m_u)) where the records hold
+// unscaled maxima (RAW: attn_pair_kernel).
 // One workgroup per (row, head, 8 queries), one thread per (query, 4 dims); all loads of a thread are
 // independent of each other and of the row length, so they make one round trip.
 enum { MERGE_MAX_UNITS = 16 };
-template <bool PACKED>
+template <bool PACKED, bool RAW>
 __global__ __launch_bounds__(256) void attn_merge_kernel(const float *__restrict__ apart, const int32_t *__restrict__ seq_len,
-                                                          int T, int H, int Dh, int units, int max_pages, void *out) {
+                                                          int T, int H, int Dh, int units, int max_pages, float c, void *out) {
     const int h = blockIdx.y, b = blockIdx.z;
     const int per_q = Dh >> 2;                              // threads per query
     const int n = blockIdx.x * (256 / per_q) + threadIdx.x / per_q;
@@ -523,7 +526,7 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(const float *__restrict
     f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int u = 0; u < MERGE_MAX_UNITS; ++u) {
-        const float w = u < units ? __expf(mu[u] - mt) : 0.f;
+        const float w = u < units ? (RAW ? __builtin_amdgcn_exp2f((mu[u] - mt) * c) : __expf(mu[u] - mt)) : 0.f;
         den += w * lu[u];
         acc += ou[u] * w;
     }
@@ -651,8 +654,10 @@ int launch_attention(hydra_ctx *c, hipStream_t s, int B, int layer, const void *
     if (wgs > 1) {
         const int q_per_wg = 256 / (Dh / 4);
         dim3 mgrid(ceil_div(T, q_per_wg), H, B), mblock(256);
-        if (packed) hipLaunchKernelGGL(attn_merge_kernel<true>, mgrid, mblock, 0, s, apart, seq_len, T, H, Dh, wgs, kv->max_pages, out);
-        else        hipLaunchKernelGGL(attn_merge_kernel<false>, mgrid, mblock, 0, s, apart, seq_len, T, H, Dh, wgs, kv->max_pages, out);
+#define MERGE(Pv, RAWv) hipLaunchKernelGGL((attn_merge_kernel<Pv, RAWv>), mgrid, mblock, 0, s, apart, seq_len, T, H, Dh, wgs, kv->max_pages, scale * LOG2E, out)
+        if (QTtot > 1) { if (packed) MERGE(true, true); else MERGE(false, true); }
+        else           { if (packed) MERGE(true, false); else MERGE(false, false); }
+#undef MERGE
         HYDRA_LAUNCH_CHECK("attn_merge_kernel");
     }
     return HYDRA_OK;

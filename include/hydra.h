@@ -293,9 +293,12 @@ int kv_compact(hydra_ctx *ctx, void *stream, int B,
                int32_t *seq_len, float *h_last, int32_t *root, int32_t *kv_index);
 
 /* The decoder layers of tree_verify_forward alone: K and V of the B * T tree
- * nodes in their cache slots, exactly as it leaves them, and none of its other
- * results; final norm, LM head and argmax are not run.  For the chunks of a prompt
- * whose hidden states and next tokens nobody reads.  Arguments as there. */
+ * nodes in their cache slots, exactly as it leaves them (by the same kernels, whichever
+ * of them the options choose), and none of its other results; final norm, LM head
+ * and argmax are not run.  For the chunks of a prompt whose hidden states and next
+ * tokens nobody reads: a kv_compact behind it advances seq_len but takes h_last and
+ * root from outputs that this call has not written, so they mean nothing before a
+ * tree_verify_forward and kv_compact of a later chunk.  Arguments as there. */
 int hydra_prefill_chunk(hydra_ctx *ctx, void *stream, int B, void *ws,
                         const int32_t *tree_tokens, const int32_t *seq_len,
                         const hydra_kv *kv);

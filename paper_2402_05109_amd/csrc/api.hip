@@ -457,7 +457,8 @@ static int lm_head_tail(hydra_ctx *c, hipStream_t s, const float *x, const void 
 }
 
 // The decoder layers of the context over its B * T tree rows.  lm_tail: final RMSNorm, LM head, argmax (the
-// verify step); otherwise the residual stream after the last layer is left in the workspace's x.
+// verify step); otherwise the residual stream after the last layer is left in the workspace's x, unless the rows are tokens: those
+// take the same kernels with and without the tail, also the persistent layer kernel, which has a buffer of its own for it.
 static int forward_layers(hydra_ctx *c, hipStream_t s, int B, void *ws, const RowSource &src, const int32_t *seq_len,
                           const hydra_kv *kv, bool lm_tail, float *hidden, int32_t *argmax, float *margin, float *logits) {
     int rc;
@@ -474,12 +475,13 @@ static int forward_layers(hydra_ctx *c, hipStream_t s, int B, void *ws, const Ro
         const int Mpad = (int)align_up(std::max<size_t>(M, 1), 128);
         RowScale rs = {ss, 1, Mpad, d, c->m.rms_eps};        // rs.nb: rows of ss the last producer filled (1 = a complete sum per row)
         const float *gain0 = (const float *)(A + c->layer[0].attn_norm);
-        if (lm_tail && src.tokens && layers_mega_eligible(c, B, kv)) {
+        if (src.tokens && layers_mega_eligible(c, B, kv)) {
             // up to 64 rows and a bounded context: all layers in one persistent kernel (bf16_layers.hip)
             LayersMegaIO io;
             if ((rc = launch_layers_mega(c, s, B, W + w.mega, seq_len, kv, flags, &io, false))) return rc;
             if ((rc = launch_embed_prep(c, s, src.tokens, io.x_first, gain0, io.xg_first, io.ss_first, io.Mpad, M, flags))) return rc;
             if ((rc = launch_layers_mega(c, s, B, W + w.mega, seq_len, kv, flags, &io, true))) return rc;
+            if (!lm_tail) return HYDRA_OK;
             const RowScale rl = {io.ss_last, io.nb_last, io.Mpad, d, c->m.rms_eps};
             return lm_head_tail(c, s, io.x_last, io.xg_last, part, apart, M, rl, io.Mpad, hidden, argmax, margin, logits);
         }

@@ -67,3 +67,21 @@ def test_a_prompt_that_does_not_fit_leaves_the_chunks_in_front_of_it_whole():
         o = sess.out("chain16")
         got.append([t.clone() for t in (sess.k_pages, sess.v_pages, sess.seq_len, sess.h_last, sess.root, o.hidden, o.argmax)])
     assert all(torch.equal(a, b) for a, b in zip(*got))
+
+
+@pytest.mark.parametrize("NL,L,chunk,B", [(2, 75, 16, 2), (3, 200, 64, 1)])
+def test_prefill_equals_whole_chunks_with_the_layer_kernel(NL, L, chunk, B, monkeypatch):
+    """HYDRA_LAYER_KERNEL=1: chunks that end early take the persistent kernel where whole ones do (up to 64 rows behind cached tokens)."""
+    monkeypatch.setenv("HYDRA_LAYER_KERNEL", "1")
+    cfg = small_shape(d=256, NL=NL, H=2, Dh=128, F=384, V=1000, K=0, T=3, dtype="bf16")
+    W = make_weights(cfg, std=0.05)
+    prompts = torch.stack([uniform_tokens(9, b, L, cfg.V) for b in range(B)])
+    got = []
+    for fn in (lambda s: s.prefill(prompts), lambda s: _whole(s, prompts)):
+        sess = gpu_session(cfg, [-1, 0, 1], B, L + 8, W, prefill_chunk=chunk, page_perm_seed=4)
+        assert sess.ctx(f"chain{chunk}").layer_kernel_info(B)[0] == 1
+        fn(sess)
+        torch.cuda.synchronize()
+        assert sess.main.read_flags() == 0
+        got.append([t.clone() for t in (sess.k_pages, sess.v_pages, sess.seq_len, sess.h_last, sess.root)])
+    assert all(torch.equal(a, b) for a, b in zip(*got))

@@ -211,7 +211,8 @@ class Session:
     def prefill(self, prompts: torch.Tensor) -> None:
         """prompts: int32 [B, L] (same length for every row).  Causal chunks through
         tree_verify_forward with a chain tree; the state update is kv_compact with the
-        identity path."""
+        identity path.  Where an exception breaks the prompt off, seq_len, h_last and root are those behind the last chunk that was
+        computed whole (behind the text in front of the prompt if there is none)."""
         B, L = prompts.shape
         assert B == self.B
         prompts = prompts.to(self.dev, torch.int32)
@@ -222,27 +223,39 @@ class Session:
         layers_only = not self.prefix and self.host_len + L <= min(self.max_pages * 16, self._max_pos)
         last = {n: i for i, n in enumerate(chunks)}
         pos = 0
-        for i, n in enumerate(chunks):
-            name = f"chain{n}"
-            c = self.ctx(name)
-            o = self._out[name]
-            o.tree_tokens.copy_(prompts[:, pos:pos + n])
-            self._hint(n)
-            if i == chunks.index(n):                  # the same for every chunk of this length
-                o.n_acc.fill_(n)
-                o.path.copy_(torch.arange(n, dtype=torch.int32, device=self.dev).expand(B, n))
-                o.last_node.fill_(n - 1)
-            if layers_only and i < last[n]:
-                c.hydra_prefill_chunk(B, self.ws, o.tree_tokens, self.seq_len, self.kv)
-            else:
-                c.tree_verify_forward(B, self.ws, o.tree_tokens, self.seq_len, self.kv, o.hidden, o.argmax, o.margin, o.logits)
-                o.next_root.copy_(o.argmax[:, n - 1])
-            c.kv_compact(B, o.n_acc, o.path, o.next_root, o.last_node, o.hidden, self.kv, self.seq_len, self.h_last,
-                         self.root, o.kv_index)
-            if self.prefix:
-                self.prefix_attention(name)           # hint: still the length before this chunk
-            pos += n
-            self.host_len += n
+        behind = None                                 # seq_len and its bound behind the last chunk that h_last and root know of, if others followed
+        try:
+            for i, n in enumerate(chunks):
+                name = f"chain{n}"
+                c = self.ctx(name)
+                o = self._out[name]
+                o.tree_tokens.copy_(prompts[:, pos:pos + n])
+                self._hint(n)
+                if i == chunks.index(n):              # the same for every chunk of this length
+                    o.n_acc.fill_(n)
+                    o.path.copy_(torch.arange(n, dtype=torch.int32, device=self.dev).expand(B, n))
+                    o.last_node.fill_(n - 1)
+                h_last, root = self.h_last, self.root
+                if layers_only and i < last[n]:
+                    if behind is None:
+                        behind = self.seq_len.clone(), self.host_len
+                    h_last, root = torch.empty_like(h_last), torch.empty_like(root)       # of outputs that are not written
+                    c.hydra_prefill_chunk(B, self.ws, o.tree_tokens, self.seq_len, self.kv)
+                else:
+                    c.tree_verify_forward(B, self.ws, o.tree_tokens, self.seq_len, self.kv, o.hidden, o.argmax, o.margin, o.logits)
+                    o.next_root.copy_(o.argmax[:, n - 1])
+                c.kv_compact(B, o.n_acc, o.path, o.next_root, o.last_node, o.hidden, self.kv, self.seq_len, h_last, root, o.kv_index)
+                if h_last is self.h_last:
+                    behind = None
+                if self.prefix:
+                    self.prefix_attention(name)       # hint: still the length before this chunk
+                pos += n
+                self.host_len += n
+        except BaseException:
+            if behind is not None:                    # broken off: back to the text that h_last and root belong to
+                self.seq_len.copy_(behind[0])
+                self.host_len = behind[1]
+            raise
 
     def draft(self, name: str = "main") -> None:
         c, o = self.ctx(name), self._out[name]

@@ -85,3 +85,37 @@ def test_prefill_equals_whole_chunks_with_the_layer_kernel(NL, L, chunk, B, monk
         assert sess.main.read_flags() == 0
         got.append([t.clone() for t in (sess.k_pages, sess.v_pages, sess.seq_len, sess.h_last, sess.root)])
     assert all(torch.equal(a, b) for a, b in zip(*got))
+
+
+def test_a_prompt_that_is_broken_off_leaves_a_state_that_belongs_together():
+    """An exception in front of the third chunk, behind two that end early: seq_len, h_last and root are those behind the text before, and
+    reading the prompt again gives what it gives without the interruption."""
+    cfg = small_shape(d=256, NL=2, H=2, Dh=128, F=384, V=1000, K=0, T=3, dtype="bf16")
+    W = make_weights(cfg)
+    first, second = (uniform_tokens(9, i, n, cfg.V).reshape(1, -1) for i, n in ((0, 20), (1, 90)))
+    sessions = [gpu_session(cfg, [-1, 0, 1], 1, 128, W, prefill_chunk=16) for _ in range(2)]
+    for s in sessions:
+        s.prefill(first)
+    s = sessions[0]
+    state = [t.clone() for t in (s.seq_len, s.h_last, s.root)]
+    c, done = s.ctx("chain16"), []
+    early = c.hydra_prefill_chunk
+
+    def broken(*a):
+        if len(done) == 2:
+            raise KeyboardInterrupt
+        done.append(early(*a))
+
+    c.hydra_prefill_chunk = broken
+    with pytest.raises(KeyboardInterrupt):
+        s.prefill(second)
+    del c.hydra_prefill_chunk
+    torch.cuda.synchronize()
+    assert len(done) == 2 and s.host_len == 20
+    assert all(torch.equal(a, b) for a, b in zip(state, (s.seq_len, s.h_last, s.root)))
+    for s in sessions:
+        s.prefill(second)
+    torch.cuda.synchronize()
+    a, b = sessions
+    assert all(torch.equal(x, y) for x, y in zip((a.k_pages, a.v_pages, a.seq_len, a.h_last, a.root), (b.k_pages, b.v_pages, b.seq_len, b.h_last, b.root)))
+    assert a.main.read_flags() == 0 and a.host_len == b.host_len == 110

@@ -2,11 +2,11 @@
 // the other tiles in bf16_gemm_tile.hip).
 //
 // 128 x 128 of several row groups: four waves of 64 x 64 twice, one k-step of a slot each.  Of a k-step eight waves of 32 x 64 read
-// 24 KB of LDS for 16 multiplications, these 16 KB, and at that size the reads are the bound: O and down of 1024 rows (K = 4096 and
-// 11008) 91.5 -> 86 us on average, the whole call of 8 layers 4731 -> 4630; 256 x 6656 x 6656 42.4 -> 40.2.  Up to 128 rows HBM is the
-// bound, and a row group of 96 rows would multiply a whole row block for nothing (LM head 53 -> 66 us).  256 x 128 and 128 x 192
-// split the same way gain nothing; four waves of 64 x 64 alone are slower than eight of 32 x 64 (102 us), one wave to a SIMD
-// hides nothing.
+// 24 KB of LDS for 16 multiplications, these 16 KB, and from three row groups on the reads are the bound: down of 1024 rows (4096 x
+// 11008) 124.8 -> 116.4 us, O 60.6 -> 58.6; 480 rows of 6656 x 6656 84.8 -> 76.4.  With one or two row groups the weights' way from HBM is
+// the bound, and a row group of 96 rows multiplies a whole row block for nothing (LM head 53 -> 66 us); takes_halves() in
+// bf16_gemm_tile.hip has the measurements and the rule.  256 x 128 and 128 x 192 split the same way gain nothing; four waves of 64 x 64
+// alone are slower than eight of 32 x 64 (102 us), one wave to a SIMD hides nothing.
 #include <hip/hip_ext.h>
 
 #include "gemm_epilogues.h"

@@ -110,6 +110,22 @@ static void launch_shape(dim3 grid, hipStream_t s, const GemmGeom &g, const Epi 
     else    hipLaunchKernelGGL((gemm_tile_kernel<S, Epi>), grid, dim3(S::WAVES * 64), S::LDS, s, GEMM_GEOM_ARGS(g), epi);
 }
 
+// 128 x 128: does the kernel of bf16_gemm_halves.hip take it?  Where the reads of LDS are the bound: from three row groups on, with
+// enough workgroups that the chip is busy.  Both kernels over 2048 to 6656 columns, K from 1024 to 17920, 160 to 1024 rows (us):
+//   three and more row groups, 192 workgroups and more   1.5 to 15 % faster (4096 x 11008, 1024 rows 124.8 -> 116.4; 2048 x 5504, 384 rows
+//                                                        17.8 -> 17.0; 5120 x 17920, 288 rows 26.5 -> 25.7), 3 % slower at worst (4096 x 4096,
+//                                                        384 rows 23.7 -> 24.4)
+//   two row groups, where cold weights are the bound     1 to 20 % slower (4096 x 11008, 224 rows 32.8 -> 36.6; 6656 x 6656, 256 rows
+//                                                        37.2 -> 38.6; 5120 x 5504, 224 rows 23.1 -> 24.8)
+//   up to 112 workgroups                                 4 to 9 % slower (64 x 2048, 896 rows 6.0 -> 6.4)
+//   K split with every CU taken                          slower (2048 x 5504, 480 rows, 4 splits 19.4 -> 22.7)
+// Tests that name the tile get it for any number of row groups.
+static bool takes_halves(const GemmGeom &g) {
+    if (getenv("HYDRA_PLAN_TILE_ID")) return g.gz > 1;
+    const int wgs = g.gx * g.gy * g.gz;
+    return g.gz > 2 && wgs >= 160 && (g.gy == 1 || wgs < 256);
+}
+
 template <class Epi>
 int launch_tile(hydra_ctx *c, hipStream_t s, const void *X, const void *W, int M, int N, int K, const GemmPlan &p, const Epi &epi, hipEvent_t e0,
                 hipEvent_t e1) {
@@ -129,8 +145,8 @@ int launch_tile(hydra_ctx *c, hipStream_t s, const void *X, const void *W, int M
         case TILE_256x128: launch_shape<Tile256x128>(grid, s, g, epi, e0, e1); break;
         case TILE_128x192: launch_shape<Tile128x192>(grid, s, g, epi, e0, e1); break;
         case TILE_128x128:
-            if (g.gz > 1) launch_tile_halves(grid, s, g, epi, e0, e1);       // bf16_gemm_halves.hip
-            else          launch_shape<Tile128x128>(grid, s, g, epi, e0, e1);
+            if (takes_halves(g)) launch_tile_halves(grid, s, g, epi, e0, e1);
+            else                 launch_shape<Tile128x128>(grid, s, g, epi, e0, e1);
             break;
         default:           launch_shape<Tile128x96>(grid, s, g, epi, e0, e1); break;
     }

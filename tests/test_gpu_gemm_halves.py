@@ -43,6 +43,27 @@ def test_row_groups(d, F, T, B, splits, monkeypatch):
         assert max_rel(to_np(o.hidden[b]), hid) <= 2e-2 and max_rel(to_np(o.logits[b]), lg) <= 2e-2
 
 
+@pytest.mark.gpu
+@pytest.mark.parametrize("T,B", [(112, 2), (96, 3), (120, 4)])
+def test_row_groups_that_the_rule_chooses(T, B):
+    """2048 x 5504 without a named tile: two row groups (the kernel of eight waves side by side), three (192 workgroups of the halves), and
+    four with a workgroup on every CU."""
+    cfg = small_shape(d=2048, NL=1, H=16, Dh=128, F=5504, V=1003, K=0, T=T, dtype="bf16")
+    W = make_weights(cfg, gain_std=0.1, std=0.02)
+    parent = random_tree(T, 5, 7)
+    toks = torch.stack([uniform_tokens(31, b, T, cfg.V) for b in range(B)]).to(torch.int32)
+    sess = gpu_session(cfg, parent, B, 32, W, page_perm_seed=5, want_logits=True)
+    o = sess.out()
+    o.tree_tokens.copy_(toks)
+    sess.verify()
+    torch.cuda.synchronize()
+    assert sess.main.read_flags() == 0
+    m = oracle_model(cfg, W)
+    for b in sorted({0, B - 1}):
+        hid, lg = O.tree_verify(m, O.FlatCache(m, T), 0, O.Tree(parent), toks[b].tolist())[:2]
+        assert max_rel(to_np(o.hidden[b]), hid) <= 2e-2 and max_rel(to_np(o.logits[b]), lg) <= 2e-2
+
+
 def test_kernels_keep_everything_in_registers():
     cmd = [build_lib._hipcc(), *build_lib.FLAGS, "-c", os.path.join(build_lib.CSRC, "bf16_gemm_halves.hip"), "-o", os.devnull, "--cuda-device-only",
            "-Rpass-analysis=kernel-resource-usage"]

@@ -109,16 +109,17 @@ __device__ __forceinline__ void load_v_tile(KVTile<DH> &kv, const a16_t *vpages,
 // 8 * DH / 32 registers per lane off a kernel that sits at the limit of 256.  They lie in the space of the O merge
 // buffers (QW * DH * 64 bytes, never more than those), which are first written behind the barrier that follows the
 // key loops of all waves.
-template <int DH, bool PACKED, bool DEV, bool QLDS>
+template <int DH, int QW, bool PACKED, bool DEV, bool QLDS>
 __device__ __forceinline__ void attn_bf16_body(
     const u32x4_t *__restrict__ qbuf, const a16_t *__restrict__ kpages, const a16_t *__restrict__ vpages,
     const int32_t *__restrict__ page_table, int max_pages, int n_pages, int layer, const int32_t *__restrict__ seq_len,
-    const TreeDev *__restrict__ tree, int T, int H, int QW, int qsplit, float scale, float *__restrict__ apart, void *out,
+    const TreeDev *__restrict__ tree, int T, int H, int qsplit, float scale, float *__restrict__ apart, void *out,
     int32_t *flags, int bx, int nbx, int h, int b, float *lds, int tid) {
     constexpr int KS = DH / 16, DT = DH / 32;
-    const int lane = tid & 63, wave = tid >> 6;
+    constexpr bool STREAM = !DEV && QW == 1;               // with two query tiles to a workgroup two of its waves read the same bytes
+    const int lane = tid & 63, wave = QW > 1 ? __builtin_amdgcn_readfirstlane(tid >> 6) : tid >> 6;      // a scalar: two query tiles are at the limit of registers
     const int hl = lane >> 5, col = lane & 31;
-    const int KWV = ATTN_WAVES / QW;
+    constexpr int KWV = ATTN_WAVES / QW;
     const int qw = wave % QW, kwv = wave / QW;
     const int QTtot = (T + 31) >> 5;
     const int Tq = QTtot * 32;
@@ -179,8 +180,8 @@ __device__ __forceinline__ void attn_bf16_body(
         {
             const int p0 = checked_page(pg[0][0], n_pages, flags);
             const int p1 = (2 * unit + 1 < row_pages) ? checked_page(pg[0][1], n_pages, flags) : p0;
-            load_k_tile<DH, !DEV>(cur, kpages, p0, p1, layer, n_pages, H, h, lane);
-            load_v_tile<DH, !DEV>(cur, vpages, p0, p1, layer, n_pages, H, h, lane);
+            load_k_tile<DH, STREAM>(cur, kpages, p0, p1, layer, n_pages, H, h, lane);
+            load_v_tile<DH, STREAM>(cur, vpages, p0, p1, layer, n_pages, H, h, lane);
         }
         int it = 0;                                        // index of tile t among this wave's tiles
         for (int t = unit; t < n_tiles; t += units, ++it) {
@@ -199,8 +200,8 @@ __device__ __forceinline__ void attn_bf16_body(
                 p0 = checked_page(p0, n_pages, flags);                  // wave-uniform
                 p1 = checked_page(p1, n_pages, flags);
                 if (!DEV) {
-                    load_k_tile<DH, !DEV>(nxt, kpages, p0, p1, layer, n_pages, H, h, lane);
-                    load_v_tile<DH, !DEV>(nxt, vpages, p0, p1, layer, n_pages, H, h, lane);
+                    load_k_tile<DH, STREAM>(nxt, kpages, p0, p1, layer, n_pages, H, h, lane);
+                    load_v_tile<DH, STREAM>(nxt, vpages, p0, p1, layer, n_pages, H, h, lane);
                 }
             }
             const int slot0 = t * 32;
@@ -227,7 +228,7 @@ __device__ __forceinline__ void attn_bf16_body(
             for (int s = 0; s < KS; ++s)
                 sc = HYDRA_MFMA16(__builtin_bit_cast(a16x8_t, cur.k[s]), __builtin_bit_cast(a16x8_t, QLDS ? qlds[qoff + s * 64] : qreg[s]), sc);
             // the layer kernel, whose waves hold weights as well, has one tile's registers: the next K comes once K is used
-            if (DEV && more) load_k_tile<DH, !DEV>(cur, kpages, p0, p1, layer, n_pages, H, h, lane);
+            if (DEV && more) load_k_tile<DH, STREAM>(cur, kpages, p0, p1, layer, n_pages, H, h, lane);
             bool moved;
             const float alpha = softmax_tile(sc, scale, slot0 + 32 > L, slot0, L, anc0, anc1, hl, m_run, l_run, moved);
             // the accumulators are rescaled only where some query's maximum moved (a factor of one otherwise; the first tile
@@ -249,7 +250,7 @@ __device__ __forceinline__ void attn_bf16_body(
                 for (int dt = 0; dt < DT; ++dt)
                     o[dt] = HYDRA_MFMA16(__builtin_bit_cast(a16x8_t, cur.v[g][dt]), __builtin_bit_cast(a16x8_t, pb), o[dt]);
             }
-            if (DEV && more) load_v_tile<DH, !DEV>(cur, vpages, p0, p1, layer, n_pages, H, h, lane);
+            if (DEV && more) load_v_tile<DH, STREAM>(cur, vpages, p0, p1, layer, n_pages, H, h, lane);
             if (!DEV && more) cur = nxt;
         }
     }

@@ -21,8 +21,9 @@
 //     32-query tile and share of the head's dims; its 8 waves split the keys and
 //     the result goes straight out as the next GEMM's input: one kernel, no
 //     partial records;
-//   longer contexts, or more rows: attn_bf16_kernel up to 32 queries, attn_pair_kernel
-//     beyond (two query tiles to a wave).  The waves of a workgroup split the keys, and
+//   longer contexts, or more rows: attn_bf16_kernel up to 32 queries (and where its
+//     waves with a query tile each fill the chip better), attn_pair_kernel beyond (two
+//     query tiles to a wave).  The waves of a workgroup split the keys, and
 //     so do several workgroups per (b, h) while the chip has room; each of those leaves
 //     a (max, sum, O) record that attn_merge_kernel combines.
 #include <algorithm>
@@ -35,14 +36,15 @@ namespace hydra {
 
 typedef __attribute__((ext_vector_type(4))) float f32x4_t;
 
-template <int DH, bool PACKED>
+// QW: query tiles of a workgroup, one or two, each with 8 / QW waves that split the keys
+template <int DH, int QW, bool PACKED>
 __global__ __launch_bounds__(ATTN_WAVES * 64) void attn_bf16_kernel(
     const u32x4_t *__restrict__ qbuf, const a16_t *__restrict__ kpages, const a16_t *__restrict__ vpages,
     const int32_t *__restrict__ page_table, int max_pages, int n_pages, int layer, const int32_t *__restrict__ seq_len,
     const TreeDev *__restrict__ tree, int T, int H, float scale, float *__restrict__ apart, void *out, int32_t *flags) {
     extern __shared__ float lds[];
-    attn_bf16_body<DH, PACKED, false, true>(qbuf, kpages, vpages, page_table, max_pages, n_pages, layer, seq_len, tree, T, H, 1, 0,
-                                             scale, apart, out, flags, (int)blockIdx.x, (int)gridDim.x, (int)blockIdx.y, (int)blockIdx.z, lds, (int)threadIdx.x);
+    attn_bf16_body<DH, QW, PACKED, false, true>(qbuf, kpages, vpages, page_table, max_pages, n_pages, layer, seq_len, tree, T, H, 0,
+                                                scale, apart, out, flags, (int)blockIdx.x, (int)gridDim.x, (int)blockIdx.y, (int)blockIdx.z, lds, (int)threadIdx.x);
 }
 
 // Short contexts: a workgroup takes one 32-query tile of one (row, head) and 1 / DS of the head's dims; its eight waves split
@@ -562,8 +564,10 @@ static size_t attn_pair_lds_bytes(int Dh, int nw) { return ((size_t)2 * (Dh / 16
 int attn_max_dynamic_lds(hydra_ctx *c) {
     (void)c;
     hipError_t e = hipSuccess;
-#define ATTR(DHv, Pv) if (e == hipSuccess) e = hipFuncSetAttribute((const void *)attn_bf16_kernel<DHv, Pv>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024)
-    ATTR(128, true); ATTR(128, false); ATTR(64, true); ATTR(64, false);
+#define ATTR(DHv, QWv) \
+    if (e == hipSuccess) e = hipFuncSetAttribute((const void *)attn_bf16_kernel<DHv, QWv, true>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024); \
+    if (e == hipSuccess) e = hipFuncSetAttribute((const void *)attn_bf16_kernel<DHv, QWv, false>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024)
+    ATTR(128, 1); ATTR(128, 2); ATTR(64, 1); ATTR(64, 2);
 #undef ATTR
 #define ATTR(DHv, DSv, STv) \
     if (e == hipSuccess) e = hipFuncSetAttribute((const void *)attn_short_kernel<DHv, DSv, STv, true>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024); \
@@ -588,14 +592,12 @@ int launch_attention(hydra_ctx *c, hipStream_t s, int B, int layer, const void *
     const int QTtot = ceil_div(T, 32);
     const int len = kv->seq_len_hint > 0 ? kv->seq_len_hint : c->m.max_pos;
     const int tiles = ceil_div(len + T, 32);
-    // Short contexts: one workgroup per 32-query tile, its 8 waves split the keys (up to five 32-key tiles each) and
-    // the result goes straight out.  Longer ones: a CU streams at most ~45 GB/s, so the keys of one head are spread
-    // over several workgroups (two tiles per wave or more) whose partial records attn_merge_kernel combines.
     const float scale = 1.0f / sqrtf((float)Dh);
     void *out = x_out ? x_out : (void *)plain_out;
     const bool packed = x_out != nullptr;
-    // short contexts, while those workgroups fit one round of the chip (at batch 8 and 16 one workgroup per (row, head) that
-    // holds all query tiles and reads each K/V byte once measured 2-3 % faster on the whole verify step); see attn_short_kernel
+    // Short contexts (attn_short_kernel: up to five tiles per wave, the result goes straight out), while those workgroups fit one round of
+    // the chip (at batch 8 and 16 one workgroup per (row, head) that holds all query tiles and reads each K/V byte once measured
+    // 2-3 % faster on the whole verify step).
     if (tiles <= ATTN_WAVES * ATTN_SHORT_TILES && QTtot * H * B <= 256) {
         int ds = Dh / 32;
         while (ds > 1 && QTtot * H * B * ds > 256) ds >>= 1;
@@ -620,14 +622,27 @@ int launch_attention(hydra_ctx *c, hipStream_t s, int B, int layer, const void *
         HYDRA_LAUNCH_CHECK("attn_short_kernel");
         return HYDRA_OK;
     }
-    // Longer contexts, or more rows: several workgroups per head, but never more of them than one round of the chip: a workgroup
-    // holds a CU by itself (registers), so a second round only repeats the fixed cost of a workgroup (first round trips, LDS
-    // merge, partial record).  Measured best at about 200 workgroups in all: 7B at 2066 / 4114 keys 4.30 -> 4.01 / 4.63 -> 4.30 ms
-    // per verify.
-    // (two tiles per wave or more)
-    const int qgroups = (QTtot + 1) / 2, nw = QTtot > 1 && H * B * qgroups > 256 ? 4 : 8;
-    const int wgs = nw == 4 ? 1 : std::max(1, std::min({ceil_div(tiles, nw * 2), std::max(1, 208 / (H * B * qgroups)), units_max}));
-    if (QTtot > 1) {                                       // two query tiles to a wave
+    // Longer contexts, or more rows: a CU streams at most ~45 GB/s, so the keys of one head are spread over several workgroups, two tiles per
+    // wave or more, whose partial records attn_merge_kernel combines.  Never more of them than one round of the chip: a workgroup
+    // holds a CU by itself (registers), so a second round only repeats the fixed cost of a workgroup (first round trips, LDS merge,
+    // partial record).  Measured best at about 200 workgroups in all: 7B at 2066 / 4114 keys 4.30 -> 4.01 / 4.63 -> 4.30 ms per verify.
+    //
+    // More than 32 queries: two query tiles to a wave (attn_pair_kernel), eight waves to a workgroup, or four where two workgroups fit a
+    // CU and all have work (more groups than CUs).  With 33 to 64 queries in all it has half as many waves as tiles to hand
+    // out, which a single short row does not make up for (attention call in us, cold, 64 queries):
+    //   up to 52 tiles (1664 keys), eight waves on no more than half of the chip (a quarter with 64 dims): a wave per query tile, as
+    //     many waves again (attn_bf16_kernel with two tiles; 16 heads behind 1250 / 1500 keys 17.1 / 18.2 against 18.9 / 19.2, 32
+    //     heads 19.6 / 20.0 against 20.2 / 20.9, 40 heads behind 1250 20.6 against 21.1; beyond: 40 heads behind 1500 22.9 against 22.2,
+    //     32 heads behind 1600 22.1 against 20.8; 32 heads of 64 dims behind 1250 15.2 against 14.5)
+    //   more tiles, eight waves on less than half of the chip, 128 dims: twice the workgroups of four waves (16 heads behind 2100 / 3200
+    //     keys 20.4 / 20.6 -> 17.8 / 20.0; with 64 dims it gains nothing, 13.9 against 14.0)
+    const int qgroups = (QTtot + 1) / 2, hb = H * B * qgroups;
+    const int eight = hb * ceil_div(tiles, ATTN_WAVES * 2);          // workgroups of eight waves with two tiles each
+    const bool apart_tiles = QTtot == 2 && tiles <= 52 && eight <= Dh;
+    const bool pair = QTtot > 1 && !apart_tiles, few = QTtot == 2 && Dh == 128 && eight < 128;
+    const int nw = pair ? (hb > 256 || few ? 4 : 8) : apart_tiles ? ATTN_WAVES / 2 : ATTN_WAVES;       // waves that split a workgroup's keys
+    const int wgs = pair && hb > 256 ? 1 : std::max(1, std::min({ceil_div(tiles, nw * 2), std::max(1, 208 / hb), units_max}));
+    if (pair) {
         const dim3 pgrid(ceil_div(H * B, 8) * 8 * qgroups * wgs);
 #define PAIR(DHv, NWv, STv)                                                                                                                       \
     hipLaunchKernelGGL((attn_pair_kernel<DHv, NWv, STv>), pgrid, dim3(NWv * 64), attn_pair_lds_bytes(DHv, NWv), s, (const u32x4_t *)qbuf,          \
@@ -642,12 +657,14 @@ int launch_attention(hydra_ctx *c, hipStream_t s, int B, int layer, const void *
     } else {
         dim3 grid(wgs, H, B), block(ATTN_WAVES * 64);
         const size_t lds = attn_lds_bytes(Dh);
-#define ATTN_CASE(DHv, Pv)                                                                                           \
-        hipLaunchKernelGGL((attn_bf16_kernel<DHv, Pv>), grid, block, lds, s, (const u32x4_t *)qbuf,                       \
+#define ATTN_CASE(DHv, QWv, Pv)                                                                                      \
+        hipLaunchKernelGGL((attn_bf16_kernel<DHv, QWv, Pv>), grid, block, lds, s, (const u32x4_t *)qbuf,                       \
                            (const a16_t *)kv->k_pages, (const a16_t *)kv->v_pages, kv->page_table, kv->max_pages,      \
                            kv->n_pages, layer, seq_len, tree_dev(c), T, H, scale, apart, out, flags)
-        if (Dh == 128) { if (packed) ATTN_CASE(128, true); else ATTN_CASE(128, false); }
-        else           { if (packed) ATTN_CASE(64, true); else ATTN_CASE(64, false); }
+#define ATTN_QW(DHv, QWv) do { if (packed) ATTN_CASE(DHv, QWv, true); else ATTN_CASE(DHv, QWv, false); } while (0)
+        if (Dh == 128) { if (apart_tiles) ATTN_QW(128, 2); else ATTN_QW(128, 1); }
+        else           { if (apart_tiles) ATTN_QW(64, 2); else ATTN_QW(64, 1); }
+#undef ATTN_QW
 #undef ATTN_CASE
         HYDRA_LAUNCH_CHECK("attn_bf16_kernel");
     }
@@ -655,8 +672,8 @@ int launch_attention(hydra_ctx *c, hipStream_t s, int B, int layer, const void *
         const int q_per_wg = 256 / (Dh / 4);
         dim3 mgrid(ceil_div(T, q_per_wg), H, B), mblock(256);
 #define MERGE(Pv, RAWv) hipLaunchKernelGGL((attn_merge_kernel<Pv, RAWv>), mgrid, mblock, 0, s, apart, seq_len, T, H, Dh, wgs, kv->max_pages, scale * LOG2E, out)
-        if (QTtot > 1) { if (packed) MERGE(true, true); else MERGE(false, true); }
-        else           { if (packed) MERGE(true, false); else MERGE(false, false); }
+        if (pair) { if (packed) MERGE(true, true); else MERGE(false, true); }
+        else      { if (packed) MERGE(true, false); else MERGE(false, false); }
 #undef MERGE
         HYDRA_LAUNCH_CHECK("attn_merge_kernel");
     }

@@ -22,14 +22,18 @@ def _reference(q, keys, vals, seen):
 @pytest.mark.parametrize("Dh,H,B,T,waves,lens", [
     (128, 24, 11, 33, 4, (0, 1, 15, 31, 32, 33, 100, 127, 128, 200, 255)),     # more groups than CUs
     (64, 64, 5, 65, 4, (0, 16, 47, 300, 2200)),                                # two groups of query tiles, the second without a partner
-    (128, 4, 2, 40, 8, (1600, 1441)),                                          # keys split over workgroups
+    (128, 52, 1, 40, 8, (2100,)),                                              # keys split over workgroups
+    (128, 4, 2, 40, 4, (1700, 1441)),                                          # ... of four waves: with eight half of the chip would idle
     (64, 6, 1, 128, 8, (3000,)),
     (64, 64, 2, 34, 8, (8300, 5)),                                             # 33 tiles for the first waves, none for the others of row 1
 ])
 def test_two_query_tiles_per_wave(Dh, H, B, T, waves, lens):
     qgroups, L = (-(-T // 32) + 1) // 2, max(lens)
-    assert (4 if H * B * qgroups > 256 else 8) == waves
-    assert -(-(L + T) // 32) > 40 or -(-T // 32) * H * B > 256                 # else the kernel of short contexts takes it
+    tiles = -(-(L + T) // 32)
+    eight = H * B * qgroups * -(-tiles // 16)
+    assert (4 if H * B * qgroups > 256 or (T <= 64 and Dh == 128 and eight < 128) else 8) == waves
+    assert tiles > 40 or -(-T // 32) * H * B > 256                             # else the kernel of short contexts takes it
+    assert T > 64 or tiles > 52 or eight > Dh                                  # or the one with a wave per query tile
     parent = random_tree(T, 4, 6)
     cfg = small_shape(d=H * Dh, NL=1, H=H, Dh=Dh, F=128, V=64, K=0, T=T, dtype="bf16")
     sess = gpu_session(cfg, parent, B, L + T, make_weights(cfg), page_perm_seed=3)

@@ -179,9 +179,9 @@ __device__ __forceinline__ void topk_load(uint32_t (&key)[N], const float *part,
         key[i] = id < V ? order_key(part_sum(part, S, split_stride, row + id)) : 0u;
     }
 }
-// the chunk's k best, best first; key 0: the chunk ran out of entries
+// the k best of a wave's 64 N ids, best first, entry t at out[t * stride]; key 0: the wave ran out of entries
 template <int N>
-__device__ __forceinline__ void topk_rounds(uint32_t (&key)[N], int k, int base, int lane, uint2 *out) {
+__device__ __forceinline__ void topk_rounds(uint32_t (&key)[N], int k, int base, int lane, uint2 *out, int stride) {
     for (int t = 0; t < k; ++t) {
         // the lane's best: the first maximum in slot order is also its lowest id
         uint32_t bk = 0u, bs = 0u;
@@ -198,17 +198,17 @@ __device__ __forceinline__ void topk_rounds(uint32_t (&key)[N], int k, int base,
             for (int i = 0; i < N; ++i)
                 if ((uint32_t)i == slot && owner) key[i] = 0u;
         }
-        if (lane == 0) out[t] = make_uint2(kmax, idmin);
+        if (lane == 0) out[t * stride] = make_uint2(kmax, idmin);
     }
 }
 
-// The k best of the entries that a wave's lanes hold, without k rounds (the second kernel): any entry among them is at least as large as the
-// k-th largest of the 64 lane maxima, so the lanes rank their maxima against each other (64 scalar broadcasts), drop
+// The k best of the entries that a wave's lanes hold, without k rounds (the second step of every kernel here): any entry among them is at least
+// as large as the k-th largest of the 64 lane maxima, so the lanes rank their maxima against each other (64 scalar broadcasts), drop
 // everything below that bound, put what is left (a little over k entries) one per lane through LDS and rank those the same
-// way; ranks follow the order, ids break ties, so nothing has to be extracted in turn.  More than 64 entries at or above the
-// bound (many equal logits) go back to k rounds of a maximum over the wave, as do one or two children: a round over sixteen
-// entries to a lane costs 0.9 us where ranking costs 1.4 in all.  topk_merge_kernel with rounds only took 7.4 us per head (7B, up
-// to 10 children), ranking sixteen entries to a lane 5.8, and 4.8 now that a lane holds no more than half the children.
+// way; ranks follow the order, ids break ties, so nothing has to be extracted in turn.  The bound is as good as the maxima are: the
+// callers deal the sorted lists of their first step out so that the lanes hold the heads of all lists (a list per group of lanes,
+// its ranks in turn), not one rank of two lists each.  More than 64 entries at or above the bound (many equal logits) go back to k
+// rounds of a maximum over the wave, as do one or two children, where two rounds cost less than ranking.
 
 // key[i] (0: no entry) with id[i]; put(t, key, id) is called for t < k by one lane each: key 0 and id ~0 past the last entry.
 // list: 64 entries of LDS.
@@ -278,7 +278,7 @@ __global__ __launch_bounds__(TOPK_CHUNK / 4) void topk_chunk_kernel(const float 
     uint32_t key[4];
     topk_load(key, part, S, split_stride, (size_t)r * part_ld, base, V, lane);
     const int k = tree->expand_k[expand_off + r % ne];
-    topk_rounds(key, k, base, lane, best + wave * k);
+    topk_rounds(key, k, base, lane, best + wave, WAVES);
     __syncthreads();
     if (wave > 0) return;
     uint2 *out = surv + ((size_t)r * gridDim.x + blockIdx.x) * HYDRA_MAX_TOPK;
@@ -292,35 +292,39 @@ __global__ __launch_bounds__(TOPK_CHUNK / 4) void topk_chunk_kernel(const float 
     wave_top_k(mk, mi, k, list, lane, [&](int t, uint32_t kk, uint32_t ii) { out[t] = make_uint2(kk, ii); });
 }
 
-__global__ __launch_bounds__(64) void topk_merge_kernel(const uint2 *surv, int chunks, const TreeDev *tree, int ne,
+__global__ __launch_bounds__(64) void topk_merge_kernel(const uint2 *surv, int chunks, int share_log2, const TreeDev *tree, int ne,
                                                          int expand_off, int32_t *tree_tokens) {
     __shared__ uint2 list[64];
     const int r = blockIdx.x, lane = threadIdx.x;
     const int b = r / ne, j = r - b * ne;
     const int k = tree->expand_k[expand_off + j];
     const int first = tree->expand_first[expand_off + j];
-    // two lanes to a chunk (at most 32 of them), every other of its survivors each: an address without a division, and no more
-    // entries per lane than half the children
-    const uint2 *in = surv + ((size_t)r * chunks + (lane >> 1)) * HYDRA_MAX_TOPK;
+    // 64 lanes over the chunks, at most 32 of them: 1 << share_log2 lanes to a chunk, which take its survivors in turn: an address without a
+    // division, and no more entries per lane than there have to be.  (Two lanes to a chunk whatever their number: five chunks kept ten
+    // lanes busy, no bound came out of their maxima and 12 and more children went back to rounds: one row of 5000 logits, 16 / 32
+    // children, a draft of one head 31.3 / 48.0 us, 20.3 / 26.0 now.)
+    const int chunk = lane >> share_log2, part = lane & ((1 << share_log2) - 1);
+    const uint2 *in = surv + ((size_t)r * chunks + chunk) * HYDRA_MAX_TOPK;
     int32_t *out = tree_tokens + (size_t)b * tree->T + first;
     auto merge = [&](auto N) {
         uint32_t mk[decltype(N)::value], mi[decltype(N)::value];
 #pragma unroll
         for (int i = 0; i < decltype(N)::value; ++i) {
-            const int q = 2 * i + (lane & 1);
+            const int q = (i << share_log2) + part;
             uint2 e = make_uint2(0u, 0xffffffffu);
-            if (q < k && (lane >> 1) < chunks) e = in[q];
+            if (q < k && chunk < chunks) e = in[q];
             mk[i] = e.x; mi[i] = e.y;
         }
         wave_top_k(mk, mi, k, list, lane, [&](int t, uint32_t, uint32_t ii) { out[t] = (int32_t)ii; });
     };
-    if (k <= 4) merge(std::integral_constant<int, 2>{});
-    else if (k <= 12) merge(std::integral_constant<int, 6>{});
+    if (k <= 2 << share_log2) merge(std::integral_constant<int, 2>{});
+    else if (k <= 6 << share_log2) merge(std::integral_constant<int, 6>{});
     else merge(std::integral_constant<int, HYDRA_MAX_TOPK / 2>{});
 }
 
 // Small vocabularies: both kernels in one, a wave per 256 ids (four to a lane: rescanning the lane's entries is what a round
-// costs) and the survivors in LDS, at most 16 * 32.  One row of 1000 logits took 7.9 + 3.8 us with the pair of kernels.
+// costs) and the survivors in LDS, at most 16 * 32.  One row of 1000 logits took 7.9 + 3.8 us with the pair of kernels; a draft of
+// one head at 4096 ids takes 10.8 / 15.6 / 25.4 us for 1 / 8 / 32 children, with the pair 12.7 / 18.5 / more.
 enum { TOPK_ROW_PART = 256, TOPK_ROW_WAVES = 16 };
 template <int WAVES>
 __global__ __launch_bounds__(64 * WAVES) void topk_row_kernel(const float *part, int S, int part_ld, size_t split_stride, int V,
@@ -332,7 +336,7 @@ __global__ __launch_bounds__(64 * WAVES) void topk_row_kernel(const float *part,
     topk_load(key, part, S, split_stride, (size_t)r * part_ld, wave * TOPK_ROW_PART, V, lane);
     const int at = expand_off + r - b * ne, k = tree->expand_k[at];
     int32_t *out = tree_tokens + (size_t)b * tree->T + tree->expand_first[at];
-    topk_rounds(key, k, wave * TOPK_ROW_PART, lane, surv + wave * k);
+    topk_rounds(key, k, wave * TOPK_ROW_PART, lane, surv + wave, waves);
     __syncthreads();
     if (wave > 0) return;
     uint32_t mk[WAVES * HYDRA_MAX_TOPK / 64], mi[WAVES * HYDRA_MAX_TOPK / 64];
@@ -395,7 +399,9 @@ int launch_topk(hydra_ctx *c, hipStream_t s, const float *part, int S, int part_
     } else if (chunks <= TOPK_MAX_CHUNKS) {
         hipLaunchKernelGGL(topk_chunk_kernel, dim3(chunks, rows), dim3(TOPK_CHUNK / 4), 0, s, part, S, part_ld, split_stride, c->m.vocab, tree_dev(c), ne, eoff, (uint2 *)scratch);
         HYDRA_LAUNCH_CHECK("topk_chunk_kernel");
-        hipLaunchKernelGGL(topk_merge_kernel, dim3(rows), dim3(64), 0, s, (const uint2 *)scratch, chunks, tree_dev(c), ne, eoff, tree_tokens);
+        int share_log2 = 1;                                    // lanes of the merge's wave per chunk
+        while (2 * chunks << share_log2 <= 64) ++share_log2;
+        hipLaunchKernelGGL(topk_merge_kernel, dim3(rows), dim3(64), 0, s, (const uint2 *)scratch, chunks, share_log2, tree_dev(c), ne, eoff, tree_tokens);
         HYDRA_LAUNCH_CHECK("topk_merge_kernel");
     } else {
         hipLaunchKernelGGL(topk_scan_kernel, dim3(rows), dim3(256), 0, s, part, S, part_ld, split_stride, c->m.vocab, tree_dev(c), phase, tree_tokens);

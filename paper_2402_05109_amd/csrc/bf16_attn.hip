@@ -43,8 +43,8 @@ __global__ __launch_bounds__(ATTN_WAVES * 64) void attn_bf16_kernel(
     const int32_t *__restrict__ page_table, int max_pages, int n_pages, int layer, const int32_t *__restrict__ seq_len,
     const TreeDev *__restrict__ tree, int T, int H, float scale, float *__restrict__ apart, void *out, int32_t *flags) {
     extern __shared__ float lds[];
-    attn_bf16_body<DH, QW, PACKED, false, true>(qbuf, kpages, vpages, page_table, max_pages, n_pages, layer, seq_len, tree, T, H, 0,
-                                                scale, apart, out, flags, (int)blockIdx.x, (int)gridDim.x, (int)blockIdx.y, (int)blockIdx.z, lds, (int)threadIdx.x);
+    attn_bf16_body<DH, QW, PACKED, false>(qbuf, kpages, vpages, page_table, max_pages, n_pages, layer, seq_len, tree, T, H, 0,
+                                          scale, apart, out, flags, (int)blockIdx.x, (int)gridDim.x, (int)blockIdx.y, (int)blockIdx.z, lds, (int)threadIdx.x);
 }
 
 // Short contexts: a workgroup takes one 32-query tile of one (row, head) and 1 / DS of the head's dims; its eight waves split

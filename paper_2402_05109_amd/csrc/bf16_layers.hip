@@ -478,7 +478,7 @@ __global__ __launch_bounds__(LK_THREADS) void layers_kernel(LayerKernelArgs A) {
         if (attn_wg) {
             const int it = (int)blockIdx.x;
             const int qt = it % A.QT, h = (it / A.QT) % A.H, b = it / (A.QT * A.H);
-            attn_bf16_body<DH, 1, true, true, true>(reinterpret_cast<const u32x4_t *>(qbuf), A.kpages, A.vpages, A.page_table, A.max_pages, A.n_pages, l,
+            attn_bf16_body<DH, 1, true, true>(reinterpret_cast<const u32x4_t *>(qbuf), A.kpages, A.vpages, A.page_table, A.max_pages, A.n_pages, l,
                                            A.seq_len, A.tree, A.T, A.H, 1, A.scale, nullptr, attn, A.flags, qt, A.QT, h, b, lds, opaque_tid());
             wg_barrier_lds();                           // the attention body's LDS is the next step's
         }

@@ -127,11 +127,14 @@ WsLayout ws_layout(const hydra_ctx *c, int B) {
         const size_t mp = align_up(m, 32), np = (size_t)gemm_npad(c, (int)n);
         part = std::max(part, (size_t)p.splits * mp * np * 4);
     };
-    need(M, 3 * d, d); need(M, d, d); need(M, 2 * F, d); need(M, d, F); need(M, V, d);
+    // (the fp32 family's products end in their results, but for the vocabulary's)
+    need(M, V, d);
+    if (c->bf16) { need(M, 3 * d, d); need(M, d, d); need(M, 2 * F, d); need(M, d, F); }
     for (int i = 1; i <= c->tree.max_depth && i <= c->h.n_draft_heads; ++i) {
         const size_t mi = (size_t)B * c->tree.n_expand[i];
         if (mi == 0) continue;
-        need(mi, d, head_in_width(c, i)); need(mi, d, d); need(mi, V, d);
+        need(mi, V, d);
+        if (c->bf16) { need(mi, d, head_in_width(c, i)); need(mi, d, d); }
     }
     w.part = off;  off += align_up(part, 256);
     const size_t Tq = align_up(T, 32);

@@ -71,3 +71,14 @@ def test_calls_without_bound_weights_fail_cleanly():
     assert lib.hydra_draft_tree(None, None, 1, ws, ws, ws, ws) == hb.E_INVALID_ARG
     assert lib.accept_greedy(h._h, None, 1, None, None, None, None, None, None) in (hb.E_STATE, hb.E_INVALID_ARG)
     assert lib.hydra_load_tensor(h._h, None, 99, 0, 0, ws) == hb.E_STATE
+
+
+def test_fp32_workspace_holds_partial_sums_of_the_vocabulary_products_only():
+    """The products of the fp32 layers and draft MLPs end in their results; a wide FFN needs its two activations, no more."""
+    F, T = 16384, 128
+    h = hb.Hydra(**dict(GOOD, ffn=F, vocab=64, parent=[-1] + list(range(T - 1)), n_draft_heads=0))
+    activations = 2 * T * F * 4
+    assert activations <= h.workspace_bytes(1) <= activations + (1 << 20)
+    v = 50000
+    wide = hb.Hydra(**dict(GOOD, ffn=256, vocab=v, parent=[-1] + list(range(T - 1)), n_draft_heads=0))
+    assert wide.workspace_bytes(1) >= T * v * 4

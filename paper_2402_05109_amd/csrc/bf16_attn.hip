@@ -17,8 +17,8 @@
 // 16-byte-per-lane loads straight from the cache pages.
 //
 // A workgroup works on one (b, h).  Launch shapes:
-//   short contexts (up to ~1200 keys): attn_short_kernel, one workgroup per
-//     32-query tile and share of the head's dims; its 8 waves split the keys and
+//   short contexts (up to 1280 keys, and no more workgroups than CUs): attn_short_kernel,
+//     one workgroup per 32-query tile and share of the head's dims; its 8 waves split the keys and
 //     the result goes straight out as the next GEMM's input: one kernel, no
 //     partial records;
 //   longer contexts, or more rows: attn_bf16_kernel up to 32 queries (and where its
@@ -577,7 +577,7 @@ int attn_max_dynamic_lds(hydra_ctx *c) {
 #define ATTR(DHv, NWv, Pv) if (e == hipSuccess) e = hipFuncSetAttribute((const void *)attn_pair_kernel<DHv, NWv, Pv>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024)
     ATTR(128, 8, true); ATTR(128, 8, false); ATTR(64, 8, true); ATTR(64, 8, false); ATTR(128, 4, true); ATTR(128, 4, false);
 #undef ATTR
-    if (e != hipSuccess) return hip_fail(e, "hipFuncSetAttribute(attn_bf16_kernel)");
+    if (e != hipSuccess) return hip_fail(e, "hipFuncSetAttribute(attention kernels)");
     return HYDRA_OK;
 }
 
@@ -595,9 +595,10 @@ int launch_attention(hydra_ctx *c, hipStream_t s, int B, int layer, const void *
     const float scale = 1.0f / sqrtf((float)Dh);
     void *out = x_out ? x_out : (void *)plain_out;
     const bool packed = x_out != nullptr;
-    // Short contexts (attn_short_kernel: up to five tiles per wave, the result goes straight out), while those workgroups fit one round of
-    // the chip (at batch 8 and 16 one workgroup per (row, head) that holds all query tiles and reads each K/V byte once measured
-    // 2-3 % faster on the whole verify step).
+    // Short contexts, up to five key tiles per wave, while a workgroup per (row, head, 32-query tile) fits one round of the chip: the
+    // result goes straight out, without records and merge.  The head's dims are shared out over more workgroups while those still fit the
+    // round.  (More rows than that: a workgroup that holds all query tiles of its head and reads each K/V byte once is 2-3 % faster on the whole
+    // verification call at batch 8 and 16.)
     if (tiles <= ATTN_WAVES * ATTN_SHORT_TILES && QTtot * H * B <= 256) {
         int ds = Dh / 32;
         while (ds > 1 && QTtot * H * B * ds > 256) ds >>= 1;

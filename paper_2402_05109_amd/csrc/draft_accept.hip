@@ -165,9 +165,9 @@ __device__ __forceinline__ Cand wave_best(Cand c) {
 // wave rescans its registers once per extracted entry, and the waves of a workgroup share four SIMDs), so the row is
 // cut into chunks of 1024 ids, one workgroup of four waves each, spread over the chip: lane l of a wave holds four ids
 // base + l, base + 64 + l, ... as monotone keys (order_key; key 0 is below every real key and marks an absent or
-// already extracted entry), and k rounds leave the wave's k best, in order, as (key, id) pairs.  The second kernel,
-// one wave per row, picks the k best of the at most 32 * k survivors of the chunks in the same (value descending, id
-// ascending) order.
+// already extracted entry), k rounds leave the wave's k best, in order, as (key, id) pairs, and the first wave picks the
+// chunk's k best of those.  The second kernel, one wave per row, picks the k best of the at most 32 * k survivors of the
+// chunks in the same (value descending, id ascending) order.
 enum { TOPK_CHUNK = 1024, TOPK_MAX_CHUNKS = 32 };
 
 // lane's share of a chunk: ids base + i * 64 + lane
@@ -208,7 +208,9 @@ __device__ __forceinline__ void topk_rounds(uint32_t (&key)[N], int k, int base,
 // way; ranks follow the order, ids break ties, so nothing has to be extracted in turn.  The bound is as good as the maxima are: the
 // callers deal the sorted lists of their first step out so that the lanes hold the heads of all lists (a list per group of lanes,
 // its ranks in turn), not one rank of two lists each.  More than 64 entries at or above the bound (many equal logits) go back to k
-// rounds of a maximum over the wave, as do one or two children, where two rounds cost less than ranking.
+// rounds of a maximum over the wave, as do one or two children.  Draft of one head, rounds against ranking: one child 15.4 / 16.0 / 22.5 us
+// against 16.9 / 17.5 / 25.8 (1000 / 4000 / 32000 ids), two 15.7 / 16.8 / 23.2 against 17.2 / 18.0 / 26.2; three 16.1 / 17.6 / 23.7 against
+// 17.4 / 18.3 / 26.4, five 17.1 / 19.1 / 25.5 against 18.0 / 19.1 / 27.0: with the few entries that a lane holds now the line could lie higher.
 
 // key[i] (0: no entry) with id[i]; put(t, key, id) is called for t < k by one lane each: key 0 and id ~0 past the last entry.
 // list: 64 entries of LDS.

@@ -106,9 +106,9 @@ __device__ __forceinline__ void load_v_tile(KVTile<DH> &kv, const a16_t *vpages,
 // output is written with device-scope stores (the reader is another workgroup of the same kernel).  The function
 // contains two workgroup barriers that every wave reaches unless the row is over capacity (uniform early return).
 // tid: the thread's index in the workgroup.  The row has QW query tiles, or qsplit (QW = 1) hands each workgroup one of
-// them: every wave holds a tile that exists.  The query tiles are kept in LDS, which takes 8 * DH / 32 registers per lane
-// off a kernel that sits at the limit of 256.  They lie in the space of the O merge buffers (QW * DH * 64 bytes, never
-// more than those), which are first written behind the barrier that follows the key loops of all waves.
+// them.  The query tiles are kept in LDS, which takes 8 * DH / 32 registers per lane off a kernel that sits at the limit
+// of 256.  They lie in the space of the O merge buffers (QW * DH * 64 bytes, never more than those), which are first
+// written behind the barrier that follows the key loops of all waves.
 template <int DH, int QW, bool PACKED, bool DEV>
 __device__ __forceinline__ void attn_bf16_body(
     const u32x4_t *__restrict__ qbuf, const a16_t *__restrict__ kpages, const a16_t *__restrict__ vpages,
@@ -129,26 +129,34 @@ __device__ __forceinline__ void attn_bf16_body(
     const int key_wgs = qsplit ? 1 : nbx;
     const int units = key_wgs * KWV;
     const int unit = (qsplit ? 0 : bx) * KWV + kwv;
+    // true in every launch; kept because without the branch the compiler lays the layer kernel out differently, and a verification call
+    // through it takes 1.3 % longer (7B, 64 rows 3827 -> 3875 us)
+    const bool active = qtile < QTtot;
     const int32_t *pt = page_table + (size_t)b * max_pages;
     // Everything whose address does not depend on the row's length is requested before the length is known:
     // the queries, the ancestor masks and the page-table entries of this wave's first key tiles (the table
     // has max_pages entries for every row, so the reads are in bounds; entries past the row's pages are not used).
     enum { PG_AHEAD = 5 };                                 // page ids of this many key tiles per wave are fetched up front
+    u32x4_t qreg[KS];
     uint64_t anc0 = 0ull, anc1 = 0ull;
     int pg[PG_AHEAD][2];
-    const int query = qtile * 32 + col;
-    if (kwv == 0) {                                        // one copy per query tile, written by the first wave of its key split
+    if (active) {
         const size_t blk = (((size_t)b * H + h) * QTtot + qtile) * KS;
-        u32x4_t *qs = reinterpret_cast<u32x4_t *>(lds + ATTN_WAVES * 64) + (size_t)qw * KS * 64;
 #pragma unroll
-        for (int s = 0; s < KS; ++s) qs[s * 64 + lane] = qbuf[(blk + s) * 64 + lane];
-    }
-    if (query < T) { anc0 = tree->anc[query][0]; anc1 = tree->anc[query][1]; }
+        for (int s = 0; s < KS; ++s) qreg[s] = qbuf[(blk + s) * 64 + lane];
+        if (kwv == 0) {                            // one copy per query tile, written by the first wave of its key split
+            u32x4_t *qs = reinterpret_cast<u32x4_t *>(lds + ATTN_WAVES * 64) + (size_t)qw * KS * 64;
 #pragma unroll
-    for (int j = 0; j < PG_AHEAD; ++j) {
-        const int t = unit + j * units;
-        pg[j][0] = pt[min(2 * t, max_pages - 1)];                 // checked below, where they are used
-        pg[j][1] = pt[min(2 * t + 1, max_pages - 1)];
+            for (int s = 0; s < KS; ++s) qs[s * 64 + lane] = qreg[s];
+        }
+        const int query = qtile * 32 + col;
+        if (query < T) { anc0 = tree->anc[query][0]; anc1 = tree->anc[query][1]; }
+#pragma unroll
+        for (int j = 0; j < PG_AHEAD; ++j) {
+            const int t = unit + j * units;
+            pg[j][0] = pt[min(2 * t, max_pages - 1)];             // checked below, where they are used
+            pg[j][1] = pt[min(2 * t + 1, max_pages - 1)];
+        }
     }
     const int L = seq_len[b];
     __syncthreads();                                       // the query tiles are in LDS (before any early return: every wave reaches it)
@@ -168,7 +176,7 @@ __device__ __forceinline__ void attn_bf16_body(
         for (int v = 0; v < 16; ++v) o[dt][v] = 0.f;
     float m_run = -INFINITY, l_run = 0.f;
 
-    if (unit < n_tiles) {
+    if (active && unit < n_tiles) {
         KVTile<DH> cur, nxt;
         // second page of a tile: absent when the row ends inside the first one (its keys are masked; any valid page will do)
         {
@@ -217,7 +225,7 @@ __device__ __forceinline__ void attn_bf16_body(
 #pragma unroll
             for (int v = 0; v < 16; ++v) sc[v] = 0.f;
             int qoff = 0;
-            asm volatile("" : "+v"(qoff));                     // keeps the LDS reads of the queries inside the loop (hoisted, they are registers again)
+            asm volatile("" : "+v"(qoff));           // keeps the LDS reads of the queries inside the loop (hoisted, they are registers again)
 #pragma unroll
             for (int s = 0; s < KS; ++s)
                 sc = HYDRA_MFMA16(__builtin_bit_cast(a16x8_t, cur.k[s]), __builtin_bit_cast(a16x8_t, qlds[qoff + s * 64]), sc);
@@ -273,7 +281,9 @@ __device__ __forceinline__ void attn_bf16_body(
             for (int v = 0; v < 16; ++v) dst[(dt * 16 + v) * 64] = o[dt][v] * mine;
     }
     __syncthreads();
+    if (!active) return;
     // the (band, group of 4 registers = 4 consecutive dims) items are shared out over the KWV waves of the query tile
+    const int query = qtile * 32 + col;
     const bool final_out = key_wgs == 1;
     const float inv = final_out ? 1.0f / l_tot : 1.0f;
     float *rec = apart + ((((size_t)b * H + h) * nbx) + bx) * apart_record(Tq, DH);
